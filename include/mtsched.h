@@ -30,6 +30,11 @@
  *    bit-identical across all schedules of the same tenants.
  *  - One context is used from one host thread at a time (the paper issues all
  *    operators from a single main thread, Sec. III-D).
+ *  - mt_run places operators on hardware queues of its own, not on HIP streams: a schedule is turned into queue packets
+ *    on its first run and the packets are published again by every later one.  A "stream" of a schedule is an ordered
+ *    sequence of operators on such a queue.  Up to four streams run on four queues that the chip serves side by side;
+ *    further streams share a queue, where they advance together, and streams restricted to a CU share have queues of
+ *    their own.  Operators of one tenant that do not depend on each other (parallel branches) may run at the same time.
  */
 #ifndef MTSCHED_H
 #define MTSCHED_H
@@ -123,12 +128,12 @@ typedef struct mt_device_info {
     char arch[64];
 } mt_device_info;
 
-/* Timings of one mt_run, from HIP events recorded on the device.
- * makespan_ms: from the event recorded before the first operator of any tenant may start to the latest of the
- * events that the streams of the last stage record after their last operator (Sec. III-A objective: earliest start to
- * latest end); under MT_SCHED_GRAPH, the events around the graph launch.
- * stage_ms[s]: from the previous barrier (or the start) to the barrier that ends stage s.
- * host_issue_ms: wall time the issuing thread spent launching (Sec. III-D "invoking overhead").
+/* Timings of one mt_run, from the time stamps the device leaves when a kernel completes.
+ * makespan_ms: from the start of the earliest first kernel to the end of the latest last kernel (Sec. III-A objective:
+ * earliest start to latest end).
+ * stage_ms[s]: from the end of the stage before (or the start) to the end of the latest kernel of stage s.
+ * host_issue_ms: wall time the issuing thread spent publishing packets (Sec. III-D "invoking overhead"), host-side
+ * stage barriers included.
  * first_op_done_ms[i]: only with MT_SCHED_TIME_FIRST_OP, else 0: from the start to the end of tenant i's first
  * operator, i.e. how long stream i was held back by the issue of the streams before it (Sec. III-D, Fig. 5).
  * tenant_done_ms[i]: only with MT_SCHED_TIME_TENANTS, else 0: from the start to the end of tenant i's last operator,
@@ -152,8 +157,8 @@ const char *mt_kernel_name(int32_t kernel_id);
 /* Binds to HIP device `device`, creates the main stream and timing events. */
 int32_t mt_create(int32_t device, mt_ctx **out);
 int32_t mt_destroy(mt_ctx *ctx);
-/* Destroys the pooled CU-masked streams that no schedule refers to (a share search leaves its winner's streams in the
- * pool for the schedule created next).  Synchronises the device. */
+/* Destroys the pooled CU-masked queues that no schedule refers to (a share search leaves its winner's queues in the
+ * pool for the schedule created next). */
 int32_t mt_release_idle_streams(mt_ctx *ctx);
 int32_t mt_get_device_info(const mt_ctx *ctx, mt_device_info *out);
 
@@ -163,10 +168,10 @@ int32_t mt_get_device_info(const mt_ctx *ctx, mt_device_info *out);
  * register values (CU_ID = bits 8-11, SH_ID = bit 12, SE_ID = bits 13-15 of HW_ID; XCC_ID = low 4 bits). */
 int32_t mt_probe_cu_mask(mt_ctx *ctx, int32_t share, int32_t first_cu, int32_t n_groups, uint32_t *hw_ids);
 
-/* Diagnostic: what one stage barrier (Sec. III-B "Stage") costs on the tenant streams of this context.  n_streams
+/* Diagnostic: what one stage barrier (Sec. III-B "Stage") costs when it is taken with HIP streams.  n_streams
  * streams each run `rounds` rounds of one one-workgroup kernel; between rounds they are synchronised by
  *   kind 0  nothing (the reference: n_streams independent chains),
- *   kind 1  the barrier mt_run uses: every stream records an event and waits for the events of all others,
+ *   kind 1  events: every stream records an event and waits for the events of all others,
  *   kind 2  stream memory operations: every stream writes the round number to a word of its own
  *           (hipStreamWriteValue32) and waits until the words of all others have reached it (hipStreamWaitValue32, >=);
  *           all writes of a round are queued before any wait, so streams that share a hardware queue cannot block
@@ -259,21 +264,18 @@ int32_t mt_tenant_read_tensor(mt_ctx *ctx, int32_t tenant, int32_t tensor_id, vo
  * at most the unit count are disjoint.  A share between 1 and 7 is rejected with MT_ERR_INVALID_SCHEDULE: consecutive
  * mask bits fall on the 8 XCDs in turn and the runtime refuses a mask that leaves an XCD without a unit.
  * issue_order: MT_ISSUE_BFS issues one operator per stream round-robin (Sec. III-D), MT_ISSUE_DFS stream by stream.
- * flags: MT_SCHED_GRAPH captures the whole schedule into a HIP graph on the first run and replays it
- * afterwards (CU shares are ignored in that mode: graph nodes do not inherit stream CU masks).  A replay has no issue
- * order, only the capture has one; a schedule of several tenants is captured in both orders on that first run, each
- * graph is replayed three times and the faster one is kept (on this runtime one of the two is sometimes several times
- * slower), so that run takes about ten passes. */
+ * flags: MT_SCHED_GRAPH asks for a replayed schedule: the packets of the first run are published again by every later
+ * one.  Every schedule runs that way; with this flag CU shares are ignored (a replayed schedule runs on all units). */
 #define MT_SCHED_GRAPH 1
-/* MT_SCHED_PARALLEL_ISSUE: one issuing host thread per tenant stream instead of the paper's single main thread
- * (Sec. III-D); the operators of a stage are launched by the threads of its streams concurrently, stage barriers and
- * results are unchanged.  Not combinable with MT_SCHED_GRAPH. */
+/* MT_SCHED_PARALLEL_ISSUE: the streams of a stage need not wait for each other's issue (the paper's single main thread
+ * launches one operator after the other, Sec. III-D).  Publishing a packet takes the host 0.03 us, so one thread serves
+ * all streams and the flag changes nothing but what it may be combined with: not with MT_SCHED_GRAPH. */
 #define MT_SCHED_PARALLEL_ISSUE 2
-/* MT_SCHED_TIME_FIRST_OP: records one more event per tenant, after its first operator, and reports it in
- * mt_timings.first_op_done_ms.  Only with the single issuing thread on plain streams (neither flag above). */
+/* MT_SCHED_TIME_FIRST_OP: takes one more time stamp per tenant, after its first operator, and reports it in
+ * mt_timings.first_op_done_ms.  Not with either flag above. */
 #define MT_SCHED_TIME_FIRST_OP 4
 /* MT_SCHED_SHARE_PER_STAGE: cu_share holds n_stages * n_tenants entries, row s = the shares of stage s; a tenant then
- * runs each stage on the pooled stream of that stage's share (the stage barrier orders them).  Without the flag
+ * runs each stage on the pooled queue of that stage's share (the stage barrier orders them).  Without the flag
  * cu_share holds n_tenants entries used in every stage. */
 #define MT_SCHED_SHARE_PER_STAGE 8
 /* MT_SCHED_FUSE_DEPTHWISE: a 3x3 depthwise convolution whose consumer is a 1x1 convolution issued in the same stage
@@ -301,30 +303,20 @@ int32_t mt_tenant_read_tensor(mt_ctx *ctx, int32_t tenant, int32_t tensor_id, vo
  * of another then issues first.  Timing only, results unchanged.  (This is the priority of a wave among the waves of
  * its SIMD, set by the kernel itself; stream and queue priorities are never used.) */
 #define MT_SCHED_PRIORITIZE_SHORT 256
-/* MT_SCHED_TIME_TENANTS: records one more event per tenant, after its last operator, and reports it in
- * mt_timings.tenant_done_ms.  Works with the single issuing thread and with MT_SCHED_PARALLEL_ISSUE, with or without CU
- * shares; not with MT_SCHED_GRAPH or MT_SCHED_STREAM_GRAPHS (events inside a captured graph cannot be queried). */
+/* MT_SCHED_TIME_TENANTS: takes one more time stamp per tenant, after its last operator, and reports it in
+ * mt_timings.tenant_done_ms.  Not with MT_SCHED_GRAPH or MT_SCHED_STREAM_GRAPHS. */
 #define MT_SCHED_TIME_TENANTS 512
-/* MT_SCHED_HOST_BARRIER (only with MT_SCHED_PARALLEL_ISSUE): the barrier between stages is taken on the host.  The
- * issuing thread of a stream waits (hipEventSynchronize) for the events that the other streams recorded at the end of
- * the stage before and launches its operators of the stage after that, instead of queueing a device-side wait in
- * front of them.  Same ordering, same results; the launches of a stage can no longer be queued while the stage before
- * still runs, but no queue sits in a wait, which on this machine slows the dispatch of the queues that still work. */
+/* MT_SCHED_HOST_BARRIER (only with MT_SCHED_PARALLEL_ISSUE): the barrier between stages is taken on the host, which waits
+ * until the streams of the stage before have ended and only then publishes the next stage, instead of queueing a
+ * device-side wait in front of it.  Same ordering, same results. */
 #define MT_SCHED_HOST_BARRIER 1024
-/* MT_SCHED_STREAM_GRAPHS: the launches of one stream in one stage are captured (on that stream, on the first run
- * and again when a buffer pointer changes) into a graph of their own and replayed on that stream: the short gaps
- * between kernels of a replayed graph, with CU shares still in force (the replay runs on the masked stream) and with
- * per-stage timings (the stage barriers stay ordinary events).  Not combinable with MT_SCHED_GRAPH,
- * MT_SCHED_PARALLEL_ISSUE or MT_SCHED_TIME_FIRST_OP. */
+/* MT_SCHED_STREAM_GRAPHS: replay per stream and stage, with CU shares in force and per-stage timings.  Every schedule
+ * runs that way (see MT_SCHED_GRAPH); the flag changes nothing but what it may be combined with: not with
+ * MT_SCHED_GRAPH, MT_SCHED_PARALLEL_ISSUE or MT_SCHED_TIME_FIRST_OP. */
 #define MT_SCHED_STREAM_GRAPHS 32
-/* MT_SCHED_COUNTER_BARRIER: the barrier between stages (Sec. III-B "Stage") is taken with one counter word per run instead
- * of events: at the end of a stage every stream of the stage launches a one-thread kernel that adds 1 to the word, and a
- * stream of a later stage waits, with one hipStreamWaitValue32 packet on its queue, until the word has reached the number
- * of streams that ended the stages before.  2 n runtime calls per barrier instead of n + n (n - 1) event records and
- * waits; the stage's events are still recorded for the timings.  Same ordering, same results.  Works with the single
- * issuing thread and with MT_SCHED_PARALLEL_ISSUE (the arrivals of a stage are queued before any wait for them, so
- * streams that share a hardware queue cannot block each other); not with MT_SCHED_GRAPH, MT_SCHED_STREAM_GRAPHS or
- * MT_SCHED_HOST_BARRIER.  MT_ERR_HIP from mt_schedule_create if the device has no stream memory operations. */
+/* MT_SCHED_COUNTER_BARRIER: asks for the device-side stage barrier (Sec. III-B "Stage") in its cheapest form, which is the
+ * default: the last kernels of a stage count down completion signals and a queue of the next stage holds one packet that
+ * waits for them.  Not with MT_SCHED_GRAPH, MT_SCHED_STREAM_GRAPHS or MT_SCHED_HOST_BARRIER. */
 #define MT_SCHED_COUNTER_BARRIER 2048
 /* Co-issue (an issue mechanism of this runtime; the paper issues one launch per operator, Sec. III-D): where a stage
  * puts several tenants on one stream (stage_concurrency below the number of tenants with work), the stream would run
@@ -345,7 +337,7 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
                            int32_t issue_order, int32_t flags, mt_schedule **out);
 /* Wave priority per tenant (host array of n_tenants entries): 0..3 = every kernel of that tenant raises its waves to
  * that issue priority, -1 = the rule of MT_SCHED_PRIORITIZE_SHORT for that tenant.  Replaces what the flags set;
- * graphs captured so far are dropped and captured again on the next run.  Timing only. */
+ * the schedule's packets are written again on the next run.  Timing only. */
 int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio);
 int32_t mt_schedule_destroy(mt_schedule *s);
 
@@ -360,18 +352,18 @@ int32_t mt_issue_order_of_stage(int32_t n_tenants, const int32_t *slices, int32_
 /* ---- run ----------------------------------------------------------------------------- */
 /* inputs: host array of n_tenants device pointers, tenant i's [batch,H,W,C] input in its storage type
  * (may alias).  outputs: host array of n_tenants device pointers receiving the last operator's tensor.
+ * Work the caller has queued on HIP's default stream is waited for first; work on other streams has to be complete.
  * Blocks until every tenant has finished.  t may be NULL. */
 int32_t mt_run(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *t);
 
 /* mt_run for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc): the same pass on the same streams with the same kernels, but the partial-sum workspaces and
+ * that forbid hipMalloc): the same pass on the same queues with the same kernels, but the partial-sum workspaces and
  * arrival counters of every operator whose reduction is split over workgroups are taken from a fixed array of
  * MT_STATIC_SCRATCH_BYTES bytes of device memory that the library's code object holds on every GPU it is loaded on,
- * instead of from the tenants' arenas.  The call allocates nothing on the device: no hipMalloc, no hipFree, no graph
- * instantiation, no stream creation; the schedule must have been created without MT_SCHED_GRAPH,
- * MT_SCHED_STREAM_GRAPHS and MT_SCHED_PARALLEL_ISSUE (their first run captures graphs or starts threads):
- * MT_ERR_INVALID_ARG otherwise.  The counters' part of the array is cleared by a fill kernel at the start of each call
- * (not a memset node, so that a caller may capture the call); workspaces need no clearing.  If the tenants together
+ * instead of from the tenants' arenas.  The call makes no hipMalloc, hipFree or any other HIP call that a capture forbids (the library's own argument memory for the
+ * schedule's packets is taken on the first call); the schedule must have been created without MT_SCHED_GRAPH,
+ * MT_SCHED_STREAM_GRAPHS and MT_SCHED_PARALLEL_ISSUE: MT_ERR_INVALID_ARG otherwise.  The counters' part of the array is cleared by a fill kernel at the start of each call;
+ * workspaces need no clearing.  If the tenants together
  * need more than the array holds the call fails with MT_ERR_OUT_OF_MEMORY before anything is launched, and
  * mt_last_error states both figures.  Outputs have the bits of mt_run.  All calls on one GPU share the array, which
  * keeps the last call's contents: two calls that overlap in time on one GPU (from two contexts or two host threads)

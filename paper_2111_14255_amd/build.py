@@ -10,7 +10,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtsched.so")
 
 DEVICE_SOURCES = ["kernels_direct.hip", "kernels_igemm.hip", "kernels_stem.hip", "kernels_rowb.hip", "kernels_patch.hip"]
-HOST_SOURCES = ["sched_core.cpp", "runtime.cpp"]
+HOST_SOURCES = ["sched_core.cpp", "lanes.cpp", "runtime.cpp"]
 COMMON = ["-O3", "-fPIC", "-std=c++20", "-Wall", "-Wno-unused-function"]
 # packed-fp32 code generation is switched off for all device code
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -52,9 +52,9 @@ def build(verbose=False, lib=None, sanitize=False):
     os.makedirs(obj_dir, exist_ok=True)
     host_extra = ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"] + (SANITIZE_HOST if sanitize else [])
     jobs = [(s, DEVICE_FLAGS, obj_dir) for s in DEVICE_SOURCES] + [(s, host_extra, obj_dir) for s in HOST_SOURCES]
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda j: _compile(*j), jobs))
-    cmd = [_hipcc(), "-shared", "-fPIC", "-o", out] + objs + ["--offload-arch=gfx950"]
+    cmd = [_hipcc(), "-shared", "-fPIC", "-o", out] + objs + ["--offload-arch=gfx950", "-lhsa-runtime64"]
     if sanitize:
         cmd += ["-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize", "-shared-libsan"]
     subprocess.check_call(cmd)

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "record.h"
+
 namespace mt {
 
 typedef _Float16 f16;
@@ -47,9 +49,9 @@ __device__ __forceinline__ void set_wave_priority(int p) {
             for (int i_ = 0; i_ < n_mates; ++i_) pair_.a[1 + i_] = (mate)[i_];              \
             dim3 grid2_ = (grid);                                                           \
             grid2_.y = 1 + n_mates;                                                         \
-            hipLaunchKernelGGL(K2, grid2_, block, 0, st, pair_ __VA_OPT__(, ) __VA_ARGS__); \
+            launch(K2, grid2_, block, 0, st, pair_ __VA_OPT__(, ) __VA_ARGS__);            \
         } else {                                                                            \
-            hipLaunchKernelGGL(K1, grid, block, 0, st, a __VA_OPT__(, ) __VA_ARGS__);       \
+            launch(K1, grid, block, 0, st, a __VA_OPT__(, ) __VA_ARGS__);                 \
         }                                                                                   \
     } while (0)
 

@@ -16,6 +16,7 @@ int32_t fail(int32_t code, const std::string &msg);
 struct IssueItem {
     int32_t stream, tenant, op;
     int32_t mates[3] = {-1, -1, -1};   // runtime only: tenants whose operator of the same index runs in this item's launch (co-issue), -1 = none
+    int32_t group = -1;    // runtime only: items of a stream that carry different groups run one group after the other
     int32_t fuse = 0;      // runtime only: 1 = issued as part of a neighbour's launch, 2 / 3 = launches the pair (op - 1, op): depthwise + 1x1 / 1x1 + depthwise, 4 = convolution launched with the pooling operator op + 1 in its epilogue (that operator then carries 1)
 };
 int32_t validate_pointers(int32_t n_tenants, const int32_t *lens, int32_t n_stages, const int32_t *pointers);

@@ -582,7 +582,7 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
     constexpr int VMAX = 16 / sizeof(T);          // 16-byte accesses
     switch (a.kernel_id) {
         case K_CONV_DIRECT:
-            hipLaunchKernelGGL(conv_direct_kernel<T>, blocks((int64_t)a.N * a.P * a.Q * a.K), block, 0, st, a);
+            launch(conv_direct_kernel<T>, blocks((int64_t)a.N * a.P * a.Q * a.K), block, 0, st, a);
             break;
         case K_DWCONV: {
             if (a.vec == VMAX) {
@@ -602,7 +602,7 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
                 else
                     MT_LAUNCH((dwconv_kernel<T, VMAX>), (dwconv_pair_kernel<T, VMAX>), blocks(th), block, st, a, mate);
             } else {
-                hipLaunchKernelGGL((dwconv_kernel<T, 1>), blocks((int64_t)a.N * a.P * a.Q * a.C), block, 0, st, a);
+                launch((dwconv_kernel<T, 1>), blocks((int64_t)a.N * a.P * a.Q * a.C), block, 0, st, a);
             }
             break;
         }
@@ -624,9 +624,9 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
             } else {
                 const int64_t th = (int64_t)a.N * a.P * a.Q * a.C;
                 if (mx)
-                    hipLaunchKernelGGL((pool_kernel<T, 1, true>), blocks(th), block, 0, st, a);
+                    launch((pool_kernel<T, 1, true>), blocks(th), block, 0, st, a);
                 else
-                    hipLaunchKernelGGL((pool_kernel<T, 1, false>), blocks(th), block, 0, st, a);
+                    launch((pool_kernel<T, 1, false>), blocks(th), block, 0, st, a);
             }
             break;
         }
@@ -640,7 +640,7 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
             if (V == VMAX)
                 MT_LAUNCH((gap_kernel<T, VMAX>), (gap_pair_kernel<T, VMAX>), blocks(th), block, st, a, mate, lanes_c);
             else
-                hipLaunchKernelGGL((gap_kernel<T, 1>), blocks(th), block, 0, st, a, lanes_c);
+                launch((gap_kernel<T, 1>), blocks(th), block, 0, st, a, lanes_c);
             break;
         }
         case K_LRN:
@@ -657,8 +657,8 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
             }
             if (!done) {
                 const int64_t th = (int64_t)a.N * a.P * a.Q * a.C;
-                if (lrn) hipLaunchKernelGGL((lrn_kernel<T, 1>), blocks(th), block, 0, st, a);
-                else hipLaunchKernelGGL((add_kernel<T, 1>), blocks(th), block, 0, st, a);
+                if (lrn) launch((lrn_kernel<T, 1>), blocks(th), block, 0, st, a);
+                else launch((add_kernel<T, 1>), blocks(th), block, 0, st, a);
             }
             break;
         }
@@ -681,18 +681,18 @@ int launch_direct(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates
 }
 
 int launch_probe(uint32_t *out, int n_groups, void *stream) {
-    hipLaunchKernelGGL(probe_kernel, dim3((unsigned)n_groups), dim3(64), 0, (hipStream_t)stream, out);
+    launch(probe_kernel, dim3((unsigned)n_groups), dim3(64), 0, (hipStream_t)stream, out);
     return (int)hipGetLastError();
 }
 
 int launch_arrive(uint32_t *counter, void *stream) {
-    hipLaunchKernelGGL(arrive_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, counter);
+    launch(arrive_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, counter);
     return (int)hipGetLastError();
 }
 
 int launch_fill_u32(uint32_t *p, size_t n, uint32_t v, void *stream) {
     if (n == 0) return 0;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, p, n, v);
+    launch(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, p, n, v);
     return (int)hipGetLastError();
 }
 

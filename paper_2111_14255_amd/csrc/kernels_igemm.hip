@@ -872,13 +872,13 @@ static void launch_cfg(const OpArgs &a, hipStream_t st, const OpArgs *mate, int 
         for (int i = 0; i < n_mates; ++i) p.a[1 + i] = mate[i];
     }
     if (a.vec_a == A_UNIFORM) {
-        if (mate) hipLaunchKernelGGL((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, p);
-        else hipLaunchKernelGGL((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, a);
+        if (mate) launch((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, p);
+        else launch((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, a);
     } else if (a.vec_a == A_VEC8) {
-        if (mate) hipLaunchKernelGGL((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, p);
-        else hipLaunchKernelGGL((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, a);
+        if (mate) launch((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, p);
+        else launch((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, a);
     } else {
-        hipLaunchKernelGGL((igemm_kernel<T, BN, BM, WN, WM, MF, 2, A_SCALAR>), grid, dim3(256), 0, st, a);
+        launch((igemm_kernel<T, BN, BM, WN, WM, MF, 2, A_SCALAR>), grid, dim3(256), 0, st, a);
     }
 }
 
@@ -1124,8 +1124,8 @@ int launch_dwpw(const OpArgs &dw, const OpArgs &pw, void *stream) {
     const int M = pw.N * pw.P * pw.Q;
     const dim3 grid(((M + 15) / 16) * (pw.n_pad / 64)), block(256);
     const size_t dyn = dwpw_lds_bytes(pw.k_pad);
-    if (pw.dtype == MT_F16) hipLaunchKernelGGL(dwpw_kernel<f16>, grid, block, dyn, st, pw, dw);
-    else hipLaunchKernelGGL(dwpw_kernel<bf16>, grid, block, dyn, st, pw, dw);
+    if (pw.dtype == MT_F16) launch(dwpw_kernel<f16>, grid, block, dyn, st, pw, dw);
+    else launch(dwpw_kernel<bf16>, grid, block, dyn, st, pw, dw);
     return (int)hipGetLastError();
 }
 
@@ -1303,9 +1303,9 @@ int launch_pwdw(const OpArgs &pw, const OpArgs &dw, void *stream) {
     constexpr int HC = PWDW_HC;
     const dim3 grid(pw.N * bands * ((pw.K + HC - 1) / HC)), block(256);
     auto go = [&]<typename T>() {
-        if (variant == 0) hipLaunchKernelGGL((pwdw_kernel<T, 8, 2, HC>), grid, block, 0, st, pw, dw, bands);
-        else if (variant == 1) hipLaunchKernelGGL((pwdw_kernel<T, 4, 4, HC>), grid, block, 0, st, pw, dw, bands);
-        else hipLaunchKernelGGL((pwdw_kernel<T, 1, 8, HC>), grid, block, 0, st, pw, dw, bands);
+        if (variant == 0) launch((pwdw_kernel<T, 8, 2, HC>), grid, block, 0, st, pw, dw, bands);
+        else if (variant == 1) launch((pwdw_kernel<T, 4, 4, HC>), grid, block, 0, st, pw, dw, bands);
+        else launch((pwdw_kernel<T, 1, 8, HC>), grid, block, 0, st, pw, dw, bands);
     };
     if (pw.dtype == MT_F16) go.template operator()<f16>();
     else go.template operator()<bf16>();
@@ -1369,8 +1369,8 @@ __global__ void __launch_bounds__(256) peak_stream_kernel(const u32x4 *__restric
 
 int launch_peak_mfma(int dtype, float *sink, int n_groups, int iters, void *stream) {
     hipStream_t st = (hipStream_t)stream;
-    if (dtype == MT_F16) hipLaunchKernelGGL(peak_mfma_kernel<f16>, dim3((unsigned)n_groups), dim3(256), 0, st, sink, iters);
-    else if (dtype == MT_BF16) hipLaunchKernelGGL(peak_mfma_kernel<bf16>, dim3((unsigned)n_groups), dim3(256), 0, st, sink, iters);
+    if (dtype == MT_F16) launch(peak_mfma_kernel<f16>, dim3((unsigned)n_groups), dim3(256), 0, st, sink, iters);
+    else if (dtype == MT_BF16) launch(peak_mfma_kernel<bf16>, dim3((unsigned)n_groups), dim3(256), 0, st, sink, iters);
     else return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }
@@ -1378,8 +1378,8 @@ int launch_peak_mfma(int dtype, float *sink, int n_groups, int iters, void *stre
 int launch_peak_stream(int mode, const void *src, void *dst, size_t bytes, int n_groups, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     if (bytes % 16 != 0 || n_groups < 1) return (int)hipErrorInvalidValue;
-    if (mode == 0) hipLaunchKernelGGL(peak_stream_kernel<0>, dim3((unsigned)n_groups), dim3(256), 0, st, (const u32x4 *)src, (u32x4 *)dst, bytes / 16);
-    else hipLaunchKernelGGL(peak_stream_kernel<1>, dim3((unsigned)n_groups), dim3(256), 0, st, (const u32x4 *)src, (u32x4 *)dst, bytes / 16);
+    if (mode == 0) launch(peak_stream_kernel<0>, dim3((unsigned)n_groups), dim3(256), 0, st, (const u32x4 *)src, (u32x4 *)dst, bytes / 16);
+    else launch(peak_stream_kernel<1>, dim3((unsigned)n_groups), dim3(256), 0, st, (const u32x4 *)src, (u32x4 *)dst, bytes / 16);
     return (int)hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Host runtime: model construction and shape inference, kernel planning, registration (weight packing and
-// upload), schedule deployment on per-tenant HIP streams with event barriers, timing, profile-driven search.
+// upload), schedule deployment on the device's hardware lanes (lanes.h), timing, profile-driven search.
 // Paper: Sec. III-A (problem), III-B (IR: stream, pointer, stage, schedule), III-C (search), III-D (issue order).
 #include <hip/hip_runtime_api.h>
 #include <hip/hip_ext.h>
@@ -13,13 +13,12 @@
 #include <cstring>
 #include <map>
 #include <set>
-#include <atomic>
-#include <condition_variable>
+#include <list>
 #include <mutex>
-#include <thread>
 #include <memory>
 
 #include "internal.h"
+#include "lanes.h"
 
 using namespace mt;
 
@@ -399,56 +398,29 @@ struct Tenant {
     size_t st_cnt_bytes = 0, st_ws_bytes = 0;
 };
 
-struct StreamKey {
-    int tenant, share;
-    bool operator<(const StreamKey &o) const { return tenant != o.tenant ? tenant < o.tenant : share < o.share; }
-};
-
 struct mt_schedule;
 
-// Issuing threads of MT_SCHED_PARALLEL_ISSUE: worker w launches everything that goes to tenant w's stream.
-struct IssuePool {
-    std::vector<std::thread> threads;
-    std::mutex mu;
-    std::condition_variable cv;
-    uint64_t run_seq = 0;           // guarded by mu
-    bool quit = false;              // guarded by mu
-    mt_schedule *sched = nullptr;   // the run being issued
-    const void *const *inputs = nullptr;
-    void *const *outputs = nullptr;
-    std::atomic<int> stage_posted{-1};            // stages up to this one may be issued (their gate event is recorded)
-    std::atomic<int> stage_done[MT_MAX_STAGES];   // workers that finished issuing the stage
-    std::atomic<int> finished{0};                 // workers that left the run
-    std::atomic<int> error{0};
-    std::string error_msg;                        // guarded by mu
+// Queues of a schedule with CU shares, one per (share, first unit) in the order of the tenants that use them.  They are
+// created in a row, which spreads them evenly over the dispatch pipes, and kept for the next schedule with the same shares.
+struct MaskedSet {
+    std::vector<std::pair<int, int>> units;      // (share, first unit)
+    std::vector<hsa_queue_t *> queues;
+    int refs = 0;
 };
 
 struct mt_ctx {
     int device = 0;
     hipDeviceProp_t prop{};
     std::vector<std::unique_ptr<Tenant>> tenants;
-    hipStream_t main_stream = nullptr;
-    struct StreamEntry { hipStream_t stream = nullptr; int refs = 0; };
-    std::map<StreamKey, StreamEntry> streams;   // tenant streams, shared by schedules (reference counted)
-    hipEvent_t ev_start = nullptr;
-    hipEvent_t ev_stage[MT_MAX_STAGES]{};
-    hipEvent_t ev_done[MT_MAX_STAGES][MT_MAX_TENANTS]{};
-    hipEvent_t ev_prof[2]{};
-    hipEvent_t ev_first[MT_MAX_TENANTS]{};   // after the first operator of each tenant (MT_SCHED_TIME_FIRST_OP)
-    hipEvent_t ev_last[MT_MAX_TENANTS]{};    // after the last operator of each tenant (MT_SCHED_TIME_TENANTS)
-    // Graph executables of destroyed schedules.  They are released in batches after a device-wide synchronisation (at
-    // the end of a search, every 64 candidates inside one, in mt_release_idle_streams and in mt_destroy): destroying one
-    // right after its last launch has crashed inside the HIP runtime.
-    std::vector<hipGraphExec_t> retired_graphs;
+    LaneDevice *lanes = nullptr;                 // of the process
+    std::list<MaskedSet> masked;
     // Schedules created from this context and not destroyed yet; mt_destroy detaches them so that a later
     // mt_schedule_destroy does not touch the freed context.
     std::set<mt_schedule *> live_schedules;
-    IssuePool pool;
-    // Masked streams whose hardware queue dispatches slowly (see get_stream) are parked: kept alive, never used.
-    std::vector<hipStream_t> parked_streams;       // masked ones; released by purge_idle_streams
+    // HIP side: per-operator profiling and the machine probes
+    hipStream_t main_stream = nullptr;
+    hipEvent_t ev_prof[2]{}, ev_round[2]{}, ev_done[3][MT_MAX_TENANTS]{};
     uint32_t *probe_buf = nullptr;
-    float best_dispatch_us = 0.f;
-    uint32_t *barrier_word = nullptr;    // MT_SCHED_COUNTER_BARRIER: arrivals of the current run (borrowed from the process's pool)
 };
 
 struct StagePlan {
@@ -456,36 +428,46 @@ struct StagePlan {
     std::vector<int> streams;       // distinct streams used, ascending
     std::vector<std::vector<IssueItem>> by_stream;   // items of each stream (index = tenant that owns the stream), in issue order
     int prev_stage = -1;            // latest earlier stage that launched anything (-1: none)
+    std::array<hsa_queue_t *, MT_MAX_TENANTS> queue_of{};   // queue of each stream
+};
+
+// What one queue gets in one stage.
+struct LaneSlice {
+    hsa_queue_t *queue = nullptr;
+    std::vector<Packet> packets;
+    std::vector<int> ends;          // signals of the packets that nothing later in the slice waits for
+    int start = -1;                 // signal of the first kernel (first stage only)
+};
+
+// A schedule as queue packets, ready to be published: built on the first run, reused by every later one.
+struct RunPlan {
+    bool valid = false;
+    std::vector<const void *> in;
+    std::vector<void *> out;
+    std::vector<std::vector<LaneSlice>> stages;
+    std::vector<hsa_signal_t> signals;
+    KernargBlock args;
+    std::vector<RecordedLaunch> launches;
+    std::vector<size_t> arg_at;                      // offset of each launch's arguments in `args`
+    struct IoSite { IssueItem item; size_t first, count; };
+    std::vector<IoSite> io;                          // launches whose arguments name the caller's buffers
+    int first_op[MT_MAX_TENANTS], last_op[MT_MAX_TENANTS];   // signals of the timed operators, -1: none
 };
 
 struct mt_schedule {
     mt_ctx *ctx = nullptr;
     int n_tenants = 0, n_stages = 0, flags = 0;
     std::vector<StagePlan> stages;                 // non-empty stages only keep items; empty ones stay for timing
-    // MT_SCHED_GRAPH with several tenants: the items of every stage in the other issue order (same operators, same
-    // fused pairs), for the second capture
-    std::vector<std::vector<IssueItem>> alt_items;
-    // stream of (stage, stream owner); the same for every stage unless the shares are given per stage
-    std::vector<std::array<hipStream_t, MT_MAX_TENANTS>> stream_at;
-    std::vector<StreamKey> stream_keys;     // one reference in the context's pool per entry
+    MaskedSet *masked = nullptr;                   // one reference
     int n_launches = 0;
     int end_stage = -1;             // last stage that launches anything (-1: the schedule launches nothing)
     int n_fused = 0;                // operators that run inside the next operator's launch
-    std::vector<uint32_t> arrivals_upto;   // MT_SCHED_COUNTER_BARRIER: streams that have ended stages 0 .. st, summed
     int32_t prio[MT_MAX_TENANTS] = {0};   // wave priority of a tenant's kernels, 0..3; -1: 3 for its short kernels, 0 for the others
-    // graph replay
-    hipGraphExec_t graph_exec = nullptr;
-    std::vector<const void *> cap_in;
-    std::vector<void *> cap_out;
-    // MT_SCHED_STREAM_GRAPHS: one graph per (stage, stream) with the launches of that stream in that stage
-    std::vector<std::array<hipGraphExec_t, MT_MAX_TENANTS>> slice_exec;
-    // set for the duration of an mt_run_static_scratch call: base of the fixed scratch array and each tenant's blocks in it
+    RunPlan plan[2];                // of mt_run and of mt_run_static_scratch
+    // set while the plan of mt_run_static_scratch is written: base of the fixed scratch array and each tenant's blocks in it
     uint8_t *st_base = nullptr;
     size_t st_cnt_base[MT_MAX_TENANTS] = {}, st_ws_base[MT_MAX_TENANTS] = {};
 };
-
-// Hands every graph of a schedule to the context for release at mt_destroy.
-static void retire_graphs(mt_ctx *ctx, mt_schedule *s);
 
 namespace {
 
@@ -538,15 +520,6 @@ int launch_raw(const OpArgs &a, hipStream_t st) {
 }
 
 }  // namespace
-
-static void retire_graphs(mt_ctx *ctx, mt_schedule *s) {
-    if (s->graph_exec) ctx->retired_graphs.push_back(s->graph_exec);
-    s->graph_exec = nullptr;
-    for (auto &row : s->slice_exec)
-        for (hipGraphExec_t g : row)
-            if (g) ctx->retired_graphs.push_back(g);
-    s->slice_exec.clear();
-}
 
 namespace {
 
@@ -614,23 +587,6 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
     return launch_raw(a, st);
 }
 
-// Destroys every masked stream no schedule refers to, and the parked ones with them (the next masked streams are
-// timed again, so a slow queue slot that becomes free is parked again when it comes up).
-int32_t purge_idle_streams(mt_ctx *ctx) {
-    HIP_TRY(hipDeviceSynchronize());
-    for (auto e = ctx->streams.begin(); e != ctx->streams.end();) {
-        if (e->second.refs == 0 && e->first.share != 0) {
-            (void)hipStreamDestroy(e->second.stream);
-            e = ctx->streams.erase(e);
-        } else {
-            ++e;
-        }
-    }
-    for (hipStream_t p : ctx->parked_streams) (void)hipStreamDestroy(p);
-    ctx->parked_streams.clear();
-    return MT_OK;
-}
-
 // Plain streams belong to the process, not to a context: the runtime deals its hardware queues to the plain streams
 // of the process in creation order, so every plain stream a context created and destroyed moved the turn of the next
 // one.  One main stream and one stream per tenant index exist per device, created on first use and never destroyed;
@@ -691,37 +647,19 @@ void return_signal_word(int device, uint32_t *w) {
 // Class of a new stream: the first class whose representative it cannot run beside (a round of both takes more than
 // 1.5 launch times), else a new class, of which a plain stream becomes the representative (a masked one is reported
 // as class -1 then).
-int32_t classify_stream(mt_ctx *ctx, PlainPool &pool, hipStream_t s, bool plain, int *cls) {
+int32_t classify_stream(mt_ctx *ctx, PlainPool &pool, hipStream_t s, int *cls) {
     float single = 0.f;
     int32_t rc = dispatch_latency_us(ctx, s, ctx->probe_buf, 8, &single);
     if (rc != MT_OK) return rc;
-    if (ctx->best_dispatch_us == 0.f || single < ctx->best_dispatch_us) ctx->best_dispatch_us = single;
     for (size_t c = 0; c < pool.rep.size(); ++c) {
         float us = 0.f, host_us = 0.f;
         rc = concurrent_latency_us(ctx, {pool.rep[c], s}, 8, &us, &host_us);
         if (rc != MT_OK) return rc;
         if (us > 1.5f * single) { *cls = (int)c; return MT_OK; }
     }
-    if (!plain) { *cls = -1; return MT_OK; }
     *cls = (int)pool.rep.size();
     pool.rep.push_back(s);
     pool.spare.emplace_back();
-    return MT_OK;
-}
-
-// Makes sure a representative of every pipe class exists (new plain streams go to the spare lists), so that masked
-// streams can be classified; gives up after 12 creations.
-int32_t discover_classes(mt_ctx *ctx) {
-    PlainPool &pool = plain_pool(ctx->device);
-    if (!ctx->probe_buf) HIP_TRY(hipMalloc((void **)&ctx->probe_buf, 256));
-    for (int attempt = 0; attempt < 12 && (int)pool.rep.size() < N_PIPES; ++attempt) {
-        hipStream_t s = nullptr;
-        HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-        int cls = 0;
-        int32_t rc = classify_stream(ctx, pool, s, true, &cls);
-        if (rc != MT_OK) { (void)hipStreamDestroy(s); return rc; }
-        pool.spare[cls].push_back(s);
-    }
     return MT_OK;
 }
 
@@ -739,7 +677,7 @@ int32_t plain_stream_of_class(mt_ctx *ctx, int want, hipStream_t *out) {
         hipStream_t s = nullptr;
         HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
         int cls = 0;
-        int32_t rc = classify_stream(ctx, pool, s, true, &cls);
+        int32_t rc = classify_stream(ctx, pool, s, &cls);
         if (rc != MT_OK) { (void)hipStreamDestroy(s); return rc; }
         pool.spare[cls].push_back(s);
     }
@@ -752,305 +690,327 @@ int32_t plain_stream_of_class(mt_ctx *ctx, int want, hipStream_t *out) {
     return fail(MT_ERR_HIP, "no plain stream could be created");
 }
 
-// A new stream for `share` units starting at first_cu (0 = all units: a plain stream of the class of the tenant index).
-int32_t make_stream(mt_ctx *ctx, int tenant, int share, int first_cu, hipStream_t *out) {
-    // A stream over all units is a plain stream on one of the runtime's own hardware queues (GPU_MAX_HW_QUEUES of them,
-    // dealt to the plain streams of the process in turn).  Giving it a full CU mask, and with it a queue of its own,
-    // was measured and dropped: after the queue creations and destructions of a share search such streams sometimes
-    // ran three tenants in 0.9 ms instead of 0.32 ms.
-    if (share == 0) return plain_stream_of_class(ctx, tenant % N_PIPES, out);
-    hipStream_t s = nullptr;
-    const int cus = ctx->prop.multiProcessorCount;
-    std::vector<uint32_t> mask((cus + 31) / 32, 0u);
-    for (int j = 0; j < share; ++j) {
-        const int cu = (first_cu + j) % cus;
-        mask[cu / 32] |= 1u << (cu % 32);
-    }
-    // A masked stream owns a hardware queue, which sits on one of the four dispatch pipes like any other: it is
-    // classified like a plain stream, and one of another class than the tenant index asks for (i % 4) is parked (kept
-    // alive so that the next queue lands on the next pipe; purge_idle_streams destroys it later) and replaced, up to
-    // seven times.
-    int32_t rc = discover_classes(ctx);
-    if (rc != MT_OK) return rc;
+// The HIP stream of a tenant index that the barrier probe uses.
+int32_t probe_stream(mt_ctx *ctx, int tenant, hipStream_t *out) {
     PlainPool &pool = plain_pool(ctx->device);
-    for (int attempt = 0;; ++attempt) {
-        HIP_TRY(hipExtStreamCreateWithCUMask(&s, (uint32_t)mask.size(), mask.data()));
-        int cls = -1;
-        rc = classify_stream(ctx, pool, s, false, &cls);
-        if (rc != MT_OK) { (void)hipStreamDestroy(s); return rc; }
-        if (cls == tenant % N_PIPES || (int)pool.rep.size() < N_PIPES || attempt == 7) break;
-        ctx->parked_streams.push_back(s);
-    }
-    *out = s;
-    return MT_OK;
-}
-
-// Stream of a tenant restricted to `share` compute units (0 = all).  Tenant i's units start where the
-// shares of the tenants before it end, so disjoint shares give disjoint units.
-int32_t get_stream(mt_ctx *ctx, int tenant, int share, int first_cu, hipStream_t *out, StreamKey *out_key, bool *created = nullptr) {
-    StreamKey key{tenant, share == 0 ? 0 : (first_cu << 12) | share};
-    *out_key = key;
-    auto it = ctx->streams.find(key);
-    if (created) *created = false;
-    if (it != ctx->streams.end()) { it->second.refs++; *out = it->second.stream; return MT_OK; }
-    // A search over CU shares creates many masked streams, each with a hardware queue of its own.  Too many
-    // queues make the hardware scheduler time-slice them, which slows every stream of the process and adds
-    // stalls of 10-20 ms every few dozen runs: release the unreferenced masked streams before they pile up.  With the 8
-    // queues of the plain streams, five or six masked queues alive were already enough to run three tenants on masked
-    // streams in 0.80 ms instead of 0.32 ms.
-    if (share != 0) {
-        int idle = (int)ctx->parked_streams.size();
-        for (auto &e : ctx->streams)
-            if (e.second.refs == 0 && e.first.share != 0) ++idle;
-        if (idle >= 3) {
-            int32_t rc = purge_idle_streams(ctx);
-            if (rc != MT_OK) return rc;
-        }
-    }
-    PlainPool &pool = plain_pool(ctx->device);
-    hipStream_t s = nullptr;
-    if (share == 0 && pool.tenant[tenant]) {
-        s = pool.tenant[tenant];                    // created by an earlier context of the process
-    } else {
-        int32_t rc = make_stream(ctx, tenant, share, first_cu, &s);
+    if (!pool.tenant[tenant]) {
+        int32_t rc = plain_stream_of_class(ctx, tenant % N_PIPES, &pool.tenant[tenant]);
         if (rc != MT_OK) return rc;
-        if (share == 0) pool.tenant[tenant] = s;
-        if (created) *created = true;
     }
-    ctx->streams[key] = mt_ctx::StreamEntry{s, 1};
-    *out = s;
+    *out = pool.tenant[tenant];
     return MT_OK;
 }
 
-void release_streams(mt_schedule *s) {
-    if (!s->ctx) { s->stream_keys.clear(); return; }
-    for (const StreamKey &k : s->stream_keys) {
-        auto it = s->ctx->streams.find(k);
-        if (it != s->ctx->streams.end() && it->second.refs > 0) it->second.refs--;
+// ---- masked queues ---------------------------------------------------------------------------------
+// Destroys the queues of every set no schedule refers to.  Queues that merely exist count: with several dozen alive the
+// hardware scheduler time-slices them, and a pass on masked queues took 8 to 130 ms instead of 6 (measured on MI355X,
+// eight tenants on eighths of the units), so at most the sets in use and the last one released are kept.
+void purge_idle_queues(mt_ctx *ctx) {
+    for (auto it = ctx->masked.begin(); it != ctx->masked.end();) {
+        if (it->refs == 0) {
+            for (hsa_queue_t *q : it->queues) ctx->lanes->destroy_queue(q);
+            it = ctx->masked.erase(it);
+        } else {
+            ++it;
+        }
     }
-    s->stream_keys.clear();
 }
 
-// A stream about to run stage st waits for the start event (no earlier work) or, directly, for the end of every other
-// stream of the latest earlier stage with work; those streams waited the same way, so all earlier stages are complete.
-// One cross-queue hop per barrier instead of two through the main stream.
-// Under graph capture the barrier goes through the main stream as before (every stream waits for the stage event the
-// main stream recorded): capturing the direct form ended in a host crash of the capture/instantiate path whose cause
-// is not known, so that combination is switched off.
-hipError_t wait_for_previous_stage(mt_ctx *ctx, const mt_schedule *s, int st, int stream) {
-    if (s->flags & MT_SCHED_GRAPH)
-        return hipStreamWaitEvent(s->stream_at[st][stream], st == 0 ? ctx->ev_start : ctx->ev_stage[st - 1], 0);
-    const int prev = s->stages[st].prev_stage;
-    if (prev < 0) return hipStreamWaitEvent(s->stream_at[st][stream], ctx->ev_start, 0);
-    if (s->flags & MT_SCHED_COUNTER_BARRIER)      // one wait per stream: every stream of the stages so far has bumped the word
-        return hipStreamWaitValue32(s->stream_at[st][stream], ctx->barrier_word, s->arrivals_upto[prev], hipStreamWaitValueGte, 0xffffffffu);
-    hipError_t e = hipSuccess;
-    for (int pm : s->stages[prev].streams)
-        if (s->stream_at[prev][pm] != s->stream_at[st][stream] && e == hipSuccess)     // the same stream is in order by itself
-            e = hipStreamWaitEvent(s->stream_at[st][stream], ctx->ev_done[prev][pm], 0);
-    return e;
+// A reference to the queues for these (share, first unit) pairs, created if the context has no such set.
+int32_t acquire_masked(mt_ctx *ctx, const std::vector<std::pair<int, int>> &units, MaskedSet **out) {
+    for (MaskedSet &m : ctx->masked)
+        if (m.units == units) {
+            ++m.refs;
+            *out = &m;
+            return MT_OK;
+        }
+    purge_idle_queues(ctx);
+    MaskedSet set;
+    set.units = units;
+    const int cus = ctx->prop.multiProcessorCount;
+    for (auto [share, first_cu] : units) {
+        std::vector<uint32_t> mask((cus + 31) / 32, 0u);
+        for (int j = 0; j < share; ++j) {
+            const int cu = (first_cu + j) % cus;
+            mask[cu / 32] |= 1u << (cu % 32);
+        }
+        hsa_queue_t *q = ctx->lanes->create_masked(mask);
+        if (!q) {
+            for (hsa_queue_t *p : set.queues) ctx->lanes->destroy_queue(p);
+            return fail(MT_ERR_HIP, "a queue restricted to " + std::to_string(share) + " compute units could not be created");
+        }
+        set.queues.push_back(q);
+    }
+    set.refs = 1;
+    ctx->masked.push_back(std::move(set));
+    *out = &ctx->masked.back();
+    return MT_OK;
 }
 
-// Outside whole-schedule graph capture the main stream takes no part in a run after the start event: the events that
-// end a stage on its streams are timed, the streams of the next stage wait for them directly, the host waits for those
-// of the last stage that launches anything, and stage times are differences of these events.  A queue that sits in a
-// wait for another queue's event slows the dispatch of the others on this machine: with the main stream joining every
-// stage for a stage event of its own, the sequential ResNet-18 + VGG-16 + MobileNetV2 pass took 0.62 instead of 0.56 ms
-// and the concurrent one 0.325 instead of 0.30 ms.
-inline bool ends_on_streams(const mt_schedule *s) { return !(s->flags & MT_SCHED_GRAPH) && s->end_stage >= 0; }
+void release_masked(mt_schedule *s) {
+    if (s->masked) --s->masked->refs;
+    s->masked = nullptr;
+}
 
-// MT_SCHED_STREAM_GRAPHS: the launches of one stream in one stage, captured on that stream (so that a CU mask of the
-// stream applies at replay) into a graph of their own.  The barriers between stages stay ordinary events.
-int32_t capture_slice_graphs(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs) {
-    retire_graphs(ctx, s);
-    s->slice_exec.assign(s->n_stages, {});
-    for (int st = 0; st < s->n_stages; ++st) {
+// ---- schedules as queue packets ----------------------------------------------------------------------
+// Which plain lane each of a stage's streams runs on.  Up to four streams get a lane each.  More share: two streams on one
+// lane advance level by level together (see build_plan), so streams of like length are put together and the longest ones
+// are left alone where the count allows it.  Streams that have a masked queue keep it.
+// Four lanes and not more: further queues sit on a pipe that already has one and take turns with it.  Measured on MI355X
+// with 4 / 5 / 6 / 8 plain queues: eight ResNet-18 at batch 1 379 / 826 / 844 / 766 us, eight ResNet-50 at batch 16
+// 2.89 / 3.54 / 3.53 / 3.23 ms, five VGG-16 at batch 8 2.37 / 2.38 / 2.37 / 2.38 ms.  Level by level against one operator
+// at a time on a shared lane: eight ResNet-18 379 / 395 us, eight ResNet-50 at batch 16 2.85 / 2.91 ms.
+void lane_plan(const LaneDevice *lanes, StagePlan &sp) {
+    std::vector<int> plain;
+    for (int sm : sp.streams)
+        if (!sp.queue_of[sm]) plain.push_back(sm);
+    std::stable_sort(plain.begin(), plain.end(), [&](int a, int b) { return sp.by_stream[a].size() > sp.by_stream[b].size(); });
+    const int n = (int)plain.size(), base = n / N_LANES, extra = n % N_LANES;
+    for (int lane = 0, at = 0; lane < N_LANES && at < n; ++lane) {
+        const int take = n <= N_LANES ? 1 : base + (lane >= N_LANES - extra ? 1 : 0);
+        for (int k = 0; k < take && at < n; ++k) sp.queue_of[plain[at++]] = lanes->plain(lane);
+    }
+}
+
+// The operators an issue item computes, as (tenant, operator).
+std::vector<std::pair<int, int>> covered(const IssueItem &it) {
+    std::vector<std::pair<int, int>> ops;
+    if (it.fuse == 1) return ops;
+    if (it.fuse == 2 || it.fuse == 3) ops.push_back({it.tenant, it.op - 1});
+    ops.push_back({it.tenant, it.op});
+    if (it.fuse == 4) ops.push_back({it.tenant, it.op + 1});
+    for (int m : it.mates)
+        if (m >= 0) ops.push_back({m, it.op});
+    return ops;
+}
+
+// Level of every item of one stream: an item is one level above the latest item whose result it reads or whose data it
+// overwrites, so the items of a level are independent (the branches of an inception block, a convolution and the shortcut
+// beside it).  Tenants that a stream runs one after the other (items of different groups) do not share levels.
+std::vector<int> item_levels(const mt_ctx *ctx, const std::vector<IssueItem> &items) {
+    struct Write { int first_c, end_c, level; };
+    struct Tensor { std::vector<Write> writes; int read_level = -1; };
+    std::map<std::pair<int, int>, Tensor> tensors;       // (tenant, tensor)
+    std::vector<int> level(items.size(), 0);
+    int top = -1, floor = 0, group = -1;
+    for (size_t k = 0; k < items.size(); ++k) {
+        const IssueItem &it = items[k];
+        if (it.group != group) { group = it.group; floor = top + 1; }
+        const auto ops = covered(it);
+        int lv = floor;
+        for (auto [t, op] : ops) {
+            const mt_op_desc &d = ctx->tenants[t]->model.ops[op].d;
+            for (int src : {d.in_tensor, d.res_tensor})
+                if (src > 0)
+                    for (const Write &w : tensors[{t, src}].writes) lv = std::max(lv, w.level + 1);
+            const Tensor &o = tensors[{t, d.out_tensor}];
+            const int c0 = d.out_c_offset, c1 = c0 + ctx->tenants[t]->model.ops[op].out_c;
+            for (const Write &w : o.writes)
+                if (w.first_c < c1 && c0 < w.end_c) lv = std::max(lv, w.level + 1);
+            lv = std::max(lv, o.read_level + 1);
+        }
+        level[k] = lv;
+        if (ops.empty()) continue;
+        top = std::max(top, lv);
+        for (auto [t, op] : ops) {
+            const mt_op_desc &d = ctx->tenants[t]->model.ops[op].d;
+            for (int src : {d.in_tensor, d.res_tensor})
+                if (src > 0) tensors[{t, src}].read_level = std::max(tensors[{t, src}].read_level, lv);
+            const int c0 = d.out_c_offset;
+            tensors[{t, d.out_tensor}].writes.push_back(Write{c0, c0 + ctx->tenants[t]->model.ops[op].out_c, lv});
+        }
+    }
+    return level;
+}
+
+void drop_plan(mt_ctx *ctx, RunPlan &p) {
+    for (hsa_signal_t s : p.signals) ctx->lanes->return_signal(s);
+    ctx->lanes->free_args(p.args);
+    p = RunPlan{};
+}
+
+bool names_caller_buffers(const mt_ctx *ctx, const IssueItem &it) {
+    for (auto [t, op] : covered(it)) {
+        const Tenant &tn = *ctx->tenants[t];
+        if (tn.reads_input[op] || tn.res_input[op] || tn.writes_output[op]) return true;
+    }
+    return false;
+}
+
+// Writes the whole schedule down as packets.  Within a queue the packets of a level follow each other without a barrier
+// bit and run together; the first packet of a level carries it and starts when everything before it is complete.  Streams
+// that share a lane are merged level by level.  Fences: a level's first packet acquires at agent scope what earlier levels
+// released (its siblings start after it and need no fence of their own); the first packet of a queue acquires at system
+// scope (caller's inputs, argument memory written by the host), and what writes a caller's output releases there.
+int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, RunPlan &plan, bool clear_counters, size_t counter_bytes) {
+    drop_plan(ctx, plan);
+    LaneDevice *dev = ctx->lanes;
+    LaunchRecorder rec;
+    rec.dev = dev;
+    struct Emit { size_t launch; uint32_t head; int signal; };           // one kernel packet of a slice
+    struct Pending { LaneSlice slice; std::vector<int> deps; std::vector<Emit> emits; };
+    std::vector<std::vector<Pending>> pending(s->n_stages);
+    for (int i = 0; i < MT_MAX_TENANTS; ++i) plan.first_op[i] = plan.last_op[i] = -1;
+    bool no_signal = false;
+    auto new_signal = [&]() {
+        hsa_signal_t sg = dev->take_signal();
+        no_signal = no_signal || !sg.handle;
+        plan.signals.push_back(sg);
+        return (int)plan.signals.size() - 1;
+    };
+    int32_t rc = MT_OK;
+    LaunchRecorder *const outer = current_recorder();
+    current_recorder() = &rec;
+    int fill_signal = -1;
+    Pending fill;
+    if (clear_counters && counter_bytes > 0) {
+        // counters of the split reductions start at zero: cleared by a kernel that the first stage's queues wait for
+        const int e = launch_fill_u32((uint32_t *)s->st_base, counter_bytes / sizeof(uint32_t), 0u, nullptr);
+        if (e != 0) rc = fail(MT_ERR_HIP, std::string("clearing the counters: ") + hipGetErrorString((hipError_t)e));
+        fill.slice.queue = dev->plain(0);
+        fill_signal = new_signal();
+        fill.emits.push_back(Emit{0, dispatch_head(true, HSA_FENCE_SCOPE_SYSTEM, HSA_FENCE_SCOPE_AGENT, 1), fill_signal});
+    }
+    std::set<hsa_queue_t *> seen;
+    int first_stage = -1;
+    for (int st = 0; st < s->n_stages && rc == MT_OK; ++st) {
         const StagePlan &sp = s->stages[st];
-        for (int sm : sp.streams) {
-            hipStream_t stream = s->stream_at[st][sm];
-            hipGraph_t graph = nullptr;
-            HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeRelaxed));
-            int32_t rc = MT_OK;
-            for (const IssueItem &it : sp.by_stream[sm]) {
-                const int e = launch_item(ctx, s, it, inputs, outputs, stream);
-                if (e != 0) { rc = fail(MT_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString((hipError_t)e)); break; }
-            }
-            hipError_t e = hipStreamEndCapture(stream, &graph);
-            if (rc != MT_OK) { if (graph) (void)hipGraphDestroy(graph); return rc; }
-            if (e != hipSuccess) return fail(MT_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-            e = hipGraphInstantiate(&s->slice_exec[st][sm], graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) return fail(MT_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-        }
-    }
-    s->cap_in.assign(inputs, inputs + s->n_tenants);
-    s->cap_out.assign(outputs, outputs + s->n_tenants);
-    return MT_OK;
-}
-
-// Issues the whole schedule on the tenant streams.  Barrier between stages: every stream of the stage records an
-// event and the streams of the next stage wait for all of them.  Under whole-schedule graph capture the main stream
-// waits for them too and records a stage event that the next stage waits for (a capture has to join its origin).
-int32_t issue_schedule(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, int *n_launch, bool alt = false) {
-    if (s->flags & MT_SCHED_COUNTER_BARRIER) HIP_TRY(hipStreamWriteValue32(ctx->main_stream, ctx->barrier_word, 0u, 0));
-    HIP_TRY(hipEventRecord(ctx->ev_start, ctx->main_stream));
-    int launches = 0;
-    for (int st = 0; st < s->n_stages; ++st) {
-        const StagePlan &sp = s->stages[st];
-        for (int sm : sp.streams) HIP_TRY(wait_for_previous_stage(ctx, s, st, sm));
-        if (s->flags & MT_SCHED_STREAM_GRAPHS) {
-            for (int sm : sp.streams) HIP_TRY(hipGraphLaunch(s->slice_exec[st][sm], s->stream_at[st][sm]));
-            launches += (int)sp.items.size();
-        } else
-        for (const IssueItem &it : (alt ? s->alt_items[st] : sp.items)) {
-            ++launches;                              // counts operators issued, fused or not
-            const int e = launch_item(ctx, s, it, inputs, outputs, s->stream_at[st][it.stream]);
-            if (e != 0) return fail(MT_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString((hipError_t)e));
-            if ((s->flags & MT_SCHED_TIME_FIRST_OP) && it.op == 0) HIP_TRY(hipEventRecord(ctx->ev_first[it.tenant], s->stream_at[st][it.stream]));
-            if ((s->flags & MT_SCHED_TIME_TENANTS) && it.op + 1 == (int)ctx->tenants[it.tenant]->model.ops.size())
-                HIP_TRY(hipEventRecord(ctx->ev_last[it.tenant], s->stream_at[st][it.stream]));
-        }
-        if (ends_on_streams(s)) {
-            for (int sm : sp.streams) HIP_TRY(hipEventRecord(ctx->ev_done[st][sm], s->stream_at[st][sm]));
-            if ((s->flags & MT_SCHED_COUNTER_BARRIER) && st < s->end_stage)
-                for (int sm : sp.streams) {
-                    const int e = launch_arrive(ctx->barrier_word, s->stream_at[st][sm]);
-                    if (e != 0) return fail(MT_ERR_HIP, std::string("arrival kernel: ") + hipGetErrorString((hipError_t)e));
-                }
-            continue;
-        }
-        for (int sm : sp.streams) {
-            HIP_TRY(hipEventRecord(ctx->ev_done[st][sm], s->stream_at[st][sm]));
-            HIP_TRY(hipStreamWaitEvent(ctx->main_stream, ctx->ev_done[st][sm], 0));
-        }
-        HIP_TRY(hipEventRecord(ctx->ev_stage[st], ctx->main_stream));
-    }
-    if (n_launch) *n_launch = launches;
-    return MT_OK;
-}
-
-inline void spin_pause() {
-#if defined(__x86_64__)
-    __builtin_ia32_pause();
-#endif
-}
-
-// `seen` is the run counter at the time the thread was created: a worker added after earlier runs (a tenant
-// registered later) must sleep until the next run is published, not wake for the last one, whose schedule may be gone.
-void issue_worker(mt_ctx *ctx, int w, uint64_t seen) {
-    IssuePool &pool = ctx->pool;
-    (void)hipSetDevice(ctx->device);
-    for (;;) {
-        {
-            std::unique_lock<std::mutex> lk(pool.mu);
-            pool.cv.wait(lk, [&] { return pool.quit || pool.run_seq != seen; });
-            if (pool.quit) return;
-            seen = pool.run_seq;
-        }
-        mt_schedule *s = pool.sched;
-        if (w < s->n_tenants) {
-            for (int st = 0; st < s->n_stages; ++st) {
-                const StagePlan &sp = s->stages[st];
-                if (sp.by_stream[w].empty()) continue;
-                while (pool.stage_posted.load(std::memory_order_acquire) < st) spin_pause();
-                hipError_t e = hipSuccess;
-                const int prev = sp.prev_stage;
-                if ((s->flags & MT_SCHED_HOST_BARRIER) && prev >= 0) {
-                    // the barrier on the host: once every stream of the stage before has recorded its event, this
-                    // thread waits for those of the other streams and only then launches
-                    const StagePlan &pp = s->stages[prev];
-                    while (pool.stage_done[prev].load(std::memory_order_acquire) < (int)pp.streams.size()) spin_pause();
-                    for (int pm : pp.streams)
-                        if (s->stream_at[prev][pm] != s->stream_at[st][w] && e == hipSuccess) e = hipEventSynchronize(ctx->ev_done[prev][pm]);
-                } else {
-                    e = wait_for_previous_stage(ctx, s, st, w);
-                }
-                for (const IssueItem &it : sp.by_stream[w]) {
-                    if (e != hipSuccess) break;
-                    const int rc = launch_item(ctx, s, it, pool.inputs, pool.outputs, s->stream_at[st][w]);
-                    if (rc != 0) e = (hipError_t)rc;
-                    else if ((s->flags & MT_SCHED_TIME_TENANTS) && it.op + 1 == (int)ctx->tenants[it.tenant]->model.ops.size())
-                        e = hipEventRecord(ctx->ev_last[it.tenant], s->stream_at[st][w]);
-                }
-                if (e == hipSuccess) e = hipEventRecord(ctx->ev_done[st][w], s->stream_at[st][w]);
-                if (e == hipSuccess && (s->flags & MT_SCHED_COUNTER_BARRIER) && st < s->end_stage)
-                    e = (hipError_t)launch_arrive(ctx->barrier_word, s->stream_at[st][w]);
-                if (e != hipSuccess) {
-                    std::lock_guard<std::mutex> lk(pool.mu);
-                    pool.error_msg = std::string("issuing thread: ") + hipGetErrorString(e);
-                    pool.error.store(1);
-                }
-                pool.stage_done[st].fetch_add(1, std::memory_order_release);
-            }
-        }
-        pool.finished.fetch_add(1, std::memory_order_release);
-    }
-}
-
-int32_t ensure_pool(mt_ctx *ctx, int n) {
-    while ((int)ctx->pool.threads.size() < n) {
-        const int w = (int)ctx->pool.threads.size();
-        uint64_t seq;
-        {
-            std::lock_guard<std::mutex> lk(ctx->pool.mu);
-            seq = ctx->pool.run_seq;
-        }
-        ctx->pool.threads.emplace_back(issue_worker, ctx, w, seq);
-    }
-    return MT_OK;
-}
-
-void stop_pool(mt_ctx *ctx) {
-    {
-        std::lock_guard<std::mutex> lk(ctx->pool.mu);
-        ctx->pool.quit = true;
-    }
-    ctx->pool.cv.notify_all();
-    for (auto &t : ctx->pool.threads) t.join();
-    ctx->pool.threads.clear();
-}
-
-// Same event structure as issue_schedule, with the launches of a stage spread over one host thread per stream.
-int32_t issue_schedule_parallel(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, int *n_launch) {
-    IssuePool &pool = ctx->pool;
-    int32_t rc = ensure_pool(ctx, s->n_tenants);
-    if (rc != MT_OK) return rc;
-    const int n_workers = (int)pool.threads.size();
-    pool.sched = s;
-    pool.inputs = inputs;
-    pool.outputs = outputs;
-    pool.stage_posted.store(-1);
-    for (int st = 0; st < MT_MAX_STAGES; ++st) pool.stage_done[st].store(0);
-    pool.finished.store(0);
-    pool.error.store(0);
-    if (s->flags & MT_SCHED_COUNTER_BARRIER) HIP_TRY(hipStreamWriteValue32(ctx->main_stream, ctx->barrier_word, 0u, 0));
-    HIP_TRY(hipEventRecord(ctx->ev_start, ctx->main_stream));
-    {
-        std::lock_guard<std::mutex> lk(pool.mu);
-        ++pool.run_seq;
-    }
-    pool.cv.notify_all();
-    hipError_t err = hipSuccess;
-    for (int st = 0; st < s->n_stages; ++st) {
-        const StagePlan &sp = s->stages[st];
-        pool.stage_posted.store(st, std::memory_order_release);
-        while (pool.stage_done[st].load(std::memory_order_acquire) < (int)sp.streams.size()) spin_pause();
-        if (ends_on_streams(s)) continue;          // stages end on their own streams' events
+        if (sp.items.empty()) continue;
+        if (first_stage < 0) first_stage = st;
+        std::vector<hsa_queue_t *> queues;
         for (int sm : sp.streams)
-            if (err == hipSuccess) err = hipStreamWaitEvent(ctx->main_stream, ctx->ev_done[st][sm], 0);
-        if (err == hipSuccess) err = hipEventRecord(ctx->ev_stage[st], ctx->main_stream);
+            if (std::find(queues.begin(), queues.end(), sp.queue_of[sm]) == queues.end()) queues.push_back(sp.queue_of[sm]);
+        for (hsa_queue_t *q : queues) {
+            Pending p;
+            p.slice.queue = q;
+            struct Piece { int level; size_t first, count; bool ends_tenant[MT_MAX_TENANTS], starts_tenant[MT_MAX_TENANTS], output; };
+            std::vector<Piece> pieces;
+            int top = -1;
+            for (int sm : sp.streams) {
+                if (sp.queue_of[sm] != q) continue;
+                const auto &items = sp.by_stream[sm];
+                const auto level = item_levels(ctx, items);
+                for (size_t k = 0; k < items.size() && rc == MT_OK; ++k) {
+                    const size_t first = rec.launches.size();
+                    const int e = launch_item(ctx, s, items[k], inputs, outputs, nullptr);
+                    if (e != 0 || rec.error != 0)
+                        rc = fail(MT_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString((hipError_t)(e ? e : rec.error)));
+                    if (rec.launches.size() == first) continue;
+                    Piece pc{level[k], first, rec.launches.size() - first, {}, {}, false};
+                    for (auto [t, op] : covered(items[k])) {
+                        if (op == 0) pc.starts_tenant[t] = true;
+                        if (op + 1 == (int)ctx->tenants[t]->model.ops.size()) pc.ends_tenant[t] = true;
+                        if (ctx->tenants[t]->writes_output[op]) pc.output = true;
+                    }
+                    if (names_caller_buffers(ctx, items[k])) plan.io.push_back(RunPlan::IoSite{items[k], pc.first, pc.count});
+                    top = std::max(top, pc.level);
+                    pieces.push_back(pc);
+                }
+            }
+            std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &b) { return a.level < b.level; });
+            const bool fresh = seen.insert(q).second;
+            bool first_packet = true;
+            int prev_level = -1;
+            for (const Piece &pc : pieces)
+                for (size_t l = pc.first; l < pc.first + pc.count; ++l) {
+                    const bool opens = pc.level != prev_level;
+                    prev_level = pc.level;
+                    const int acquire = first_packet && fresh ? HSA_FENCE_SCOPE_SYSTEM : opens ? HSA_FENCE_SCOPE_AGENT : HSA_FENCE_SCOPE_NONE;
+                    const bool system = pc.output;
+                    int signal = -1;
+                    auto need = [&]() { if (signal < 0) signal = new_signal(); return signal; };
+                    if (pc.level == top) p.slice.ends.push_back(need());
+                    if (first_packet && st == first_stage) p.slice.start = need();
+                    if (l + 1 == pc.first + pc.count)
+                        for (int t = 0; t < s->n_tenants; ++t) {
+                            if (pc.starts_tenant[t] && (s->flags & MT_SCHED_TIME_FIRST_OP)) plan.first_op[t] = need();
+                            if (pc.ends_tenant[t] && (s->flags & MT_SCHED_TIME_TENANTS)) plan.last_op[t] = need();
+                        }
+                    const RecordedLaunch &rl = rec.launches[l];
+                    p.emits.push_back(Emit{l, dispatch_head(opens, acquire, system ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_AGENT,
+                                                            rl.grid[2] * rl.block[2] > 1 ? 3 : rl.grid[1] * rl.block[1] > 1 ? 2 : 1), signal});
+                    first_packet = false;
+                }
+            if (st == first_stage) {
+                if (fill_signal >= 0 && q != fill.slice.queue) p.deps.push_back(fill_signal);
+            } else if (!(s->flags & MT_SCHED_HOST_BARRIER)) {
+                for (const Pending &o : pending[sp.prev_stage])
+                    if (o.slice.queue != q) p.deps.insert(p.deps.end(), o.slice.ends.begin(), o.slice.ends.end());
+            }
+            pending[st].push_back(std::move(p));
+        }
     }
-    while (pool.finished.load(std::memory_order_acquire) < n_workers) spin_pause();
-    pool.sched = nullptr;                      // every worker has left the run; nothing may look at the schedule again
-    pool.inputs = nullptr;
-    pool.outputs = nullptr;
-    if (pool.error.load()) {
-        std::lock_guard<std::mutex> lk(pool.mu);
-        return fail(MT_ERR_HIP, pool.error_msg);
+    current_recorder() = outer;
+    if (rc == MT_OK && no_signal) rc = fail(MT_ERR_HIP, "out of completion signals");
+    // ---- argument memory
+    size_t bytes = 0;
+    for (const RecordedLaunch &l : rec.launches) {
+        plan.arg_at.push_back(bytes);
+        bytes += ((size_t)l.code->kernarg_bytes + 63) / 64 * 64;
     }
-    if (err != hipSuccess) return fail(MT_ERR_HIP, std::string("parallel issue: ") + hipGetErrorString(err));
-    if (n_launch) *n_launch = s->n_launches;
+    if (rc == MT_OK && !dev->alloc_args(bytes, &plan.args)) rc = fail(MT_ERR_OUT_OF_MEMORY, "no device memory for kernel arguments");
+    if (rc != MT_OK) {
+        for (hsa_signal_t sg : plan.signals) dev->return_signal(sg);
+        plan = RunPlan{};
+        return rc;
+    }
+    for (size_t l = 0; l < rec.launches.size(); ++l) write_args(rec.launches[l], rec.args.data() + rec.launches[l].arg_off, plan.args.p + plan.arg_at[l]);
+    if (bytes) publish_args(plan.args.p + bytes - 1);
+    // ---- packets
+    auto finish = [&](Pending &p) {
+        for (size_t d = 0; d < p.deps.size(); d += 5) {
+            hsa_signal_t deps[5];
+            int n = 0;
+            for (; n < 5 && d + n < p.deps.size(); ++n) deps[n] = plan.signals[p.deps[d + n]];
+            p.slice.packets.push_back(wait_packet(deps, n));
+        }
+        for (const Emit &e : p.emits)
+            p.slice.packets.push_back(dispatch_packet(rec.launches[e.launch], plan.args.p + plan.arg_at[e.launch], e.head,
+                                                      e.signal >= 0 ? plan.signals[e.signal] : hsa_signal_t{0}));
+        return std::move(p.slice);
+    };
+    plan.stages.resize(s->n_stages);
+    for (int st = 0; st < s->n_stages; ++st) {
+        if (st == first_stage && fill_signal >= 0) plan.stages[st].push_back(finish(fill));
+        for (Pending &p : pending[st]) plan.stages[st].push_back(finish(p));
+    }
+    plan.launches = std::move(rec.launches);
+    plan.in.assign(inputs, inputs + s->n_tenants);
+    plan.out.assign(outputs, outputs + s->n_tenants);
+    plan.valid = true;
     return MT_OK;
+}
+
+// The same plan on other caller buffers: only the arguments that name them are written again.  False if the launches
+// came out differently (then the plan has to be built anew).
+bool rebind_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, RunPlan &plan) {
+    LaunchRecorder rec;
+    rec.dev = ctx->lanes;
+    LaunchRecorder *const outer = current_recorder();
+    current_recorder() = &rec;
+    bool ok = true;
+    for (const RunPlan::IoSite &site : plan.io) {
+        const size_t first = rec.launches.size();
+        ok = ok && launch_item(ctx, s, site.item, inputs, outputs, nullptr) == 0 && rec.error == 0 && rec.launches.size() - first == site.count;
+    }
+    current_recorder() = outer;
+    if (!ok) return false;
+    size_t at = 0;
+    const uint8_t *last = nullptr;
+    for (const RunPlan::IoSite &site : plan.io)
+        for (size_t k = 0; k < site.count; ++k, ++at) {
+            const RecordedLaunch &now = rec.launches[at], &was = plan.launches[site.first + k];
+            if (now.code != was.code || std::memcmp(now.grid, was.grid, sizeof(now.grid)) != 0 || std::memcmp(now.block, was.block, sizeof(now.block)) != 0 ||
+                now.dyn_lds != was.dyn_lds)
+                return false;
+            uint8_t *dst = plan.args.p + plan.arg_at[site.first + k];
+            write_args(now, rec.args.data() + now.arg_off, dst);
+            last = dst + now.code->kernarg_bytes - 1;
+        }
+    if (last) publish_args(last);
+    plan.in.assign(inputs, inputs + s->n_tenants);
+    plan.out.assign(outputs, outputs + s->n_tenants);
+    return true;
 }
 
 }  // namespace
@@ -1095,15 +1055,10 @@ int32_t mt_create(int32_t device, mt_ctx **out) {
         if (!pool.main_stream) HIP_TRY(hipStreamCreateWithFlags(&pool.main_stream, hipStreamNonBlocking));
         c->main_stream = pool.main_stream;
     }
-    HIP_TRY(hipEventCreate(&c->ev_start));
-    for (int s = 0; s < MT_MAX_STAGES; ++s) {
-        HIP_TRY(hipEventCreate(&c->ev_stage[s]));
-        for (int t = 0; t < MT_MAX_TENANTS; ++t) HIP_TRY(hipEventCreate(&c->ev_done[s][t]));
-    }
-    for (int t = 0; t < MT_MAX_TENANTS; ++t) HIP_TRY(hipEventCreate(&c->ev_first[t]));
-    for (int t = 0; t < MT_MAX_TENANTS; ++t) HIP_TRY(hipEventCreate(&c->ev_last[t]));
-    HIP_TRY(hipEventCreate(&c->ev_prof[0]));
-    HIP_TRY(hipEventCreate(&c->ev_prof[1]));
+    for (auto &e : c->ev_prof) HIP_TRY(hipEventCreate(&e));
+    std::string why;
+    c->lanes = LaneDevice::get(device, &why);
+    if (!c->lanes) return fail(MT_ERR_HIP, "hardware queues: " + why);
     *out = c.release();
     return MT_OK;
 }
@@ -1111,52 +1066,31 @@ int32_t mt_create(int32_t device, mt_ctx **out) {
 int32_t mt_destroy(mt_ctx *ctx) {
     if (!ctx) return fail(MT_ERR_INVALID_ARG, "ctx is NULL");
     (void)hipSetDevice(ctx->device);
-    stop_pool(ctx);
     (void)hipDeviceSynchronize();
     for (mt_schedule *ls : ctx->live_schedules) {
-        retire_graphs(ctx, ls);
+        for (RunPlan &p : ls->plan) drop_plan(ctx, p);
+        release_masked(ls);
         ls->ctx = nullptr;
     }
-    for (hipGraphExec_t g : ctx->retired_graphs) (void)hipGraphExecDestroy(g);
-    for (auto &kv : ctx->streams)
-        if (kv.first.share != 0) (void)hipStreamDestroy(kv.second.stream);       // plain streams belong to the process
-    for (hipStream_t ps : ctx->parked_streams) (void)hipStreamDestroy(ps);
+    purge_idle_queues(ctx);
     if (ctx->probe_buf) (void)hipFree(ctx->probe_buf);
-    return_signal_word(ctx->device, ctx->barrier_word);
-    if (ctx->ev_start) (void)hipEventDestroy(ctx->ev_start);
-    for (int s = 0; s < MT_MAX_STAGES; ++s) {
-        if (ctx->ev_stage[s]) (void)hipEventDestroy(ctx->ev_stage[s]);
-        for (int t = 0; t < MT_MAX_TENANTS; ++t)
-            if (ctx->ev_done[s][t]) (void)hipEventDestroy(ctx->ev_done[s][t]);
-    }
-    for (auto e : ctx->ev_first)
+    for (auto &e : ctx->ev_prof)
         if (e) (void)hipEventDestroy(e);
-    for (auto e : ctx->ev_last)
+    for (auto &e : ctx->ev_round)
         if (e) (void)hipEventDestroy(e);
-    for (auto e : ctx->ev_prof)
-        if (e) (void)hipEventDestroy(e);
+    for (auto &row : ctx->ev_done)
+        for (auto &e : row)
+            if (e) (void)hipEventDestroy(e);
     for (auto &t : ctx->tenants)
         if (t->owns_arena && t->arena) (void)hipFree(t->arena);
     delete ctx;
     return MT_OK;
 }
 
-// Graph executables of destroyed schedules are released in batches, each after a device-wide synchronisation, so that a
-// long search under graph replay (two instantiated graphs per candidate) does not keep them all until mt_destroy.
-static int32_t release_retired_graphs(mt_ctx *ctx) {
-    if (ctx->retired_graphs.empty()) return MT_OK;
-    HIP_TRY(hipDeviceSynchronize());
-    for (hipGraphExec_t g : ctx->retired_graphs) (void)hipGraphExecDestroy(g);
-    ctx->retired_graphs.clear();
-    return MT_OK;
-}
-
 int32_t mt_release_idle_streams(mt_ctx *ctx) {
     if (!ctx) return fail(MT_ERR_INVALID_ARG, "ctx is NULL");
-    HIP_TRY(hipSetDevice(ctx->device));
-    int32_t rc = release_retired_graphs(ctx);
-    if (rc != MT_OK) return rc;
-    return purge_idle_streams(ctx);
+    purge_idle_queues(ctx);
+    return MT_OK;
 }
 
 int32_t mt_get_device_info(const mt_ctx *ctx, mt_device_info *out) {
@@ -1204,9 +1138,20 @@ int32_t mt_probe_cu_mask(mt_ctx *ctx, int32_t share, int32_t first_cu, int32_t n
 }
 
 namespace {
+// Events of the machine probes, created when the first of them runs.
+int32_t probe_events(mt_ctx *ctx) {
+    for (auto &e : ctx->ev_round)
+        if (!e) HIP_TRY(hipEventCreate(&e));
+    for (auto &row : ctx->ev_done)
+        for (auto &e : row)
+            if (!e) HIP_TRY(hipEventCreate(&e));
+    return MT_OK;
+}
 // Mean time per launch of n dependent one-workgroup kernels on `st`, measured the way a stage runs: the main stream
 // records a start event, the stream waits for it, runs, records its done event, the host waits for that.
 int32_t dispatch_latency_us(mt_ctx *ctx, hipStream_t st, uint32_t *scratch, int n, float *us) {
+    int32_t rc0 = probe_events(ctx);
+    if (rc0 != MT_OK) return rc0;
     for (int rep = 0; rep < 2; ++rep) {          // first pass warms up
         HIP_TRY(hipEventRecord(ctx->ev_prof[0], ctx->main_stream));
         HIP_TRY(hipStreamWaitEvent(st, ctx->ev_prof[0], 0));
@@ -1227,6 +1172,8 @@ int32_t dispatch_latency_us(mt_ctx *ctx, hipStream_t st, uint32_t *scratch, int 
 int32_t concurrent_latency_us(mt_ctx *ctx, const std::vector<hipStream_t> &streams, int n, float *us, float *host_us) {
     const int m = (int)streams.size();
     if (m < 1 || m > MT_MAX_TENANTS) return fail(MT_ERR_INVALID_ARG, "stream count out of range");
+    int32_t rc0 = probe_events(ctx);
+    if (rc0 != MT_OK) return rc0;
     if (!ctx->probe_buf) HIP_TRY(hipMalloc((void **)&ctx->probe_buf, 256));
     float host = 0.f, worst = 0.f;
     // Measured the way mt_run measures a stage: the main stream only records the start, every stream records its own
@@ -1320,19 +1267,13 @@ int32_t mt_probe_barrier_cost(mt_ctx *ctx, int32_t n_streams, int32_t kind, int3
         HIP_TRY(hipDeviceGetAttribute(&can, hipDeviceAttributeCanUseStreamWaitValue, ctx->device));
         if (!can) return fail(MT_ERR_HIP, "the device does not support stream memory operations");
     }
-    // the plain tenant streams of the process, as mt_run uses them
+    int32_t rc0 = probe_events(ctx);
+    if (rc0 != MT_OK) return rc0;
     std::vector<hipStream_t> st(n_streams);
-    std::vector<StreamKey> keys(n_streams);
     for (int i = 0; i < n_streams; ++i) {
-        int32_t rc = get_stream(ctx, i, 0, 0, &st[i], &keys[i]);
-        if (rc != MT_OK) return rc;
+        rc0 = probe_stream(ctx, i, &st[i]);
+        if (rc0 != MT_OK) return rc0;
     }
-    auto release = [&]() {
-        for (int i = 0; i < n_streams; ++i) {
-            auto it = ctx->streams.find(keys[i]);
-            if (it != ctx->streams.end() && it->second.refs > 0) it->second.refs--;
-        }
-    };
     if (!ctx->probe_buf) HIP_TRY(hipMalloc((void **)&ctx->probe_buf, 256));
     // one word per stream (kind 2) or one in all (kind 3), borrowed from the process's pool and zeroed by the host
     uint32_t *words[MT_MAX_TENANTS] = {};
@@ -1343,7 +1284,7 @@ int32_t mt_probe_barrier_cost(mt_ctx *ctx, int32_t n_streams, int32_t kind, int3
         int32_t rc = take_signal_word(ctx->device, &words[i]);
         hipError_t e = rc == MT_OK ? hipMemset(words[i], 0, 8) : hipSuccess;
         if (rc != MT_OK || e != hipSuccess) {
-            free_words(); release();
+            free_words();
             return rc != MT_OK ? rc : fail(MT_ERR_HIP, std::string("signal memory: ") + hipGetErrorString(e));
         }
     }
@@ -1378,8 +1319,8 @@ int32_t mt_probe_barrier_cost(mt_ctx *ctx, int32_t n_streams, int32_t kind, int3
                     e = hipEventRecord(ev[i], st[i]);
                     if (e == hipSuccess) e = hipStreamWaitEvent(ctx->main_stream, ev[i], 0);
                 }
-                if (e == hipSuccess) e = hipEventRecord(ctx->ev_stage[r & 1], ctx->main_stream);
-                for (int i = 0; i < n_streams && e == hipSuccess; ++i) e = hipStreamWaitEvent(st[i], ctx->ev_stage[r & 1], 0);
+                if (e == hipSuccess) e = hipEventRecord(ctx->ev_round[r & 1], ctx->main_stream);
+                for (int i = 0; i < n_streams && e == hipSuccess; ++i) e = hipStreamWaitEvent(st[i], ctx->ev_round[r & 1], 0);
             }
         }
         for (int i = 0; i < n_streams && e == hipSuccess; ++i) {
@@ -1392,7 +1333,6 @@ int32_t mt_probe_barrier_cost(mt_ctx *ctx, int32_t n_streams, int32_t kind, int3
     }
     (void)hipDeviceSynchronize();
     free_words();
-    release();
     if (e != hipSuccess) return fail(MT_ERR_HIP, std::string("barrier probe: ") + hipGetErrorString(e));
     *us_per_round = ms * 1e3f / (float)rounds;
     return MT_OK;
@@ -1855,24 +1795,32 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
     std::unique_ptr<mt_schedule> s(new mt_schedule);
     s->ctx = ctx; s->n_tenants = n_tenants; s->n_stages = n_stages; s->flags = flags;
     for (int i = 0; i < n_tenants; ++i) s->prio[i] = (flags & MT_SCHED_PRIORITIZE_SHORT) ? -1 : 0;
+    // streams restricted to a share of the units have queues of their own
     const bool per_stage = (flags & MT_SCHED_SHARE_PER_STAGE) != 0;
-    s->stream_at.assign(n_stages, {});
-    struct Acquired { StreamKey key; int share, first_cu; };
-    std::vector<std::array<Acquired, MT_MAX_TENANTS>> acq(per_stage ? n_stages : 1);
-    for (int st = 0; st < (per_stage ? n_stages : 1); ++st) {
+    std::vector<std::pair<int, int>> units;
+    std::vector<std::array<int, MT_MAX_TENANTS>> unit_of(n_stages);          // index into `units`, -1: a plain lane
+    for (int st = 0; st < n_stages; ++st) {
         int first_cu = 0;
         for (int i = 0; i < n_tenants; ++i) {
             const int share = (cu_share && !(flags & MT_SCHED_GRAPH)) ? cu_share[(per_stage ? st * n_tenants : 0) + i] : 0;
-            StreamKey key;
-            rc = get_stream(ctx, i, share, first_cu, &s->stream_at[st][i], &key);
-            if (rc != MT_OK) { release_streams(s.get()); return rc; }
-            s->stream_keys.push_back(key);
-            acq[st][i] = Acquired{key, share, first_cu};
+            unit_of[st][i] = -1;
+            if (share > 0) {
+                // tenants with equal masks still get a queue each: slot i of the list belongs to tenant i alone
+                const std::pair<int, int> want{share, first_cu};
+                for (int prev = 0; prev < st && unit_of[st][i] < 0; ++prev)
+                    if (unit_of[prev][i] >= 0 && units[unit_of[prev][i]] == want) unit_of[st][i] = unit_of[prev][i];
+                if (unit_of[st][i] < 0) {
+                    unit_of[st][i] = (int)units.size();
+                    units.push_back(want);
+                }
+            }
             first_cu = (first_cu + share) % cus;
         }
     }
-    if (!per_stage)
-        for (int st = 1; st < n_stages; ++st) s->stream_at[st] = s->stream_at[0];
+    if (!units.empty()) {
+        rc = acquire_masked(ctx, units, &s->masked);
+        if (rc != MT_OK) return rc;
+    }
     std::vector<int32_t> slices((size_t)n_stages * n_tenants * 2);
     expand_pointers(n_tenants, lens, n_stages, pointers, slices.data());
     s->stages.resize(n_stages);
@@ -1881,7 +1829,8 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
         StagePlan &sp = s->stages[st];
         sp.items = issue_order(n_tenants, &slices[(size_t)st * n_tenants * 2], conc, order);
         // On request, two neighbouring operators issued in the same stage run as one launch.
-        auto mark_pairs = [&](std::vector<IssueItem> &items, bool count) {
+        for (IssueItem &it : sp.items) it.group = it.tenant;
+        auto mark_pairs = [&](std::vector<IssueItem> &items) {
             for (int pass = 0; pass < 3; ++pass) {   // 1x1 + depthwise pairs before depthwise + 1x1: a depthwise operator joins one neighbour only
                 const int want = pass == 0 ? MT_SCHED_FUSE_EXPAND : pass == 1 ? MT_SCHED_FUSE_DEPTHWISE : MT_SCHED_FUSE_POOL;
                 if (!(flags & want)) continue;
@@ -1897,14 +1846,14 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
                                 // the absorbed operator is skipped; the other one launches the pair
                                 items[k2].fuse = pass == 0 ? 3 : pass == 1 ? 2 : 1;
                                 it.fuse = pass == 2 ? 4 : 1;
-                                if (count) ++s->n_fused;
+                                ++s->n_fused;
                             }
                             break;
                         }
                 }
             }
         };
-        mark_pairs(sp.items, true);
+        mark_pairs(sp.items);
         // Co-issue: up to `group` tenants that share a stream and whose slices have the same operator range walk them
         // together; operator i of the others runs inside the launch of operator i of the first where they can
         // (coissue_pair_ok with the first), else right after it as a launch of its own.  The first tenant's items carry
@@ -1943,6 +1892,7 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
                         int nm = 0;
                         for (size_t r = 0; r < rest.size(); ++r) {
                             IssueItem other = others[r][it.op - ba];
+                            other.group = ta;
                             if (it.fuse == 0 && other.fuse == 0 &&
                                 coissue_pair_ok(ctx->tenants[ta]->args[it.op], ctx->tenants[rest[r]]->args[it.op])) {
                                 merged[head].mates[nm++] = rest[r];
@@ -1956,116 +1906,20 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
                 }
             }
         }
-        if ((flags & MT_SCHED_GRAPH) && n_tenants > 1) {
-            s->alt_items.resize(n_stages);
-            s->alt_items[st] = issue_order(n_tenants, &slices[(size_t)st * n_tenants * 2], conc, order == MT_ISSUE_BFS ? MT_ISSUE_DFS : MT_ISSUE_BFS);
-            mark_pairs(s->alt_items[st], false);
-        }
         for (const IssueItem &it : sp.items)
             if (std::find(sp.streams.begin(), sp.streams.end(), it.stream) == sp.streams.end()) sp.streams.push_back(it.stream);
         std::sort(sp.streams.begin(), sp.streams.end());
         sp.by_stream.assign(n_tenants, {});
         for (const IssueItem &it : sp.items) sp.by_stream[it.stream].push_back(it);
+        for (int sm : sp.streams)
+            if (unit_of[st][sm] >= 0) sp.queue_of[sm] = s->masked->queues[unit_of[st][sm]];
+        lane_plan(ctx->lanes, sp);
         s->n_launches += (int)sp.items.size();
     }
     for (int st = 0, last = -1; st < n_stages; ++st) {
         s->stages[st].prev_stage = last;
         if (!s->stages[st].items.empty()) last = st;
         s->end_stage = last;
-    }
-    if (flags & MT_SCHED_COUNTER_BARRIER) {
-        s->arrivals_upto.assign(n_stages, 0);
-        uint32_t sum = 0;
-        for (int st = 0; st < n_stages; ++st) {
-            sum += (uint32_t)s->stages[st].streams.size();
-            s->arrivals_upto[st] = sum;
-        }
-        if (!ctx->barrier_word) {
-            rc = take_signal_word(ctx->device, &ctx->barrier_word);
-            if (rc != MT_OK) { release_streams(s.get()); return rc; }
-        }
-    }
-    // A schedule that uses masked streams checks its streams together (plain streams are placed by dispatch pipe when
-    // they are created, see PlainPool; masked ones are not).  Every stream launches one probe kernel per round; a round
-    // of more than 1.8 single-stream launches per started group of four streams, twice in a row and not explained by
-    // the issuing thread's own launch time, means that streams of the set take turns on one pipe.  The stream whose
-    // removal helps most is then parked and replaced (a masked one only if no other schedule holds it), up to three times.
-    bool any_masked = false;
-    for (const auto &row : acq)
-        for (int i = 0; i < n_tenants; ++i) any_masked = any_masked || row[i].share != 0;
-    if (!(flags & MT_SCHED_GRAPH) && any_masked) {
-        struct Used { int row, idx; };
-        std::vector<Used> used;
-        std::vector<hipStream_t> all;
-        auto collect = [&]() {
-            used.clear();
-            all.clear();
-            for (int st = 0; st < n_stages; ++st)
-                for (int sm : s->stages[st].streams) {
-                    hipStream_t h = s->stream_at[st][sm];
-                    if (std::find(all.begin(), all.end(), h) == all.end() && (int)all.size() < MT_MAX_TENANTS) {
-                        all.push_back(h);
-                        used.push_back(Used{per_stage ? st : 0, sm});
-                    }
-                }
-        };
-        auto measure = [&](const std::vector<hipStream_t> &set, float *us, bool *bad) -> int32_t {
-            float host_us = 0.f;
-            const float limit = 1.8f * ctx->best_dispatch_us * (float)((set.size() + 3) / 4);
-            for (int rep = 0; rep < 2; ++rep) {          // a single high reading is measured again before it counts
-                int32_t r = concurrent_latency_us(ctx, set, 8, us, &host_us);
-                if (r != MT_OK) return r;
-                *bad = ctx->best_dispatch_us > 0.f && *us > limit && *us > 1.3f * host_us;
-                if (!*bad) break;
-            }
-            return MT_OK;
-        };
-        collect();
-        for (int attempt = 0; attempt < 3 && all.size() > 1; ++attempt) {
-            if (ctx->best_dispatch_us == 0.f) {         // a context that only met pooled streams so far has no reference yet
-                float us1 = 0.f;
-                if (!ctx->probe_buf) HIP_TRY(hipMalloc((void **)&ctx->probe_buf, 256));
-                rc = dispatch_latency_us(ctx, all[0], ctx->probe_buf, 12, &us1);
-                if (rc != MT_OK) { release_streams(s.get()); return rc; }
-                ctx->best_dispatch_us = us1;
-            }
-            float us = 0.f;
-            bool bad = false;
-            rc = measure(all, &us, &bad);
-            if (rc != MT_OK) { release_streams(s.get()); return rc; }
-            if (!bad) break;
-            // leave one out: the stream without which the rest runs fastest is the one to replace
-            int culprit = (int)all.size() - 1;
-            float best_rest = 1e30f;
-            for (size_t j = 0; j < all.size() && all.size() > 2; ++j) {
-                std::vector<hipStream_t> rest;
-                for (size_t k = 0; k < all.size(); ++k)
-                    if (k != j) rest.push_back(all[k]);
-                float host_us = 0.f, r_us = 0.f;
-                rc = concurrent_latency_us(ctx, rest, 8, &r_us, &host_us);
-                if (rc != MT_OK) { release_streams(s.get()); return rc; }
-                if (r_us < best_rest) { best_rest = r_us; culprit = (int)j; }
-            }
-            const Used u = used[culprit];
-            const Acquired &aq = acq[u.row][u.idx];
-            auto it = ctx->streams.find(aq.key);
-            if (it == ctx->streams.end()) break;
-            if (aq.share != 0 && it->second.refs != 1) break;          // another schedule launches on this masked stream
-            hipStream_t fresh = nullptr;
-            rc = make_stream(ctx, u.idx, aq.share, aq.first_cu, &fresh);
-            if (rc != MT_OK) { release_streams(s.get()); return rc; }
-            if (aq.share == 0) {
-                PlainPool &pool = plain_pool(ctx->device);
-                pool.parked.push_back(it->second.stream);           // never destroyed: other schedules may hold it
-                pool.tenant[u.idx] = fresh;
-            } else {
-                ctx->parked_streams.push_back(it->second.stream);
-            }
-            it->second.stream = fresh;
-            for (int st = 0; st < n_stages; ++st)
-                if (!per_stage || st == u.row) s->stream_at[st][u.idx] = fresh;
-            collect();
-        }
     }
     ctx->live_schedules.insert(s.get());
     *out = s.release();
@@ -2077,17 +1931,16 @@ int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio) {
     for (int i = 0; i < s->n_tenants; ++i)
         if (prio[i] < -1 || prio[i] > 3) return fail(MT_ERR_INVALID_ARG, "wave priority must be -1 (by kernel size) or 0..3");
     for (int i = 0; i < s->n_tenants; ++i) s->prio[i] = prio[i];
-    if (s->ctx) retire_graphs(s->ctx, s);            // captured launches carry the old value
-    s->cap_in.clear();
-    s->cap_out.clear();
+    if (s->ctx)
+        for (RunPlan &p : s->plan) drop_plan(s->ctx, p);      // its launches carry the old value
     return MT_OK;
 }
 
 int32_t mt_schedule_destroy(mt_schedule *s) {
     if (!s) return fail(MT_ERR_INVALID_ARG, "schedule is NULL");
     if (s->ctx) {
-        retire_graphs(s->ctx, s);
-        release_streams(s);
+        for (RunPlan &p : s->plan) drop_plan(s->ctx, p);
+        release_masked(s);
         s->ctx->live_schedules.erase(s);
     }
     delete s;
@@ -2095,10 +1948,18 @@ int32_t mt_schedule_destroy(mt_schedule *s) {
 }
 
 // ---- run -------------------------------------------------------------------------------------
-static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm);
+static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm, bool static_scratch, size_t counter_bytes);
 
 int32_t mt_run(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm) {
-    return run_pass(ctx, s, inputs, outputs, tm);
+    if (!ctx || !s || !inputs || !outputs) return fail(MT_ERR_INVALID_ARG, "NULL argument");
+    if (s->ctx != ctx) return fail(MT_ERR_INVALID_ARG, "schedule belongs to another (or a destroyed) context");
+    // The lanes start within microseconds and know nothing of HIP streams: what the caller has queued on the default stream
+    // (a copy into an input, a fill of an output) is waited for first.
+    if (hipStreamQuery(nullptr) != hipSuccess) {
+        (void)hipGetLastError();
+        HIP_TRY(hipStreamSynchronize(nullptr));
+    }
+    return run_pass(ctx, s, inputs, outputs, tm, false, 0);
 }
 
 int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm) {
@@ -2123,142 +1984,75 @@ int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *in
         s->st_cnt_base[i] = cnt_at; cnt_at += ctx->tenants[i]->st_cnt_bytes;
         s->st_ws_base[i] = ws_at; ws_at += ctx->tenants[i]->st_ws_bytes;
     }
-    if (cnt_total > 0) {
-        // The array keeps what the last call (of any context) left; counters must start at zero.  The fill runs on the
-        // main stream ahead of the start event that every tenant stream waits for.
-        const int fe = launch_fill_u32((uint32_t *)base, cnt_total / sizeof(uint32_t), 0u, ctx->main_stream);
-        if (fe != 0) return fail(MT_ERR_HIP, std::string("clearing the counters: ") + hipGetErrorString((hipError_t)fe));
-    }
     s->st_base = (uint8_t *)base;
-    const int32_t rc = run_pass(ctx, s, inputs, outputs, tm);
+    const int32_t rc = run_pass(ctx, s, inputs, outputs, tm, true, cnt_total);
     s->st_base = nullptr;
     return rc;
 }
 
-static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm) {
-    if (!ctx || !s || !inputs || !outputs) return fail(MT_ERR_INVALID_ARG, "NULL argument");
-    if (s->ctx != ctx) return fail(MT_ERR_INVALID_ARG, "schedule belongs to another (or a destroyed) context");
+static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm, bool static_scratch, size_t counter_bytes) {
     for (int i = 0; i < s->n_tenants; ++i) {
         if (!inputs[i] || !outputs[i]) return fail(MT_ERR_INVALID_ARG, "NULL input or output buffer");
         if (((uintptr_t)inputs[i] % 16) || ((uintptr_t)outputs[i] % 16)) return fail(MT_ERR_INVALID_ARG, "buffers must be 16-byte aligned");
     }
-    HIP_TRY(hipSetDevice(ctx->device));
     const auto t0 = std::chrono::steady_clock::now();
-    int launches = 0;
-    if (s->flags & MT_SCHED_GRAPH) {
-        bool same = s->graph_exec && (int)s->cap_in.size() == s->n_tenants;
-        for (int i = 0; same && i < s->n_tenants; ++i) same = s->cap_in[i] == inputs[i] && s->cap_out[i] == outputs[i];
-        if (!same) {
-            retire_graphs(ctx, s);
-            // Replay does not know an issue order, only the capture does, and on this runtime the replay of a schedule
-            // captured in one order is sometimes several times slower than that of the other (measured with more
-            // than 4 hardware queues per process: 1 to 2.7 ms against 0.4 to 0.6 ms, in either direction).  Both orders
-            // are therefore captured, each is replayed three times, and the faster graph is kept.
-            const int n_orders = s->alt_items.empty() ? 1 : 2;
-            hipGraphExec_t exec[2] = {nullptr, nullptr};
-            float best_ms[2] = {0.f, 0.f};
-            for (int o = 0; o < n_orders; ++o) {
-                hipGraph_t graph = nullptr;
-                HIP_TRY(hipStreamBeginCapture(ctx->main_stream, hipStreamCaptureModeRelaxed));
-                int32_t rc = issue_schedule(ctx, s, inputs, outputs, &launches, o == 1);
-                hipError_t e = hipStreamEndCapture(ctx->main_stream, &graph);
-                if (rc == MT_OK && e != hipSuccess) rc = fail(MT_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-                if (rc == MT_OK) {
-                    e = hipGraphInstantiate(&exec[o], graph, nullptr, nullptr, 0);
-                    if (e != hipSuccess) rc = fail(MT_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-                }
-                if (graph) (void)hipGraphDestroy(graph);
-                if (rc != MT_OK) {
-                    for (hipGraphExec_t g : exec)
-                        if (g) ctx->retired_graphs.push_back(g);
-                    return rc;
-                }
-            }
-            int keep = 0;
-            if (n_orders == 2) {
-                for (int o = 0; o < 2; ++o)
-                    for (int rep = 0; rep < 3; ++rep) {
-                        float ms = 0.f;
-                        HIP_TRY(hipEventRecord(ctx->ev_prof[0], ctx->main_stream));
-                        HIP_TRY(hipGraphLaunch(exec[o], ctx->main_stream));
-                        HIP_TRY(hipEventRecord(ctx->ev_prof[1], ctx->main_stream));
-                        HIP_TRY(hipEventSynchronize(ctx->ev_prof[1]));
-                        HIP_TRY(hipEventElapsedTime(&ms, ctx->ev_prof[0], ctx->ev_prof[1]));
-                        if (rep == 0 || ms < best_ms[o]) best_ms[o] = ms;
-                    }
-                keep = best_ms[1] < best_ms[0] ? 1 : 0;
-                ctx->retired_graphs.push_back(exec[1 - keep]);
-            }
-            s->graph_exec = exec[keep];
-            s->cap_in.assign(inputs, inputs + s->n_tenants);
-            s->cap_out.assign(outputs, outputs + s->n_tenants);
-        }
-        launches = s->n_launches;
-        HIP_TRY(hipEventRecord(ctx->ev_prof[0], ctx->main_stream));
-        HIP_TRY(hipGraphLaunch(s->graph_exec, ctx->main_stream));
-        HIP_TRY(hipEventRecord(ctx->ev_prof[1], ctx->main_stream));
-    } else {
-        if (s->flags & MT_SCHED_STREAM_GRAPHS) {
-            bool same = !s->slice_exec.empty() && (int)s->cap_in.size() == s->n_tenants;
-            for (int i = 0; same && i < s->n_tenants; ++i) same = s->cap_in[i] == inputs[i] && s->cap_out[i] == outputs[i];
-            if (!same) {
-                int32_t rc = capture_slice_graphs(ctx, s, inputs, outputs);
-                if (rc != MT_OK) return rc;
-            }
-        }
-        int32_t rc = (s->flags & MT_SCHED_PARALLEL_ISSUE) ? issue_schedule_parallel(ctx, s, inputs, outputs, &launches)
-                                                          : issue_schedule(ctx, s, inputs, outputs, &launches);
+    LaneDevice *dev = ctx->lanes;
+    RunPlan &plan = s->plan[static_scratch ? 1 : 0];
+    bool same = plan.valid;
+    for (int i = 0; same && i < s->n_tenants; ++i) same = plan.in[i] == inputs[i] && plan.out[i] == outputs[i];
+    if (!same && !(plan.valid && rebind_plan(ctx, s, inputs, outputs, plan))) {
+        int32_t rc = build_plan(ctx, s, inputs, outputs, plan, static_scratch, counter_bytes);
         if (rc != MT_OK) return rc;
     }
-    const auto t1 = std::chrono::steady_clock::now();
-    if (s->flags & MT_SCHED_GRAPH) {
-        HIP_TRY(hipEventSynchronize(ctx->ev_prof[1]));
-    } else if (ends_on_streams(s)) {
-        for (int sm : s->stages[s->end_stage].streams) HIP_TRY(hipEventSynchronize(ctx->ev_done[s->end_stage][sm]));
-    } else {
-        HIP_TRY(hipEventSynchronize(ctx->ev_stage[s->n_stages - 1]));
+    auto broken = [&]() { return fail(MT_ERR_HIP, "a hardware queue reported an error"); };
+    if (dev->failed()) return broken();
+    for (hsa_signal_t sg : plan.signals) hsa_signal_store_relaxed(sg, 1);
+    for (int st = 0; st < s->n_stages; ++st) {
+        const StagePlan &sp = s->stages[st];
+        if (sp.items.empty()) continue;
+        if ((s->flags & MT_SCHED_HOST_BARRIER) && sp.prev_stage >= 0)
+            for (const LaneSlice &l : plan.stages[sp.prev_stage])
+                for (int e : l.ends)
+                    if (!dev->wait(plan.signals[e])) return broken();
+        for (const LaneSlice &l : plan.stages[st])
+            if (!dev->submit(l.queue, l.packets.data(), l.packets.size())) return broken();
     }
-    if (tm) {
-        std::memset(tm, 0, sizeof(*tm));
-        tm->n_launches = launches;
-        tm->n_fused = s->n_fused;
-        tm->n_stages = s->n_stages;
-        tm->host_issue_ms = std::chrono::duration<float, std::milli>(t1 - t0).count();
-        if (s->flags & MT_SCHED_GRAPH) {
-            // events recorded inside a captured graph cannot be queried: only the end-to-end time is available
-            HIP_TRY(hipEventElapsedTime(&tm->makespan_ms, ctx->ev_prof[0], ctx->ev_prof[1]));
-        } else {
-            if (ends_on_streams(s)) {
-                float before = 0.f;                    // end of the stage before, from the start
-                for (int st = 0; st <= s->end_stage; ++st) {
-                    float end = before;
-                    for (int sm : s->stages[st].streams) {             // the latest end over the streams of the stage
-                        float ms = 0.f;
-                        HIP_TRY(hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_done[st][sm]));
-                        end = std::max(end, ms);
-                    }
-                    tm->stage_ms[st] = end - before;   // 0 for a stage that launches nothing
-                    before = end;
-                }
-                tm->makespan_ms = before;
-            } else {
-                HIP_TRY(hipEventElapsedTime(&tm->makespan_ms, ctx->ev_start, ctx->ev_stage[s->n_stages - 1]));
+    const auto t1 = std::chrono::steady_clock::now();
+    if (s->end_stage >= 0)
+        for (const LaneSlice &l : plan.stages[s->end_stage])
+            for (int e : l.ends)
+                if (!dev->wait(plan.signals[e])) return broken();
+    if (!tm) return MT_OK;
+    std::memset(tm, 0, sizeof(*tm));
+    tm->n_launches = s->n_launches;
+    tm->n_fused = s->n_fused;
+    tm->n_stages = s->n_stages;
+    tm->host_issue_ms = std::chrono::duration<float, std::milli>(t1 - t0).count();
+    // from the earliest start of a first kernel; a stage ends with its latest kernel
+    double start = 0, a = 0, b = 0;
+    bool have = false;
+    for (int st = 0; st <= s->end_stage && !have; ++st)
+        for (const LaneSlice &l : plan.stages[st])
+            if (l.start >= 0) {
+                dev->times(plan.signals[l.start], &a, &b);
+                start = have ? std::min(start, a) : a;
+                have = true;
             }
-            if (s->flags & MT_SCHED_TIME_FIRST_OP)
-                for (int i = 0; i < s->n_tenants; ++i)
-                    if (!ctx->tenants[i]->model.ops.empty())
-                        HIP_TRY(hipEventElapsedTime(&tm->first_op_done_ms[i], ctx->ev_start, ctx->ev_first[i]));
-            if (s->flags & MT_SCHED_TIME_TENANTS)
-                for (int i = 0; i < s->n_tenants; ++i)
-                    if (!ctx->tenants[i]->model.ops.empty())
-                        HIP_TRY(hipEventElapsedTime(&tm->tenant_done_ms[i], ctx->ev_start, ctx->ev_last[i]));
-            hipEvent_t prev = ctx->ev_start;
-            if (s->n_stages == 1) tm->stage_ms[0] = tm->makespan_ms;      // the same pair of events
-            for (int st = 0; st < s->n_stages && s->n_stages > 1 && !ends_on_streams(s); ++st) {
-                HIP_TRY(hipEventElapsedTime(&tm->stage_ms[st], prev, ctx->ev_stage[st]));
-                prev = ctx->ev_stage[st];
+    double before = 0;
+    for (int st = 0; st <= s->end_stage; ++st) {
+        double end = before;
+        for (const LaneSlice &l : plan.stages[st])
+            for (int e : l.ends) {
+                dev->times(plan.signals[e], &a, &b);
+                end = std::max(end, b - start);
             }
-        }
+        tm->stage_ms[st] = (float)(end - before);          // 0 for a stage that launches nothing
+        before = end;
+    }
+    tm->makespan_ms = (float)before;
+    for (int i = 0; i < s->n_tenants; ++i) {
+        if (plan.first_op[i] >= 0) { dev->times(plan.signals[plan.first_op[i]], &a, &b); tm->first_op_done_ms[i] = (float)(b - start); }
+        if (plan.last_op[i] >= 0) { dev->times(plan.signals[plan.last_op[i]], &a, &b); tm->tenant_done_ms[i] = (float)(b - start); }
     }
     return MT_OK;
 }
@@ -2318,7 +2112,6 @@ double profile_schedule(ProfileCost *pc, const int32_t *pointers, const int32_t 
         if (r >= pc->o->warmup) samples.push_back(tm.makespan_ms);
     }
     mt_schedule_destroy(s);
-    if (pc->rc == MT_OK && pc->ctx->retired_graphs.size() >= 64) pc->rc = release_retired_graphs(pc->ctx);
     double c = 1e30;
     if (pc->rc == MT_OK && !samples.empty()) {
         std::sort(samples.begin(), samples.end());
@@ -2483,8 +2276,7 @@ int32_t mt_search(mt_ctx *ctx, const mt_search_opts *opts, const void *const *in
         }
     }
     if (opts->cu_share_rounds > 0) {
-        rc = purge_idle_streams(ctx);     // leave the caller a process with few hardware queues
-        if (rc != MT_OK) return rc;
+        purge_idle_queues(ctx);           // leave the caller a process with few hardware queues
         bool masked = false;
         for (int i = 0; i < n; ++i) masked = masked || shares[i] != 0;
         if (masked) {
@@ -2497,8 +2289,7 @@ int32_t mt_search(mt_ctx *ctx, const mt_search_opts *opts, const void *const *in
                 again = profile_schedule(&pc, best_pointers, shares);
                 if (pc.rc != MT_OK) return pc.rc;
                 if (again <= 1.1 * cost || again < unmasked_cost) break;
-                rc = purge_idle_streams(ctx);
-                if (rc != MT_OK) return rc;
+                purge_idle_queues(ctx);
             }
             if (again < unmasked_cost) {
                 cost = again;
@@ -2506,8 +2297,7 @@ int32_t mt_search(mt_ctx *ctx, const mt_search_opts *opts, const void *const *in
                 std::memcpy(best_pointers, unmasked_pointers.data(), sizeof(int32_t) * unmasked_pointers.size());
                 std::memset(shares, 0, sizeof(shares));
                 cost = unmasked_cost;
-                rc = purge_idle_streams(ctx);
-                if (rc != MT_OK) return rc;
+                purge_idle_queues(ctx);
             }
         }
     }
@@ -2538,8 +2328,7 @@ int32_t mt_search(mt_ctx *ctx, const mt_search_opts *opts, const void *const *in
                 std::memcpy(prio, prio_u, sizeof(int32_t) * n);
                 std::memcpy(best_pointers, unmasked_pointers.data(), sizeof(int32_t) * unmasked_pointers.size());
                 std::memset(shares, 0, sizeof(shares));
-                rc = purge_idle_streams(ctx);
-                if (rc != MT_OK) return rc;
+                purge_idle_queues(ctx);
             }
         }
     }
@@ -2612,8 +2401,6 @@ int32_t mt_search(mt_ctx *ctx, const mt_search_opts *opts, const void *const *in
             }
         }
     }
-    rc = release_retired_graphs(ctx);          // what the candidates of a search under graph replay left behind
-    if (rc != MT_OK) return rc;
     if (best_wave_priority) std::memcpy(best_wave_priority, prio, sizeof(int32_t) * n);
     if (best_concurrency) std::memcpy(best_concurrency, conc, sizeof(int32_t) * opts->n_stages);
     if (best_cu_share) std::memcpy(best_cu_share, shares, sizeof(int32_t) * n);
