@@ -46,7 +46,7 @@ inline bool is_gemm_kernel(int32_t id);
 // The kernel and tile of an operator are a pure function of its shape and storage type, never of the
 // stream, CU share or stage it runs in; that is what makes outputs bit-identical across schedules.
 enum KernelId : int32_t {
-    K_CONV_DIRECT = 0,      // one thread per output element, any shape, any storage type
+    K_CONV_DIRECT = 0,      // fp32: operands straight from memory to the matrix cores (wk = tiling, 1 ..), or one thread per output element (wk = 0)
     K_IGEMM_128x128 = 1,    // MFMA implicit GEMM, 128 output channels x 128 pixels per workgroup
     K_IGEMM_64x64 = 2,      // MFMA implicit GEMM, 64 x 64
     K_IGEMM_64x16 = 3,      // MFMA implicit GEMM, 64 output channels x 16 pixels (tiny-M layers, FC)
@@ -90,7 +90,7 @@ struct OpArgs {
     int32_t k_pad;               // packed weight row length (multiple of the k tile)
     int32_t n_pad;               // packed weight rows (multiple of the channel tile)
     int32_t split_k;
-    int32_t wk;                  // wave groups that share an output tile (64x64 tile only): 1 or 2
+    int32_t wk;                  // wave groups that share an output tile (64x64 tile only): 1 or 2; fp32 convolution: its tiling (dconv_f32_plan)
     int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
     int32_t pool2;               // 1: the epilogue applies a 2x2 / stride-2 max pooling; pixels are then walked quad by quad and y is the pooled tensor
     // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
@@ -107,6 +107,9 @@ struct OpArgs {
     float *ws;                   // split-K partial sums
     uint32_t *counters;          // split-K arrival counters, one per output tile, zero between launches
 };
+
+// Kernels whose filter bank is packed as [groups][n_pad][k_pad], rows zero padded.
+inline bool packed_rows(const OpArgs &a) { return is_gemm_kernel(a.kernel_id) || (a.kernel_id == K_CONV_DIRECT && a.wk > 0); }
 
 // Up to four operators of different tenants that run as one launch (co-issue): workgroups with blockIdx.y == i work on
 // a[i].  All of them have the same kernel, tile, split and launch shape; only their buffers differ.
@@ -152,6 +155,12 @@ int pconv_patch_pixels(int W);
 int launch_pconv(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
 bool rowb_patch_form(const OpArgs &a);   // 3x3, stride 1: activations staged once per tile as an input patch in LDS
 int launch_rowb(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
+
+// fp32 convolution on the matrix cores: the tiling for an M x K x gemm_k problem with C input channels (0: none, the layer
+// runs on one thread per output), its workgroups, its launcher.
+int dconv_f32_plan(int M, int K, int gemm_k, int C);
+int dconv_f32_grid(int form, int M, int K);
+int launch_dconv_f32(const OpArgs &a, void *stream);
 
 // Launchers (defined in the .hip files).  Return a hipError_t as int.
 int launch_direct(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);

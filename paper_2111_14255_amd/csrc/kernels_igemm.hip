@@ -642,11 +642,11 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
 // Matrix-vector form for 1x1 / fully connected layers with at most 8 output pixels (batch <= 8): the filter
 // bank is streamed once with 16-byte loads, ROWS output channels per wavefront, the lanes stride along the
 // reduction index and combine through a fixed butterfly of wavefront shuffles.  Bandwidth bound.
-template <typename T>
-__device__ __forceinline__ void unpack8(u32x4 v, float (&f)[8]) {
+template <typename T, int V>
+__device__ __forceinline__ void unpack16(u32x4 v, float (&f)[V]) {
     const T *e = reinterpret_cast<const T *>(&v);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = to_f32(e[i]);
+    for (int i = 0; i < V; ++i) f[i] = to_f32(e[i]);
 }
 
 template <typename T, int MB, int ROWS, bool STREAM_W>
@@ -656,9 +656,10 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
     const int lane = threadIdx.x & 63;
     const int k0 = wave * ROWS;
     if (k0 >= a.K) return;                           // whole wave
-    const int J = a.gemm_k;                          // multiple of 8
+    constexpr int V = 16 / sizeof(T);                // elements of a 16-byte piece
+    const int J = a.gemm_k;                          // multiple of V
     const T *x = (const T *)a.x;
-    const uint16_t *wp = (const uint16_t *)a.w;
+    const T *wp = (const T *)a.w;
     float acc[ROWS][MB];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -668,11 +669,11 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) bias_k[r] = a.bias[k0 + r];
     constexpr int UNROLL = 4;
-    for (int j0 = lane * 8; j0 < J; j0 += 64 * 8 * UNROLL) {
+    for (int j0 = lane * V; j0 < J; j0 += 64 * V * UNROLL) {
         u32x4 wv[UNROLL][ROWS], xv[UNROLL][MB];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            const int j = j0 + u * 64 * 8;
+            const int j = j0 + u * 64 * V;
             const bool ok = j < J;
 #pragma unroll
             for (int r = 0; r < ROWS; ++r)      // rows beyond K exist in the padded bank (zeros)
@@ -689,17 +690,17 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            float xf[MB][8];
+            float xf[MB][V];
 #pragma unroll
-            for (int m = 0; m < MB; ++m) unpack8<T>(xv[u][m], xf[m]);
+            for (int m = 0; m < MB; ++m) unpack16<T, V>(xv[u][m], xf[m]);
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
-                float wf[8];
-                unpack8<T>(wv[u][r], wf);
+                float wf[V];
+                unpack16<T, V>(wv[u][r], wf);
 #pragma unroll
                 for (int m = 0; m < MB; ++m)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[r][m] = fmaf(wf[e], xf[m][e], acc[r][m]);
+                    for (int e = 0; e < V; ++e) acc[r][m] = fmaf(wf[e], xf[m][e], acc[r][m]);
             }
         }
     }
@@ -883,6 +884,20 @@ static void launch_cfg(const OpArgs &a, hipStream_t st, const OpArgs *mate, int 
 }
 
 template <typename T>
+static void launch_gemv(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
+    const dim3 grid(a.grid_x), block(256);
+    const bool stream_w = (int64_t)a.n_pad * a.k_pad * (int)sizeof(T) >= (16ll << 20);
+    auto go = [&]<int MB>() {
+        if (stream_w) MT_LAUNCH((gemv_kernel<T, MB, 2, true>), (gemv_pair_kernel<T, MB, 2, true>), grid, block, st, a, mate);
+        else MT_LAUNCH((gemv_kernel<T, MB, 2, false>), (gemv_pair_kernel<T, MB, 2, false>), grid, block, st, a, mate);
+    };
+    if (a.N <= 1) go.template operator()<1>();
+    else if (a.N <= 2) go.template operator()<2>();
+    else if (a.N <= 4) go.template operator()<4>();
+    else go.template operator()<8>();
+}
+
+template <typename T>
 static int launch_igemm_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
     switch (a.kernel_id) {
         case K_IGEMM_128x128: launch_cfg<T, 128, 128, 2, 2, 32, 2>(a, st, mate, n_mates); break;
@@ -901,19 +916,7 @@ static int launch_igemm_typed(const OpArgs &a, hipStream_t st, const OpArgs *mat
             else MT_LAUNCH((pw_direct_kernel<T, 1>), (pw_direct_pair_kernel<T, 1>), grid, block, st, a, mate);
             break;
         }
-        case K_GEMV: {
-            const dim3 grid(a.grid_x), block(256);
-            const bool stream_w = (int64_t)a.n_pad * a.k_pad * 2 >= (16ll << 20);
-            auto go = [&]<int MB>() {
-                if (stream_w) MT_LAUNCH((gemv_kernel<T, MB, 2, true>), (gemv_pair_kernel<T, MB, 2, true>), grid, block, st, a, mate);
-                else MT_LAUNCH((gemv_kernel<T, MB, 2, false>), (gemv_pair_kernel<T, MB, 2, false>), grid, block, st, a, mate);
-            };
-            if (a.N <= 1) go.template operator()<1>();
-            else if (a.N <= 2) go.template operator()<2>();
-            else if (a.N <= 4) go.template operator()<4>();
-            else go.template operator()<8>();
-            break;
-        }
+        case K_GEMV: launch_gemv<T>(a, st, mate, n_mates); break;
         default: return (int)hipErrorInvalidValue;
     }
     return (int)hipGetLastError();
@@ -1416,6 +1419,10 @@ int launch_igemm(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates)
     if (mate && !coissue_supported(a)) return (int)hipErrorInvalidValue;
     if (a.dtype == MT_F16) return launch_igemm_typed<f16>(a, st, mate, n_mates);
     if (a.dtype == MT_BF16) return launch_igemm_typed<bf16>(a, st, mate, n_mates);
+    if (a.dtype == MT_F32 && a.kernel_id == K_GEMV) {
+        launch_gemv<float>(a, st, nullptr, 0);
+        return (int)hipGetLastError();
+    }
     return (int)hipErrorInvalidValue;
 }
 

@@ -237,7 +237,23 @@ int32_t finalize_model(mt_model *m) {
                 o.flops = 2.0 * out_elems * gemm_k;
                 o.bytes = (in_elems + out_elems + (double)o.out_c * gemm_k + (res_ct ? out_elems : 0)) * es + 4.0 * o.out_c;
                 if (m->dtype == MT_F32) {
+                    if (d.kind == MT_FC) { p.H = p.W = 1; p.C = gemm_k; p.x_ct = gemm_k; p.R = p.S = 1; }
+                    const int M = m->batch * o.out_h * o.out_w, Kg = o.out_c / groups;
+                    p.n_pad = (Kg + 63) / 64 * 64;
+                    p.k_pad = (gemm_k + 15) / 16 * 16;
+                    if (M <= 8 && p.H == 1 && p.W == 1 && p.R == 1 && p.S == 1 && gemm_k % 4 == 0 && groups == 1) {
+                        p.kernel_id = K_GEMV;
+                        p.grid_x = ((Kg + 1) / 2 + 3) / 4;             // as for the 16-bit types
+                        break;
+                    }
                     p.kernel_id = K_CONV_DIRECT;
+                    p.wk = dconv_f32_plan(M, Kg, gemm_k, p.C);
+                    if (p.wk > 0) {
+                        p.grid_x = dconv_f32_grid(p.wk, M, Kg);
+                        p.tile_order = ((double)Kg * gemm_k > in_elems) ? 1 : 0;
+                        make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
+                        make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
+                    }
                 } else {
                     // a fully connected layer is a 1x1 convolution over a 1x1 map with H*W*C channels
                     if (d.kind == MT_FC) { p.H = p.W = 1; p.C = gemm_k; p.x_ct = gemm_k; p.R = p.S = 1; }
@@ -328,7 +344,7 @@ int32_t finalize_model(mt_model *m) {
     for (OpRec &o : m->ops) {
         const OpArgs &p = o.plan;
         if (needs_weights(p.kind)) {
-            bool igemm = is_gemm_kernel(p.kernel_id) || p.kernel_id == K_STEM || p.kernel_id == K_ROWB || p.kernel_id == K_PCONV;
+            bool igemm = packed_rows(p) || p.kernel_id == K_STEM || p.kernel_id == K_ROWB || p.kernel_id == K_PCONV;
             size_t wcount = igemm ? (size_t)p.groups * p.n_pad * p.k_pad
                                   : (p.kind == MT_DWCONV ? (size_t)p.C * p.R * p.S : (size_t)p.groups * p.K * o.plan.R * o.plan.S * p.C);
             if (p.kind == MT_FC && !igemm) wcount = (size_t)p.K * o.in_h * o.in_w * o.in_c;
@@ -482,6 +498,7 @@ int launch_kernel(const OpArgs &a, hipStream_t st, const OpArgs *mate = nullptr,
     if (a.kernel_id == K_STEM) return launch_stem(a, st, mate, n_mates);
     if (a.kernel_id == K_ROWB) return launch_rowb(a, st, mate, n_mates);
     if (a.kernel_id == K_PCONV) return launch_pconv(a, st, mate, n_mates);
+    if (a.kernel_id == K_CONV_DIRECT && a.wk > 0) return mate ? (int)hipErrorInvalidValue : launch_dconv_f32(a, st);
     return is_gemm_kernel(a.kernel_id) ? launch_igemm(a, st, mate, n_mates) : launch_direct(a, st, mate, n_mates);
 }
 
@@ -504,7 +521,7 @@ bool coissue_pair_ok(const OpArgs &a, const OpArgs &b) {
 int launch_raw(const OpArgs &a, hipStream_t st) {
     if (a.groups <= 1) return launch_kernel(a, st);
     const size_t es = a.dtype == MT_F32 ? 4 : 2;
-    const bool igemm = is_gemm_kernel(a.kernel_id);
+    const bool igemm = packed_rows(a);
     for (int g = 0; g < a.groups; ++g) {
         OpArgs b = a;
         b.groups = 1;
@@ -1566,7 +1583,7 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
     for (size_t i = 0; i < nops; ++i) {
         OpRec &o = t->model.ops[i];
         OpArgs a = o.plan;
-        const bool igemm = is_gemm_kernel(a.kernel_id) || a.kernel_id == K_STEM || a.kernel_id == K_ROWB || a.kernel_id == K_PCONV;
+        const bool igemm = packed_rows(a) || a.kernel_id == K_STEM || a.kernel_id == K_ROWB || a.kernel_id == K_PCONV;
         if (needs_weights(a.kind)) {
             const uint8_t *src = o.w_host.data();
             if (a.kernel_id == K_STEM) {
