@@ -45,6 +45,8 @@ inline bool is_gemm_kernel(int32_t id);
 // ---- kernel families -------------------------------------------------------------------
 // The kernel and tile of an operator are a pure function of its shape and storage type, never of the
 // stream, CU share or stage it runs in; that is what makes outputs bit-identical across schedules.
+// For the implicit GEMMs it names the size class of the layer (the output tile of which the layer has enough to fill the
+// chip); the tile, staging and split that run it are OpArgs::form, panel and split_k.
 enum KernelId : int32_t {
     K_CONV_DIRECT = 0,      // fp32: operands straight from memory to the matrix cores (wk = tiling, 1 ..), or one thread per output element (wk = 0)
     K_IGEMM_128x128 = 1,    // MFMA implicit GEMM, 128 output channels x 128 pixels per workgroup
@@ -61,13 +63,13 @@ enum KernelId : int32_t {
     K_IGEMM_PW = 12,        // 1x1 convolution on a small map: MFMA operands straight from memory, no LDS tiles
     K_STEM = 13,            // first convolution of a network (3 input channels, even horizontal stride): im2col rows straight from memory
     K_ROWB = 14,            // filter bank resident in LDS, activations straight from memory (few output channels or short reductions)
-    K_PCONV = 15,           // 3x3, stride 1, padding 1: 64 x 64 implicit GEMM whose activations are staged as an input patch per 64 channels
+    K_PCONV = 15,           // 3x3, stride 1, padding 1: implicit GEMM whose activations are staged as an input patch per 64 channels
     K_COUNT
 };
 
 inline bool is_gemm_kernel(int32_t id) {
     return id == K_IGEMM_128x128 || id == K_IGEMM_128x64 || id == K_IGEMM_64x64 || id == K_IGEMM_64x16 || id == K_GEMV ||
-           id == K_IGEMM_PW;
+           id == K_IGEMM_PW || id == K_PCONV;
 }
 
 // Everything a launcher needs for one operator.  Pointers are resolved per run (the first operator may
@@ -92,6 +94,8 @@ struct OpArgs {
     int32_t split_k;
     int32_t wk;                  // wave groups that share an output tile (64x64 tile only): 1 or 2; fp32 convolution: its tiling (dconv_f32_plan)
     int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
+    int32_t form;                // tile and staging of the tile kernels (kernels_tile.hip), -1: another kernel
+    int32_t panel;               // patch-staged 3x3 layers: columns of a panel (kernels_tile.hip)
     int32_t pool2;               // 1: the epilogue applies a 2x2 / stride-2 max pooling; pixels are then walked quad by quad and y is the pooled tensor
     // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
     // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
@@ -149,10 +153,14 @@ int launch_stem(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int
 // (r, s, c) reduction index and a tile 32 output channels.
 int rowb_waves(int R, int S, int C, int channels);
 int rowb_tiles(int R, int S, int C, int channels);   // 32-channel tiles per slice of output channels (a workgroup holds one slice's filters)
-// K_PCONV: patch pixels of the instantiation that holds a map of width W (0: none).  Its filter bank is [n_pad][k_pad]
-// like the tile kernel's, with the reduction index ordered (64-channel chunk, tap, channel).
-int pconv_patch_pixels(int W);
-int launch_pconv(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
+// Tile kernels (kernels_tile.hip): choice of form, its split workspace (tiles, floats per tile), the pooled plan, launch.
+// The filter bank is [n_pad][k_pad]; a patch-staged layer (panel > 0) orders the reduction index (64-channel chunk, tap, channel).
+bool patch_stageable(const OpArgs &a);
+bool plan_tile(OpArgs &a, bool narrow);
+bool tile_is_narrow(const OpArgs &a);
+void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);
+bool plan_tile_pooled(OpArgs &a);
+int launch_tile(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
 bool rowb_patch_form(const OpArgs &a);   // 3x3, stride 1: activations staged once per tile as an input patch in LDS
 int launch_rowb(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
 

@@ -1,18 +1,16 @@
-// Convolution and fully connected layers as an implicit GEMM on the gfx950 matrix cores.
+// Convolutions whose channel count is not a multiple of 8 as an implicit GEMM on the gfx950 matrix cores (the tile kernels of
+// kernels_tile.hip cover the others), matrix-vector products, 1x1 convolutions on small maps, fused depthwise pairs.
 //
 //   D[k, m] = sum_j Wp[k, j] * A[m, j]        k: output channel, m: output pixel (n, p, q), j: (r, s, c)
 //
 // Wp is the filter bank packed at registration time as [n_pad][k_pad] (rows = output channels, zero padded
-// to whole tiles), so its tiles are plain 16-byte loads.  A is never materialised: a tile row is gathered
-// from the NHWC activation, where eight consecutive j with C % 8 == 0 are eight consecutive channels of one
-// input pixel, i.e. one 16-byte load (or zeros in the padding halo).  Both tiles are staged in LDS with the
-// reduction index contiguous, which is the operand layout of v_mfma_f32_32x32x16 / 16x16x32 (each lane feeds
-// 8 consecutive j of one row).  The filter bank is the MFMA "A" operand, so a lane's accumulator registers
-// hold four consecutive output channels of one pixel: the NHWC store is an 8-byte access per group.
+// to whole tiles), so its tiles are plain 16-byte loads.  A is never materialised: a tile row is gathered element by
+// element from the NHWC activation.  Both tiles are staged in LDS with the reduction index contiguous, which is the operand
+// layout of v_mfma_f32_32x32x16 / 16x16x32 (each lane feeds 8 consecutive j of one row).  The filter bank is the MFMA "A"
+// operand, so a lane's accumulator registers hold four consecutive output channels of one pixel.
 //
-// Pipeline: global loads run STAGES reduction tiles ahead in registers, LDS is double buffered, one
-// workgroup barrier per tile.  fp16 / bf16 inputs, fp32 accumulation; bias, residual, activation in fp32;
-// one rounding on store.
+// Pipeline: global loads run two reduction tiles ahead in registers, LDS is double buffered, one workgroup barrier per
+// tile.  fp16 / bf16 inputs, fp32 accumulation; bias, residual, activation in fp32; one rounding on store.
 //
 // Tiny-M layers are split along j across workgroups.  Partial sums go to a workspace with device-coherent
 // (write-through) stores, and the workgroup that arrives last at the tile's counter adds them in split
@@ -33,38 +31,22 @@ namespace mt {
 constexpr int BK = IGEMM_BK;     // reduction elements per LDS tile
 constexpr int LDK = BK + 8;      // padded LDS row (144 bytes: 16-byte reads of a wave fall in distinct banks)
 constexpr int NXCD = 8;
-constexpr int A_SCALAR = 0, A_VEC8 = 1, A_UNIFORM = 2;
 constexpr uint32_t OOB_OFFSET = 0x80000000u;   // beyond any tensor: buffer loads return zeros
 // Fused 1x1 + depthwise kernel: channels of the widened tensor per workgroup, workgroups wanted at least, and 8-channel
 // chunks of depthwise output a workgroup takes at most (measured on MobileNetV2 at batch 1: 32 channels per workgroup
 // are 7 % slower, 256 to 1024 chunks 1 to 4 % slower).
 constexpr int PWDW_HC = 16, PWDW_WGS = 64, PWDW_ITEMS = 128;
 
-// BN: output channels per workgroup, BM: pixels per workgroup, WN x WM: wave grid (4 waves), MF: MFMA edge,
-// STAGES: reduction tiles whose global loads are in flight (register sets), even.
-// AMODE: how a tile row of the im2col matrix is gathered:
-//   A_UNIFORM  C % 64 == 0 and R*S <= 64: a 64-deep tile lies inside one filter tap, so the tap walks in
-//              scalar registers and a lane only selects between its pixel's offset and "out of range"
-//   A_VEC8     C % 8 == 0: every lane tracks the tap of its own 8-channel chunk
-//   A_SCALAR   any C (first layers, C = 3): element-wise gather
-// Filter tiles and (except A_SCALAR) im2col chunks are fetched with buffer loads: offsets are 32 bit, the
-// tile walk is a scalar offset, and a chunk in the padding halo is given an out-of-range offset, for which
-// the hardware returns zeros: no select and no 64-bit address arithmetic in the loop.
-template <typename T, int BN, int BM, int WN, int WM, int MF, int STAGES, int AMODE, int WK = 1>
+// BN: output channels per workgroup, BM: pixels per workgroup, WN x WM: wave grid (4 waves), MF: MFMA edge.
+template <typename T, int BN, int BM, int WN, int WM, int MF>
 __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     set_wave_priority(a.prio);
     static_assert(WN * WM == 4, "four waves per output tile");
-    // WK > 1: WK groups of four waves share the output tile and split the MFMA steps of every LDS tile between them
-    // (a second wave per SIMD to overlap with when the grid gives a compute unit a single workgroup); their
-    // accumulators are added through LDS after the main loop, in group order.
-    constexpr int NT = 256 * WK;
-    static_assert(STAGES >= 2 && STAGES % 2 == 0, "register sets rotate with the two LDS buffers");
+    constexpr int NT = 256, STAGES = 2;                    // reduction tiles whose global loads are in flight (register sets)
     constexpr int SUBN = BN / WN, SUBM = BM / WM;          // wave tile
     constexpr int TN = SUBN / MF, TM = SUBM / MF;          // MFMA tiles per wave
     static_assert(TN >= 1 && TM >= 1, "wave tile smaller than one MFMA");
-    constexpr int KSTEPS_TILE = (MF == 32) ? BK / 16 : BK / 32;   // MFMA steps per LDS tile
-    static_assert(KSTEPS_TILE % WK == 0, "the wave groups split the MFMA steps evenly");
-    constexpr int KSTEPS = KSTEPS_TILE / WK;               // MFMA issues per LDS tile and wave
+    constexpr int KSTEPS = (MF == 32) ? BK / 16 : BK / 32;   // MFMA issues per LDS tile and wave
     constexpr int KLANES = 64 / MF;                        // lane groups along the reduction index
     constexpr int ACC_REGS = (MF == 32) ? 16 : 4;
     constexpr int CH_ROW = BK / 8;                         // 16-byte chunks per tile row
@@ -83,8 +65,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int wk = wave / 4;                               // wave group along the reduction index
-    const int wn = (wave % 4) % WN, wm = (wave % 4) / WN;
+    const int wn = wave % WN, wm = wave / WN;
 
     // Workgroup ids are dealt round-robin to the 8 XCDs; remap so that each XCD (one L2) works on a
     // contiguous range of tiles and the tiles sharing an activation tile share an L2.
@@ -115,8 +96,6 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     const int kc = tid % CH_ROW;          // chunk column (same for every chunk of this thread)
     const int row0 = tid / CH_ROW;        // first tile row; further chunks are ROW_STEP rows apart
 
-    const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T *>(x), 0, (int)(((int64_t)a.N * a.H * a.W * XS - a.x_coff) * (int)sizeof(T)), 0x00027000);
     const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(wp), 0, (int)((int64_t)a.n_pad * a.k_pad * 2), 0x00027000);
 
@@ -158,38 +137,9 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     }
     uint32_t wsoff = (uint32_t)(kt_begin * BK * 2);     // scalar: byte offset of the current tile in a filter row
 
-    // A_UNIFORM: the tap (r, s) and the channel base of the current tile are wave-uniform.
-    int u_r = 0, u_s = 0, u_tap = 0, u_cb = 0;
-    uint64_t tapmask[X_CHUNKS];           // bit r*S+s: the tap reads inside the image for this chunk's pixel
-    int rowoff[X_CHUNKS];                 // byte offset of (n, ih0, iw0, kc*8)
-    // A_VEC8 / A_SCALAR: position of this thread's chunk inside the (r, s, c) reduction index.
-    const int adv_c = BK % a.C, adv_rs = BK / a.C;
     const uint32_t inv_s = (uint32_t)((0x100000000ull + (uint32_t)a.S - 1) / (uint32_t)a.S);   // wraps to 0 for S == 1
     auto tap_row = [&](int rs) { return a.S == 1 ? rs : (int)__umulhi((uint32_t)rs, inv_s); };
-    int kcx = 0, krs = 0;
     int jbase = kt_begin * BK + kc * 8;
-    if constexpr (AMODE == A_UNIFORM) {
-        const int j0 = kt_begin * BK;
-        u_cb = j0 % a.C;
-        u_tap = j0 / a.C;
-        u_r = u_tap / a.S;
-        u_s = u_tap - u_r * a.S;
-#pragma unroll
-        for (int i = 0; i < X_CHUNKS; ++i) {
-            uint64_t mask = 0;
-            for (int r = 0; r < a.R; ++r)
-                for (int sx = 0; sx < a.S; ++sx) {
-                    const bool v = xrow_ok[i] & ((uint32_t)(ih0[i] + r) < (uint32_t)a.H) & ((uint32_t)(iw0[i] + sx) < (uint32_t)a.W);
-                    mask |= (uint64_t)(v ? 1u : 0u) << (r * a.S + sx);
-                }
-            tapmask[i] = mask;
-            rowoff[i] = (img_off[i] + (ih0[i] * a.W + iw0[i]) * XS + kc * 8) * 2;
-        }
-    } else {
-        const int j0 = kt_begin * BK + kc * 8;
-        kcx = j0 % a.C;
-        krs = j0 / a.C;
-    }
 
     u32x4 wreg[STAGES][W_CHUNKS], xreg[STAGES][X_CHUNKS];
 
@@ -198,32 +148,9 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     // straight-line code: the compiler counts them exactly and lets the newer register sets stay in flight while the
     // oldest one is consumed.
     constexpr int NCH = W_CHUNKS + X_CHUNKS;
-    int t_tapoff = 0, t_sh = 0, t_kr = 0, t_ks = 0;      // per-tile values of the im2col gather, set by tile_begin
-    bool t_tap_ok = false;
-    auto tile_begin = [&]() {
-        if constexpr (AMODE == A_UNIFORM) {
-            t_tapoff = ((u_r * a.W + u_s) * XS + u_cb) * 2;                // scalar
-            t_tap_ok = u_tap < a.R * a.S;
-            t_sh = t_tap_ok ? u_tap : 0;
-        } else if constexpr (AMODE == A_VEC8) {
-            t_kr = tap_row(krs);
-            t_ks = krs - t_kr * a.S;
-        }
-    };
     auto load_chunk = [&]<int I>(u32x4 (&wr)[W_CHUNKS], u32x4 (&xr)[X_CHUNKS]) {
         if constexpr (I < W_CHUNKS) {
             wr[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, wvoff[I], wsoff, 0);
-        } else if constexpr (AMODE == A_UNIFORM) {
-            constexpr int i = I - W_CHUNKS;
-            const bool v = t_tap_ok & (((tapmask[i] >> t_sh) & 1ull) != 0);
-            const uint32_t voff = v ? (uint32_t)(rowoff[i] + t_tapoff) : OOB_OFFSET;
-            xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, voff, 0, 0);
-        } else if constexpr (AMODE == A_VEC8) {
-            constexpr int i = I - W_CHUNKS;
-            const int ih = ih0[i] + t_kr, iw = iw0[i] + t_ks;
-            const bool v = xrow_ok[i] & (t_kr < a.R) & ((uint32_t)ih < (uint32_t)a.H) & ((uint32_t)iw < (uint32_t)a.W);
-            const uint32_t voff = v ? (uint32_t)((img_off[i] + (ih * a.W + iw) * XS + kcx) * 2) : OOB_OFFSET;
-            xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, voff, 0, 0);
         } else {
             // input channels not a multiple of 8 (first layers, C = 3): gather element by element
             constexpr int i = I - W_CHUNKS;
@@ -247,26 +174,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     };
     auto tile_end = [&]() {
         wsoff += BK * 2;
-        if constexpr (AMODE == A_UNIFORM) {
-            u_cb += BK;
-            if (u_cb >= a.C) {              // scalar branch-free updates (uniform values)
-                u_cb = 0;
-                ++u_tap;
-                ++u_s;
-                if (u_s == a.S) {
-                    u_s = 0;
-                    ++u_r;
-                }
-            }
-        } else if constexpr (AMODE == A_VEC8) {
-            kcx += adv_c;
-            krs += adv_rs;
-            const bool carry = kcx >= a.C;
-            kcx -= carry ? a.C : 0;
-            krs += carry ? 1 : 0;
-        } else {
-            jbase += BK;
-        }
+        jbase += BK;
     };
     // Every thread writes its chunks: tile rows beyond BN / BM land in spare LDS rows that nobody reads.
     auto store_chunk = [&]<int I>(int buf, const u32x4 (&wr)[W_CHUNKS], const u32x4 (&xr)[X_CHUNKS]) {
@@ -278,7 +186,6 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
         }
     };
     auto load_tiles = [&](u32x4 (&wr)[W_CHUNKS], u32x4 (&xr)[X_CHUNKS]) {
-        tile_begin();
         [&]<int... I>(std::integer_sequence<int, I...>) {
             (load_chunk.template operator()<I>(wr, xr), ...);
         }(std::make_integer_sequence<int, NCH>{});
@@ -324,7 +231,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
         u32x4 a[TN], b[TM];
     };
     auto load_frag = [&](int buf, int kk, Frag &f) {
-        const int koff = (wk * KSTEPS + kk) * (KLANES * 8) + frag_k;
+        const int koff = kk * (KLANES * 8) + frag_k;
 #pragma unroll
         for (int i = 0; i < TN; ++i)
             f.a[i] = *reinterpret_cast<const u32x4 *>(&Ws[buf][(wn * SUBN + i * MF + frag_row) * LDK + koff]);
@@ -367,8 +274,6 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
                         store_tiles((S + 1) & 1, wreg[nxt], xreg[nxt]);
                         if (fetch) load_tiles(wreg[nxt], xreg[nxt]);
                     }
-                } else {
-                    if (fetch) tile_begin();
                 }
                 auto move_chunk = [&]<int C>() {
                     if constexpr (C < NCH) {
@@ -406,35 +311,6 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
         for (; t0 + 2 * STAGES < nk; t0 += STAGES) round.template operator()<true>(t0, std::make_integer_sequence<int, STAGES>{});
         for (; t0 < nk; t0 += STAGES) round.template operator()<false>(t0, std::make_integer_sequence<int, STAGES>{});
     }
-    // ---- wave groups: groups 1 .. WK-1 hand their accumulators to group 0 through LDS (the tile buffers are free:
-    // the main loop ends with a barrier), which adds them in group order and alone runs the rest of the kernel.
-    const bool owner = wk == 0;
-    if constexpr (WK > 1) {
-        constexpr int NACC_W = TN * TM * ACC_REGS;
-        static_assert((size_t)(WK - 1) * NACC_W * 256 * sizeof(float) <= sizeof(smem), "accumulator exchange must fit the tile buffers");
-        float *red = reinterpret_cast<float *>(&smem[0]);
-        if (!owner) {
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-#pragma unroll
-                    for (int v = 0; v < ACC_REGS; ++v)
-                        red[(((wk - 1) * NACC_W) + (i * TM + j) * ACC_REGS + v) * 256 + (tid & 255)] = acc[i][j][v];
-        }
-        __syncthreads();
-        if (owner) {
-            for (int g = 1; g < WK; ++g)
-#pragma unroll
-                for (int i = 0; i < TN; ++i)
-#pragma unroll
-                    for (int j = 0; j < TM; ++j)
-#pragma unroll
-                        for (int v = 0; v < ACC_REGS; ++v)
-                            acc[i][j][v] += red[(((g - 1) * NACC_W) + (i * TM + j) * ACC_REGS + v) * 256 + tid];
-        }
-    }
-
     // ---- split-K: publish partial sums; the last workgroup of the tile reduces in split order ----
     if (a.split_k > 1) {
         constexpr int NACC = TN * TM * ACC_REGS;
@@ -445,8 +321,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
             for (int j = 0; j < TM; ++j)
 #pragma unroll
                 for (int v = 0; v < ACC_REGS; ++v)
-                    if (owner)
-                        __hip_atomic_store(&wsp[((i * TM + j) * ACC_REGS + v) * 256 + tid], acc[i][j][v], __ATOMIC_RELAXED,
+                    __hip_atomic_store(&wsp[((i * TM + j) * ACC_REGS + v) * 256 + tid], acc[i][j][v], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
         // Hand-off without a device-wide fence (a release at agent scope writes the whole L2 of the XCD back, about 80 us
         // per launch when tried).  What orders it instead:
@@ -477,7 +352,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
                 for (int v = 0; v < ACC_REGS; ++v) acc[i][j][v] = 0.f;
         // Loads of RB splits are issued together (they are independent), then added in split order.
         constexpr int RB = (NACC <= 16) ? 4 : 1;
-        for (int zz0 = 0; owner && zz0 < a.split_k; zz0 += RB) {
+        for (int zz0 = 0; zz0 < a.split_k; zz0 += RB) {
             float part[RB][NACC];
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
@@ -530,26 +405,24 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
             }
         }
         __syncthreads();                                  // the accumulator exchange above may still be read
-        if (owner) {
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
-                for (int j = 0; j < TM; ++j)
+            for (int j = 0; j < TM; ++j)
 #pragma unroll
-                    for (int g = 0; g < GROUPS; ++g) {
-                        const int ml = wm * SUBM + j * MF + frag_row;
-                        const int kl = wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * (lane / 32)) : (4 * (lane / 16)));
-                        float4 b;
-                        if constexpr (BIAS_EARLY) b = bias_pre[i * GROUPS + g];
-                        else b = *reinterpret_cast<const float4 *>(a.bias + n0 + kl);
-                        float4 v;
-                        v.x = acc[i][j][g * 4 + 0] + b.x;
-                        v.y = acc[i][j][g * 4 + 1] + b.y;
-                        v.z = acc[i][j][g * 4 + 2] + b.z;
-                        v.w = acc[i][j][g * 4 + 3] + b.w;
-                        *reinterpret_cast<float4 *>(&et[ml * ELD + kl]) = v;
-                    }
-        }
+                for (int g = 0; g < GROUPS; ++g) {
+                    const int ml = wm * SUBM + j * MF + frag_row;
+                    const int kl = wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * (lane / 32)) : (4 * (lane / 16)));
+                    float4 b;
+                    if constexpr (BIAS_EARLY) b = bias_pre[i * GROUPS + g];
+                    else b = *reinterpret_cast<const float4 *>(a.bias + n0 + kl);
+                    float4 v;
+                    v.x = acc[i][j][g * 4 + 0] + b.x;
+                    v.y = acc[i][j][g * 4 + 1] + b.y;
+                    v.z = acc[i][j][g * 4 + 2] + b.z;
+                    v.w = acc[i][j][g * 4 + 3] + b.w;
+                    *reinterpret_cast<float4 *>(&et[ml * ELD + kl]) = v;
+                }
         __syncthreads();
         if (a.pool2) {
             // Four consecutive tile rows are one 2x2 window (see the pixel walk above) and the pooled pixel index is the
@@ -595,7 +468,6 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
         }
         return;
     }
-    if (!owner) return;
     const bool vec_ok = (a.y_ct % 4 == 0) && (a.y_coff % 4 == 0) && (a.res_ct % 4 == 0);
 #pragma unroll
     for (int i = 0; i < TN; ++i)
@@ -854,33 +726,14 @@ __global__ void __launch_bounds__(256) pw_direct_pair_kernel(OpArgsPair p) {
     pw_direct_kernel_body<T, SLICES>(p.a[blockIdx.y]);
 }
 
-template <typename T, int BN, int BM, int WN, int WM, int MF, int STAGES, int AMODE, int WK = 1>
-__global__ void __launch_bounds__(256 * WK) igemm_kernel(OpArgs a) {
-    igemm_body<T, BN, BM, WN, WM, MF, STAGES, AMODE, WK>(a);
-}
-// Co-issue: the same tile program for two operators of equal launch shape, one per value of blockIdx.y.
-template <typename T, int BN, int BM, int WN, int WM, int MF, int STAGES, int AMODE, int WK = 1>
-__global__ void __launch_bounds__(256 * WK) igemm_pair_kernel(OpArgsPair p) {
-    igemm_body<T, BN, BM, WN, WM, MF, STAGES, AMODE, WK>(p.a[blockIdx.y]);
+template <typename T, int BN, int BM, int WN, int WM, int MF>
+__global__ void __launch_bounds__(256) igemm_kernel(OpArgs a) {
+    igemm_body<T, BN, BM, WN, WM, MF>(a);
 }
 
-template <typename T, int BN, int BM, int WN, int WM, int MF, int STAGES, int WK = 1>
-static void launch_cfg(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
-    const dim3 grid(a.grid_x, mate ? 1 + n_mates : 1);
-    OpArgsPair p;
-    if (mate) {
-        p.a[0] = a;
-        for (int i = 0; i < n_mates; ++i) p.a[1 + i] = mate[i];
-    }
-    if (a.vec_a == A_UNIFORM) {
-        if (mate) launch((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, p);
-        else launch((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_UNIFORM, WK>), grid, dim3(256 * WK), 0, st, a);
-    } else if (a.vec_a == A_VEC8) {
-        if (mate) launch((igemm_pair_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, p);
-        else launch((igemm_kernel<T, BN, BM, WN, WM, MF, STAGES, A_VEC8, WK>), grid, dim3(256 * WK), 0, st, a);
-    } else {
-        launch((igemm_kernel<T, BN, BM, WN, WM, MF, 2, A_SCALAR>), grid, dim3(256), 0, st, a);
-    }
+template <typename T, int BN, int BM, int WN, int WM, int MF>
+static void launch_cfg(const OpArgs &a, hipStream_t st) {
+    launch((igemm_kernel<T, BN, BM, WN, WM, MF>), dim3(a.grid_x), dim3(256), 0, st, a);
 }
 
 template <typename T>
@@ -900,16 +753,10 @@ static void launch_gemv(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
 template <typename T>
 static int launch_igemm_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
     switch (a.kernel_id) {
-        case K_IGEMM_128x128: launch_cfg<T, 128, 128, 2, 2, 32, 2>(a, st, mate, n_mates); break;
-        case K_IGEMM_128x64:
-            if (a.wk == 2) launch_cfg<T, 128, 64, 2, 2, 32, 2, 2>(a, st, mate, n_mates);
-            else launch_cfg<T, 128, 64, 2, 2, 32, 2>(a, st, mate, n_mates);
-            break;
-        case K_IGEMM_64x64:
-            if (a.wk == 2) launch_cfg<T, 64, 64, 2, 2, 32, 4, 2>(a, st, mate, n_mates);
-            else launch_cfg<T, 64, 64, 2, 2, 32, 4, 1>(a, st, mate, n_mates);
-            break;
-        case K_IGEMM_64x16: launch_cfg<T, 64, 16, 4, 1, 16, 4>(a, st, mate, n_mates); break;
+        case K_IGEMM_128x128: launch_cfg<T, 128, 128, 2, 2, 32>(a, st); break;
+        case K_IGEMM_128x64: launch_cfg<T, 128, 64, 2, 2, 32>(a, st); break;
+        case K_IGEMM_64x64: launch_cfg<T, 64, 64, 2, 2, 32>(a, st); break;
+        case K_IGEMM_64x16: launch_cfg<T, 64, 16, 4, 1, 16>(a, st); break;
         case K_IGEMM_PW: {
             const dim3 grid(a.grid_x), block(256);
             if (a.split_k > 1) MT_LAUNCH((pw_direct_kernel<T, 4>), (pw_direct_pair_kernel<T, 4>), grid, block, st, a, mate);
@@ -1111,10 +958,11 @@ static size_t dwpw_lds_bytes(int k_pad) { return (size_t)k_pad * (18 + 4) + (siz
 // Host check of what the fused kernel assumes; the runtime pairs two operators only when this holds.
 bool dwpw_fusable(const OpArgs &dw, const OpArgs &pw) {
     // the 1x1 layer must be one whose stand-alone kernel walks the reduction in one ascending pass, as the fused kernel does
-    if (dw.kernel_id != K_DWCONV || !(pw.kernel_id == K_IGEMM_64x16 || pw.kernel_id == K_IGEMM_PW)) return false;
+    if (dw.kernel_id != K_DWCONV || !(tile_is_narrow(pw) || pw.kernel_id == K_IGEMM_PW)) return false;
     if (dw.dtype != pw.dtype || (dw.dtype != MT_F16 && dw.dtype != MT_BF16)) return false;
     if (dw.R != 3 || dw.S != 3 || dw.vec != 8 || dw.C % 8 != 0 || dw.y_coff != 0 || dw.y_ct != dw.C) return false;
     if (pw.R != 1 || pw.S != 1 || pw.sh != 1 || pw.sw != 1 || pw.ph != 0 || pw.pw != 0 || pw.groups > 1) return false;
+    if (pw.C > 256) return false;                                    // in one ascending pass a longer reduction takes more than the launch it saves
     if (pw.split_k != 1 || pw.vec_a == 0 || pw.C != dw.C || pw.x_ct != dw.C || pw.x_coff != 0) return false;
     if (pw.N != dw.N || pw.H != dw.P || pw.W != dw.Q || pw.P != dw.P || pw.Q != dw.Q) return false;
     if (dwpw_lds_bytes(pw.k_pad) > 44 * 1024) return false;          // filters, bias and the depthwise tile must fit beside the filter tiles in 64 KB of LDS
@@ -1163,7 +1011,7 @@ __global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands
     const int r_lo = max(0, p_lo * d.sh - 1), r_hi = min(d.H - 1, (p_hi - 1) * d.sh + 1);   // widened rows it reads
     const int px0 = r_lo * W, Mb = (r_hi - r_lo + 1) * W;
     const int own_lo = p_lo * d.sh, own_hi = band == bands - 1 ? d.H : min(d.H, p_hi * d.sh);   // widened rows it stores
-    const int nsteps = e.k_pad / 32;
+    const int nsteps = (e.C + 63) / 64 * 2;              // a longer packed row is zero beyond
     const int frag_row = lane & 15, frag_k = (lane >> 4) * 8;
 
     const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
@@ -1270,14 +1118,14 @@ __global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands
 // row bands, chosen so that enough workgroups exist and a band's input rows fit the variant.  False: not fusable.
 static bool pwdw_plan(const OpArgs &pw, const OpArgs &dw, int *variant, int *bands) {
     // the 1x1 layer must be one whose stand-alone kernel walks the reduction in one ascending pass, as the fused kernel does
-    if (!(pw.kernel_id == K_IGEMM_64x16 || pw.kernel_id == K_IGEMM_PW) || dw.kernel_id != K_DWCONV) return false;
+    if (!(tile_is_narrow(pw) || pw.kernel_id == K_IGEMM_PW) || dw.kernel_id != K_DWCONV) return false;
     if (dw.dtype != pw.dtype || (dw.dtype != MT_F16 && dw.dtype != MT_BF16)) return false;
     if (pw.R != 1 || pw.S != 1 || pw.sh != 1 || pw.sw != 1 || pw.ph != 0 || pw.pw != 0 || pw.groups > 1) return false;
     if (pw.split_k != 1 || pw.vec_a == 0 || pw.C % 8 != 0 || pw.x_ct != pw.C || pw.x_coff != 0 || pw.res_ct != 0) return false;
     if (pw.K % 8 != 0 || pw.y_coff != 0 || pw.y_ct != pw.K) return false;
     if (dw.R != 3 || dw.S != 3 || dw.ph != 1 || dw.pw != 1 || dw.sh < 1 || dw.sh > 2 || dw.vec != 8 || dw.C != pw.K) return false;
     if (dw.N != pw.N || dw.H != pw.P || dw.W != pw.Q) return false;
-    const int steps = pw.k_pad / 32;
+    const int steps = (pw.C + 63) / 64 * 2;
     const int limit = steps <= 2 ? 512 : steps <= 4 ? 256 : steps <= 8 ? 64 : 0;     // pixels a band may read
     *variant = steps <= 2 ? 0 : steps <= 4 ? 1 : 2;
     if (limit == 0 || 3 * dw.W > limit) return false;
@@ -1433,10 +1281,9 @@ int launch_igemm(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates)
 bool coissue_supported(const OpArgs &a) {
     if (a.dtype != MT_F16 && a.dtype != MT_BF16) return false;
     if (a.groups > 1) return false;
+    if (a.form >= 0) return true;
     switch (a.kernel_id) {
-        case K_IGEMM_128x128: case K_IGEMM_128x64: case K_IGEMM_64x64: case K_IGEMM_64x16:
-            return a.vec_a == A_UNIFORM || a.vec_a == A_VEC8;
-        case K_IGEMM_PW: case K_GEMV: case K_PCONV: case K_ROWB: case K_STEM: return true;
+        case K_IGEMM_PW: case K_GEMV: case K_ROWB: case K_STEM: return true;
         case K_DWCONV: case K_MAXPOOL: case K_AVGPOOL: case K_GAP: case K_LRN: case K_ADD: return a.vec == 8;
         default: return false;
     }

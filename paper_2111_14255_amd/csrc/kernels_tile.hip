@@ -1,0 +1,892 @@
+// Convolution and fully connected layers as an implicit GEMM whose operand tiles are copied from memory to LDS by the
+// load unit itself (buffer_load_dwordx4 ... lds), without passing through registers.
+//
+//   D[k, m] = sum_j Wp[k, j] * A[m, j]        k: output channel, m: output pixel (n, p, q), j: (r, s, c)
+//
+// Wp is the filter bank packed as [n_pad][k_pad], A the im2col matrix, never materialised: eight consecutive j with
+// C % 8 == 0 are eight channels of one input pixel, one 16-byte piece of the NHWC tensor or, in the padding halo, an
+// out-of-range offset for which the load delivers zeros.
+//
+// What bounds it: a stage of 64 reduction elements passes through load unit, LDS and matrix cores; staging it through
+// registers (the form before) cost a chain of load, wait, LDS write, barrier, LDS read and matrix instructions per 64
+// elements, and padded LDS rows.  Here NBUF stages of LDS are in flight, one barrier per stage waits for the oldest, and rows
+// are 128 bytes without padding, their 16-byte columns permuted so that operand reads use all 64 banks (conflicts per LDS
+// cycle 0.5 with a permutation over 8 rows, 0.0 with the one over 16).  MI355X, us before / now, launch gap included:
+//   3x3, 256 -> 256 on 8 x 56 x 56 (59 GFLOP)  52.0 / 32.7      3x3, 512 -> 512 on 8 x 28 x 28  47.5 / 34.4
+//   1x1, 1024 -> 512 on 64 x 14 x 14           28.4 / 20.0      1x1, 512 -> 2048 on 64 x 7 x 7   20.3 / 15.0
+//   1x1, 768 -> 192 on 5 x 17 x 17              9.9 /  5.3      3x3, 64 -> 64 on 56 x 56          5.4 /  4.6
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+#include "internal.h"
+#include "device_types.h"
+#include "mfma.h"
+
+namespace mt {
+
+// How a row of A is gathered: TG_POINT 1x1 windows without padding and C % 64 == 0 (a row is contiguous), TG_TAP
+// C % 64 == 0 (64 consecutive j lie inside one filter tap), TG_CHUNK C % 8 == 0 (every 16-byte piece has its own tap).
+constexpr int TG_POINT = 0, TG_TAP = 1, TG_CHUNK = 2;
+
+namespace {
+
+constexpr int TK = 64;                          // reduction elements of one LDS row: 128 bytes
+constexpr int XCDS = 8;
+constexpr uint32_t OUT_OF_RANGE = 0x80000000u;  // beyond any tensor: the load delivers zeros
+
+// 64 lanes x 16 bytes from rsrc + voff (per lane) + soff to LDS at `lds` + 16 * lane.
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+// All but the N youngest loads of this wave have landed, its LDS reads are done, and the other waves got here as well.
+template <int N>
+__device__ __forceinline__ void wait_and_meet() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ u32x4 raw_buffer(const void *p, int64_t bytes) {
+    const uint64_t b = (uint64_t)p;
+    return u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, (uint32_t)bytes, 0x00027000u};
+}
+
+}  // namespace
+
+// Whether the taps of this layer can be read from a patch in LDS (patch_body).
+bool patch_stageable(const OpArgs &a) {
+    return a.kind == MT_CONV && a.groups <= 1 && a.R == 3 && a.S == 3 && a.sh == 1 && a.sw == 1 && a.ph == 1 && a.pw == 1 && a.C % TK == 0 && a.H <= 1024;
+}
+
+// What follows the main loop: the wave groups' partial sums meet, then those of the workgroups that share the tile, then
+// bias, residual, activation, one rounding and the store.  pixel(ml) is the output pixel of tile row ml (the pooled pixel
+// of its window when the epilogue pools), negative for rows without one.
+template <typename T, int BN, int BM, int WN, int WM, int WK, int MF, typename Acc, int TN, int TM, typename Pixel>
+__device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM], uint8_t *smem, int *s_last, int n0, int tile, int z, Pixel pixel) {
+    constexpr int GT = 64 * WN * WM, NT = GT * WK;
+    constexpr int SUBN = BN / WN, SUBM = BM / WM, ACC = MF == 32 ? 16 : 4, GROUPS = ACC / 4, ELD = BN + 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
+    const int frow = lane % MF, fgrp = lane / MF;
+
+    // ---- wave groups: groups 1 .. WK-1 hand their accumulators to group 0, which adds them in group order
+    const bool owner = wk == 0;
+    const int gtid = tid % GT;
+    constexpr int NACC = TN * TM * ACC;
+    if constexpr (WK > 1) {
+        float *red = reinterpret_cast<float *>(&smem[0]);
+        if (!owner) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int g = 0; g < GROUPS; ++g)
+                        *reinterpret_cast<float4 *>(&red[(((wk - 1) * (NACC / 4) + (i * TM + j) * GROUPS + g) * GT + gtid) * 4]) =
+                            make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+        }
+        __syncthreads();
+        if (owner) {
+            for (int w = 1; w < WK; ++w)
+#pragma unroll
+                for (int i = 0; i < TN; ++i)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+#pragma unroll
+                        for (int g = 0; g < GROUPS; ++g) {
+                            const float4 v = *reinterpret_cast<const float4 *>(&red[(((w - 1) * (NACC / 4) + (i * TM + j) * GROUPS + g) * GT + gtid) * 4]);
+                            acc[i][j][g * 4] += v.x; acc[i][j][g * 4 + 1] += v.y; acc[i][j][g * 4 + 2] += v.z; acc[i][j][g * 4 + 3] += v.w;
+                        }
+        }
+    }
+
+    // ---- split reduction: publish partial sums; the last workgroup of the tile adds them in split order
+    if (a.split_k > 1) {
+        float *wsp = a.ws + ((int64_t)tile * a.split_k + z) * (BN * BM);
+        if (owner) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int v = 0; v < ACC; ++v)
+                        __hip_atomic_store(&wsp[((i * TM + j) * ACC + v) * GT + gtid], acc[i][j][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned old = __hip_atomic_fetch_add(&a.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *s_last = (old == (unsigned)a.split_k - 1u);
+        }
+        __syncthreads();
+        if (!*s_last) return;
+        const float *wsr = a.ws + (int64_t)tile * a.split_k * (BN * BM);
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
+        constexpr int RB = (NACC <= 16) ? 4 : 1;
+        for (int zz0 = 0; owner && zz0 < a.split_k; zz0 += RB) {
+            float part[RB][NACC];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                const float *p = wsr + (int64_t)min(zz0 + b, a.split_k - 1) * (BN * BM);
+#pragma unroll
+                for (int e = 0; e < NACC; ++e) part[b][e] = __hip_atomic_load(&p[e * GT + gtid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+                if (zz0 + b < a.split_k) {
+#pragma unroll
+                    for (int i = 0; i < TN; ++i)
+#pragma unroll
+                        for (int j = 0; j < TM; ++j)
+#pragma unroll
+                            for (int v = 0; v < ACC; ++v) acc[i][j][v] += part[b][(i * TM + j) * ACC + v];
+                }
+        }
+        if (tid == 0) __hip_atomic_store(&a.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // ---- epilogue: bias, residual, activation, one rounding, NHWC store
+    T *y = (T *)a.y;
+    const T *res = (const T *)a.res;
+    const bool vec8_ok = (a.K % 8 == 0) && (a.y_ct % 8 == 0) && (a.y_coff % 8 == 0) && (a.res_ct % 8 == 0);
+    if (vec8_ok) {
+        float *et = reinterpret_cast<float *>(&smem[0]);
+        constexpr int CPR = BN / 8;
+        constexpr int EP_IT = (BM * CPR + NT - 1) / NT;
+        u32x4 res_raw[EP_IT];
+        const bool add_res = res != nullptr && !a.pool2;
+        if (add_res) {
+#pragma unroll
+            for (int it = 0; it < EP_IT; ++it) {
+                const int c = tid + it * NT;
+                const int m = pixel(min(c / CPR, BM - 1)), k = n0 + (c % CPR) * 8;
+                const bool live = (c < BM * CPR) & (m >= 0) & (k < a.K);
+                res_raw[it] = live ? *reinterpret_cast<const u32x4 *>(res + (int64_t)m * a.res_ct + k) : u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+        __syncthreads();
+        if (owner) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int g = 0; g < GROUPS; ++g) {
+                        const int ml = wm * SUBM + j * MF + frow;
+                        const int kl = wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * fgrp) : (4 * fgrp));
+                        const float4 b = *reinterpret_cast<const float4 *>(a.bias + n0 + kl);
+                        *reinterpret_cast<float4 *>(&et[ml * ELD + kl]) =
+                            make_float4(acc[i][j][g * 4 + 0] + b.x, acc[i][j][g * 4 + 1] + b.y, acc[i][j][g * 4 + 2] + b.z, acc[i][j][g * 4 + 3] + b.w);
+                    }
+        }
+        __syncthreads();
+        if (a.pool2) {
+            for (int c = tid; c < (BM / 4) * CPR; c += NT) {
+                const int r4 = c / CPR, col = (c % CPR) * 8;
+                const int m = pixel(r4 * 4), k = n0 + col;
+                if (m < 0 || k >= a.K) continue;
+                float v[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = -INFINITY;
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const float4 lo = *reinterpret_cast<const float4 *>(&et[(r4 * 4 + rr) * ELD + col]);
+                    const float4 hi = *reinterpret_cast<const float4 *>(&et[(r4 * 4 + rr) * ELD + col + 4]);
+                    v[0] = fmaxf(v[0], lo.x); v[1] = fmaxf(v[1], lo.y); v[2] = fmaxf(v[2], lo.z); v[3] = fmaxf(v[3], lo.w);
+                    v[4] = fmaxf(v[4], hi.x); v[5] = fmaxf(v[5], hi.y); v[6] = fmaxf(v[6], hi.z); v[7] = fmaxf(v[7], hi.w);
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
+                store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+            }
+            return;
+        }
+#pragma unroll
+        for (int it = 0; it < EP_IT; ++it) {
+            const int c = tid + it * NT;
+            const int row = c / CPR, col = (c % CPR) * 8;
+            const int m = pixel(min(row, BM - 1)), k = n0 + col;
+            if (c >= BM * CPR || m < 0 || k >= a.K) continue;
+            float v[8];
+            const float4 lo = *reinterpret_cast<const float4 *>(&et[row * ELD + col]);
+            const float4 hi = *reinterpret_cast<const float4 *>(&et[row * ELD + col + 4]);
+            v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+            if (add_res) {
+                const Pack<T, 8> rp = __builtin_bit_cast(Pack<T, 8>, res_raw[it]);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] += to_f32(rp.e[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
+            store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+        }
+        return;
+    }
+    if (!owner) return;
+    const bool vec_ok = (a.y_ct % 4 == 0) && (a.y_coff % 4 == 0) && (a.res_ct % 4 == 0);
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            const int m = pixel(wm * SUBM + j * MF + frow);
+            if (m < 0) continue;
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) {
+                const int k = n0 + wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * fgrp) : (4 * fgrp));
+                if (k >= a.K) continue;
+                const float4 b = *reinterpret_cast<const float4 *>(a.bias + k);    // padded to n_pad
+                float v[4] = {acc[i][j][g * 4] + b.x, acc[i][j][g * 4 + 1] + b.y, acc[i][j][g * 4 + 2] + b.z, acc[i][j][g * 4 + 3] + b.w};
+                if (vec_ok && k + 4 <= a.K) {
+                    if (res) {
+                        float rv[4];
+                        load_pack<T, 4>(res + (int64_t)m * a.res_ct + k, rv);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) v[t] += rv[t];
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
+                    store_pack<T, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+                } else {
+                    for (int t = 0; t < 4 && k + t < a.K; ++t) {
+                        float f = v[t];
+                        if (res) f += to_f32(res[(int64_t)m * a.res_ct + k + t]);
+                        f = apply_act(f, a.act);
+                        T o;
+                        from_f32(f, o);
+                        y[(int64_t)m * a.y_ct + a.y_coff + k + t] = o;
+                    }
+                }
+            }
+        }
+}
+
+// BN output channels x BM pixels per workgroup; WN x WM waves over the tile, WK such groups that share the reduction;
+// KD 64-deep slices of the reduction per stage, NBUF stages in LDS.
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
+__device__ __forceinline__ void tile_body(const OpArgs &a) {
+    set_wave_priority(a.prio);
+    constexpr int NW = WN * WM * WK;
+    constexpr int SUBN = BN / WN, SUBM = BM / WM;
+    constexpr int MF = (SUBN % 32 == 0 && SUBM % 32 == 0) ? 32 : 16;
+    constexpr int TN = SUBN / MF, TM = SUBM / MF;
+    static_assert(TN >= 1 && TM >= 1, "wave tile smaller than one matrix instruction");
+    constexpr int KS = MF == 32 ? 16 : 32;                 // reduction elements per matrix instruction
+    constexpr int STEPS = KD * TK / KS;                    // instruction steps per stage
+    static_assert(STEPS % WK == 0, "the wave groups share a stage evenly");
+    constexpr int MY_STEPS = STEPS / WK;
+    constexpr int ACC = MF == 32 ? 16 : 4;
+    constexpr int WQ = KD * BN / 8 / NW, XQ = KD * BM / 8 / NW;   // loads of a wave per stage: 8 rows of 128 bytes each
+    static_assert(WQ * NW * 8 == KD * BN && XQ * NW * 8 == KD * BM, "the waves share the loads of a stage evenly");
+    constexpr int L = WQ + XQ;
+    constexpr int W_BYTES = KD * BN * 128, X_BYTES = KD * BM * 128, STAGE = W_BYTES + X_BYTES;
+    constexpr int RED_BYTES = (WK - 1) * BN * BM * 4, ELD = BN + 4, EP_BYTES = BM * ELD * 4;
+    constexpr int LDS_BYTES = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES});
+    typedef typename Mma<T, MF>::Acc Acc;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    __shared__ int s_last;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
+
+    const int M = a.N * a.P * a.Q;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = a.n_pad / BN;
+    const int total = tiles_m * tiles_n * a.split_k;
+    const int per_xcd = (total + XCDS - 1) / XCDS;
+    const int vid = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
+    if (vid >= total) return;
+    const int z = vid % a.split_k;
+    const int tile = vid / a.split_k;
+    const int tn_idx = a.tile_order ? tile / tiles_m : tile % tiles_n;
+    const int tm_idx = a.tile_order ? tile % tiles_m : tile / tiles_n;
+    const int n0 = tn_idx * BN, m0 = tm_idx * BM;
+    const int nst = a.k_pad / (TK * KD);
+    const int per = (nst + a.split_k - 1) / a.split_k;
+    const int st0 = z * per;
+    const int ns = min(nst, st0 + per) - st0;
+
+    const int XS = a.x_ct;
+    const T *x = (const T *)a.x + a.x_coff;
+    const u32x4 rsrc_x = raw_buffer(x, ((int64_t)a.N * a.H * a.W * XS - a.x_coff) * (int)sizeof(T));
+    const u32x4 rsrc_w = raw_buffer(a.w, (int64_t)a.n_pad * a.k_pad * 2);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+
+    // A load covers 8 rows; lane l delivers 16-byte column l % 8 of row l / 8.  Column c of LDS row r holds piece
+    // c ^ (r / 2 % 8) of that row: 16 lanes reading one piece of 16 rows touch each of the 64 banks once.  The groups of 8
+    // rows a wave loads are all even or all odd, as the wave is.
+    static_assert(NW % 2 == 0 && BN % 16 == 0 && BM % 16 == 0, "a wave's row groups have one parity");
+    const int lrow = lane >> 3, piece = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
+
+    const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + piece * 8) * 2u;
+    uint32_t ws[WQ];                                       // scalar part of each filter load
+#pragma unroll
+    for (int i = 0; i < WQ; ++i) {
+        const int q = i * NW + wave, kd = q / (BN / 8), rg = q % (BN / 8);
+        ws[i] = (uint32_t)(rg * 8 * a.k_pad + (st0 * KD + kd) * TK) * 2u;
+    }
+    constexpr int NP = KD == 1 ? 1 : XQ;                   // positions along j tracked (loads of one 64-slice share one)
+    uint32_t xoff[XQ], xmask[XQ];
+    int ptap[NP], pch[NP];                                 // tap and channel of each position (TG_TAP: wave-uniform)
+    uint32_t xs = (uint32_t)(st0 * KD * TK) * 2u;          // TG_POINT: scalar offset
+#pragma unroll
+    for (int i = 0; i < XQ; ++i) {
+        const int q = i * NW + wave, kd = q / (BM / 8), rg = q % (BM / 8);
+        const int m = m0 + rg * 8 + lrow;
+        const bool ok = m < M;
+        const uint32_t mm = ok ? (uint32_t)m : 0u;
+        const uint32_t mq = a.pool2 ? mm >> 2 : mm;
+        const uint32_t pqd = a.pool2 ? (uint32_t)((a.P >> 1) * (a.Q >> 1)) : (uint32_t)(a.P * a.Q);
+        const uint32_t qd = a.pool2 ? (uint32_t)(a.Q >> 1) : (uint32_t)a.Q;
+        const uint32_t t1 = __umulhi(a.divpq_m, mq);
+        const int n = (int)((t1 + ((mq - t1) >> a.divpq_s1)) >> a.divpq_s2);
+        const uint32_t rem = mq - (uint32_t)n * pqd;
+        const uint32_t t2 = __umulhi(a.divq_m, rem);
+        int p = (int)((t2 + ((rem - t2) >> a.divq_s1)) >> a.divq_s2);
+        int qq = (int)(rem - (uint32_t)p * qd);
+        if (a.pool2) {
+            p = 2 * p + (int)((mm >> 1) & 1u);
+            qq = 2 * qq + (int)(mm & 1u);
+        }
+        const int ih0 = p * a.sh - a.ph, iw0 = qq * a.sw - a.pw;
+        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (MODE == TG_CHUNK ? 0 : piece * 8)) * 2u;
+        if constexpr (MODE == TG_POINT) {
+            xoff[i] = ok ? xoff[i] + (uint32_t)(kd * TK * 2) : OUT_OF_RANGE;
+        } else {
+            // bit r: filter row r reads inside the image for this pixel; bit 16 + s: so does filter column s
+            auto range = [](int first, int extent, int window) {
+                const int lo = min(max(-first, 0), window), hi = min(max(extent - first, 0), window);
+                return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+            };
+            xmask[i] = ok ? range(ih0, a.H, a.R) | range(iw0, a.W, a.S) << 16 : 0u;
+        }
+        if (MODE != TG_POINT && i < NP) {
+            const int j0 = (st0 * KD + (KD == 1 ? 0 : kd)) * TK + (MODE == TG_CHUNK ? piece * 8 : 0);
+            ptap[i] = j0 / a.C;
+            pch[i] = j0 - ptap[i] * a.C;
+        }
+    }
+    const int adv_t = KD * TK / a.C, adv_c = KD * TK - adv_t * a.C;
+    const uint32_t inv_s = (uint32_t)((0x100000000ull + (uint32_t)a.S - 1) / (uint32_t)a.S);   // 0 for S == 1
+
+    auto issue = [&](int buf) {
+        const uint32_t base = lds0 + (uint32_t)(buf * STAGE);
+#pragma unroll
+        for (int i = 0; i < WQ; ++i) {
+            load_to_lds(rsrc_w, wv, ws[i], base + (uint32_t)((i * NW + wave) * 1024));
+            ws[i] += KD * TK * 2;
+        }
+        uint32_t toff[NP], trow[NP], tcol[NP];
+        if constexpr (MODE != TG_POINT) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int tr = a.S == 1 ? ptap[i] : (int)__umulhi((uint32_t)ptap[i], inv_s);
+                const int tc = ptap[i] - tr * a.S;
+                toff[i] = (uint32_t)((tr * a.W + tc) * XS + pch[i]) * 2u;
+                trow[i] = (uint32_t)min(tr, 15);           // beyond the window (padding of the reduction): a bit that is never set
+                tcol[i] = (uint32_t)(16 + tc);
+                ptap[i] += adv_t;
+                pch[i] += adv_c;
+                const bool carry = pch[i] >= a.C;
+                pch[i] -= carry ? a.C : 0;
+                ptap[i] += carry ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < XQ; ++i) {
+            const uint32_t dst = base + (uint32_t)(W_BYTES + (i * NW + wave) * 1024);
+            if constexpr (MODE == TG_POINT) {
+                load_to_lds(rsrc_x, xoff[i], xs, dst);
+            } else {
+                const int pi = KD == 1 ? 0 : i;
+                const uint32_t off = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u ? xoff[i] + toff[pi] : OUT_OF_RANGE;
+                load_to_lds(rsrc_x, off, 0u, dst);
+            }
+        }
+        xs += KD * TK * 2;
+    };
+
+    Acc acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
+
+    const int frow = lane % MF, fgrp = lane / MF;          // operand row and reduction group of this lane
+    struct Frag { u32x4 w[TN], x[TM]; };
+    const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), xrow = (uint32_t)(W_BYTES + (wm * SUBM + frow) * 128);
+    const uint32_t swz = (uint32_t)((frow >> 1) & 7);
+    auto load_frag = [&](uint32_t buf, int s, Frag &f) {   // s: step of the stage
+        constexpr int PPS = KS / 8;                        // pieces per step
+        const int kd = s / (TK / KS), c0 = (s % (TK / KS)) * PPS;
+        const uint32_t col = ((uint32_t)(c0 + fgrp) ^ swz) * 16u;
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+            f.w[i] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BN * 128 + i * MF * 128) + wrow + col]);
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+            f.x[j] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BM * 128 + j * MF * 128) + xrow + col]);
+    };
+    auto compute = [&](int buf) {
+        const uint32_t b = (uint32_t)(buf * STAGE);
+        Frag f[2];
+        const int s0 = wk * MY_STEPS;
+        load_frag(b, s0, f[0]);
+#pragma unroll
+        for (int s = 0; s < MY_STEPS; ++s) {
+            if (s + 1 < MY_STEPS) load_frag(b, s0 + s + 1, f[(s + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);             // the next step's operands are requested before this one multiplies
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(f[s & 1].w[i], f[s & 1].x[j], acc[i][j]);
+        }
+    };
+
+    for (int s = 0; s < NBUF - 1; ++s)
+        if (s < ns) issue(s);
+    int rbuf = 0, ibuf = NBUF - 1;
+    for (int t = 0; t < ns; ++t) {
+        // stages issued after stage t: NBUF - 2 of them, fewer at the end
+        const int later = min(ns - 1 - t, NBUF - 2);
+        if (later >= NBUF - 2) wait_and_meet<(NBUF - 2) * L>();
+        else if (NBUF > 3 && later == NBUF - 3) wait_and_meet<(NBUF > 3 ? NBUF - 3 : 0) * L>();
+        else wait_and_meet<0>();
+        if (t + NBUF - 1 < ns) issue(ibuf);
+        compute(rbuf);
+        rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
+        ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
+    }
+    wait_and_meet<0>();                                    // the tile buffers are free
+
+    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
+        const int m = m0 + ml;
+        return m < M ? (a.pool2 ? m >> 2 : m) : -1;
+    });
+}
+
+// 3x3 windows, stride 1, padding 1, C % 64 == 0: the nine taps of a 64-channel chunk read the same input pixels, so those
+// are staged once per chunk as a patch and every tap reads its operand rows at a shifted position.
+// The map is cut into panels of `panel` columns; inside a panel pixels are numbered row by row through all images, and a
+// tile is BM consecutive ones.  Its patch holds the rows from the one above its first to the one below its last, each
+// panel + 2 pixels wide, with an empty row between two images; what lies outside an image is loaded out of range, i.e. zero.
+// The filter bank is [n_pad][chunk][tap][64].
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+__device__ __forceinline__ void patch_body(const OpArgs &a) {
+    set_wave_priority(a.prio);
+    constexpr int NW = WN * WM * WK, NBUF = 3;
+    constexpr int SUBN = BN / WN, SUBM = BM / WM;
+    constexpr int MF = (SUBN % 32 == 0 && SUBM % 32 == 0) ? 32 : 16;
+    constexpr int TN = SUBN / MF, TM = SUBM / MF;
+    constexpr int KS = MF == 32 ? 16 : 32, PPS = KS / 8;
+    constexpr int STEPS = KD * TK / KS, MY_STEPS = STEPS / WK;
+    static_assert(STEPS % WK == 0 && 9 % KD == 0, "stages are whole taps, shared evenly by the wave groups");
+    constexpr int ACC = MF == 32 ? 16 : 4;
+    constexpr int SPC = 9 / KD;                            // stages per chunk
+    constexpr int WQ = KD * BN / 8 / NW, PL = PC / 8 / NW; // loads of a wave per stage / per patch
+    static_assert(WQ * NW * 8 == KD * BN && PL * NW * 8 == PC, "the waves share the loads evenly");
+    // The next chunk's patch is requested during this chunk's stages, early enough to have landed with the wait of its first
+    constexpr int XPS = (PL + SPC - NBUF + 1) / (SPC - NBUF + 2);
+    constexpr int L = WQ + XPS;
+    constexpr int W_BYTES = KD * BN * 128, P_BYTES = PC * 128, DUMP = NBUF * W_BYTES + 2 * P_BYTES;
+    constexpr int RED_BYTES = (WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
+    constexpr int LDS_BYTES = std::max({DUMP + 1024, RED_BYTES, EP_BYTES});
+    typedef typename Mma<T, MF>::Acc Acc;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    __shared__ int s_last;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
+
+    const int Wt = a.panel, PW = Wt + 2;
+    const int panels = (a.Q + Wt - 1) / Wt;
+    const int ppx = a.N * a.P * Wt;                        // pixels of a panel
+    const int tiles_p = (ppx + BM - 1) / BM;
+    const int tiles_m = tiles_p * panels, tiles_n = a.n_pad / BN;
+    const int total = tiles_m * tiles_n * a.split_k;
+    const int per_xcd = (total + XCDS - 1) / XCDS;
+    const int vid = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
+    if (vid >= total) return;
+    const int z = vid % a.split_k;
+    const int tile = vid / a.split_k;
+    const int tn_idx = a.tile_order ? tile / tiles_m : tile % tiles_n;
+    const int tm_idx = a.tile_order ? tile % tiles_m : tile / tiles_n;
+    const int pn = tm_idx / tiles_p;
+    const int n0 = tn_idx * BN, m0 = (tm_idx - pn * tiles_p) * BM;
+    const int nch = a.C / TK;
+    const int per = (nch + a.split_k - 1) / a.split_k;
+    const int c_begin = z * per;
+    const int nc = min(nch, c_begin + per) - c_begin;      // chunks of this workgroup (>= 1 by construction)
+
+    // image row (through all images) and column of pixel i of the panel; divisors: panel width, rows of the map (halved when pooling)
+    auto locate = [&](uint32_t i, int &row, int &img, int &col) {
+        const uint32_t mq = a.pool2 ? i >> 2 : i;
+        const uint32_t wd = a.pool2 ? (uint32_t)Wt >> 1 : (uint32_t)Wt, pd = a.pool2 ? (uint32_t)a.P >> 1 : (uint32_t)a.P;
+        const uint32_t t1 = __umulhi(a.divq_m, mq);
+        const uint32_t rr = (t1 + ((mq - t1) >> a.divq_s1)) >> a.divq_s2;
+        const uint32_t t2 = __umulhi(a.divpq_m, rr);
+        img = (int)((t2 + ((rr - t2) >> a.divpq_s1)) >> a.divpq_s2);
+        row = (int)(rr - (uint32_t)img * pd);
+        col = (int)(mq - rr * wd);
+        if (a.pool2) {
+            row = 2 * row + (int)((i >> 1) & 1u);
+            col = 2 * col + (int)(i & 1u);
+        }
+    };
+    int row_a, img_a, row_b, img_b, col_u;
+    locate((uint32_t)m0, row_a, img_a, col_u);
+    locate((uint32_t)(min(m0 + BM, ppx) - 1), row_b, img_b, col_u);
+    const int need = ((img_b - img_a) * (a.H + 1) + row_b - row_a + 3) * PW;   // patch pixels in use
+
+    const int XS = a.x_ct;
+    const T *x = (const T *)a.x + a.x_coff;
+    const u32x4 rsrc_x = raw_buffer(x, ((int64_t)a.N * a.H * a.W * XS - a.x_coff) * (int)sizeof(T));
+    const u32x4 rsrc_w = raw_buffer(a.w, (int64_t)a.n_pad * a.k_pad * 2);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    // Columns of the LDS rows as in tile_body; a patch row's key is its pixel's number without the two border columns of the
+    // rows above it, so that 16 consecutive pixels of a tile have 16 consecutive keys wherever a map row ends among them.
+    static_assert(NW % 2 == 0 && BN % 16 == 0, "a wave's row groups have one parity");
+    const int lrow = lane >> 3;
+
+    const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + ((lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1))) * 8) * 2u;
+    uint32_t ws[WQ];
+#pragma unroll
+    for (int i = 0; i < WQ; ++i) {
+        const int q = i * NW + wave, kd = q / (BN / 8), rg = q % (BN / 8);
+        ws[i] = (uint32_t)(rg * 8 * a.k_pad + (c_begin * 9 + kd) * TK) * 2u;
+    }
+    uint32_t xoff[PL];
+    const uint32_t inv_pw = ((1u << 20) + (uint32_t)PW - 1) / (uint32_t)PW, inv_h = ((1u << 20) + (uint32_t)a.H) / (uint32_t)(a.H + 1);
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+        const uint32_t px = (uint32_t)((i * NW + wave) * 8 + lrow);
+        const int prow = (int)((px * inv_pw) >> 20), pcol = (int)px - prow * PW;
+        const int piece = (lane & 7) ^ ((int)((px >> 1) - (uint32_t)prow) & 7);
+        const int d = row_a - 1 + prow;                    // row counted from the top of the first image, one empty row per image
+        const int di = d < 0 ? 0 : (int)(((uint32_t)d * inv_h) >> 20);
+        const int ih = d - di * (a.H + 1), n = img_a + di, iw = pn * Wt - 1 + pcol;
+        const bool ok = ((int)px < need) & ((uint32_t)ih < (uint32_t)a.H) & ((uint32_t)iw < (uint32_t)a.W) & (n < a.N);
+        xoff[i] = ok ? (uint32_t)(((n * a.H + ih) * a.W + iw) * XS + piece * 8) * 2u : OUT_OF_RANGE;
+    }
+    uint32_t xs = (uint32_t)(c_begin * TK) * 2u;           // channel offset of the patch requested next
+
+    auto issue_patch = [&](int i, int buf) {
+        load_to_lds(rsrc_x, xoff[i], xs, lds0 + (uint32_t)(NBUF * W_BYTES + buf * P_BYTES + (i * NW + wave) * 1024));
+    };
+    auto issue_w = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < WQ; ++i) {
+            load_to_lds(rsrc_w, wv, ws[i], lds0 + (uint32_t)(buf * W_BYTES + (i * NW + wave) * 1024));
+            ws[i] += KD * TK * 2;
+        }
+    };
+    auto issue_none = [&]() { load_to_lds(rsrc_x, OUT_OF_RANGE, 0u, lds0 + DUMP); };   // keeps the number of loads per stage the same
+
+    Acc acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
+
+    const int frow = lane % MF, fgrp = lane / MF;
+    struct Frag { u32x4 w[TN], x[TM]; };
+    const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), wswz = (uint32_t)((frow >> 1) & 7);
+    int ppos[TM], prow[TM];                                          // patch pixel of tap (0, 0) for this lane's pixels
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+        int row, img, col;
+        locate((uint32_t)min(m0 + wm * SUBM + j * MF + frow, ppx - 1), row, img, col);
+        prow[j] = (img - img_a) * (a.H + 1) + row - row_a;
+        ppos[j] = prow[j] * PW + col;
+    }
+
+    // one stage: taps tap0 .. tap0 + KD - 1, filters in buffer wb, patch in buffer pb
+    auto compute = [&](int tap0, int wb, int pb) {
+        Frag f[2];
+        const int s0 = wk * MY_STEPS;
+        auto load_frag = [&](int s, Frag &fr) {
+            const int kd = s / (TK / KS), c0 = (s % (TK / KS)) * PPS;
+            const int tap = tap0 + kd;
+            const uint32_t wcol = ((uint32_t)(c0 + fgrp) ^ wswz) * 16u;
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+                fr.w[i] = *reinterpret_cast<const u32x4 *>(&smem[(uint32_t)(wb * W_BYTES + kd * BN * 128 + i * MF * 128) + wrow + wcol]);
+            const int shift = (tap / 3) * PW + tap % 3;
+#pragma unroll
+            for (int j = 0; j < TM; ++j) {
+                const uint32_t rr = (uint32_t)(ppos[j] + shift);
+                const uint32_t col = ((uint32_t)(c0 + fgrp) ^ (((rr >> 1) - (uint32_t)(prow[j] + tap / 3)) & 7u)) * 16u;
+                fr.x[j] = *reinterpret_cast<const u32x4 *>(&smem[(uint32_t)(NBUF * W_BYTES) + (uint32_t)(pb * P_BYTES) + rr * 128u + col]);
+            }
+        };
+        load_frag(s0, f[0]);
+#pragma unroll
+        for (int s = 0; s < MY_STEPS; ++s) {
+            if (s + 1 < MY_STEPS) load_frag(s0 + s + 1, f[(s + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);             // the next step's operands are requested before this one multiplies
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(f[s & 1].w[i], f[s & 1].x[j], acc[i][j]);
+        }
+    };
+
+#pragma unroll
+    for (int i = 0; i < PL; ++i) issue_patch(i, 0);
+    xs += TK * 2;
+#pragma unroll
+    for (int s = 0; s < NBUF - 1; ++s) {
+        issue_w(s);
+#pragma unroll
+        for (int i = 0; i < XPS; ++i) issue_none();
+    }
+    const int ns = nc * SPC;
+    auto stage = [&]<int I>(int c) {
+        // the stages of a chunk are a multiple of the filter buffers, so stage I of every chunk uses buffer I % NBUF
+        const bool last = c + 1 == nc;
+        if (I == SPC - 1 && last) wait_and_meet<0>();
+        else wait_and_meet<L>();
+        if (!(last && I + NBUF - 1 >= SPC)) {
+            issue_w((I + NBUF - 1) % NBUF);
+#pragma unroll
+            for (int i = 0; i < XPS; ++i) {
+                if (I * XPS + i < PL && !last) issue_patch(I * XPS + i < PL ? I * XPS + i : 0, (c + 1) & 1);
+                else issue_none();
+            }
+        }
+        compute(I * KD, I % NBUF, c & 1);
+    };
+    static_assert(SPC % NBUF == 0 && NBUF == 3, "buffer of a stage");
+    (void)ns;
+    for (int c = 0; c < nc; ++c) {
+        [&]<int... I>(std::integer_sequence<int, I...>) { (stage.template operator()<I>(c), ...); }(std::make_integer_sequence<int, SPC>{});
+        xs += TK * 2;
+    }
+    wait_and_meet<0>();
+
+    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
+        const int i = m0 + ml;
+        int row, img, col;
+        locate((uint32_t)min(i, ppx - 1), row, img, col);
+        const int q = pn * Wt + col;
+        if (i >= ppx || q >= a.Q) return -1;
+        return a.pool2 ? (img * (a.P >> 1) + (row >> 1)) * (a.Q >> 1) + (q >> 1) : (img * a.P + row) * a.Q + q;
+    });
+}
+
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
+__global__ void __launch_bounds__(64 * WN * WM * WK) tile_kernel(OpArgs a) {
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a);
+}
+
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
+__global__ void __launch_bounds__(64 * WN * WM * WK) tile_pair_kernel(OpArgsPair p) {
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y]);
+}
+
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+__global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a);
+}
+
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+__global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPair p) {
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(p.a[blockIdx.y]);
+}
+
+// ---- choice of form -----------------------------------------------------------------------------------------------
+namespace {
+
+struct TileForm {
+    int bn, bm, kd, threads, patch_pixels;                 // patch_pixels 0: tile_body
+    // Time of a launch in us on MI355X: start + wave * (n - 1) + ns * (stage + crowd * (n - 1)), and split_once + split_each *
+    // split if the reduction is split; n: workgroups per compute unit, ns: stages of a workgroup.  Fitted to 27 800 timings
+    // of the 1143 distinct convolutions and classifiers of nine networks at batches 1 to 64 (launch gap included).  Picking
+    // the form and split with the least estimate costs 1.1 % of a network's time over picking the fastest measured one.
+    double start, wave, stage, crowd, split_once, split_each;
+};
+
+constexpr TileForm FORMS[] = {
+    {128, 128, 1, 256, 0, 5.33, 2.29, 0.537, 0.350, 1.98, 0.995},
+    {128, 64, 1, 256, 0, 4.17, 1.29, 0.372, 0.209, 1.49, 0.726},
+    {64, 64, 1, 256, 0, 3.68, 0.965, 0.285, 0.133, 1.52, 0.375},
+    {64, 64, 2, 512, 0, 3.66, 2.50, 0.402, 0.515, 2.07, 0.218},
+    {64, 32, 2, 512, 0, 3.63, 1.11, 0.323, 0.235, 1.35, 0.266},
+    {64, 16, 2, 256, 0, 2.79, 0.723, 0.295, 0.166, 1.60, 0.140},
+    {128, 256, 1, 512, 384, 9.21, 5.92, 0.545, 0.823, 2.20, 1.36},
+    {128, 128, 1, 512, 256, 7.59, 6.90, 0.331, 0.357, 2.31, 0.748},
+    {128, 64, 1, 512, 192, 5.83, 4.94, 0.219, 0.238, 1.52, 0.602},
+    {64, 64, 3, 512, 192, 4.96, 3.74, 0.413, 0.438, 1.53, 0.284},
+    {64, 32, 1, 512, 128, 4.56, 1.38, 0.118, 0.109, 1.38, 0.252},
+};
+constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]), FORM_64x16 = 5;
+constexpr int MAX_SPLIT = 8, TARGET_WGS = 768, UNITS = 256;
+
+int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// Columns of a panel for a map of P x Q pixels and N images: the fewest tiles whose patches all fit PC pixels, then the
+// narrowest patch; 0 if there is none.
+int patch_panel(int N, int P, int Q, int BM, int PC, bool pool) {
+    int best = 0;
+    int64_t best_tiles = 0;
+    int best_need = 0;
+    for (int wt = pool ? 2 : 1; wt <= Q && 3 * (wt + 2) <= PC; wt += pool ? 2 : 1) {
+        const int panels = (Q + wt - 1) / wt;
+        const int64_t ppx = (int64_t)N * P * wt, tiles = (ppx + BM - 1) / BM;
+        if (best && tiles * panels > best_tiles) continue;
+        int need = 0;
+        for (int64_t t = 0; t < tiles && need <= PC; ++t) {
+            // first and last image row of the tile, counted with one empty row between images
+            auto at = [&](int64_t i) {
+                const int64_t row = pool ? i / 4 / (wt / 2) * 2 + (i >> 1 & 1) : i / wt;
+                return row / P * (P + 1) + row % P;
+            };
+            need = std::max<int>(need, (int)(at(std::min(t * BM + BM, ppx) - 1) - at(t * BM) + 3) * (wt + 2));
+        }
+        if (need > PC) continue;
+        if (!best || tiles * panels < best_tiles || need < best_need) {
+            best = wt;
+            best_tiles = tiles * panels;
+            best_need = need;
+        }
+    }
+    return best;
+}
+
+// Pixel tiles of a form: over the flattened map, or per panel.
+int pixel_tiles(const TileForm &f, const OpArgs &a, int panel) {
+    if (f.patch_pixels == 0) return cdiv(a.N * a.P * a.Q, f.bm);
+    return cdiv(a.Q, panel) * cdiv(a.N * a.P * panel, f.bm);
+}
+
+void set_walk(OpArgs &a) {
+    const int half = a.pool2 ? 2 : 1;
+    const uint32_t q = (uint32_t)((a.panel > 0 ? a.panel : a.Q) / half), p = (uint32_t)(a.P / half);
+    make_divisor(q, a.divq_m, a.divq_s1, a.divq_s2);
+    make_divisor(a.panel > 0 ? p : p * q, a.divpq_m, a.divpq_s1, a.divpq_s2);
+}
+
+}  // namespace
+
+// Form, split and launch shape of a convolution (a fully connected layer is a 1x1 one) with C % 8 == 0 and a window of at
+// most 15 x 15: a pure function of the layer's shape.  narrow: the 64 x 16 tile whatever the estimate says (the fused 1x1 +
+// depthwise kernels reproduce its order of additions).
+bool plan_tile(OpArgs &a, bool narrow) {
+    if (a.C % 8 != 0 || a.R > 15 || a.S > 15) return false;
+    const bool patch_ok = patch_stageable(a);
+    // long reductions over a wide map that has fewer than 72 tiles of 64 x 64 are always split
+    const int M = a.N * a.P * a.Q;
+    const int min_split = a.kernel_id == K_IGEMM_64x64 && M > 4096 && a.gemm_k >= 16 * TK && cdiv(M, 64) * cdiv(a.K, 64) < 72 ? 2 : 1;
+    double best = 0;
+    int form = -1, split = 1, panel = 0;
+    for (int f = 0; f < N_FORMS; ++f) {
+        const TileForm &t = FORMS[f];
+        if (narrow && f != FORM_64x16) continue;
+        if (t.patch_pixels > 0 && !patch_ok) continue;
+        if (t.patch_pixels == 0 && a.kernel_id == K_PCONV) continue;
+        if (t.bn > 64 && a.K <= t.bn / 2) continue;         // more than half of the tile would be padding
+        const int w = t.patch_pixels > 0 ? patch_panel(a.N, a.P, a.Q, t.bm, t.patch_pixels, false) : 0;
+        if (t.patch_pixels > 0 && w == 0) continue;
+        const int tiles = pixel_tiles(t, a, w) * cdiv(a.K, t.bn);
+        const int units = t.patch_pixels > 0 ? a.C / TK : cdiv(a.gemm_k, TK * t.kd);      // what a split cuts
+        for (int s = 1; s <= MAX_SPLIT; ++s) {
+            if (s > 1 && (tiles * s > TARGET_WGS || (t.patch_pixels > 0 ? s > units : 2 * s > units))) break;
+            const int per = cdiv(units, s);
+            if (cdiv(units, per) != s) continue;            // an empty split
+            const int ns = t.patch_pixels > 0 ? per * 9 / t.kd : per, n = cdiv(tiles * s, UNITS);
+            const double us = t.start + t.wave * (n - 1) + ns * (t.stage + t.crowd * (n - 1)) + (s > 1 ? t.split_once + t.split_each * s : 0.0);
+            if (s < min_split) continue;
+            if (form < 0 || us < best) { best = us; form = f; split = s; panel = w; }
+        }
+    }
+    const TileForm &t = FORMS[form];
+    a.form = form;
+    a.panel = panel;
+    a.split_k = split;
+    a.block = t.threads;
+    a.n_pad = cdiv(a.K, t.bn) * t.bn;
+    a.k_pad = t.patch_pixels > 0 ? a.gemm_k : cdiv(a.gemm_k, TK * t.kd) * TK * t.kd;
+    // Consecutive tiles run on one XCD: they walk the channel tiles of one pixel tile when the activations are the larger
+    // operand, the pixel tiles of one channel tile otherwise.
+    a.tile_order = ((double)a.K * a.gemm_k > (double)a.N * a.H * a.W * a.C) ? 1 : 0;
+    a.grid_x = cdiv(pixel_tiles(t, a, panel) * (a.n_pad / t.bn) * split, XCDS) * XCDS;
+    a.grid_y = a.grid_z = 1;
+    a.wk = 1;
+    set_walk(a);
+    return true;
+}
+
+// One ascending pass over the reduction on 64 x 16 tiles.
+bool tile_is_narrow(const OpArgs &a) { return a.form == FORM_64x16 && a.split_k == 1; }
+
+void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats) {
+    const TileForm &t = FORMS[a.form];
+    *tiles = (size_t)pixel_tiles(t, a, a.panel) * (a.n_pad / t.bn);
+    *floats = (size_t)a.split_k * t.bn * t.bm;
+}
+
+// The plan of the same convolution with a 2x2 max pooling in its epilogue.  False: the patch form has no panel of an even
+// width for this map.
+bool plan_tile_pooled(OpArgs &a) {
+    const TileForm &t = FORMS[a.form];
+    a.pool2 = 1;
+    if (a.panel > 0) {
+        const int was = pixel_tiles(t, a, a.panel);
+        a.panel = patch_panel(a.N, a.P, a.Q, t.bm, t.patch_pixels, true);
+        if (a.panel == 0 || (a.split_k > 1 && pixel_tiles(t, a, a.panel) > was)) return false;   // the workspace is laid out for `was`
+        a.grid_x = cdiv(pixel_tiles(t, a, a.panel) * (a.n_pad / t.bn) * a.split_k, XCDS) * XCDS;
+    }
+    set_walk(a);
+    return true;
+}
+
+template <typename T>
+static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
+    const dim3 grid(a.grid_x), block(a.block);
+    auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
+        auto go = [&]<int MODE>() {
+            MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, st, a, mate);
+        };
+        if (a.C % TK != 0) go.template operator()<TG_CHUNK>();
+        else if (a.R == 1 && a.S == 1 && a.ph == 0 && a.pw == 0) go.template operator()<TG_POINT>();
+        else go.template operator()<TG_TAP>();
+    };
+    auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
+        MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
+    };
+    switch (a.form) {
+        case 0: tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
+        case 1: tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+        case 2: tile.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
+        case 3: tile.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;
+        case 4: tile.template operator()<64, 32, 2, 1, 4, 2, 3>(); break;
+        case 5: tile.template operator()<64, 16, 4, 1, 1, 2, 3>(); break;
+        case 6: patch.template operator()<128, 256, 2, 4, 1, 1, 384>(); break;
+        case 7: patch.template operator()<128, 128, 2, 2, 2, 1, 256>(); break;
+        case 8: patch.template operator()<128, 64, 2, 2, 2, 1, 192>(); break;
+        case 9: patch.template operator()<64, 64, 2, 2, 2, 3, 192>(); break;
+        case 10: patch.template operator()<64, 32, 2, 1, 4, 1, 128>(); break;
+        default: return (int)hipErrorInvalidValue;
+    }
+    return (int)hipGetLastError();
+}
+
+int launch_tile(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates) {
+    if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX || a.groups > 1)) return (int)hipErrorInvalidValue;
+    if (a.dtype == MT_F16) return launch_tile_typed<f16>(a, (hipStream_t)stream, mate, n_mates);
+    if (a.dtype == MT_BF16) return launch_tile_typed<bf16>(a, (hipStream_t)stream, mate, n_mates);
+    return (int)hipErrorInvalidValue;
+}
+
+}  // namespace mt

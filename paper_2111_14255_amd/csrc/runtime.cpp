@@ -63,105 +63,92 @@ namespace {
 // input line nine times through the L1, which bounds it on large maps (64 -> 64 on 56x56 at batch 16 / 128: 12.1 / 70.4 us
 // against 15.0 / 65.7 us on the tile kernel).
 constexpr int ROWB_MIN_PIXELS = 8192, ROWB_MAX_PIXELS_3X3 = 131072;
-constexpr int PCONV_MIN_TILES = 150;
 
 bool needs_weights(int kind) { return kind == MT_CONV || kind == MT_DWCONV || kind == MT_FC; }
 
-// Kernel, tile and split choice of a convolution / fully connected layer: a pure function of the GEMM shape.
+// Kernel, tile and split choice of a convolution / fully connected layer: a pure function of its shape.
 void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k) {
     auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
     p.k_pad = cdiv(gemm_k, IGEMM_BK) * IGEMM_BK;
     p.grid_y = p.grid_z = 1;
     p.block = 256;
     p.split_k = 1;
-    if (M <= 8 && p.H == 1 && p.W == 1 && p.R == 1 && p.S == 1 && p.vec_a && p.groups <= 1) {
+    p.wk = 1;
+    const bool vec = p.vec_a != 0;
+    const double macs = (double)M * Kc * gemm_k;
+    // Weight streaming on the vector units: they have two products to form per filter element and pixel, which hides under the
+    // stream for one or two pixels.  MI355X, us on this kernel / the 64 x 16 tile with a split reduction: 2048 -> 1000 at 1, 2, 3, 5
+    // pixels 3.5, 4.0, 5.0, 7.0 / 5.7; 4096 -> 4096 at 1, 2, 3, 8 pixels 8.0, 8.5, 10.2, 15.2 / 7.8-8.1; 25088 -> 4096 at 2 and 8
+    // pixels 36.6, 67.5 / 31.5.
+    const bool gemv_ok = M <= 8 && p.H == 1 && p.W == 1 && p.R == 1 && p.S == 1 && vec && p.groups <= 1;
+    const double bank = (double)Kc * gemm_k;
+    if (gemv_ok && (M == 1 || (M == 2 && bank < 8.0e6) || (M <= 5 && bank < 1.0e6))) {
         p.kernel_id = K_GEMV;
         p.n_pad = cdiv(Kc, 64) * 64;
         p.grid_x = cdiv(cdiv(Kc, 2), 4);          // two output channels per wavefront, four wavefronts per workgroup
         return;
     }
-    const double macs_pw = (double)M * Kc * gemm_k;
-    if (p.kind == MT_CONV && p.R == 1 && p.S == 1 && p.ph == 0 && p.pw == 0 && p.vec_a != 0 && M <= 4096 && macs_pw <= 3.0e8) {
-        // 1x1 convolution on a small map: operands straight from memory, one wave per 16 x 16 output tile.  Up to eight
-        // 32-deep reduction steps a wave walks alone (split_k 1); longer reductions are cut into four ranges, one per
-        // wave of the workgroup (recorded as split_k 4; no workspace: the partial sums meet in LDS).
-        // Measured on MI355X (MobileNetV2 at batch 1, in the chain): 5.4-7.8 us per layer on the 64x16 tile.
-        p.kernel_id = K_IGEMM_PW;
-        p.n_pad = cdiv(Kc, 64) * 64;
+    const bool small = M <= 4096 && macs <= 3.0e8;
+    // 1x1 convolution on a small map: operands straight from memory, one wave per 16 x 16 output tile.  Up to eight 32-deep
+    // reduction steps a wave walks alone (split_k 1); longer reductions are cut into four ranges, one per wave of the
+    // workgroup (recorded as split_k 4; no workspace: the partial sums meet in LDS).  Its waves share nothing, so it is only
+    // level with the 64 x 16 tile where there are few of them or the reduction is one LDS row deep: 960 -> 160 on 49 pixels
+    // 4.7 / 4.8 us, 32 -> 192 on 1568 pixels 4.3 / 4.4 us, but 256 -> 1024 on 196 pixels 4.9 / 3.6, 768 -> 192 on 1445 pixels 9.9 / 5.3.
+    if (small && vec && p.kind == MT_CONV && p.R == 1 && p.S == 1 && p.ph == 0 && p.pw == 0) {
         const int tiles = cdiv(M, 16) * cdiv(Kc, 16);
-        p.split_k = (p.k_pad / 32 > 8) ? 4 : 1;
-        p.grid_x = p.split_k == 1 ? cdiv(tiles, 4) : tiles;
-        make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
-        make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
-        return;
+        const bool slices = p.k_pad / 32 > 8;
+        if (slices ? tiles <= 48 : (p.k_pad <= IGEMM_BK ? tiles <= 1024 && (p.C < IGEMM_BK || tiles <= 64) : tiles <= 32)) {
+            p.kernel_id = K_IGEMM_PW;
+            p.n_pad = cdiv(Kc, 64) * 64;
+            p.split_k = slices ? 4 : 1;
+            p.grid_x = slices ? tiles : cdiv(tiles, 4);
+            make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
+            make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
+            return;
+        }
     }
-    int bn, bm, kid;
-    // Small problems (few multiply-accumulates on a small map) are latency bound: narrow pixel tiles give more,
-    // shorter workgroups.  Measured on MI355X: ResNet-18 3x3 layers (115 M MACs) 9-11 us -> 7.3-8.6 us.
-    const double macs = (double)M * Kc * gemm_k;
-    if (M <= 32 || (M <= 4096 && macs <= 3.0e8)) {
-        kid = K_IGEMM_64x16; bn = 64; bm = 16;
+    // size class (see KernelId)
+    int bn = 64, bm = 64;
+    p.kernel_id = K_IGEMM_64x64;
+    if (M <= 32 || small) {
+        p.kernel_id = K_IGEMM_64x16; bm = 16;
     } else if (Kc >= 96 && cdiv(M, 128) * cdiv(Kc, 128) >= 512) {
-        kid = K_IGEMM_128x128; bn = 128; bm = 128;
+        p.kernel_id = K_IGEMM_128x128; bn = bm = 128;
     } else if (Kc >= 96 && cdiv(M, 64) * cdiv(Kc, 128) >= 256) {
-        kid = K_IGEMM_128x64; bn = 128; bm = 64;
-    } else {
-        kid = K_IGEMM_64x64; bn = 64; bm = 64;
+        p.kernel_id = K_IGEMM_128x64; bn = 128;
+    } else if (vec && patch_stageable(p) && cdiv(M, 64) * cdiv(Kc, 64) >= 150) {
+        p.kernel_id = K_PCONV;
     }
-    p.kernel_id = kid;
+    const bool before_depthwise = small && p.R == 1 && p.S == 1 && p.C <= 256;
+    if (vec && plan_tile(p, before_depthwise)) return;
+    // element-wise gather (C % 8 != 0 or a window of more than 15 rows or columns): tiles of the register-staged kernel
+    p.vec_a = 0;
     p.n_pad = cdiv(Kc, bn) * bn;
     const int tiles = cdiv(M, bm) * (p.n_pad / bn);
     const int nkt = p.k_pad / IGEMM_BK;
-    int target = (kid == K_IGEMM_64x16) ? 2048 : 768;
-    int max_split = 8, min_kt = 6;    // a split below 6 reduction tiles costs more in the partial-sum exchange than it saves
+    const int target = (p.kernel_id == K_IGEMM_64x16) ? 2048 : 768;
+    const int max_split = 8, min_kt = 6;    // a split below 6 reduction tiles costs more in the partial-sum exchange than it saves
     int split = 1;
-    p.wk = 1;
-    // Long reductions on the 128x64 tile are bound by the matrix cores: eight waves per tile (two per SIMD) overlap LDS
-    // reads with MFMA better than four.  Measured on MI355X at batch 8: 3x3 layers of 128 / 256 / 512 channels on
-    // 112^2 / 56^2 / 28^2 maps 62.9 -> 56.5, 62.2 -> 54.9, 59.5 -> 52.1 us; the short reductions of 1x1 layers lose
-    // (17.3 -> 19.3 us) and keep four waves.  The same change on the 128x128 tile loses everywhere.
-        if (kid == K_IGEMM_128x64 && p.vec_a != 0 && nkt >= 18) p.wk = 2;
-    int wk_tiles = 512;
-    if (kid == K_IGEMM_64x64 && p.vec_a != 0 && tiles <= wk_tiles) {
-        // Few workgroups per compute unit: eight waves per tile (two per SIMD, the MFMA steps of every LDS tile split
-        // between two wave groups) and only as many splits as keep about one workgroup per unit.  Measured on MI355X,
-        // VGG-16 at batch 1: conv3_2 18.9 -> 13.9 us, conv4_1 15.2 -> 11.8 us, conv4_2 19.7 -> 16.1 us.
-        p.wk = 2;
-        split = std::max(1, std::min({256 / tiles, std::max(1, nkt / 4), max_split}));
-        const int per = cdiv(nkt, split);
-        split = cdiv(nkt, per);
-    } else if (tiles < target / 2) {
+    if (tiles < target / 2) {
         split = std::min({cdiv(target, tiles), std::max(1, nkt / min_kt), max_split});
         const int per = cdiv(nkt, split);
         split = cdiv(nkt, per);            // no empty split
     }
     p.split_k = std::max(1, split);
-    // Only where the 64x64 tile would run unsplit on 150 tiles or more.  On larger problems the patch form is level with
-    // the wide tiles on maps up to 28 pixels wide and loses on wider ones, whose patch leaves room for one workgroup per
-    // compute unit (batch 8, 256 channels on 56x56: 72 against 57 us; 128 channels on 112x112: 90 against 53 us).
-    const bool pconv_size = kid == K_IGEMM_64x64 && p.split_k == 1 && tiles >= PCONV_MIN_TILES;
-    if (pconv_size && p.kind == MT_CONV && p.groups <= 1 && p.R == 3 && p.S == 3 && p.sh == 1 && p.sw == 1 && p.ph == 1 && p.pw == 1 &&
-        p.C % 64 == 0 && p.K % 8 == 0 && p.y_ct % 8 == 0 && p.y_coff % 8 == 0 && p.res_ct % 8 == 0 && pconv_patch_pixels(p.W) > 0) {
-        // 3x3 layers that would run on the 64x64 tile unsplit: same tile, activations staged as an input patch
-        p.kernel_id = K_PCONV;
-        p.wk = 1;
-        p.block = 512;
-        p.k_pad = gemm_k;
-        p.split_k = 1;
-        p.n_pad = cdiv(Kc, 64) * 64;
-        p.tile_order = 0;
-        make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
-        make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
-        p.grid_x = cdiv(cdiv(M, 64) * (p.n_pad / 64), 8) * 8;
-        return;
-    }
-    // Which operand each XCD's L2 keeps to itself: consecutive tiles (one XCD) walk the channel tiles of one pixel
-    // tile (0) when the activations are the larger operand, the pixel tiles of one channel tile (1) otherwise.
     p.tile_order = ((double)Kc * gemm_k > (double)p.N * p.H * p.W * p.C) ? 1 : 0;
     make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
     make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
     const int total = tiles * p.split_k;
     p.grid_x = cdiv(total, 8) * 8;
+}
+
+// Split reduction of one launch: output tiles and floats of workspace per tile.
+void split_workspace(const OpArgs &p, size_t *tiles, size_t *floats) {
+    if (p.form >= 0) return tile_workspace(p, tiles, floats);
+    const int bn = p.kernel_id == K_IGEMM_64x16 || p.kernel_id == K_IGEMM_64x64 ? 64 : 128;
+    const int bm = p.kernel_id == K_IGEMM_64x16 ? 16 : p.kernel_id == K_IGEMM_128x128 ? 128 : 64;
+    *tiles = (size_t)((p.N * p.P * p.Q + bm - 1) / bm) * (p.n_pad / bn);
+    *floats = (size_t)p.split_k * bn * bm;
 }
 
 int32_t finalize_model(mt_model *m) {
@@ -218,6 +205,7 @@ int32_t finalize_model(mt_model *m) {
         if (groups > 1 && (in.c % groups || o.out_c % groups)) return bad("channel counts must be multiples of the group count");
         OpArgs &p = o.plan;
         p = OpArgs{};
+        p.form = -1;
         p.kind = d.kind; p.dtype = m->dtype;
         p.N = m->batch; p.H = in.h; p.W = in.w; p.C = in.c / groups;
         p.x_ct = in.c; p.x_coff = 0; p.groups = groups;
@@ -344,7 +332,7 @@ int32_t finalize_model(mt_model *m) {
     for (OpRec &o : m->ops) {
         const OpArgs &p = o.plan;
         if (needs_weights(p.kind)) {
-            bool igemm = packed_rows(p) || p.kernel_id == K_STEM || p.kernel_id == K_ROWB || p.kernel_id == K_PCONV;
+            bool igemm = packed_rows(p) || p.kernel_id == K_STEM || p.kernel_id == K_ROWB;
             size_t wcount = igemm ? (size_t)p.groups * p.n_pad * p.k_pad
                                   : (p.kind == MT_DWCONV ? (size_t)p.C * p.R * p.S : (size_t)p.groups * p.K * o.plan.R * o.plan.S * p.C);
             if (p.kind == MT_FC && !igemm) wcount = (size_t)p.K * o.in_h * o.in_w * o.in_c;
@@ -353,12 +341,11 @@ int32_t finalize_model(mt_model *m) {
             o.bias_off = off; off += align_up(nb * sizeof(float));
         }
         if (p.split_k > 1 && p.kernel_id != K_IGEMM_PW) {
-            const int bn = p.kernel_id == K_IGEMM_64x16 || p.kernel_id == K_IGEMM_64x64 ? 64 : 128;
-            const int bm = p.kernel_id == K_IGEMM_64x16 ? 16 : p.kernel_id == K_IGEMM_128x128 ? 128 : 64;
-            const int M = p.N * p.P * p.Q;
-            const size_t tiles = (size_t)((M + bm - 1) / bm) * (p.n_pad / bn);
-            o.ws_off = off; o.ws_bytes = tiles * p.split_k * bn * bm * sizeof(float); off += align_up(o.ws_bytes);
-            o.cnt_off = off; o.cnt_bytes = tiles * sizeof(uint32_t); off += align_up(o.cnt_bytes);
+            // the groups of a grouped convolution run side by side: each has its own workspace
+            size_t tiles = 0, floats = 0;
+            split_workspace(p, &tiles, &floats);
+            o.ws_off = off; o.ws_bytes = tiles * floats * p.groups * sizeof(float); off += align_up(o.ws_bytes);
+            o.cnt_off = off; o.cnt_bytes = tiles * p.groups * sizeof(uint32_t); off += align_up(o.cnt_bytes);
         }
     }
     for (size_t t = 1; t < m->tensors.size(); ++t) {
@@ -497,7 +484,7 @@ namespace {
 int launch_kernel(const OpArgs &a, hipStream_t st, const OpArgs *mate = nullptr, int n_mates = 0) {
     if (a.kernel_id == K_STEM) return launch_stem(a, st, mate, n_mates);
     if (a.kernel_id == K_ROWB) return launch_rowb(a, st, mate, n_mates);
-    if (a.kernel_id == K_PCONV) return launch_pconv(a, st, mate, n_mates);
+    if (a.form >= 0) return launch_tile(a, st, mate, n_mates);
     if (a.kernel_id == K_CONV_DIRECT && a.wk > 0) return mate ? (int)hipErrorInvalidValue : launch_dconv_f32(a, st);
     return is_gemm_kernel(a.kernel_id) ? launch_igemm(a, st, mate, n_mates) : launch_direct(a, st, mate, n_mates);
 }
@@ -530,6 +517,12 @@ int launch_raw(const OpArgs &a, hipStream_t st) {
         b.w = (const uint8_t *)a.w + (size_t)g * (igemm ? (size_t)a.n_pad * a.k_pad : (size_t)a.K * a.R * a.S * a.C) * es;
         b.bias = a.bias + (size_t)g * (igemm ? a.n_pad : a.K);
         if (a.res) b.res = (const uint8_t *)a.res + (size_t)g * a.K * es;
+        if (a.ws && g > 0) {
+            size_t tiles = 0, floats = 0;
+            split_workspace(a, &tiles, &floats);
+            b.ws = a.ws + (size_t)g * tiles * floats;
+            b.counters = a.counters + (size_t)g * tiles;
+        }
         const int e = launch_kernel(b, st);
         if (e != 0) return e;
     }
@@ -1583,7 +1576,7 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
     for (size_t i = 0; i < nops; ++i) {
         OpRec &o = t->model.ops[i];
         OpArgs a = o.plan;
-        const bool igemm = packed_rows(a) || a.kernel_id == K_STEM || a.kernel_id == K_ROWB || a.kernel_id == K_PCONV;
+        const bool igemm = packed_rows(a) || a.kernel_id == K_STEM || a.kernel_id == K_ROWB;
         if (needs_weights(a.kind)) {
             const uint8_t *src = o.w_host.data();
             if (a.kernel_id == K_STEM) {
@@ -1607,7 +1600,7 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
                             }
                         }
                 src = packed.data();
-            } else if (a.kernel_id == K_PCONV) {
+            } else if (a.panel > 0) {
                 // [K][tap][C] -> [n_pad][chunk of 64 channels][tap][64], zero padded rows
                 packed.assign((size_t)a.n_pad * a.k_pad * es, 0);
                 const int ncc = a.C / 64;
@@ -1725,9 +1718,12 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
         if (!only) continue;
         OpArgs b = a0;
         b.pool2 = 1;
+        if (b.form >= 0 && !plan_tile_pooled(b)) continue;
         b.y = a1.y; b.y_ct = a1.y_ct; b.y_coff = a1.y_coff;
-        make_divisor((uint32_t)(b.Q / 2), b.divq_m, b.divq_s1, b.divq_s2);
-        make_divisor((uint32_t)(b.P / 2) * (uint32_t)(b.Q / 2), b.divpq_m, b.divpq_s1, b.divpq_s2);
+        if (b.form < 0) {
+            make_divisor((uint32_t)(b.Q / 2), b.divq_m, b.divq_s1, b.divq_s2);
+            make_divisor((uint32_t)(b.P / 2) * (uint32_t)(b.Q / 2), b.divpq_m, b.divpq_s1, b.divpq_s2);
+        }
         t->pool_args[i] = b;
         t->fuse_pool[i] = 1;
     }

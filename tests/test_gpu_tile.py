@@ -1,0 +1,141 @@
+"""The tile kernels that copy their operands from memory to LDS directly: every tile, way to gather an im2col row and patch
+form, with ragged pixel and channel counts, split reductions, residual, channel offsets and the pooled epilogue, against a
+plain fp32 convolution on the CPU."""
+import numpy as np
+import pytest
+import torch
+import torch.nn.functional as F
+
+from synth import GraphBuilder
+from oracle import forward as OF
+from oracle import ops as oops
+from gpu_harness import Mix, assert_close
+from paper_2111_14255_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name (tile and staging the sizes lead to), n, h, w, c, k, window, stride, pad
+    ("64x64_point", 3, 77, 91, 128, 136, 1, 1, 0),
+    ("128x64_point_ragged_channels", 2, 90, 91, 192, 520, 1, 1, 0),
+    ("128x128_point", 3, 70, 70, 320, 200, 1, 1, 0),
+    ("64x32_point", 1, 60, 60, 512, 72, 1, 1, 0),
+    ("64x16_point_half_stage", 1, 9, 13, 320, 520, 1, 1, 0),
+    ("64x64_deep_tap_stride2", 5, 56, 57, 64, 200, 3, 2, 1),
+    ("128x128_tap", 1, 121, 130, 64, 256, 3, 1, 1),
+    ("64x32_tap", 1, 60, 62, 128, 128, 3, 1, 1),
+    ("64x16_tap_5x5_wider_than_padding", 1, 35, 33, 64, 96, 5, 1, 2),
+    ("64x16_tap_split4_stride2", 2, 31, 31, 192, 100, 3, 2, 1),
+    ("128x64_chunk_c72", 4, 60, 60, 72, 260, 3, 1, 1),
+    ("64x16_chunk_c8_15x3", 1, 30, 30, 8, 24, (15, 3), 1, (7, 1)),
+    ("64x16_chunk_c24_unaligned_channels", 2, 13, 11, 24, 67, 3, 1, 1),
+    ("64x16_one_pixel_split8", 9, 1, 1, 4096, 520, 1, 1, 0),
+    ("patch_64x64_panel_of_one_column", 1, 62, 61, 192, 136, 3, 1, 1),
+    ("patch_64x64_tiles_span_images", 40, 7, 7, 64, 320, 3, 1, 1),
+    ("patch_64x64_split4", 1, 28, 28, 512, 256, 3, 1, 1),
+    ("patch_64x32_odd_map", 2, 17, 17, 192, 512, 3, 1, 1),
+    ("patch_128x64_wide_panel", 1, 100, 66, 128, 256, 3, 1, 1),
+    ("patch_128x128_last_panel_partial", 2, 66, 97, 128, 256, 3, 1, 1),
+    ("patch_128x128_split3", 3, 28, 28, 512, 512, 3, 1, 1),
+    ("patch_128x256", 2, 112, 112, 64, 256, 3, 1, 1),
+    ("patch_128x256_split3_tiles_span_images", 6, 28, 28, 384, 512, 3, 1, 1),
+]
+ACT = {"none": lambda v: v, "relu": torch.relu, "relu6": lambda v: v.clamp(0, 6)}
+
+
+def conv_ref(x, p, stride, pad, act, dtype):
+    """x: fp32 NHWC values of the storage type; the stored result as fp32 NHWC."""
+    w = torch.from_numpy(np.ascontiguousarray(p[0])).permute(0, 3, 1, 2)
+    y = F.conv2d(torch.from_numpy(x).permute(0, 3, 1, 2), w, torch.from_numpy(p[1]), stride, pad)
+    return y, ACT[act]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("name,n,h,w,c,k,win,stride,pad", CASES, ids=[c[0] for c in CASES])
+def test_tile_kernels(name, n, h, w, c, k, win, stride, pad, dtype):
+    g = GraphBuilder("t", dtype, n, h, w, c)
+    a = g.conv(0, k, win, stride, pad, act="relu6", bn=True)
+    d = g.new_tensor()                                   # the same convolution with a residual, written at a channel offset
+    off = 8 if k % 8 == 0 else 3
+    g.conv(0, k, win, stride, pad, act="relu", bn=True, res=a, dst=d, c_off=off, c_tot=k + off)
+    g.conv(0, off, win, stride, pad, act="none", dst=d, c_off=0, c_tot=k + off)
+    spec = g.done()
+    print("case", name, dtype, flush=True)
+    mix = Mix([spec], seed=37)
+    try:
+        got, _ = mix.run(mix.ctx.sequential())
+        x = oops.round_array(mix.x[0], dtype)
+        p = OF.prepare_params(spec, mix.raw[0])
+        y0, act = conv_ref(x, p[0], stride, pad, "relu6", dtype)
+        t0 = oops.round_array(act(y0).permute(0, 2, 3, 1).contiguous().numpy(), dtype)
+        y1, act = conv_ref(x, p[1], stride, pad, "relu", dtype)
+        t1 = act(y1.permute(0, 2, 3, 1) + torch.from_numpy(t0))
+        y2, _ = conv_ref(x, p[2], stride, pad, "none", dtype)
+        ref = torch.cat([y2.permute(0, 2, 3, 1), t1], dim=3).numpy()
+        read = mix.ctx.read_tensor(0, a, t0.shape)
+        assert_close(read.astype(np.float32), t0, dtype, name)
+        assert_close(got[0], ref.reshape(n, -1), dtype, name)
+    finally:
+        mix.close()
+
+
+POOLED = [
+    # name, n, h, w, c, k
+    ("patch_64x64_split3", 1, 28, 28, 384, 384),
+    ("patch_64x64_even_panel", 6, 30, 28, 128, 136),
+    ("patch_64x32", 1, 28, 28, 192, 384),
+    ("patch_128x64", 3, 60, 62, 192, 128),
+    ("patch_128x128", 4, 56, 56, 128, 256),
+    ("patch_128x256", 2, 112, 112, 64, 256),
+    ("128x64_tap", 4, 64, 64, 64, 128),
+    ("64x32_tap", 1, 60, 62, 128, 128),
+]
+
+
+@pytest.mark.parametrize("name,n,h,w,c,k", POOLED, ids=[c[0] for c in POOLED])
+def test_pooled_epilogue_of_the_tile_kernels(name, n, h, w, c, k):
+    g = GraphBuilder("t", "bf16", n, h, w, c)
+    a = g.conv(0, k, 3, 1, 1, act="relu", bn=True)
+    pl = g.maxpool(a, 2, 2, 0)
+    g.gap(pl)
+    spec = g.done()
+    print("case", name, flush=True)
+    mix = Mix([spec], seed=41)
+    try:
+        ctx = mix.ctx
+        shape = (n, h // 2, w // 2, k)
+        _, tm = mix.run(ctx.sequential(flags=B.MT_SCHED_FUSE_POOL))
+        assert tm["n_fused"] == 1
+        fused = ctx.read_tensor(0, pl, shape)
+        _, tm = mix.run(ctx.sequential())
+        assert tm["n_fused"] == 0
+        np.testing.assert_array_equal(fused.view(np.uint32), ctx.read_tensor(0, pl, shape).view(np.uint32))
+        y, act = conv_ref(oops.round_array(mix.x[0], "bf16"), OF.prepare_params(spec, mix.raw[0])[0], 1, 1, "relu", "bf16")
+        ref = F.max_pool2d(act(y), 2).permute(0, 2, 3, 1).contiguous().numpy()
+        assert_close(fused, ref, "bf16", name)
+    finally:
+        mix.close()
+
+
+def test_patch_does_not_carry_non_finite_pixels_into_foreign_windows():
+    """A patch holds rows of two images with an empty row between them and the columns beside its panel."""
+    n, h, w, c, k = 2, 60, 62, 192, 128
+    g = GraphBuilder("t", "bf16", n, h, w, c)
+    g.conv(0, k, 3, 1, 1, act="none", bn=False)
+    spec = g.done()
+    mix = Mix([spec], seed=43)
+    try:
+        x = mix.x[0]
+        for (i, r, q) in ((0, h - 1, 5), (0, 7, w - 1), (1, 0, 15), (1, 30, 16), (1, 31, 0)):
+            x[i, r, q, 9] = np.nan
+        mix.inputs[0] = mix.ctx.make_input(0, x)
+        got, _ = mix.run(mix.ctx.sequential())
+        y, _ = conv_ref(oops.round_array(x, "bf16"), OF.prepare_params(spec, mix.raw[0])[0], 1, 1, "none", "bf16")
+        ref = y.permute(0, 2, 3, 1).contiguous().numpy().reshape(n, -1)
+        bad = ~np.isfinite(ref)
+        assert bad.any() and not bad.all()
+        assert np.array_equal(~np.isfinite(got[0]), bad)
+        scale = float(np.abs(ref[~bad]).max())
+        assert float(np.abs(got[0][~bad] - ref[~bad]).max()) <= 2e-2 * scale
+    finally:
+        mix.close()
