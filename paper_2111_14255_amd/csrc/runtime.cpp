@@ -1966,12 +1966,6 @@ static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, 
 int32_t mt_run(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm) {
     if (!ctx || !s || !inputs || !outputs) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     if (s->ctx != ctx) return fail(MT_ERR_INVALID_ARG, "schedule belongs to another (or a destroyed) context");
-    // The lanes start within microseconds and know nothing of HIP streams: what the caller has queued on the default stream
-    // (a copy into an input, a fill of an output) is waited for first.
-    if (hipStreamQuery(nullptr) != hipSuccess) {
-        (void)hipGetLastError();
-        HIP_TRY(hipStreamSynchronize(nullptr));
-    }
     return run_pass(ctx, s, inputs, outputs, tm, false, 0);
 }
 
@@ -2003,11 +1997,29 @@ int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *in
     return rc;
 }
 
+// The lanes start within microseconds and know nothing of HIP streams: what the caller has queued on the default stream
+// (a copy into an input, a fill of an output) is waited for first.  A pass does not take part in a capture that the caller
+// has under way on another stream and must not disturb it, hence the relaxed capture mode.
+static hipError_t wait_for_default_stream() {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return e;
+    e = hipStreamQuery(nullptr);
+    if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        e = hipStreamSynchronize(nullptr);
+    }
+    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+    return e != hipSuccess ? e : back;
+}
+
 static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, mt_timings *tm, bool static_scratch, size_t counter_bytes) {
     for (int i = 0; i < s->n_tenants; ++i) {
         if (!inputs[i] || !outputs[i]) return fail(MT_ERR_INVALID_ARG, "NULL input or output buffer");
         if (((uintptr_t)inputs[i] % 16) || ((uintptr_t)outputs[i] % 16)) return fail(MT_ERR_INVALID_ARG, "buffers must be 16-byte aligned");
     }
+    HIP_TRY(hipSetDevice(ctx->device));
+    HIP_TRY(wait_for_default_stream());
     const auto t0 = std::chrono::steady_clock::now();
     LaneDevice *dev = ctx->lanes;
     RunPlan &plan = s->plan[static_scratch ? 1 : 0];

@@ -94,3 +94,42 @@ def test_two_contexts_on_two_threads_share_the_lanes():
     assert not bad and not any(t.is_alive() for t in threads)
     for m in mixes:
         m.close()
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_a_pass_beside_a_capture_and_after_work_on_the_default_stream(static):
+    import torch
+    mix = Mix([zoo.BUILDERS["tinyC"]("f16", 2), zoo.BUILDERS["tinyA"]("f16", 1)], 36, "uniform")
+    try:
+        ref, _ = mix.run(mix.ctx.sequential())
+        run = mix.ctx.run_static_scratch if static else mix.ctx.run
+        sched = mix.ctx.all_concurrent()
+        outs = [mix.ctx.make_output(t) for t in range(2)]
+        # the caller captures work of its own: the pass neither joins the graph nor breaks the capture
+        a = torch.arange(64, dtype=torch.float32, device="cuda")
+        b = torch.empty_like(a)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            torch.mul(a, 2.0, out=b)
+            run(sched, mix.inputs, outs)
+        assert same([mix.ctx.output_to_numpy(t, o) for t, o in enumerate(outs)], ref)
+        for k in range(3):
+            a.add_(1.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(b, 2.0 * a)
+        # the inputs arrive behind a long fill on the default stream, the outputs are poisoned there
+        big = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
+        late = [torch.zeros_like(x) for x in mix.inputs]
+        run(sched, late, outs)
+        for k in range(4):
+            big.fill_(float(k))
+        for x, y in zip(late, mix.inputs):
+            x.copy_(y)
+        for o in outs:
+            o.fill_(float("nan"))
+        run(sched, late, outs)
+        assert same([mix.ctx.output_to_numpy(t, o) for t, o in enumerate(outs)], ref)
+    finally:
+        mix.close()
