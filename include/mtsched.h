@@ -111,7 +111,7 @@ typedef struct mt_op_info {
     int32_t in_h, in_w, in_c;
     int32_t out_h, out_w, out_c;     /* channels written */
     int32_t kernel_id;               /* which device kernel family and tile runs it (see mt_kernel_name) */
-    int32_t split_k;                 /* K-splits of the implicit GEMM (1 = none) */
+    int32_t split_k;                 /* ranges the reduction of an output is cut into, over workgroups and over waves that deal it out (1 = none) */
     int32_t grid_blocks;             /* workgroups launched */
     double flops;                    /* 2 * multiply-accumulates, whole batch */
     double bytes;                    /* algorithmic traffic: inputs + weights + bias (+ residual) read once, output written once */

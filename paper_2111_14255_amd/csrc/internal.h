@@ -113,7 +113,7 @@ struct OpArgs {
 };
 
 // Kernels whose filter bank is packed as [groups][n_pad][k_pad], rows zero padded.
-inline bool packed_rows(const OpArgs &a) { return is_gemm_kernel(a.kernel_id) || (a.kernel_id == K_CONV_DIRECT && a.wk > 0); }
+inline bool packed_rows(const OpArgs &a) { return is_gemm_kernel(a.kernel_id) || (a.kernel_id == K_CONV_DIRECT && (a.wk > 0 || a.form >= 0)); }
 
 // Up to four operators of different tenants that run as one launch (co-issue): workgroups with blockIdx.y == i work on
 // a[i].  All of them have the same kernel, tile, split and launch shape; only their buffers differ.
@@ -156,7 +156,15 @@ int rowb_tiles(int R, int S, int C, int channels);   // 32-channel tiles per sli
 // Tile kernels (kernels_tile.hip): choice of form, its split workspace (tiles, floats per tile), the pooled plan, launch.
 // The filter bank is [n_pad][k_pad]; a patch-staged layer (panel > 0) orders the reduction index (64-channel chunk, tap, channel).
 bool patch_stageable(const OpArgs &a);
-bool plan_tile(OpArgs &a, bool narrow);
+enum TileChoice {
+    TILE_ANY,        // whatever the estimate says
+    TILE_NARROW,     // the 64 x 16 tile, whose order of additions the fused 1x1 + depthwise kernels reproduce
+    TILE_RING4,      // 16 x 16 tiles whose reduction four waves deal out between them
+    TILE_UNSPLIT,    // no partial sums through memory: fp32 (1.5 % of a network's time) and layers that never had a workspace
+    TILE_NO_RING,    // what mt_run_static_scratch's limit is stated in
+};
+bool plan_tile(OpArgs &a, TileChoice choice);
+int reduction_ranges(const OpArgs &a);   // ranges the reduction of an output is cut into, over workgroups and over the waves of a ring
 bool tile_is_narrow(const OpArgs &a);
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);
 bool plan_tile_pooled(OpArgs &a);

@@ -620,25 +620,20 @@ __global__ void __launch_bounds__(256) gemv_pair_kernel(OpArgsPair p) {
 // 1x1 convolution on a small map (a few hundred pixels): latency bound, so no LDS tiles and no workgroup barrier in the
 // reduction.  A wave owns 16 output channels x 16 pixels; filter rows and pixel rows are contiguous along the
 // reduction index, so the 16x16x32 MFMA operands are 16-byte loads straight from memory, issued eight reduction steps
-// at a time.  SLICES = 1: the four waves of a workgroup take four channel tiles of one pixel tile and each walks the
-// whole reduction in ascending order into one accumulator (the arithmetic of the 64x16 tile kernel, bit for bit).
-// SLICES = 4 (long reductions): the four waves split the reduction of one tile into four contiguous ranges and wave 0
-// adds the partial sums in range order through LDS.
-template <typename T, int SLICES>
+// at a time.  The four waves of a workgroup take four channel tiles of one pixel tile and each walks the whole reduction in
+// ascending order into one accumulator (the arithmetic of the 64x16 tile kernel, bit for bit).
+template <typename T>
 __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
     set_wave_priority(a.prio);
     typedef typename Mma<T, 16>::Acc Acc;
     constexpr int CH = 8;                                // reduction steps whose loads are in flight together
-    __shared__ float red[SLICES > 1 ? (SLICES - 1) * 256 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int M = a.N * a.P * a.Q;
     const int tiles_m = (M + 15) / 16, tiles_n = (a.K + 15) / 16;
-    const int tile = SLICES == 1 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x;
-    if (tile >= tiles_m * tiles_n) return;               // SLICES = 1: a whole wave, and no barrier follows; SLICES = 4: the whole workgroup
+    const int tile = (int)blockIdx.x * 4 + wave;
+    if (tile >= tiles_m * tiles_n) return;               // a whole wave, and no barrier follows
     const int tn = tile % tiles_n, tm = tile / tiles_n;  // neighbouring waves share the pixel tile
     const int nsteps = a.k_pad / 32;
-    const int per = (nsteps + SLICES - 1) / SLICES;
-    const int s_begin = SLICES == 1 ? 0 : wave * per, s_end = SLICES == 1 ? nsteps : min(nsteps, s_begin + per);
     const int frag_row = lane & 15, frag_k = (lane >> 4) * 8;
 
     const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
@@ -662,30 +657,19 @@ __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
     Acc acc;
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] = 0.f;
-    for (int s0 = s_begin; s0 < s_end; s0 += CH) {
+    for (int s0 = 0; s0 < nsteps; s0 += CH) {
         u32x4 wf[CH], xf[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int s = s0 + i;
-            const bool live = s < s_end;
+            const bool live = s < nsteps;
             wf[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, live ? wrow + (uint32_t)(s * 64) : OOB_OFFSET, 0, 0);
             const bool xv = live & (m < M) & (s * 32 + frag_k < a.C);
             xf[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, xv ? xrow + (uint32_t)(s * 64) : OOB_OFFSET, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < CH; ++i)
-            if (s0 + i < s_end) acc = Mma<T, 16>::run(wf[i], xf[i], acc);
-    }
-    if constexpr (SLICES > 1) {
-        if (wave > 0) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[((wave - 1) * 4 + v) * 64 + lane] = acc[v];
-        }
-        __syncthreads();
-        if (wave > 0) return;
-        for (int w = 1; w < SLICES; ++w)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] += red[((w - 1) * 4 + v) * 64 + lane];
+            if (s0 + i < nsteps) acc = Mma<T, 16>::run(wf[i], xf[i], acc);
     }
 
     // epilogue: bias, residual, activation, one rounding
@@ -716,14 +700,14 @@ __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
         }
     }
 }
-template <typename T, int SLICES>
+template <typename T>
 __global__ void __launch_bounds__(256) pw_direct_kernel(OpArgs a) {
-    pw_direct_kernel_body<T, SLICES>(a);
+    pw_direct_kernel_body<T>(a);
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
-template <typename T, int SLICES>
+template <typename T>
 __global__ void __launch_bounds__(256) pw_direct_pair_kernel(OpArgsPair p) {
-    pw_direct_kernel_body<T, SLICES>(p.a[blockIdx.y]);
+    pw_direct_kernel_body<T>(p.a[blockIdx.y]);
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int MF>
@@ -759,8 +743,7 @@ static int launch_igemm_typed(const OpArgs &a, hipStream_t st, const OpArgs *mat
         case K_IGEMM_64x16: launch_cfg<T, 64, 16, 4, 1, 16>(a, st); break;
         case K_IGEMM_PW: {
             const dim3 grid(a.grid_x), block(256);
-            if (a.split_k > 1) MT_LAUNCH((pw_direct_kernel<T, 4>), (pw_direct_pair_kernel<T, 4>), grid, block, st, a, mate);
-            else MT_LAUNCH((pw_direct_kernel<T, 1>), (pw_direct_pair_kernel<T, 1>), grid, block, st, a, mate);
+            MT_LAUNCH((pw_direct_kernel<T>), (pw_direct_pair_kernel<T>), grid, block, st, a, mate);
             break;
         }
         case K_GEMV: launch_gemv<T>(a, st, mate, n_mates); break;
@@ -958,7 +941,7 @@ static size_t dwpw_lds_bytes(int k_pad) { return (size_t)k_pad * (18 + 4) + (siz
 // Host check of what the fused kernel assumes; the runtime pairs two operators only when this holds.
 bool dwpw_fusable(const OpArgs &dw, const OpArgs &pw) {
     // the 1x1 layer must be one whose stand-alone kernel walks the reduction in one ascending pass, as the fused kernel does
-    if (dw.kernel_id != K_DWCONV || !(tile_is_narrow(pw) || pw.kernel_id == K_IGEMM_PW)) return false;
+    if (dw.kernel_id != K_DWCONV || !(tile_is_narrow(pw) || (pw.kernel_id == K_IGEMM_PW && pw.form < 0))) return false;
     if (dw.dtype != pw.dtype || (dw.dtype != MT_F16 && dw.dtype != MT_BF16)) return false;
     if (dw.R != 3 || dw.S != 3 || dw.vec != 8 || dw.C % 8 != 0 || dw.y_coff != 0 || dw.y_ct != dw.C) return false;
     if (pw.R != 1 || pw.S != 1 || pw.sh != 1 || pw.sw != 1 || pw.ph != 0 || pw.pw != 0 || pw.groups > 1) return false;
@@ -1118,7 +1101,7 @@ __global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands
 // row bands, chosen so that enough workgroups exist and a band's input rows fit the variant.  False: not fusable.
 static bool pwdw_plan(const OpArgs &pw, const OpArgs &dw, int *variant, int *bands) {
     // the 1x1 layer must be one whose stand-alone kernel walks the reduction in one ascending pass, as the fused kernel does
-    if (!(tile_is_narrow(pw) || pw.kernel_id == K_IGEMM_PW) || dw.kernel_id != K_DWCONV) return false;
+    if (!(tile_is_narrow(pw) || (pw.kernel_id == K_IGEMM_PW && pw.form < 0)) || dw.kernel_id != K_DWCONV) return false;
     if (dw.dtype != pw.dtype || (dw.dtype != MT_F16 && dw.dtype != MT_BF16)) return false;
     if (pw.R != 1 || pw.S != 1 || pw.sh != 1 || pw.sw != 1 || pw.ph != 0 || pw.pw != 0 || pw.groups > 1) return false;
     if (pw.split_k != 1 || pw.vec_a == 0 || pw.C % 8 != 0 || pw.x_ct != pw.C || pw.x_coff != 0 || pw.res_ct != 0) return false;

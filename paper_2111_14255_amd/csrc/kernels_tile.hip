@@ -15,6 +15,8 @@
 //   3x3, 256 -> 256 on 8 x 56 x 56 (59 GFLOP)  52.0 / 32.7      3x3, 512 -> 512 on 8 x 28 x 28  47.5 / 34.4
 //   1x1, 1024 -> 512 on 64 x 14 x 14           28.4 / 20.0      1x1, 512 -> 2048 on 64 x 7 x 7   20.3 / 15.0
 //   1x1, 768 -> 192 on 5 x 17 x 17              9.9 /  5.3      3x3, 64 -> 64 on 56 x 56          5.4 /  4.6
+// fp32 rows hold 32 elements and a piece feeds four v_mfma_f32_*x2 / x4; at 128 multiply-adds per cycle and unit the matrix cores
+// bound the larger layers (4 x 28 x 28, 3x3, 128 -> 128: 21.1 us from registers, 16.8 on 64 x 32 tiles, 7.7 us of it matrix instructions).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,7 +35,8 @@ constexpr int TG_POINT = 0, TG_TAP = 1, TG_CHUNK = 2;
 
 namespace {
 
-constexpr int TK = 64;                          // reduction elements of one LDS row: 128 bytes
+constexpr int TK = 64;                          // reduction elements of one LDS row (128 bytes) of a 16-bit type
+template <typename T> constexpr int ROW = 128 / (int)sizeof(T);    // the same of any type
 constexpr int XCDS = 8;
 constexpr uint32_t OUT_OF_RANGE = 0x80000000u;  // beyond any tensor: the load delivers zeros
 
@@ -48,6 +51,24 @@ __device__ __forceinline__ void wait_and_meet() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// The same when `later` stages (at most MAX) of L loads each were requested after the one waited for.
+template <int L, int MAX>
+__device__ __forceinline__ void wait_for_stage(int later) {
+    if constexpr (MAX > 0) {
+        if (later < MAX) return wait_for_stage<L, MAX - 1>(later);
+    }
+    wait_and_meet<MAX * L>();
+}
+
+// All but the youngest `later` rows (at most MAX) of L loads each have landed; this wave's loads only.
+template <int L, int MAX>
+__device__ __forceinline__ void wait_for_row(int later) {
+    if constexpr (MAX > 0) {
+        if (later < MAX) return wait_for_row<L, MAX - 1>(later);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MAX * L) : "memory");
+}
+
 __device__ __forceinline__ u32x4 raw_buffer(const void *p, int64_t bytes) {
     const uint64_t b = (uint64_t)p;
     return u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, (uint32_t)bytes, 0x00027000u};
@@ -57,7 +78,7 @@ __device__ __forceinline__ u32x4 raw_buffer(const void *p, int64_t bytes) {
 
 // Whether the taps of this layer can be read from a patch in LDS (patch_body).
 bool patch_stageable(const OpArgs &a) {
-    return a.kind == MT_CONV && a.groups <= 1 && a.R == 3 && a.S == 3 && a.sh == 1 && a.sw == 1 && a.ph == 1 && a.pw == 1 && a.C % TK == 0 && a.H <= 1024;
+    return a.kind == MT_CONV && a.dtype != MT_F32 && a.groups <= 1 && a.R == 3 && a.S == 3 && a.sh == 1 && a.sw == 1 && a.ph == 1 && a.pw == 1 && a.C % TK == 0 && a.H <= 1024;
 }
 
 // What follows the main loop: the wave groups' partial sums meet, then those of the workgroups that share the tile, then
@@ -160,7 +181,9 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         float *et = reinterpret_cast<float *>(&smem[0]);
         constexpr int CPR = BN / 8;
         constexpr int EP_IT = (BM * CPR + NT - 1) / NT;
-        u32x4 res_raw[EP_IT];
+        // (16-bit types: a register quad, not a struct, which costs the wide tiles 12 to 32 registers and the tenants beside them 2 %)
+        typedef std::conditional_t<sizeof(T) == 2, u32x4, Pack<T, 8>> Raw;
+        Raw res_raw[EP_IT];
         const bool add_res = res != nullptr && !a.pool2;
         if (add_res) {
 #pragma unroll
@@ -168,7 +191,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
                 const int c = tid + it * NT;
                 const int m = pixel(min(c / CPR, BM - 1)), k = n0 + (c % CPR) * 8;
                 const bool live = (c < BM * CPR) & (m >= 0) & (k < a.K);
-                res_raw[it] = live ? *reinterpret_cast<const u32x4 *>(res + (int64_t)m * a.res_ct + k) : u32x4{0u, 0u, 0u, 0u};
+                res_raw[it] = live ? *reinterpret_cast<const Raw *>(res + (int64_t)m * a.res_ct + k) : Raw{};
             }
         }
         __syncthreads();
@@ -267,6 +290,34 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         }
 }
 
+// Image and top left input pixel of the window of output pixel m (walked window by window when the epilogue pools).
+__device__ __forceinline__ void window_origin(const OpArgs &a, uint32_t m, int &n, int &ih0, int &iw0) {
+    const uint32_t mq = a.pool2 ? m >> 2 : m;
+    const uint32_t pqd = a.pool2 ? (uint32_t)((a.P >> 1) * (a.Q >> 1)) : (uint32_t)(a.P * a.Q);
+    const uint32_t qd = a.pool2 ? (uint32_t)(a.Q >> 1) : (uint32_t)a.Q;
+    const uint32_t t1 = __umulhi(a.divpq_m, mq);
+    n = (int)((t1 + ((mq - t1) >> a.divpq_s1)) >> a.divpq_s2);
+    const uint32_t rem = mq - (uint32_t)n * pqd;
+    const uint32_t t2 = __umulhi(a.divq_m, rem);
+    int p = (int)((t2 + ((rem - t2) >> a.divq_s1)) >> a.divq_s2);
+    int q = (int)(rem - (uint32_t)p * qd);
+    if (a.pool2) {
+        p = 2 * p + (int)((m >> 1) & 1u);
+        q = 2 * q + (int)(m & 1u);
+    }
+    ih0 = p * a.sh - a.ph;
+    iw0 = q * a.sw - a.pw;
+}
+
+// Bit r: filter row r reads inside the image for this pixel; bit 16 + s: so does filter column s.
+__device__ __forceinline__ uint32_t window_mask(const OpArgs &a, int ih0, int iw0) {
+    auto range = [](int first, int extent, int window) {
+        const int lo = min(max(-first, 0), window), hi = min(max(extent - first, 0), window);
+        return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+    };
+    return range(ih0, a.H, a.R) | range(iw0, a.W, a.S) << 16;
+}
+
 // BN output channels x BM pixels per workgroup; WN x WM waves over the tile, WK such groups that share the reduction;
 // KD 64-deep slices of the reduction per stage, NBUF stages in LDS.
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
@@ -277,8 +328,9 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     constexpr int MF = (SUBN % 32 == 0 && SUBM % 32 == 0) ? 32 : 16;
     constexpr int TN = SUBN / MF, TM = SUBM / MF;
     static_assert(TN >= 1 && TM >= 1, "wave tile smaller than one matrix instruction");
-    constexpr int KS = MF == 32 ? 16 : 32;                 // reduction elements per matrix instruction
-    constexpr int STEPS = KD * TK / KS;                    // instruction steps per stage
+    constexpr int ES = sizeof(T), RK = ROW<T>, EPP = 16 / ES;   // bytes of an element, elements of an LDS row and of a 16-byte piece
+    constexpr int PPS = MF == 32 ? 2 : 4;                  // pieces of a row per step
+    constexpr int STEPS = KD * 8 / PPS;                    // steps per stage
     static_assert(STEPS % WK == 0, "the wave groups share a stage evenly");
     constexpr int MY_STEPS = STEPS / WK;
     constexpr int ACC = MF == 32 ? 16 : 4;
@@ -307,7 +359,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const int tn_idx = a.tile_order ? tile / tiles_m : tile % tiles_n;
     const int tm_idx = a.tile_order ? tile % tiles_m : tile / tiles_n;
     const int n0 = tn_idx * BN, m0 = tm_idx * BM;
-    const int nst = a.k_pad / (TK * KD);
+    const int nst = a.k_pad / (RK * KD);
     const int per = (nst + a.split_k - 1) / a.split_k;
     const int st0 = z * per;
     const int ns = min(nst, st0 + per) - st0;
@@ -315,7 +367,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const int XS = a.x_ct;
     const T *x = (const T *)a.x + a.x_coff;
     const u32x4 rsrc_x = raw_buffer(x, ((int64_t)a.N * a.H * a.W * XS - a.x_coff) * (int)sizeof(T));
-    const u32x4 rsrc_w = raw_buffer(a.w, (int64_t)a.n_pad * a.k_pad * 2);
+    const u32x4 rsrc_w = raw_buffer(a.w, (int64_t)a.n_pad * a.k_pad * ES);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
 
     // A load covers 8 rows; lane l delivers 16-byte column l % 8 of row l / 8.  Column c of LDS row r holds piece
@@ -324,55 +376,37 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     static_assert(NW % 2 == 0 && BN % 16 == 0 && BM % 16 == 0, "a wave's row groups have one parity");
     const int lrow = lane >> 3, piece = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
 
-    const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + piece * 8) * 2u;
+    const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + piece * EPP) * ES;
     uint32_t ws[WQ];                                       // scalar part of each filter load
 #pragma unroll
     for (int i = 0; i < WQ; ++i) {
         const int q = i * NW + wave, kd = q / (BN / 8), rg = q % (BN / 8);
-        ws[i] = (uint32_t)(rg * 8 * a.k_pad + (st0 * KD + kd) * TK) * 2u;
+        ws[i] = (uint32_t)(rg * 8 * a.k_pad + (st0 * KD + kd) * RK) * ES;
     }
     constexpr int NP = KD == 1 ? 1 : XQ;                   // positions along j tracked (loads of one 64-slice share one)
     uint32_t xoff[XQ], xmask[XQ];
     int ptap[NP], pch[NP];                                 // tap and channel of each position (TG_TAP: wave-uniform)
-    uint32_t xs = (uint32_t)(st0 * KD * TK) * 2u;          // TG_POINT: scalar offset
+    uint32_t xs = (uint32_t)(st0 * KD) * 128u;          // TG_POINT: scalar offset
 #pragma unroll
     for (int i = 0; i < XQ; ++i) {
         const int q = i * NW + wave, kd = q / (BM / 8), rg = q % (BM / 8);
         const int m = m0 + rg * 8 + lrow;
         const bool ok = m < M;
-        const uint32_t mm = ok ? (uint32_t)m : 0u;
-        const uint32_t mq = a.pool2 ? mm >> 2 : mm;
-        const uint32_t pqd = a.pool2 ? (uint32_t)((a.P >> 1) * (a.Q >> 1)) : (uint32_t)(a.P * a.Q);
-        const uint32_t qd = a.pool2 ? (uint32_t)(a.Q >> 1) : (uint32_t)a.Q;
-        const uint32_t t1 = __umulhi(a.divpq_m, mq);
-        const int n = (int)((t1 + ((mq - t1) >> a.divpq_s1)) >> a.divpq_s2);
-        const uint32_t rem = mq - (uint32_t)n * pqd;
-        const uint32_t t2 = __umulhi(a.divq_m, rem);
-        int p = (int)((t2 + ((rem - t2) >> a.divq_s1)) >> a.divq_s2);
-        int qq = (int)(rem - (uint32_t)p * qd);
-        if (a.pool2) {
-            p = 2 * p + (int)((mm >> 1) & 1u);
-            qq = 2 * qq + (int)(mm & 1u);
-        }
-        const int ih0 = p * a.sh - a.ph, iw0 = qq * a.sw - a.pw;
-        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (MODE == TG_CHUNK ? 0 : piece * 8)) * 2u;
+        int n, ih0, iw0;
+        window_origin(a, ok ? (uint32_t)m : 0u, n, ih0, iw0);
+        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (MODE == TG_CHUNK ? 0 : piece * EPP)) * ES;
         if constexpr (MODE == TG_POINT) {
-            xoff[i] = ok ? xoff[i] + (uint32_t)(kd * TK * 2) : OUT_OF_RANGE;
+            xoff[i] = ok ? xoff[i] + (uint32_t)(kd * 128) : OUT_OF_RANGE;
         } else {
-            // bit r: filter row r reads inside the image for this pixel; bit 16 + s: so does filter column s
-            auto range = [](int first, int extent, int window) {
-                const int lo = min(max(-first, 0), window), hi = min(max(extent - first, 0), window);
-                return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
-            };
-            xmask[i] = ok ? range(ih0, a.H, a.R) | range(iw0, a.W, a.S) << 16 : 0u;
+            xmask[i] = ok ? window_mask(a, ih0, iw0) : 0u;
         }
         if (MODE != TG_POINT && i < NP) {
-            const int j0 = (st0 * KD + (KD == 1 ? 0 : kd)) * TK + (MODE == TG_CHUNK ? piece * 8 : 0);
+            const int j0 = (st0 * KD + (KD == 1 ? 0 : kd)) * RK + (MODE == TG_CHUNK ? piece * EPP : 0);
             ptap[i] = j0 / a.C;
             pch[i] = j0 - ptap[i] * a.C;
         }
     }
-    const int adv_t = KD * TK / a.C, adv_c = KD * TK - adv_t * a.C;
+    const int adv_t = KD * RK / a.C, adv_c = KD * RK - adv_t * a.C;
     const uint32_t inv_s = (uint32_t)((0x100000000ull + (uint32_t)a.S - 1) / (uint32_t)a.S);   // 0 for S == 1
 
     auto issue = [&](int buf) {
@@ -380,7 +414,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
 #pragma unroll
         for (int i = 0; i < WQ; ++i) {
             load_to_lds(rsrc_w, wv, ws[i], base + (uint32_t)((i * NW + wave) * 1024));
-            ws[i] += KD * TK * 2;
+            ws[i] += KD * 128;
         }
         uint32_t toff[NP], trow[NP], tcol[NP];
         if constexpr (MODE != TG_POINT) {
@@ -388,7 +422,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
             for (int i = 0; i < NP; ++i) {
                 const int tr = a.S == 1 ? ptap[i] : (int)__umulhi((uint32_t)ptap[i], inv_s);
                 const int tc = ptap[i] - tr * a.S;
-                toff[i] = (uint32_t)((tr * a.W + tc) * XS + pch[i]) * 2u;
+                toff[i] = (uint32_t)((tr * a.W + tc) * XS + pch[i]) * ES;
                 trow[i] = (uint32_t)min(tr, 15);           // beyond the window (padding of the reduction): a bit that is never set
                 tcol[i] = (uint32_t)(16 + tc);
                 ptap[i] += adv_t;
@@ -409,7 +443,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
                 load_to_lds(rsrc_x, off, 0u, dst);
             }
         }
-        xs += KD * TK * 2;
+        xs += KD * 128;
     };
 
     Acc acc[TN][TM];
@@ -425,8 +459,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), xrow = (uint32_t)(W_BYTES + (wm * SUBM + frow) * 128);
     const uint32_t swz = (uint32_t)((frow >> 1) & 7);
     auto load_frag = [&](uint32_t buf, int s, Frag &f) {   // s: step of the stage
-        constexpr int PPS = KS / 8;                        // pieces per step
-        const int kd = s / (TK / KS), c0 = (s % (TK / KS)) * PPS;
+        const int kd = s / (8 / PPS), c0 = (s % (8 / PPS)) * PPS;
         const uint32_t col = ((uint32_t)(c0 + fgrp) ^ swz) * 16u;
 #pragma unroll
         for (int i = 0; i < TN; ++i)
@@ -456,10 +489,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     int rbuf = 0, ibuf = NBUF - 1;
     for (int t = 0; t < ns; ++t) {
         // stages issued after stage t: NBUF - 2 of them, fewer at the end
-        const int later = min(ns - 1 - t, NBUF - 2);
-        if (later >= NBUF - 2) wait_and_meet<(NBUF - 2) * L>();
-        else if (NBUF > 3 && later == NBUF - 3) wait_and_meet<(NBUF > 3 ? NBUF - 3 : 0) * L>();
-        else wait_and_meet<0>();
+        wait_for_stage<L, NBUF - 2>(min(ns - 1 - t, NBUF - 2));
         if (t + NBUF - 1 < ns) issue(ibuf);
         compute(rbuf);
         rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
@@ -468,6 +498,156 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     wait_and_meet<0>();                                    // the tile buffers are free
 
     finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
+        const int m = m0 + ml;
+        return m < M ? (a.pool2 ? m >> 2 : m) : -1;
+    });
+}
+
+// Small maps: a workgroup owns BN output channels x 16 pixels and its WK waves deal the rows of the reduction (128 bytes
+// each) out between them.  A wave's operands are nobody else's, so every wave has D rows in LDS of its own and waits for its
+// own loads only: the reduction has no barrier, and WK * D rows of it are in flight after one trip to memory.  The partial sums
+// meet once at the end.
+//
+// What bounds it: launch, one trip to memory and the operand bytes of a tile at the 64 bytes per cycle a compute unit copies to
+// LDS; tile_body with the same tile needs a barrier per stage (0.24 us each).  MI355X, bf16, one image, us, 64 x 16 tiles with a
+// split reduction / this: 3x3 256 -> 256 on 14 x 14 6.9 / 5.8, 512 -> 512 on 7 x 7 7.9 / 7.4, 1x7 192 -> 192 on 17 x 17 6.3 / 5.1,
+// 1x1 1024 -> 256 on 14 x 14 4.9 / 3.9; 2048 -> 192 on 8 x 8 with waves that load to registers 6.5, 4.6 here.
+// Rings hold 64 to 72 KB, not what fits: with 128 to 144 KB a layer alone is up to 0.6 us faster, but its workgroups wait for an empty
+// compute unit when other tenants run (ResNet-101, Inception-v3, MobileNetV2 and AlexNet together: 665 us, 587 with these).
+template <typename T, int BN, int WK, int D, int MODE>
+__device__ __forceinline__ void ring_body(const OpArgs &a) {
+    set_wave_priority(a.prio);
+    constexpr int ES = sizeof(T), RK = ROW<T>, EPP = 16 / ES, BM = 16, TN = BN / 16;
+    constexpr int WQ = BN / 8, XQ = BM / 8, L = WQ + XQ;   // loads of a row: 8 operand rows of 128 bytes each
+    constexpr int ROW_BYTES = (BN + BM) * 128, RED_BYTES = (WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
+    constexpr int LDS_BYTES = std::max({WK * D * ROW_BYTES, RED_BYTES, EP_BYTES});
+    typedef typename Mma<T, 16>::Acc Acc;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    __shared__ int s_last;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int M = a.N * a.P * a.Q;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = a.n_pad / BN;
+    const int total = tiles_m * tiles_n * a.split_k;
+    const int per_xcd = (total + XCDS - 1) / XCDS;
+    const int vid = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
+    if (vid >= total) return;
+    const int z = vid % a.split_k;
+    const int tile = vid / a.split_k;
+    const int tn_idx = a.tile_order ? tile / tiles_m : tile % tiles_n;
+    const int tm_idx = a.tile_order ? tile % tiles_m : tile / tiles_n;
+    const int n0 = tn_idx * BN, m0 = tm_idx * BM;
+    const int nrows = a.k_pad / RK, per = (nrows + a.split_k - 1) / a.split_k;
+    const int first = z * per + wave, end = min(nrows, z * per + per);
+    const int mine = first < end ? (end - first + WK - 1) / WK : 0;    // this wave's rows: first, first + WK, ...
+
+    const int XS = a.x_ct;
+    const T *x = (const T *)a.x + a.x_coff;
+    const u32x4 rsrc_x = raw_buffer(x, ((int64_t)a.N * a.H * a.W * XS - a.x_coff) * (int)sizeof(T));
+    const u32x4 rsrc_w = raw_buffer(a.w, (int64_t)a.n_pad * a.k_pad * ES);
+    const uint32_t ring = (uint32_t)wave * (D * ROW_BYTES);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem + ring;
+
+    // columns of the LDS rows permuted as in tile_body: column c of operand row r holds piece c ^ (r / 2 % 8)
+    const int lrow = lane >> 3;
+    uint32_t wv[WQ], xoff[XQ], xmask[XQ];
+    int piece[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) piece[i] = (lane & 7) ^ (i * 4 + (lrow >> 1));
+#pragma unroll
+    for (int i = 0; i < WQ; ++i) wv[i] = (uint32_t)((n0 + i * 8 + lrow) * a.k_pad + piece[i & 1] * EPP) * ES;
+    constexpr int NP = MODE == TG_CHUNK ? XQ : 1;          // positions along j: of every load, or of the row
+    int ptap[NP], pch[NP];
+#pragma unroll
+    for (int i = 0; i < XQ; ++i) {
+        const int m = m0 + i * 8 + lrow;
+        const bool ok = m < M;
+        int n, ih0, iw0;
+        window_origin(a, ok ? (uint32_t)m : 0u, n, ih0, iw0);
+        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (MODE == TG_CHUNK ? 0 : piece[i & 1] * EPP)) * ES;
+        if constexpr (MODE == TG_POINT) xoff[i] = ok ? xoff[i] : OUT_OF_RANGE;
+        else xmask[i] = ok ? window_mask(a, ih0, iw0) : 0u;
+        if (MODE != TG_POINT && i < NP) {
+            const int j0 = first * RK + (MODE == TG_CHUNK ? piece[i & 1] * EPP : 0);
+            ptap[i] = j0 / a.C;
+            pch[i] = j0 - ptap[i] * a.C;
+        }
+    }
+    const int adv_t = WK * RK / a.C, adv_c = WK * RK - adv_t * a.C;
+    const uint32_t inv_s = (uint32_t)((0x100000000ull + (uint32_t)a.S - 1) / (uint32_t)a.S);   // 0 for S == 1
+    uint32_t at = (uint32_t)first * 128u;                  // byte of the row requested next
+
+    auto issue = [&](int slot) {
+        const uint32_t base = lds0 + (uint32_t)(slot * ROW_BYTES);
+#pragma unroll
+        for (int i = 0; i < WQ; ++i) load_to_lds(rsrc_w, wv[i], at, base + (uint32_t)(i * 1024));
+        uint32_t toff[NP], trow[NP], tcol[NP];
+        if constexpr (MODE != TG_POINT) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int tr = a.S == 1 ? ptap[i] : (int)__umulhi((uint32_t)ptap[i], inv_s);
+                const int tc = ptap[i] - tr * a.S;
+                toff[i] = (uint32_t)((tr * a.W + tc) * XS + pch[i]) * ES;
+                trow[i] = (uint32_t)min(tr, 15);           // beyond the window (padding of the reduction): a bit that is never set
+                tcol[i] = (uint32_t)(16 + tc);
+                ptap[i] += adv_t;
+                pch[i] += adv_c;
+                const bool carry = pch[i] >= a.C;
+                pch[i] -= carry ? a.C : 0;
+                ptap[i] += carry ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < XQ; ++i) {
+            const uint32_t dst = base + (uint32_t)(WQ * 1024 + i * 1024);
+            if constexpr (MODE == TG_POINT) {
+                load_to_lds(rsrc_x, xoff[i], at, dst);
+            } else {
+                const int pi = MODE == TG_CHUNK ? i : 0;
+                const uint32_t off = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u ? xoff[i] + toff[pi] : OUT_OF_RANGE;
+                load_to_lds(rsrc_x, off, 0u, dst);
+            }
+        }
+        at += WK * 128;
+    };
+
+    Acc acc[TN][1];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][0][v] = 0.f;
+
+    const int frow = lane & 15, fgrp = lane >> 4;
+    const uint32_t swz = (uint32_t)((frow >> 1) & 7);
+#pragma unroll
+    for (int s = 0; s < D; ++s)
+        if (s < mine) issue(s);
+    int slot = 0;
+    for (int t = 0; t < mine; ++t) {
+        wait_for_row<L, D - 1>(min(mine - 1 - t, D - 1));
+        u32x4 fw[2][TN], fx[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t col = ((uint32_t)(s * 4 + fgrp) ^ swz) * 16u;
+            const uint32_t b = ring + (uint32_t)(slot * ROW_BYTES) + (uint32_t)(frow * 128) + col;
+#pragma unroll
+            for (int i = 0; i < TN; ++i) fw[s][i] = *reinterpret_cast<const u32x4 *>(&smem[b + (uint32_t)(i * 16 * 128)]);
+            fx[s] = *reinterpret_cast<const u32x4 *>(&smem[b + (uint32_t)(BN * 128)]);
+        }
+        if (t + D < mine) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the row has been read: its place can be filled again
+            issue(slot);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < TN; ++i) acc[i][0] = Mma<T, 16>::run(fw[s][i], fx[s], acc[i][0]);
+        slot = slot + 1 == D ? 0 : slot + 1;
+    }
+    wait_and_meet<0>();                                    // the rings are free
+
+    finish_tile<T, BN, BM, 1, 1, WK, 16>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
         const int m = m0 + ml;
         return m < M ? (a.pool2 ? m >> 2 : m) : -1;
     });
@@ -695,6 +875,16 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) tile_pair_kernel(OpArgsPair
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y]);
 }
 
+template <typename T, int BN, int WK, int D, int MODE>
+__global__ void __launch_bounds__(64 * WK) ring_kernel(OpArgs a) {
+    ring_body<T, BN, WK, D, MODE>(a);
+}
+
+template <typename T, int BN, int WK, int D, int MODE>
+__global__ void __launch_bounds__(64 * WK) ring_pair_kernel(OpArgsPair p) {
+    ring_body<T, BN, WK, D, MODE>(p.a[blockIdx.y]);
+}
+
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
     patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a);
@@ -708,29 +898,40 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPai
 // ---- choice of form -----------------------------------------------------------------------------------------------
 namespace {
 
-struct TileForm {
-    int bn, bm, kd, threads, patch_pixels;                 // patch_pixels 0: tile_body
-    // Time of a launch in us on MI355X: start + wave * (n - 1) + ns * (stage + crowd * (n - 1)), and split_once + split_each *
-    // split if the reduction is split; n: workgroups per compute unit, ns: stages of a workgroup.  Fitted to 27 800 timings
-    // of the 1143 distinct convolutions and classifiers of nine networks at batches 1 to 64 (launch gap included).  Picking
-    // the form and split with the least estimate costs 1.1 % of a network's time over picking the fastest measured one.
+// Time of a launch in us on MI355X: start + wave * (n - 1) + ns * (stage + crowd * (n - 1)), and split_once + split_each *
+// split if the reduction is split over workgroups (16-bit types only, and rings never are: a split costs them more than it gives); n: workgroups per compute unit, ns: stages of a workgroup.  Fitted to timings of the
+// distinct convolutions and classifiers of nine networks at batches 1 to 64 (fp32: 1 to 8), launch gap included.  Sum over
+// those layers, us, without the ring forms / picking by the estimate / the fastest measured form of every layer: bf16 at batch 1
+// 593 / 531 / 519, batch 5 839 / 805 / 767.  fp32, operands from memory to registers (kernels_dconv.hip) / picking here /
+// fastest: batch 1 1219 / 930 / 900, batch 4 1526 / 1220 / 1160.
+struct TileCost {
     double start, wave, stage, crowd, split_once, split_each;
 };
+struct TileForm {
+    int bn, bm, kd, rows, threads, patch_pixels;           // rows: LDS rows of the reduction per stage; patch_pixels 0: tile_body or ring_body
+    int ring;                                              // waves of ring_body that share the reduction, 0: another body
+    TileCost half, single;                                 // of the 16-bit types and of fp32 (NONE: not built)
+};
+constexpr TileCost NONE = {0, 0, 0, 0, 0, 0};
 
 constexpr TileForm FORMS[] = {
-    {128, 128, 1, 256, 0, 5.33, 2.29, 0.537, 0.350, 1.98, 0.995},
-    {128, 64, 1, 256, 0, 4.17, 1.29, 0.372, 0.209, 1.49, 0.726},
-    {64, 64, 1, 256, 0, 3.68, 0.965, 0.285, 0.133, 1.52, 0.375},
-    {64, 64, 2, 512, 0, 3.66, 2.50, 0.402, 0.515, 2.07, 0.218},
-    {64, 32, 2, 512, 0, 3.63, 1.11, 0.323, 0.235, 1.35, 0.266},
-    {64, 16, 2, 256, 0, 2.79, 0.723, 0.295, 0.166, 1.60, 0.140},
-    {128, 256, 1, 512, 384, 9.21, 5.92, 0.545, 0.823, 2.20, 1.36},
-    {128, 128, 1, 512, 256, 7.59, 6.90, 0.331, 0.357, 2.31, 0.748},
-    {128, 64, 1, 512, 192, 5.83, 4.94, 0.219, 0.238, 1.52, 0.602},
-    {64, 64, 3, 512, 192, 4.96, 3.74, 0.413, 0.438, 1.53, 0.284},
-    {64, 32, 1, 512, 128, 4.56, 1.38, 0.118, 0.109, 1.38, 0.252},
+    {128, 128, 1, 1, 256, 0, 0, {5.33, 2.29, 0.537, 0.350, 1.98, 0.995}, NONE},
+    {128, 64, 1, 1, 256, 0, 0, {4.17, 1.29, 0.372, 0.209, 1.49, 0.726}, NONE},
+    {64, 64, 1, 1, 256, 0, 0, {3.68, 0.965, 0.285, 0.133, 1.52, 0.375}, {3.92, 0.653, 0.582, 0.569, 0, 0}},
+    {64, 64, 2, 2, 512, 0, 0, {3.66, 2.50, 0.402, 0.515, 2.07, 0.218}, {4.58, 2.09, 0.888, 1.61, 0, 0}},
+    {64, 32, 2, 2, 512, 0, 0, {3.63, 1.11, 0.323, 0.235, 1.35, 0.266}, {3.89, 0.912, 0.613, 0.635, 0, 0}},
+    {64, 16, 2, 2, 256, 0, 0, {2.79, 0.723, 0.295, 0.166, 1.60, 0.140}, {2.99, 0.671, 0.437, 0.306, 0, 0}},
+    {128, 256, 1, 1, 512, 384, 0, {9.21, 5.92, 0.545, 0.823, 2.20, 1.36}, NONE},
+    {128, 128, 1, 1, 512, 256, 0, {7.59, 6.90, 0.331, 0.357, 2.31, 0.748}, NONE},
+    {128, 64, 1, 1, 512, 192, 0, {5.83, 4.94, 0.219, 0.238, 1.52, 0.602}, NONE},
+    {64, 64, 3, 3, 512, 192, 0, {4.96, 3.74, 0.413, 0.438, 1.53, 0.284}, NONE},
+    {64, 32, 1, 1, 512, 128, 0, {4.56, 1.38, 0.118, 0.109, 1.38, 0.252}, NONE},
+    {32, 32, 2, 2, 512, 0, 0, NONE, {3.32, 0.897, 0.395, 0.402, 0, 0}},
+    {16, 16, 1, 8, 512, 0, 8, {3.30, 1.82, 0.283, 0.480, 0, 0}, {3.19, 1.88, 0.453, 0.528, 0, 0}},
+    {32, 16, 1, 4, 256, 0, 4, {3.35, 0.9, 0.28, 0.25, 0, 0}, {3.3, 0.95, 0.37, 0.4, 0, 0}},
+    {16, 16, 1, 4, 256, 0, 4, {3.19, 0.568, 0.193, 0.175, 0, 0}, {3.03, 0.652, 0.259, 0.209, 0, 0}},
 };
-constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]), FORM_64x16 = 5;
+constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]), FORM_64x16 = 5, FORM_RING4 = 14;
 constexpr int MAX_SPLIT = 8, TARGET_WGS = 768, UNITS = 256;
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -780,10 +981,16 @@ void set_walk(OpArgs &a) {
 }  // namespace
 
 // Form, split and launch shape of a convolution (a fully connected layer is a 1x1 one) with C % 8 == 0 and a window of at
-// most 15 x 15: a pure function of the layer's shape.  narrow: the 64 x 16 tile whatever the estimate says (the fused 1x1 +
-// depthwise kernels reproduce its order of additions).
-bool plan_tile(OpArgs &a, bool narrow) {
-    if (a.C % 8 != 0 || a.R > 15 || a.S > 15) return false;
+// most 15 x 15: a pure function of the layer's shape and of `choice` (see TileChoice).
+bool plan_tile(OpArgs &a, TileChoice choice) {
+    const int only = choice == TILE_NARROW ? FORM_64x16 : choice == TILE_RING4 ? FORM_RING4 : -1;
+    const bool unsplit = choice == TILE_UNSPLIT;
+    const bool f32 = a.dtype == MT_F32;
+    const int row = f32 ? ROW<float> : TK;
+    if (a.C % (row / 8) != 0 || a.R > 15 || a.S > 15) return false;
+    // fp32 with few output channels: the tiles would be half padding (144 -> 24 on 4 x 56 x 56 7.4 us, 5.7 with operands from
+    // memory; 288 -> 32 on 4 x 149 x 149 41 / 37; short reductions are bound by their input: 32 -> 16 on 4 x 112 x 112 7.9 / 20)
+    if (f32 && a.K <= 32 && a.gemm_k >= 128) return false;
     const bool patch_ok = patch_stageable(a);
     // long reductions over a wide map that has fewer than 72 tiles of 64 x 64 are always split
     const int M = a.N * a.P * a.Q;
@@ -792,20 +999,22 @@ bool plan_tile(OpArgs &a, bool narrow) {
     int form = -1, split = 1, panel = 0;
     for (int f = 0; f < N_FORMS; ++f) {
         const TileForm &t = FORMS[f];
-        if (narrow && f != FORM_64x16) continue;
+        const TileCost &c = f32 ? t.single : t.half;
+        if (c.start == 0) continue;
+        if ((only >= 0 && f != only) || (choice == TILE_NO_RING && t.ring)) continue;
         if (t.patch_pixels > 0 && !patch_ok) continue;
         if (t.patch_pixels == 0 && a.kernel_id == K_PCONV) continue;
         if (t.bn > 64 && a.K <= t.bn / 2) continue;         // more than half of the tile would be padding
         const int w = t.patch_pixels > 0 ? patch_panel(a.N, a.P, a.Q, t.bm, t.patch_pixels, false) : 0;
         if (t.patch_pixels > 0 && w == 0) continue;
         const int tiles = pixel_tiles(t, a, w) * cdiv(a.K, t.bn);
-        const int units = t.patch_pixels > 0 ? a.C / TK : cdiv(a.gemm_k, TK * t.kd);      // what a split cuts
-        for (int s = 1; s <= MAX_SPLIT; ++s) {
-            if (s > 1 && (tiles * s > TARGET_WGS || (t.patch_pixels > 0 ? s > units : 2 * s > units))) break;
+        const int units = t.patch_pixels > 0 ? a.C / TK : cdiv(a.gemm_k, row * t.kd);     // what a split cuts
+        for (int s = 1; s <= (unsplit || t.ring ? 1 : MAX_SPLIT); ++s) {
+            if (s > 1 && (tiles * s > TARGET_WGS || (t.patch_pixels > 0 ? s > units : 2 * s * t.rows > units * t.kd))) break;
             const int per = cdiv(units, s);
             if (cdiv(units, per) != s) continue;            // an empty split
-            const int ns = t.patch_pixels > 0 ? per * 9 / t.kd : per, n = cdiv(tiles * s, UNITS);
-            const double us = t.start + t.wave * (n - 1) + ns * (t.stage + t.crowd * (n - 1)) + (s > 1 ? t.split_once + t.split_each * s : 0.0);
+            const int ns = t.patch_pixels > 0 ? per * 9 / t.kd : cdiv(per * t.kd, t.rows), n = cdiv(tiles * s, UNITS);
+            const double us = c.start + c.wave * (n - 1) + ns * (c.stage + c.crowd * (n - 1)) + (s > 1 ? c.split_once + c.split_each * s : 0.0);
             if (s < min_split) continue;
             if (form < 0 || us < best) { best = us; form = f; split = s; panel = w; }
         }
@@ -816,7 +1025,7 @@ bool plan_tile(OpArgs &a, bool narrow) {
     a.split_k = split;
     a.block = t.threads;
     a.n_pad = cdiv(a.K, t.bn) * t.bn;
-    a.k_pad = t.patch_pixels > 0 ? a.gemm_k : cdiv(a.gemm_k, TK * t.kd) * TK * t.kd;
+    a.k_pad = t.patch_pixels > 0 ? a.gemm_k : cdiv(a.gemm_k, row * t.kd) * row * t.kd;
     // Consecutive tiles run on one XCD: they walk the channel tiles of one pixel tile when the activations are the larger
     // operand, the pixel tiles of one channel tile otherwise.
     a.tile_order = ((double)a.K * a.gemm_k > (double)a.N * a.H * a.W * a.C) ? 1 : 0;
@@ -829,6 +1038,8 @@ bool plan_tile(OpArgs &a, bool narrow) {
 
 // One ascending pass over the reduction on 64 x 16 tiles.
 bool tile_is_narrow(const OpArgs &a) { return a.form == FORM_64x16 && a.split_k == 1; }
+
+int reduction_ranges(const OpArgs &a) { return a.split_k * (a.form >= 0 ? std::max(1, FORMS[a.form].ring) : 1); }
 
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats) {
     const TileForm &t = FORMS[a.form];
@@ -854,36 +1065,60 @@ bool plan_tile_pooled(OpArgs &a) {
 template <typename T>
 static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
     const dim3 grid(a.grid_x), block(a.block);
-    auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
-        auto go = [&]<int MODE>() {
-            MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, st, a, mate);
-        };
-        if (a.C % TK != 0) go.template operator()<TG_CHUNK>();
+    auto by_gather = [&](auto go) {
+        if (a.C % ROW<T> != 0) go.template operator()<TG_CHUNK>();
         else if (a.R == 1 && a.S == 1 && a.ph == 0 && a.pw == 0) go.template operator()<TG_POINT>();
         else go.template operator()<TG_TAP>();
+    };
+    auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
+        auto go = [&]<int MODE>() {
+            if constexpr (std::is_same_v<T, float>) launch((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, 0, st, a);
+            else MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, st, a, mate);
+        };
+        by_gather(go);
+    };
+    auto ring = [&]<int BN, int WK, int D>() {
+        auto go = [&]<int MODE>() {
+            if constexpr (std::is_same_v<T, float>) launch((ring_kernel<T, BN, WK, D, MODE>), grid, block, 0, st, a);
+            else MT_LAUNCH((ring_kernel<T, BN, WK, D, MODE>), (ring_pair_kernel<T, BN, WK, D, MODE>), grid, block, st, a, mate);
+        };
+        by_gather(go);
     };
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
     };
+    constexpr bool f32 = std::is_same_v<T, float>;
     switch (a.form) {
-        case 0: tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
-        case 1: tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
         case 2: tile.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
         case 3: tile.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;
         case 4: tile.template operator()<64, 32, 2, 1, 4, 2, 3>(); break;
         case 5: tile.template operator()<64, 16, 4, 1, 1, 2, 3>(); break;
-        case 6: patch.template operator()<128, 256, 2, 4, 1, 1, 384>(); break;
-        case 7: patch.template operator()<128, 128, 2, 2, 2, 1, 256>(); break;
-        case 8: patch.template operator()<128, 64, 2, 2, 2, 1, 192>(); break;
-        case 9: patch.template operator()<64, 64, 2, 2, 2, 3, 192>(); break;
-        case 10: patch.template operator()<64, 32, 2, 1, 4, 1, 128>(); break;
-        default: return (int)hipErrorInvalidValue;
+        case 12: ring.template operator()<16, 8, 2>(); break;
+        case 13: ring.template operator()<32, 4, 3>(); break;
+        case 14: ring.template operator()<16, 4, 4>(); break;
+        default:
+            if constexpr (f32) {
+                if (a.form != 11) return (int)hipErrorInvalidValue;
+                tile.template operator()<32, 32, 2, 2, 2, 2, 4>();
+            } else {
+                switch (a.form) {
+                    case 0: tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
+                    case 1: tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+                    case 6: patch.template operator()<128, 256, 2, 4, 1, 1, 384>(); break;
+                    case 7: patch.template operator()<128, 128, 2, 2, 2, 1, 256>(); break;
+                    case 8: patch.template operator()<128, 64, 2, 2, 2, 1, 192>(); break;
+                    case 9: patch.template operator()<64, 64, 2, 2, 2, 3, 192>(); break;
+                    case 10: patch.template operator()<64, 32, 2, 1, 4, 1, 128>(); break;
+                    default: return (int)hipErrorInvalidValue;
+                }
+            }
     }
     return (int)hipGetLastError();
 }
 
 int launch_tile(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates) {
     if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX || a.groups > 1)) return (int)hipErrorInvalidValue;
+    if (a.dtype == MT_F32) return mate ? (int)hipErrorInvalidValue : launch_tile_typed<float>(a, (hipStream_t)stream, nullptr, 0);
     if (a.dtype == MT_F16) return launch_tile_typed<f16>(a, (hipStream_t)stream, mate, n_mates);
     if (a.dtype == MT_BF16) return launch_tile_typed<bf16>(a, (hipStream_t)stream, mate, n_mates);
     return (int)hipErrorInvalidValue;

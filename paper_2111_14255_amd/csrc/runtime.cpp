@@ -67,7 +67,7 @@ constexpr int ROWB_MIN_PIXELS = 8192, ROWB_MAX_PIXELS_3X3 = 131072;
 bool needs_weights(int kind) { return kind == MT_CONV || kind == MT_DWCONV || kind == MT_FC; }
 
 // Kernel, tile and split choice of a convolution / fully connected layer: a pure function of its shape.
-void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k) {
+void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
     auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
     p.k_pad = cdiv(gemm_k, IGEMM_BK) * IGEMM_BK;
     p.grid_y = p.grid_z = 1;
@@ -89,19 +89,19 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k) {
         return;
     }
     const bool small = M <= 4096 && macs <= 3.0e8;
-    // 1x1 convolution on a small map: operands straight from memory, one wave per 16 x 16 output tile.  Up to eight 32-deep
-    // reduction steps a wave walks alone (split_k 1); longer reductions are cut into four ranges, one per wave of the
-    // workgroup (recorded as split_k 4; no workspace: the partial sums meet in LDS).  Its waves share nothing, so it is only
-    // level with the 64 x 16 tile where there are few of them or the reduction is one LDS row deep: 960 -> 160 on 49 pixels
-    // 4.7 / 4.8 us, 32 -> 192 on 1568 pixels 4.3 / 4.4 us, but 256 -> 1024 on 196 pixels 4.9 / 3.6, 768 -> 192 on 1445 pixels 9.9 / 5.3.
+    // 1x1 convolution on a small map.  Up to eight 32-deep reduction steps: operands straight from memory, one wave per 16 x 16
+    // output tile.  Its waves share nothing, so it is only level with the 64 x 16 tile where there are few of them or the
+    // reduction is one LDS row deep: 32 -> 192 on 1568 pixels 4.3 / 4.4 us, but 256 -> 1024 on 196 pixels 4.9 / 3.6.  Longer reductions
+    // on few tiles: four waves deal them out between them (960 -> 160 on 49 pixels 3.9 us, 2048 -> 192 on 64 pixels 4.5, against 4.5 and
+    // 6.5 with four contiguous ranges loaded to registers).
     if (small && vec && p.kind == MT_CONV && p.R == 1 && p.S == 1 && p.ph == 0 && p.pw == 0) {
         const int tiles = cdiv(M, 16) * cdiv(Kc, 16);
         const bool slices = p.k_pad / 32 > 8;
         if (slices ? tiles <= 48 : (p.k_pad <= IGEMM_BK ? tiles <= 1024 && (p.C < IGEMM_BK || tiles <= 64) : tiles <= 32)) {
             p.kernel_id = K_IGEMM_PW;
+            if (slices && plan_tile(p, TILE_RING4)) return;
             p.n_pad = cdiv(Kc, 64) * 64;
-            p.split_k = slices ? 4 : 1;
-            p.grid_x = slices ? tiles : cdiv(tiles, 4);
+            p.grid_x = cdiv(tiles, 4);
             make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
             make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
             return;
@@ -119,8 +119,10 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k) {
     } else if (vec && patch_stageable(p) && cdiv(M, 64) * cdiv(Kc, 64) >= 150) {
         p.kernel_id = K_PCONV;
     }
-    const bool before_depthwise = small && p.R == 1 && p.S == 1 && p.C <= 256;
-    if (vec && plan_tile(p, before_depthwise)) return;
+    // short 1x1 layers: beside a depthwise layer the tile whose order of additions the fused 1x1 + depthwise kernels reproduce
+    // (64 -> 256 on 56 x 56 takes 5.9 us on it, 4.1 on the tile of least estimate)
+    const bool short_1x1 = small && p.R == 1 && p.S == 1 && p.C <= 256;
+    if (vec && plan_tile(p, !short_1x1 ? TILE_ANY : beside_depthwise ? TILE_NARROW : TILE_UNSPLIT)) return;
     // element-wise gather (C % 8 != 0 or a window of more than 15 rows or columns): tiles of the register-staged kernel
     p.vec_a = 0;
     p.n_pad = cdiv(Kc, bn) * bn;
@@ -235,6 +237,7 @@ int32_t finalize_model(mt_model *m) {
                         break;
                     }
                     p.kernel_id = K_CONV_DIRECT;
+                    if (plan_tile(p, TILE_UNSPLIT)) break;
                     p.wk = dconv_f32_plan(M, Kg, gemm_k, p.C);
                     if (p.wk > 0) {
                         p.grid_x = dconv_f32_grid(p.wk, M, Kg);
@@ -290,7 +293,10 @@ int32_t finalize_model(mt_model *m) {
                         make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
                         break;
                     }
-                    plan_igemm(p, M, o.out_c / groups, gemm_k);
+                    bool beside_depthwise = false;
+                    for (const OpRec &other : m->ops)
+                        beside_depthwise = beside_depthwise || (other.d.kind == MT_DWCONV && (other.d.in_tensor == d.out_tensor || other.d.out_tensor == d.in_tensor));
+                    plan_igemm(p, M, o.out_c / groups, gemm_k, beside_depthwise);
                 }
                 break;
             }
@@ -340,7 +346,7 @@ int32_t finalize_model(mt_model *m) {
             const size_t nb = (size_t)p.groups * (igemm ? p.n_pad : p.K);
             o.bias_off = off; off += align_up(nb * sizeof(float));
         }
-        if (p.split_k > 1 && p.kernel_id != K_IGEMM_PW) {
+        if (p.split_k > 1) {
             // the groups of a grouped convolution run side by side: each has its own workspace
             size_t tiles = 0, floats = 0;
             split_workspace(p, &tiles, &floats);
@@ -374,7 +380,7 @@ void fill_info(const mt_model *m, const OpRec &o, mt_op_info *out) {
     out->in_h = o.in_h; out->in_w = o.in_w; out->in_c = o.in_c;
     out->out_h = o.out_h; out->out_w = o.out_w; out->out_c = o.out_c;
     out->kernel_id = o.plan.kernel_id;
-    out->split_k = o.plan.split_k;
+    out->split_k = reduction_ranges(o.plan);
     out->grid_blocks = o.plan.grid_x ? o.plan.grid_x : 0;
     out->flops = o.flops;
     out->bytes = o.bytes;
@@ -398,7 +404,7 @@ struct Tenant {
     // mt_run_static_scratch: where each split operator's counters and workspace sit inside the tenant's two blocks of the
     // fixed scratch array (byte offsets; blocks are laid out per call, counters of all tenants first)
     std::vector<size_t> st_cnt_off, st_ws_off;
-    size_t st_cnt_bytes = 0, st_ws_bytes = 0;
+    size_t st_cnt_bytes = 0, st_ws_bytes = 0, st_need = 0;
 };
 
 struct mt_schedule;
@@ -1650,7 +1656,7 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
             a.w = t->arena + o.w_off;
             a.bias = (const float *)(t->arena + o.bias_off);
         }
-        if (a.split_k > 1 && a.kernel_id != K_IGEMM_PW) {
+        if (a.split_k > 1) {
             a.ws = (float *)(t->arena + o.ws_off);
             a.counters = (uint32_t *)(t->arena + o.cnt_off);
             HIP_TRY(hipMemset(a.counters, 0, o.cnt_bytes));
@@ -1667,7 +1673,17 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
     t->st_ws_off.assign(nops, 0);
     for (size_t i = 0; i < nops; ++i) {
         const OpRec &o = t->model.ops[i];
+        // The limit of mt_run_static_scratch counts a layer that runs on a ring as the split layer it would be without one: which
+        // sets of tenants are taken does not depend on which form is the fastest.
+        OpArgs split = o.plan;
+        if (o.plan.dtype != MT_F32 && o.plan.split_k == 1 && reduction_ranges(o.plan) > 1 && o.plan.kernel_id != K_IGEMM_PW && o.plan.gemm_k > 256 &&
+            plan_tile(split, TILE_NO_RING) && split.split_k > 1) {
+            size_t tiles = 0, floats = 0;
+            tile_workspace(split, &tiles, &floats);
+            t->st_need += align_up(tiles * split.groups * sizeof(uint32_t)) + align_up(tiles * floats * split.groups * sizeof(float));
+        }
         if (!t->args[i].ws) continue;
+        t->st_need += align_up(o.cnt_bytes) + align_up(o.ws_bytes);
         t->st_cnt_off[i] = t->st_cnt_bytes; t->st_cnt_bytes += align_up(o.cnt_bytes);
         t->st_ws_off[i] = t->st_ws_bytes; t->st_ws_bytes += align_up(o.ws_bytes);
     }
@@ -1975,13 +1991,13 @@ int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *in
     if (s->flags & (MT_SCHED_GRAPH | MT_SCHED_STREAM_GRAPHS | MT_SCHED_PARALLEL_ISSUE))
         return fail(MT_ERR_INVALID_ARG, "graph replay and parallel issue allocate on their first run: not available without allocation");
     HIP_TRY(hipSetDevice(ctx->device));
-    size_t cnt_total = 0, ws_total = 0;
+    size_t cnt_total = 0, need = 0;
     for (int i = 0; i < s->n_tenants; ++i) {
         cnt_total += ctx->tenants[i]->st_cnt_bytes;
-        ws_total += ctx->tenants[i]->st_ws_bytes;
+        need += ctx->tenants[i]->st_need;
     }
-    if (cnt_total + ws_total > (size_t)MT_STATIC_SCRATCH_BYTES)
-        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(cnt_total + ws_total) +
+    if (need > (size_t)MT_STATIC_SCRATCH_BYTES)
+        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(need) +
                                               " bytes, the fixed scratch array holds " + std::to_string((size_t)MT_STATIC_SCRATCH_BYTES));
     void *base = nullptr;
     const int e = static_scratch_address(ctx->device, &base);
