@@ -441,10 +441,11 @@ def report_layers(args):
 
 def _family_of(kernel_name):
     import re
-    m = re.search(r"igemm_kernel<[^,]+, (\d+), (\d+)", kernel_name) or re.match(r"_ZN2mt12igemm_kernelI(?:DF16_|NS_4bf16E)Li(\d+)ELi(\d+)E", kernel_name)
+    m = re.search(r"(igemm|tile|patch)_(?:pair_)?kernel<[^,]+, (\d+), (\d+)", kernel_name) or \
+        re.match(r"_ZN2mt\d+(igemm|tile|patch)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)Li(\d+)ELi(\d+)E", kernel_name)
     if m:
-        return "igemm_%sx%s" % (m.group(1), m.group(2))
-    for key, fam in (("stem_kernel", "stem_rows"), ("rowb_kernel", "igemm_resident_filters"), ("rowp_kernel", "igemm_resident_filters"), ("pconv_kernel", "igemm_patch_64x64"), ("pw_direct_kernel", "igemm_pointwise"), ("gemv_kernel", "gemv"), ("dwconv", "dwconv"), ("gap_kernel", "global_avgpool"),
+        return "igemm_%s%sx%s" % ("patch_" if m.group(1) == "patch" else "", m.group(2), m.group(3))
+    for key, fam in (("stem_kernel", "stem_rows"), ("rowb_kernel", "igemm_resident_filters"), ("rowp_kernel", "igemm_resident_filters"), ("ring_kernel", "igemm_rings"), ("ring_pair_kernel", "igemm_rings"), ("pw_direct_kernel", "igemm_pointwise"), ("gemv_kernel", "gemv"), ("dwconv", "dwconv"), ("gap_kernel", "global_avgpool"),
                      ("pool", "pool"), ("conv_direct", "conv_direct"), ("lrn_kernel", "lrn"), ("add_kernel", "add")):
         if key in kernel_name:
             return fam
