@@ -284,6 +284,8 @@ void LaneDevice::return_signal(hsa_signal_t s) {
 
 // ---- packets --------------------------------------------------------------------------------------
 bool LaneDevice::submit(hsa_queue_t *q, const Packet *p, size_t n) {
+    // one producer at a time: the doorbell has to rise with the packets, whichever thread rings it
+    std::lock_guard<std::mutex> lk(producer_[((uintptr_t)q >> 6) % N_PRODUCERS]);
     while (n > 0) {
         const size_t part = std::min<size_t>(n, q->size / 2);
         const uint64_t at = hsa_queue_add_write_index_relaxed(q, part);

@@ -82,6 +82,10 @@ private:
     double ms_per_tick_ = 0;
     hsa_queue_t *plain_[N_LANES] = {};
     std::vector<hsa_executable_t> code_;
+    // Held while packets are placed and the doorbell is rung.  Two queues may share one: what a queue waits for is always in its
+    // queue already, so the holder never waits for another thread's packets.
+    static constexpr int N_PRODUCERS = 16;
+    std::mutex producer_[N_PRODUCERS];
     std::mutex mu_;                                      // kernels_, idle_signals_, the argument allocator
     std::unordered_map<const void *, std::unique_ptr<KernelCode>> kernels_;
     std::vector<hsa_signal_t> idle_signals_;
