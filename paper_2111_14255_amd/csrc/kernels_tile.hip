@@ -387,6 +387,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     uint32_t xoff[XQ], xmask[XQ];
     int ptap[NP], pch[NP];                                 // tap and channel of each position (TG_TAP: wave-uniform)
     uint32_t xs = (uint32_t)(st0 * KD) * 128u;          // TG_POINT: scalar offset
+    const uint32_t x_end = (uint32_t)a.gemm_k * ES;
 #pragma unroll
     for (int i = 0; i < XQ; ++i) {
         const int q = i * NW + wave, kd = q / (BM / 8), rg = q % (BM / 8);
@@ -436,7 +437,10 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
         for (int i = 0; i < XQ; ++i) {
             const uint32_t dst = base + (uint32_t)(W_BYTES + (i * NW + wave) * 1024);
             if constexpr (MODE == TG_POINT) {
-                load_to_lds(rsrc_x, xoff[i], xs, dst);
+                // Slices of the last stage that lie beyond the reduction (C is not a multiple of KD rows) hold the next pixel's channels:
+                // the filters are zero there, but zero times infinity or NaN is NaN
+                const uint32_t slice = (uint32_t)((i * NW + wave) / (BM / 8) * 128);
+                load_to_lds(rsrc_x, KD == 1 || xs + slice < x_end ? xoff[i] : OUT_OF_RANGE, xs, dst);
             } else {
                 const int pi = KD == 1 ? 0 : i;
                 const uint32_t off = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u ? xoff[i] + toff[pi] : OUT_OF_RANGE;
