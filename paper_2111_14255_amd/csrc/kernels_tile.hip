@@ -999,6 +999,18 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     // long reductions over a wide map that has fewer than 72 tiles of 64 x 64 are always split
     const int M = a.N * a.P * a.Q;
     const int min_split = a.kernel_id == K_IGEMM_64x64 && M > 4096 && a.gemm_k >= 16 * TK && cdiv(M, 64) * cdiv(a.K, 64) < 72 ? 2 : 1;
+    int panels[N_FORMS] = {};                               // of the patch forms; 0: no panel fits the patch
+    bool patch_fits = false;
+    for (int f = 0; patch_ok && f < N_FORMS; ++f) {
+        if (FORMS[f].patch_pixels == 0) continue;
+        panels[f] = patch_panel(a.N, a.P, a.Q, FORMS[f].bm, FORMS[f].patch_pixels, false);
+        patch_fits = patch_fits || panels[f] > 0;
+    }
+    // Layers of K_PCONV's size run on a patch wherever one fits (not on maps of a pixel or two, whose tiles span too many
+    // images): the estimate, fitted to all layers, sometimes puts another tile first there, and it is the slower one.  us,
+    // patch / tile of least estimate: 8 x 28 x 28 128 -> 128 7.6 / 8.7, 56 x 56 128 -> 256 7.5 / 8.7, 112 x 112 64 -> 128 7.8 / 8.1,
+    // 5 x 35 x 35 64 -> 96 6.2 / 6.8, 40 x 7 x 7 64 -> 320 6.2 / 6.7, 60 x 7 x 7 128 -> 256 7.7 / 8.6.
+    if (a.kernel_id == K_PCONV && !patch_fits) a.kernel_id = K_IGEMM_64x64;
     double best = 0;
     int form = -1, split = 1, panel = 0;
     for (int f = 0; f < N_FORMS; ++f) {
@@ -1006,10 +1018,9 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
         const TileCost &c = f32 ? t.single : t.half;
         if (c.start == 0) continue;
         if ((only >= 0 && f != only) || (choice == TILE_NO_RING && t.ring)) continue;
-        if (t.patch_pixels > 0 && !patch_ok) continue;
         if (t.patch_pixels == 0 && a.kernel_id == K_PCONV) continue;
         if (t.bn > 64 && a.K <= t.bn / 2) continue;         // more than half of the tile would be padding
-        const int w = t.patch_pixels > 0 ? patch_panel(a.N, a.P, a.Q, t.bm, t.patch_pixels, false) : 0;
+        const int w = panels[f];
         if (t.patch_pixels > 0 && w == 0) continue;
         const int tiles = pixel_tiles(t, a, w) * cdiv(a.K, t.bn);
         const int units = t.patch_pixels > 0 ? a.C / TK : cdiv(a.gemm_k, row * t.kd);     // what a split cuts
@@ -1023,6 +1034,7 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
             if (form < 0 || us < best) { best = us; form = f; split = s; panel = w; }
         }
     }
+    if (form < 0) return false;
     const TileForm &t = FORMS[form];
     a.form = form;
     a.panel = panel;

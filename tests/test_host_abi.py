@@ -9,7 +9,7 @@ import pytest
 
 from paper_2111_14255_amd import binding as B, api
 from oracle import schedule as S, fold as ofold, ops as oops
-from synth import zoo, weights
+from synth import GraphBuilder, zoo, weights
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 I32 = C.c_int32
@@ -256,6 +256,22 @@ def test_shape_inference_matches_model_tables(name):
     assert flops == 2 * spec.macs()
     assert m.out_features() == spec.out_features
     assert m.arena_bytes() > 0
+
+
+@pytest.mark.parametrize("c,k", [(64, 320), (512, 512), (512, 2048)])
+def test_3x3_layers_on_maps_of_a_few_pixels_have_a_kernel_at_every_batch(c, k):
+    """The taps of a 3x3 layer are read from a patch of input pixels in LDS, which holds the rows around a tile in every image
+    the tile touches: on maps of a pixel or two those of a batch are more than any patch holds."""
+    for h, w in ((1, 1), (1, 2), (2, 1), (2, 2), (1, 3), (3, 1), (1, 7), (7, 1)):
+        for n in (1, 2, 31, 65, 300, 800, 1200, 2048, 5000):
+            for dtype in ("f16", "f32"):
+                g = GraphBuilder("t", dtype, n, h, w, c)
+                g.conv(0, k, 3, pad=1)
+                m = api.Model(g.done())
+                info = m.op_info(0)
+                assert info.grid_blocks > 0 and info.split_k >= 1
+                assert m.arena_bytes() < (1 << 31)
+                m.close()
 
 
 def _model(ops, dtype=B.MT_F16, dims=(1, 8, 8, 8)):
