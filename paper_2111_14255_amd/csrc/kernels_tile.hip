@@ -996,9 +996,6 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     // memory; 288 -> 32 on 4 x 149 x 149 41 / 37; short reductions are bound by their input: 32 -> 16 on 4 x 112 x 112 7.9 / 20)
     if (f32 && a.K <= 32 && a.gemm_k >= 128) return false;
     const bool patch_ok = patch_stageable(a);
-    // long reductions over a wide map that has fewer than 72 tiles of 64 x 64 are always split
-    const int M = a.N * a.P * a.Q;
-    const int min_split = a.kernel_id == K_IGEMM_64x64 && M > 4096 && a.gemm_k >= 16 * TK && cdiv(M, 64) * cdiv(a.K, 64) < 72 ? 2 : 1;
     int panels[N_FORMS] = {};                               // of the patch forms; 0: no panel fits the patch
     bool patch_fits = false;
     for (int f = 0; patch_ok && f < N_FORMS; ++f) {
@@ -1030,7 +1027,6 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
             if (cdiv(units, per) != s) continue;            // an empty split
             const int ns = t.patch_pixels > 0 ? per * 9 / t.kd : cdiv(per * t.kd, t.rows), n = cdiv(tiles * s, UNITS);
             const double us = c.start + c.wave * (n - 1) + ns * (c.stage + c.crowd * (n - 1)) + (s > 1 ? c.split_once + c.split_each * s : 0.0);
-            if (s < min_split) continue;
             if (form < 0 || us < best) { best = us; form = f; split = s; panel = w; }
         }
     }

@@ -51,7 +51,7 @@ CONV_CASES = [
     ("ig64_concat_unaligned", dict(n=1, h=8, w=8, c=16, k=10, r=3, pad=1, coff=3, ctot=18), IG64),
     ("ig64_concat_aligned", dict(n=1, h=8, w=8, c=16, k=32, r=1, coff=64, ctot=128), IG64),
     ("ig16_conv_tiny_map", dict(n=2, h=4, w=4, c=64, k=70, r=3, pad=1), IG16),
-    ("ig64_splitk_wide", dict(n=1, h=66, w=66, c=128, k=64, r=3, pad=1, res=True), IG64),
+    ("ig64_splitk_wide", dict(n=1, h=66, w=66, c=72, k=24, r=5, pad=2, res=True), IG64),
     ("gemv_1x1_m1", dict(n=1, h=1, w=1, c=1280, k=1000, r=1, act="none"), GEMV),
     ("gemv_1x1_m5_res", dict(n=5, h=1, w=1, c=520, k=77, r=1, res=True), GEMV),
     ("pw_1x1_m12", dict(n=12, h=1, w=1, c=512, k=100, r=1), PW),
