@@ -1001,12 +1001,13 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     for (int f = 0; patch_ok && f < N_FORMS; ++f) {
         if (FORMS[f].patch_pixels == 0) continue;
         panels[f] = patch_panel(a.N, a.P, a.Q, FORMS[f].bm, FORMS[f].patch_pixels, false);
-        patch_fits = patch_fits || panels[f] > 0;
+        patch_fits = patch_fits || (panels[f] > 0 && FORMS[f].bm >= 64);
     }
-    // Layers of K_PCONV's size run on a patch wherever one fits (not on maps of a pixel or two, whose tiles span too many
-    // images): the estimate, fitted to all layers, sometimes puts another tile first there, and it is the slower one.  us,
-    // patch / tile of least estimate: 8 x 28 x 28 128 -> 128 7.6 / 8.7, 56 x 56 128 -> 256 7.5 / 8.7, 112 x 112 64 -> 128 7.8 / 8.1,
-    // 5 x 35 x 35 64 -> 96 6.2 / 6.8, 40 x 7 x 7 64 -> 320 6.2 / 6.7, 60 x 7 x 7 128 -> 256 7.7 / 8.6.
+    // Layers of K_PCONV's size run on a patch wherever one of 64 pixels or more fits: the estimate, fitted to all layers,
+    // sometimes puts another tile first there, and it is the slower one.  us, patch / tile of least estimate: 8 x 28 x 28
+    // 128 -> 128 7.6 / 8.7, 56 x 56 128 -> 256 7.5 / 8.7, 112 x 112 64 -> 128 7.8 / 8.1, 5 x 35 x 35 64 -> 96 6.2 / 6.8, 40 x 7 x 7
+    // 64 -> 320 6.2 / 6.7, 60 x 7 x 7 128 -> 256 7.7 / 8.6.  On maps of a few pixels a tile touches more images than such a patch
+    // holds, and the estimate chooses among all forms (700 x 2 x 2, 512 -> 512: 64 x 32 patch 33.0, 128 x 64 tile 27.8).
     if (a.kernel_id == K_PCONV && !patch_fits) a.kernel_id = K_IGEMM_64x64;
     double best = 0;
     int form = -1, split = 1, panel = 0;

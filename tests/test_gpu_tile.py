@@ -40,6 +40,7 @@ CASES = [
     ("patch_128x256", 2, 112, 112, 64, 256, 3, 1, 1),
     ("patch_128x256_split3_tiles_span_images", 6, 28, 28, 384, 512, 3, 1, 1),
     ("one_pixel_maps_no_patch_holds_the_batch", 300, 1, 1, 512, 2048, 3, 1, 1),
+    ("2x2_maps_only_a_narrow_patch_fits", 700, 2, 2, 256, 512, 3, 1, 1),
     ("two_pixel_maps_no_patch_holds_the_batch", 800, 1, 2, 256, 512, 3, 1, 1),
 ]
 ACT = {"none": lambda v: v, "relu": torch.relu, "relu6": lambda v: v.clamp(0, 6)}
