@@ -45,14 +45,13 @@ def time_schedule(ctx, torch, sched, inputs, outputs, warmup, steps):
 
 
 def kernel_rooflines(ctx, inputs, outputs, dtype, repeats):
-    """Per kernel family: launches, total time, algorithmic flops and bytes, from back-to-back timed launches."""
-    from paper_2111_14255_amd import binding as B
+    """Per kernel (its name as mt_op_form gives it): launches, total time, algorithmic flops and bytes, from back-to-back timed launches."""
     fam = {}
     for t in range(ctx.num_tenants()):
         ms = ctx.profile_ops(t, inputs[t], outputs[t], repeats)
         for i, d in enumerate(ms):
             info = ctx.op_info(t, i)
-            name = B.load().mt_kernel_name(info.kernel_id).decode()
+            name = ctx.op_form(t, i).name.decode()
             f = fam.setdefault(name, {"launches": 0, "ms": 0.0, "flops": 0.0, "bytes": 0.0})
             f["launches"] += 1
             f["ms"] += d

@@ -110,12 +110,24 @@ typedef struct mt_op_info {
     int32_t kind;
     int32_t in_h, in_w, in_c;
     int32_t out_h, out_w, out_c;     /* channels written */
-    int32_t kernel_id;               /* which device kernel family and tile runs it (see mt_kernel_name) */
-    int32_t split_k;                 /* ranges the reduction of an output is cut into, over workgroups and over waves that deal it out (1 = none) */
+    int32_t kernel_id;               /* kernel family (see mt_kernel_name); for an implicit GEMM its size class, see mt_op_form for the kernel that runs it */
+    int32_t split_k;                 /* workgroups that share the reduction of an output tile and meet in memory (1 = none) */
     int32_t grid_blocks;             /* workgroups launched */
     double flops;                    /* 2 * multiply-accumulates, whole batch */
     double bytes;                    /* algorithmic traffic: inputs + weights + bias (+ residual) read once, output written once */
 } mt_op_info;
+
+/* The kernel an operator runs on and how it divides the work. */
+typedef struct mt_op_form {
+    char name[32];                   /* tile_64x64, ring_16x16, patch_128x64, elements_64x16 (channels x pixels of a workgroup's output tile) or the kernel family's name */
+    int32_t tile_channels;           /* output channels and pixels of a workgroup's tile; 0: the kernel has no such tiles */
+    int32_t tile_pixels;
+    int32_t stage_slices;            /* 128-byte slices of the reduction (64 elements, fp32: 32) a workgroup loads per stage; 0: not staged in slices */
+    int32_t split_k;                 /* as in mt_op_info */
+    int32_t ring_waves;              /* waves of a workgroup that deal the reduction of its tile out between them and meet in LDS (rings); 0: no ring */
+    int32_t panel_columns;           /* 3x3 layers whose input is staged as a patch: columns of the map a patch covers; 0: no patch */
+    int64_t workspace_bytes;         /* device memory for partial sums and arrival counters of a split reduction */
+} mt_op_form;
 
 typedef struct mt_device_info {
     int32_t cu_count;
@@ -219,6 +231,7 @@ int32_t mt_model_end(mt_model *m);
 int32_t mt_model_destroy(mt_model *m);
 int32_t mt_model_num_ops(const mt_model *m, int32_t *out);
 int32_t mt_model_op_info(const mt_model *m, int32_t op_index, mt_op_info *out);
+int32_t mt_model_op_form(const mt_model *m, int32_t op_index, mt_op_form *out);
 int32_t mt_model_out_features(const mt_model *m, int64_t *out);
 /* w: host, storage type, layout as above, exactly w_bytes bytes; bias: host fp32 [n_bias] or NULL (zeros). */
 int32_t mt_model_set_weights(mt_model *m, int32_t op_index, const void *w, size_t w_bytes,
@@ -246,6 +259,7 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
 int32_t mt_num_tenants(const mt_ctx *ctx, int32_t *out);
 int32_t mt_tenant_num_ops(const mt_ctx *ctx, int32_t tenant, int32_t *out);
 int32_t mt_tenant_op_info(const mt_ctx *ctx, int32_t tenant, int32_t op_index, mt_op_info *out);
+int32_t mt_tenant_op_form(const mt_ctx *ctx, int32_t tenant, int32_t op_index, mt_op_form *out);
 /* Debug aid: copies tensor `tensor_id` of a tenant (as left by the last run) to host memory. */
 int32_t mt_tenant_read_tensor(mt_ctx *ctx, int32_t tenant, int32_t tensor_id, void *host_dst, size_t bytes);
 

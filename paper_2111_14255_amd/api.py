@@ -123,6 +123,11 @@ class Model:
         B.check(B.load().mt_model_op_info(self.h, i, C.byref(info)))
         return info
 
+    def op_form(self, i):
+        form = B.mt_op_form()
+        B.check(B.load().mt_model_op_form(self.h, i, C.byref(form)))
+        return form
+
     def out_features(self):
         n = C.c_int64()
         B.check(B.load().mt_model_out_features(self.h, C.byref(n)))
@@ -205,6 +210,11 @@ class Context:
         info = B.mt_op_info()
         B.check(self.lib.mt_tenant_op_info(self.h, tenant, i, C.byref(info)))
         return info
+
+    def op_form(self, tenant, i):
+        form = B.mt_op_form()
+        B.check(self.lib.mt_tenant_op_form(self.h, tenant, i, C.byref(form)))
+        return form
 
     def release_idle_streams(self):
         B.check(self.lib.mt_release_idle_streams(self.h))

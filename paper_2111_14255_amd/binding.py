@@ -53,6 +53,12 @@ class mt_op_info(C.Structure):
         ("flops", C.c_double), ("bytes", C.c_double)]
 
 
+class mt_op_form(C.Structure):
+    _fields_ = [("name", C.c_char * 32)] + [(n, C.c_int32) for n in (
+        "tile_channels", "tile_pixels", "stage_slices", "split_k", "ring_waves", "panel_columns")] + [
+        ("workspace_bytes", C.c_int64)]
+
+
 class mt_device_info(C.Structure):
     _fields_ = [("cu_count", C.c_int32), ("wavefront_size", C.c_int32), ("lds_bytes_per_block", C.c_int32),
                 ("clock_khz", C.c_int32), ("l2_bytes", C.c_int64), ("hbm_bytes", C.c_int64),
@@ -99,6 +105,7 @@ SIGNATURES = {
     "mt_model_destroy": (_i32, [_vp]),
     "mt_model_num_ops": (_i32, [_vp, _pi32]),
     "mt_model_op_info": (_i32, [_vp, _i32, C.POINTER(mt_op_info)]),
+    "mt_model_op_form": (_i32, [_vp, _i32, C.POINTER(mt_op_form)]),
     "mt_model_out_features": (_i32, [_vp, C.POINTER(_i64)]),
     "mt_model_set_weights": (_i32, [_vp, _i32, _vp, _sz, _pf, _sz]),
     "mt_model_arena_bytes": (_i32, [_vp, C.POINTER(_sz)]),
@@ -108,6 +115,7 @@ SIGNATURES = {
     "mt_num_tenants": (_i32, [_vp, _pi32]),
     "mt_tenant_num_ops": (_i32, [_vp, _i32, _pi32]),
     "mt_tenant_op_info": (_i32, [_vp, _i32, _i32, C.POINTER(mt_op_info)]),
+    "mt_tenant_op_form": (_i32, [_vp, _i32, _i32, C.POINTER(mt_op_form)]),
     "mt_tenant_read_tensor": (_i32, [_vp, _i32, _i32, _vp, _sz]),
     "mt_schedule_create": (_i32, [_vp, _i32, _i32, _pi32, _pi32, _pi32, _i32, _i32, C.POINTER(_vp)]),
     "mt_release_idle_streams": (_i32, [_vp]),

@@ -166,6 +166,7 @@ enum TileChoice {
 bool plan_tile(OpArgs &a, TileChoice choice);
 int reduction_ranges(const OpArgs &a);   // ranges the reduction of an output is cut into, over workgroups and over the waves of a ring
 bool tile_is_narrow(const OpArgs &a);
+void describe_tile(const OpArgs &a, mt_op_form *out);    // all but the workspace
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);
 bool plan_tile_pooled(OpArgs &a);
 int launch_tile(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
@@ -175,6 +176,7 @@ int launch_rowb(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int
 // fp32 convolution on the matrix cores: the tiling for an M x K x gemm_k problem with C input channels (0: none, the layer
 // runs on one thread per output), its workgroups, its launcher.
 int dconv_f32_plan(int M, int K, int gemm_k, int C);
+void dconv_f32_tile(int form, int *channels, int *pixels);
 int dconv_f32_grid(int form, int M, int K);
 int launch_dconv_f32(const OpArgs &a, void *stream);
 

@@ -287,6 +287,10 @@ int dconv_f32_plan(int M, int K, int gemm_k, int C) {
     }
     return pick;
 }
+void dconv_f32_tile(int form, int *channels, int *pixels) {
+    *channels = DC_F32[form - 1].bn;
+    *pixels = DC_F32[form - 1].bm;
+}
 int dconv_f32_grid(int form, int M, int K) {
     const DcTile &t = DC_F32[form - 1];
     return (((M + t.bm - 1) / t.bm) * ((K + t.bn - 1) / t.bn) + 7) / 8 * 8;

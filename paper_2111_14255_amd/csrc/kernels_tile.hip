@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
 #include <type_traits>
 #include <utility>
 
@@ -1053,6 +1054,16 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
 bool tile_is_narrow(const OpArgs &a) { return a.form == FORM_64x16 && a.split_k == 1; }
 
 int reduction_ranges(const OpArgs &a) { return a.split_k * (a.form >= 0 ? std::max(1, FORMS[a.form].ring) : 1); }
+
+void describe_tile(const OpArgs &a, mt_op_form *out) {
+    const TileForm &t = FORMS[a.form];
+    std::snprintf(out->name, sizeof(out->name), "%s_%dx%d", t.ring ? "ring" : t.patch_pixels ? "patch" : "tile", t.bn, t.bm);
+    out->tile_channels = t.bn;
+    out->tile_pixels = t.bm;
+    out->stage_slices = t.kd;
+    out->ring_waves = t.ring;
+    out->panel_columns = a.panel;
+}
 
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats) {
     const TileForm &t = FORMS[a.form];

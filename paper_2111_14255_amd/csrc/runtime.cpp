@@ -144,11 +144,17 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
     p.grid_x = cdiv(total, 8) * 8;
 }
 
+// Output tile of the register-staged kernel (element-wise gather).
+void element_tile(const OpArgs &p, int *bn, int *bm) {
+    *bn = p.kernel_id == K_IGEMM_64x16 || p.kernel_id == K_IGEMM_64x64 ? 64 : 128;
+    *bm = p.kernel_id == K_IGEMM_64x16 ? 16 : p.kernel_id == K_IGEMM_128x128 ? 128 : 64;
+}
+
 // Split reduction of one launch: output tiles and floats of workspace per tile.
 void split_workspace(const OpArgs &p, size_t *tiles, size_t *floats) {
     if (p.form >= 0) return tile_workspace(p, tiles, floats);
-    const int bn = p.kernel_id == K_IGEMM_64x16 || p.kernel_id == K_IGEMM_64x64 ? 64 : 128;
-    const int bm = p.kernel_id == K_IGEMM_64x16 ? 16 : p.kernel_id == K_IGEMM_128x128 ? 128 : 64;
+    int bn = 0, bm = 0;
+    element_tile(p, &bn, &bm);
     *tiles = (size_t)((p.N * p.P * p.Q + bm - 1) / bm) * (p.n_pad / bn);
     *floats = (size_t)p.split_k * bn * bm;
 }
@@ -380,11 +386,31 @@ void fill_info(const mt_model *m, const OpRec &o, mt_op_info *out) {
     out->in_h = o.in_h; out->in_w = o.in_w; out->in_c = o.in_c;
     out->out_h = o.out_h; out->out_w = o.out_w; out->out_c = o.out_c;
     out->kernel_id = o.plan.kernel_id;
-    out->split_k = reduction_ranges(o.plan);
+    out->split_k = o.plan.split_k;
     out->grid_blocks = o.plan.grid_x ? o.plan.grid_x : 0;
     out->flops = o.flops;
     out->bytes = o.bytes;
     (void)m;
+}
+
+void fill_form(const OpRec &o, mt_op_form *out) {
+    const OpArgs &p = o.plan;
+    std::memset(out, 0, sizeof(*out));
+    out->split_k = p.split_k;
+    out->workspace_bytes = (int64_t)(o.ws_bytes + o.cnt_bytes);
+    const bool elements = p.kernel_id == K_IGEMM_64x16 || p.kernel_id == K_IGEMM_64x64 || p.kernel_id == K_IGEMM_128x64 || p.kernel_id == K_IGEMM_128x128;
+    if (p.form >= 0) {
+        describe_tile(p, out);
+    } else if (elements) {
+        element_tile(p, &out->tile_channels, &out->tile_pixels);
+        out->stage_slices = 1;
+        std::snprintf(out->name, sizeof(out->name), "elements_%dx%d", out->tile_channels, out->tile_pixels);
+    } else if (p.kernel_id == K_CONV_DIRECT && p.wk > 0) {
+        dconv_f32_tile(p.wk, &out->tile_channels, &out->tile_pixels);
+        std::snprintf(out->name, sizeof(out->name), "registers_%dx%d", out->tile_channels, out->tile_pixels);
+    } else {
+        std::snprintf(out->name, sizeof(out->name), "%s", mt_kernel_name(p.kernel_id));
+    }
 }
 
 }  // namespace
@@ -1459,6 +1485,14 @@ int32_t mt_model_op_info(const mt_model *m, int32_t i, mt_op_info *out) {
     return MT_OK;
 }
 
+int32_t mt_model_op_form(const mt_model *m, int32_t i, mt_op_form *out) {
+    if (!m || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
+    if (!m->finalized) return fail(MT_ERR_NOT_FINALIZED, "model is not finalised");
+    if (i < 0 || i >= (int)m->ops.size()) return fail(MT_ERR_INVALID_ARG, "operator index out of range");
+    fill_form(m->ops[i], out);
+    return MT_OK;
+}
+
 int32_t mt_model_out_features(const mt_model *m, int64_t *out) {
     if (!m || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     if (!m->finalized) return fail(MT_ERR_NOT_FINALIZED, "model is not finalised");
@@ -1767,6 +1801,12 @@ int32_t mt_tenant_op_info(const mt_ctx *ctx, int32_t tenant, int32_t i, mt_op_in
     if (!ctx || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     if (tenant < 0 || tenant >= (int)ctx->tenants.size()) return fail(MT_ERR_INVALID_ARG, "no such tenant");
     return mt_model_op_info(&ctx->tenants[tenant]->model, i, out);
+}
+
+int32_t mt_tenant_op_form(const mt_ctx *ctx, int32_t tenant, int32_t i, mt_op_form *out) {
+    if (!ctx || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
+    if (tenant < 0 || tenant >= (int)ctx->tenants.size()) return fail(MT_ERR_INVALID_ARG, "no such tenant");
+    return mt_model_op_form(&ctx->tenants[tenant]->model, i, out);
 }
 
 int32_t mt_tenant_read_tensor(mt_ctx *ctx, int32_t tenant, int32_t tensor_id, void *host_dst, size_t bytes) {

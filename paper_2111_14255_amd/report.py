@@ -419,9 +419,10 @@ def report_layers(args):
         K = op.r * op.s * (info.in_c // max(1, op.groups)) if op.kind in ("conv", "fc") else op.r * op.s
         us = d * 1e3
         bound = max(info.flops / 2.5e15, info.bytes / 8e12) * 1e6
-        kn = B.load().mt_kernel_name(info.kernel_id).decode()
+        form = ctx.op_form(t, i)
+        kn = form.name.decode()
         print("| %d | %s | %d | %d | %d | %dx%d s%d | %s | %d | %d | %.2f | %.2f | %.3f | %.1f | %.0f |" % (
-            i, op.kind, M, info.out_c, K, op.r, op.s, op.stride_h, kn, info.split_k, info.grid_blocks, us, bound, bound / us,
+            i, op.kind, M, info.out_c, K, op.r, op.s, op.stride_h, kn + (", %d waves" % form.ring_waves if form.ring_waves else ""), info.split_k, info.grid_blocks, us, bound, bound / us,
             info.flops / (d * 1e-3) / 1e12, info.bytes / (d * 1e-3) / 1e9))
         tot += us
         totb += bound
@@ -440,12 +441,19 @@ def report_layers(args):
 
 
 def _family_of(kernel_name):
+    """The name mt_op_form gives a kernel, from its name in a trace (demangled or not)."""
     import re
-    m = re.search(r"(igemm|tile|patch)_(?:pair_)?kernel<[^,]+, (\d+), (\d+)", kernel_name) or \
-        re.match(r"_ZN2mt\d+(igemm|tile|patch)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)Li(\d+)ELi(\d+)E", kernel_name)
+    m = re.search(r"(igemm|tile|patch|ring|dconv)_(?:pair_)?kernel<[^,]+, ([\d, ]+)", kernel_name) or \
+        re.match(r"_ZN2mt\d+(igemm|tile|patch|ring|dconv)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)((?:Li\d+E)+)", kernel_name)
     if m:
-        return "igemm_%s%sx%s" % ("patch_" if m.group(1) == "patch" else "", m.group(2), m.group(3))
-    for key, fam in (("stem_kernel", "stem_rows"), ("rowb_kernel", "igemm_resident_filters"), ("rowp_kernel", "igemm_resident_filters"), ("ring_kernel", "igemm_rings"), ("ring_pair_kernel", "igemm_rings"), ("pw_direct_kernel", "igemm_pointwise"), ("gemv_kernel", "gemv"), ("dwconv", "dwconv"), ("gap_kernel", "global_avgpool"),
+        kind, p = m.group(1), [int(v) for v in re.findall(r"\d+", m.group(2))]
+        if kind == "ring":
+            return "ring_%dx16" % p[0]
+        if kind == "dconv":                       # 16 x 16 pieces of a wave, waves over the tile
+            return "registers_%dx%d" % (16 * p[0] * p[2], 16 * p[1] * p[3])
+        return "%s_%dx%d" % ("elements" if kind == "igemm" else kind, p[0], p[1])
+    for key, fam in (("stem_kernel", "stem_rows"), ("rowb_kernel", "igemm_resident_filters"), ("rowp_kernel", "igemm_resident_filters"),
+                     ("pw_direct_kernel", "igemm_pointwise"), ("gemv_kernel", "gemv"), ("dwconv", "dwconv"), ("gap_kernel", "global_avgpool"),
                      ("pool", "pool"), ("conv_direct", "conv_direct"), ("lrn_kernel", "lrn"), ("add_kernel", "add")):
         if key in kernel_name:
             return fam

@@ -98,8 +98,8 @@ def test_coissued_split_layers_in_the_fixed_scratch_array():
     # both tenants' layers are split along the reduction: the pair's partial sums and arrival counters live side by
     # side, in the arenas (mt_run) or in the library's fixed array (mt_run_static_scratch)
     def net():
-        g = GraphBuilder("small_split", "f16", 1, 7, 7, 256)
-        t = g.conv(0, 256, 3, pad=1, bn=True)
+        g = GraphBuilder("small_split", "f16", 1, 4, 4, 1024)
+        t = g.conv(0, 1024, 3, pad=1, bn=True)
         t = g.conv(t, 512, 3, pad=1, bn=True)
         t = g.gap(t)
         g.fc(t, 100)
@@ -108,7 +108,7 @@ def test_coissued_split_layers_in_the_fixed_scratch_array():
     mix = Mix([net(), net(), net()], seed=924)
     try:
         ctx = mix.ctx
-        assert any(ctx.op_info(0, i).split_k > 1 for i in range(ctx.lens()[0]))
+        assert all(ctx.op_form(t, i).split_k > 1 and ctx.op_form(t, i).workspace_bytes > 0 for t in range(3) for i in range(2))
         s = ctx.schedule([[], [], []], 1, concurrency=[1], flags=CO, label="co-issue")
         fused = compare(mix, ctx.sequential(), [s], "f16")
         assert fused[0] == 2 * ctx.lens()[0]              # one group of three: two of every three operators

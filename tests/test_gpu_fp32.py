@@ -1,5 +1,7 @@
 """fp32 convolution and fully connected layers on the matrix cores: every tiling, every way to gather an im2col row, ragged
 channel and pixel counts, groups, residual and channel offsets, against the CPU oracle."""
+import re
+
 import pytest
 
 from synth import GraphBuilder
@@ -8,24 +10,33 @@ from gpu_harness import Mix, assert_close
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # name, n, h, w, c, k, window, stride, pad, groups
-    ("64x64_tiles_uniform", 4, 57, 59, 64, 70, 3, 1, 1, 1),
-    ("64x64_tiles_elements_7x7", 2, 201, 190, 3, 64, 7, 2, 3, 1),
-    ("32x32_tiles_uniform", 1, 57, 55, 64, 100, 3, 1, 1, 1),
-    ("32x32_tiles_pieces_c20", 1, 60, 61, 20, 96, 3, 1, 1, 1),
-    ("32x16_tiles_uniform", 1, 29, 27, 128, 128, 3, 1, 1, 1),
-    ("16x16_tiles_uniform", 1, 7, 7, 96, 72, 3, 1, 1, 1),
-    ("16x16_tiles_pointwise_c144", 1, 14, 14, 144, 24, 1, 1, 0, 1),
-    ("pieces_c4_step_over_four_taps", 3, 10, 11, 4, 9, 3, 1, 1, 1),
-    ("pieces_c12_stride2", 2, 15, 13, 12, 33, 5, 2, 2, 1),
-    ("elements_c3_11x11_stride4", 1, 59, 59, 3, 96, 11, 4, 0, 1),
-    ("elements_c1", 2, 9, 9, 1, 5, 3, 1, 1, 1),
-    ("elements_c33_asymmetric", 1, 9, 21, 33, 17, (1, 7), 1, (0, 3), 1),
-    ("table_too_small_c255", 1, 6, 6, 255, 8, 3, 1, 1, 1),
-    ("groups_of_16", 2, 12, 12, 48, 96, 3, 1, 1, 3),
-    ("groups_of_4", 2, 12, 12, 8, 20, 3, 1, 1, 2),
-    ("groups_of_3", 1, 12, 12, 9, 12, 3, 1, 1, 3),
-    ("one_pixel_one_channel", 1, 1, 1, 16, 1, 1, 1, 0, 1),
+    # name (the form the sizes lead to first), n, h, w, c, k, window, stride, pad, groups
+    ("tile_32x32_uniform", 4, 57, 59, 64, 70, 3, 1, 1, 1),
+    ("registers_32x32_elements_7x7", 2, 201, 190, 3, 64, 7, 2, 3, 1),
+    ("tile_64x32_uniform", 1, 57, 55, 64, 100, 3, 1, 1, 1),
+    ("tile_64x32_pieces_c20", 1, 60, 61, 20, 96, 3, 1, 1, 1),
+    ("ring_32x16_uniform", 1, 29, 27, 128, 128, 3, 1, 1, 1),
+    ("ring_16x16_uniform", 1, 7, 7, 96, 72, 3, 1, 1, 1),
+    ("registers_16x16_pointwise_c144", 1, 14, 14, 144, 24, 1, 1, 0, 1),
+    ("ring_16x16_pieces_c4_row_over_eight_taps", 3, 10, 11, 4, 9, 3, 1, 1, 1),
+    ("ring_16x16_pieces_c12_stride2", 2, 15, 13, 12, 33, 5, 2, 2, 1),
+    ("registers_16x16_elements_c3_11x11_stride4", 1, 59, 59, 3, 96, 11, 4, 0, 1),
+    ("registers_64x64_elements_c1", 2, 9, 9, 1, 5, 3, 1, 1, 1),
+    ("registers_16x16_elements_c33_asymmetric", 1, 9, 21, 33, 17, (1, 7), 1, (0, 3), 1),
+    ("conv_direct_table_too_small_c255", 1, 6, 6, 255, 8, 3, 1, 1, 1),
+    ("registers_16x16_groups_of_16", 2, 12, 12, 48, 96, 3, 1, 1, 3),
+    ("ring_16x16_groups_of_4", 2, 12, 12, 8, 20, 3, 1, 1, 2),
+    ("registers_16x16_groups_of_3", 1, 12, 12, 9, 12, 3, 1, 1, 3),
+    ("tile_64x64_uniform", 4, 57, 57, 32, 70, 3, 1, 1, 1),
+    ("tile_64x64_pieces_c20", 2, 57, 57, 20, 70, 3, 1, 1, 1),
+    ("tile_64x16_uniform", 1, 41, 41, 32, 70, 3, 1, 1, 1),
+    ("registers_32x32_uniform", 2, 57, 57, 16, 8, 3, 1, 1, 1),
+    ("registers_32x32_pieces_c20", 2, 57, 57, 20, 8, 3, 1, 1, 1),
+    ("registers_32x16_uniform", 1, 57, 57, 16, 24, 3, 1, 1, 1),
+    ("registers_32x16_pieces_c20", 4, 28, 28, 20, 24, 3, 1, 1, 1),
+    ("registers_32x16_elements_c3", 1, 29, 29, 3, 70, 3, 1, 1, 1),
+    ("registers_16x16_pieces_c20", 1, 7, 7, 20, 8, 3, 1, 1, 1),
+    ("gemv_one_pixel_one_channel", 1, 1, 1, 16, 1, 1, 1, 0, 1),
 ]
 
 
@@ -41,6 +52,7 @@ def test_fp32_convolution(name, n, h, w, c, k, win, stride, pad, groups):
     print("case", name, flush=True)
     mix = Mix([spec], seed=41)
     try:
+        assert mix.ctx.op_form(0, 0).name.decode() == re.match(r"(tile|ring|registers)_\d+x\d+|conv_direct|gemv", name).group(0)
         got, _ = mix.run(mix.ctx.sequential())
         assert_close(got[0], mix.oracle()[0], "f32", name)
     finally:

@@ -15,24 +15,24 @@ from paper_2111_14255_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # name, n, h, w, c, k, window, stride, pad, groups, ranges the reduction is cut into (16-bit types, fp32; None: any)
-    ("16x16_tap_full_rings", 1, 14, 14, 256, 256, 3, 1, 1, 1, 8, 8),
-    ("16x16_tap_ragged_pixels_span_images", 3, 9, 7, 128, 72, 3, 1, 1, 1, 8, None),
-    ("16x16_point_ragged", 1, 15, 13, 1024, 264, 1, 1, 0, 1, 8, 8),
-    ("16x16_chunk_c72", 1, 13, 13, 72, 200, 3, 1, 1, 1, None, 8),
-    ("16x16_chunk_c200_unaligned_channels", 1, 10, 10, 200, 67, 3, 1, 1, 1, 8, None),
-    ("16x16_216_rows", 1, 5, 5, 1536, 512, 3, 1, 1, 1, 8, 8),
-    ("16x16_1x7", 1, 17, 17, 192, 192, (1, 7), 1, (0, 3), 1, 8, None),
-    ("16x16_stride2", 1, 28, 28, 256, 264, 3, 2, 1, 1, 8, 8),
-    ("32x16_tap_ragged", 1, 29, 27, 128, 136, 3, 1, 1, 1, 4, 4),
-    ("32x16_many_rows", 1, 14, 14, 512, 512, 3, 1, 1, 1, 4, 4),
-    ("four_waves_point", 1, 7, 7, 960, 160, 1, 1, 0, 1, 4, 8),
-    ("four_waves_uneven_rows_c264", 1, 4, 4, 264, 40, 1, 1, 0, 1, 4, None),
-    ("four_waves_short_reduction", 1, 17, 17, 64, 100, 3, 1, 1, 1, 4, 4),
-    ("64x64_tiles", 2, 60, 61, 64, 136, 3, 1, 1, 1, None, None),
-    ("64x32_tiles_chunk_c20", 2, 41, 40, 40, 132, 3, 1, 1, 1, None, None),
-    ("groups_of_96", 2, 13, 13, 192, 128, 3, 1, 1, 2, None, None),
-    ("channels_of_one_output_tile", 1, 6, 6, 512, 12, 3, 1, 1, 1, 8, None),
+    # name, n, h, w, c, k, window, stride, pad, groups, form of the 16-bit types and of fp32 (a ring's with its waves)
+    ("16x16_tap_full_rings", 1, 14, 14, 256, 256, 3, 1, 1, 1, "ring_16x16/8", "ring_16x16/8"),
+    ("16x16_tap_ragged_pixels_span_images", 3, 9, 7, 128, 72, 3, 1, 1, 1, "ring_16x16/8", "ring_16x16/4"),
+    ("16x16_point_ragged", 1, 15, 13, 1024, 264, 1, 1, 0, 1, "ring_16x16/8", "ring_16x16/8"),
+    ("16x16_chunk_c72", 1, 13, 13, 72, 200, 3, 1, 1, 1, "ring_16x16/4", "ring_16x16/8"),
+    ("16x16_chunk_c200_unaligned_channels", 1, 10, 10, 200, 67, 3, 1, 1, 1, "ring_16x16/8", "ring_16x16/8"),
+    ("216_rows", 1, 5, 5, 1536, 512, 3, 1, 1, 1, "tile_64x16", "ring_16x16/8"),
+    ("16x16_1x7", 1, 17, 17, 192, 192, (1, 7), 1, (0, 3), 1, "ring_16x16/8", "ring_16x16/4"),
+    ("16x16_stride2", 1, 28, 28, 256, 264, 3, 2, 1, 1, "ring_16x16/8", "ring_16x16/8"),
+    ("32x16_tap_ragged", 1, 29, 27, 128, 136, 3, 1, 1, 1, "ring_32x16/4", "ring_32x16/4"),
+    ("32x16_many_rows", 1, 14, 14, 512, 512, 3, 1, 1, 1, "ring_32x16/4", "ring_32x16/4"),
+    ("four_waves_point", 1, 7, 7, 960, 160, 1, 1, 0, 1, "ring_16x16/4", "ring_16x16/8"),
+    ("four_waves_uneven_rows_c264", 1, 4, 4, 264, 40, 1, 1, 0, 1, "ring_16x16/4", "ring_16x16/4"),
+    ("four_waves_short_reduction", 1, 17, 17, 64, 100, 3, 1, 1, 1, "ring_16x16/4", "ring_16x16/4"),
+    ("wide_map", 2, 60, 61, 64, 136, 3, 1, 1, 1, "patch_128x64", "tile_64x32"),
+    ("chunk_c40", 2, 41, 40, 40, 132, 3, 1, 1, 1, "tile_64x64", "tile_64x64"),
+    ("groups_of_96", 2, 13, 13, 192, 128, 3, 1, 1, 2, "ring_16x16/8", "ring_16x16/4"),
+    ("channels_of_one_output_tile", 1, 6, 6, 512, 12, 3, 1, 1, 1, "ring_16x16/8", "registers_16x16"),
 ]
 ACT = {"relu": torch.relu, "relu6": lambda v: v.clamp(0, 6), "none": lambda v: v}
 
@@ -44,8 +44,8 @@ def conv_ref(x, p, stride, pad, groups):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
-@pytest.mark.parametrize("name,n,h,w,c,k,win,stride,pad,groups,ranges16,ranges32", CASES, ids=[c[0] for c in CASES])
-def test_ring_and_fp32_tiles(name, n, h, w, c, k, win, stride, pad, groups, ranges16, ranges32, dtype):
+@pytest.mark.parametrize("name,n,h,w,c,k,win,stride,pad,groups,form16,form32", CASES, ids=[c[0] for c in CASES])
+def test_ring_and_fp32_tiles(name, n, h, w, c, k, win, stride, pad, groups, form16, form32, dtype):
     g = GraphBuilder("t", dtype, n, h, w, c)
     a = g.conv(0, k, win, stride, pad, act="relu6", bn=True, groups=groups)
     d = g.new_tensor()                                   # the same convolution with a residual, written at a channel offset
@@ -56,9 +56,8 @@ def test_ring_and_fp32_tiles(name, n, h, w, c, k, win, stride, pad, groups, rang
     print("case", name, dtype, flush=True)
     mix = Mix([spec], seed=47)
     try:
-        want = ranges32 if dtype == "f32" else ranges16
-        if want is not None:
-            assert mix.ctx.op_info(0, 0).split_k == want
+        form = mix.ctx.op_form(0, 0)
+        assert form.name.decode() + ("/%d" % form.ring_waves if form.ring_waves else "") == (form32 if dtype == "f32" else form16)
         x = oops.round_array(mix.x[0], dtype)
         p = OF.prepare_params(spec, mix.raw[0])
         t0 = oops.round_array(ACT["relu6"](conv_ref(x, p[0], stride, pad, groups)).float().contiguous().numpy(), dtype)
@@ -75,7 +74,7 @@ def test_ring_and_fp32_tiles(name, n, h, w, c, k, win, stride, pad, groups, rang
         mix.close()
 
 
-@pytest.mark.parametrize("name,n,h,w,c,k", [("16x16", 1, 14, 14, 256, 256), ("32x16", 1, 28, 28, 128, 136), ("16x16_216_rows", 1, 6, 6, 1536, 264)])
+@pytest.mark.parametrize("name,n,h,w,c,k", [("16x16", 1, 14, 14, 256, 256), ("32x16", 1, 28, 28, 128, 136), ("16x16_four_waves", 1, 12, 12, 64, 96)])
 def test_pooled_epilogue_of_the_rings(name, n, h, w, c, k):
     g = GraphBuilder("t", "bf16", n, h, w, c)
     a = g.conv(0, k, 3, 1, 1, act="relu", bn=True)
@@ -84,7 +83,7 @@ def test_pooled_epilogue_of_the_rings(name, n, h, w, c, k):
     print("case pooled", name, flush=True)
     mix = Mix([g.done()], seed=48)
     try:
-        assert mix.ctx.op_info(0, 0).split_k % 4 == 0
+        assert mix.ctx.op_form(0, 0).name.decode() == "ring_" + name[:5]
         shape = (n, h // 2, w // 2, k)
         _, tm = mix.run(mix.ctx.sequential(flags=B.MT_SCHED_FUSE_POOL))
         assert tm["n_fused"] == 1

@@ -1,6 +1,8 @@
 """The tile kernels that copy their operands from memory to LDS directly: every tile, way to gather an im2col row and patch
 form, with ragged pixel and channel counts, split reductions, residual, channel offsets and the pooled epilogue, against a
 plain fp32 convolution on the CPU."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -15,7 +17,7 @@ from paper_2111_14255_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # name (tile and staging the sizes lead to), n, h, w, c, k, window, stride, pad
+    # name (the form the sizes lead to, "tile_" left out, and the split), n, h, w, c, k, window, stride, pad
     ("64x64_point", 3, 77, 91, 128, 136, 1, 1, 0),
     ("128x64_point_ragged_channels", 2, 90, 91, 192, 520, 1, 1, 0),
     ("128x128_point", 3, 70, 70, 320, 200, 1, 1, 0),
@@ -24,12 +26,20 @@ CASES = [
     ("64x64_deep_tap_stride2", 5, 56, 57, 64, 200, 3, 2, 1),
     ("128x128_tap", 1, 121, 130, 64, 256, 3, 1, 1),
     ("64x32_tap", 1, 60, 62, 128, 128, 3, 1, 1),
-    ("64x16_tap_5x5_wider_than_padding", 1, 35, 33, 64, 96, 5, 1, 2),
-    ("64x16_tap_split4_stride2", 2, 31, 31, 192, 100, 3, 2, 1),
+    ("64x16_tap_5x5_wider_than_padding", 1, 41, 39, 64, 96, 5, 1, 2),
+    ("64x16_tap_split8_stride2", 2, 9, 9, 1024, 100, 3, 2, 1),
+    ("64x32_tap_split3", 1, 46, 46, 256, 64, 3, 1, 1),
+    ("64x64_chunk_split3_5x5", 1, 66, 66, 72, 24, 5, 1, 2),
+    ("128x64_chunk_split3_5x5", 6, 27, 27, 96, 256, 5, 1, 2),
+    ("128x128_tap_split3_stride2", 12, 56, 56, 256, 256, 3, 2, 1),
+    ("ring_32x16_tap_5x5", 1, 35, 33, 64, 96, 5, 1, 2),
+    ("ring_16x16_tap_stride2", 2, 31, 31, 192, 100, 3, 2, 1),
     ("128x64_chunk_c72", 4, 60, 60, 72, 260, 3, 1, 1),
-    ("64x16_chunk_c8_15x3", 1, 30, 30, 8, 24, (15, 3), 1, (7, 1)),
+    ("64x16_chunk_c8_15x3", 1, 50, 50, 8, 24, (15, 3), 1, (7, 1)),
+    ("ring_16x16_chunk_c8_15x3", 1, 30, 30, 8, 24, (15, 3), 1, (7, 1)),
     ("64x16_chunk_c24_unaligned_channels", 2, 13, 11, 24, 67, 3, 1, 1),
-    ("64x16_one_pixel_split8", 9, 1, 1, 4096, 520, 1, 1, 0),
+    ("64x16_one_pixel_split8", 9, 1, 1, 9216, 1000, 1, 1, 0),
+    ("ring_16x16_one_pixel", 9, 1, 1, 4096, 520, 1, 1, 0),
     ("patch_64x64_panel_of_one_column", 1, 62, 61, 192, 136, 3, 1, 1),
     ("patch_64x64_tiles_span_images", 40, 7, 7, 64, 320, 3, 1, 1),
     ("patch_64x64_split4", 1, 28, 28, 512, 256, 3, 1, 1),
@@ -39,9 +49,9 @@ CASES = [
     ("patch_128x128_split3", 3, 28, 28, 512, 512, 3, 1, 1),
     ("patch_128x256", 2, 112, 112, 64, 256, 3, 1, 1),
     ("patch_128x256_split3_tiles_span_images", 6, 28, 28, 384, 512, 3, 1, 1),
-    ("one_pixel_maps_no_patch_holds_the_batch", 300, 1, 1, 512, 2048, 3, 1, 1),
-    ("2x2_maps_only_a_narrow_patch_fits", 700, 2, 2, 256, 512, 3, 1, 1),
-    ("two_pixel_maps_no_patch_holds_the_batch", 800, 1, 2, 256, 512, 3, 1, 1),
+    ("128x64_split3_one_pixel_maps_no_patch_holds_the_batch", 300, 1, 1, 512, 2048, 3, 1, 1),
+    ("128x64_2x2_maps_only_a_narrow_patch_fits", 700, 2, 2, 256, 512, 3, 1, 1),
+    ("64x64_two_pixel_maps_no_patch_holds_the_batch", 800, 1, 2, 256, 512, 3, 1, 1),
 ]
 ACT = {"none": lambda v: v, "relu": torch.relu, "relu6": lambda v: v.clamp(0, 6)}
 
@@ -51,6 +61,15 @@ def conv_ref(x, p, stride, pad, act, dtype):
     w = torch.from_numpy(np.ascontiguousarray(p[0])).permute(0, 3, 1, 2)
     y = F.conv2d(torch.from_numpy(x).permute(0, 3, 1, 2), w, torch.from_numpy(p[1]), stride, pad)
     return y, ACT[act]
+
+
+def check_form(ctx, name):
+    want = re.match(r"(patch_|ring_)?(\d+x\d+)", name)
+    split = re.search(r"split(\d+)", name)
+    form = ctx.op_form(0, 0)
+    assert form.name.decode() == (want.group(1) or "tile_") + want.group(2)
+    assert form.split_k == (int(split.group(1)) if split else 1)
+    assert (form.workspace_bytes > 0) == (form.split_k > 1)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -66,6 +85,7 @@ def test_tile_kernels(name, n, h, w, c, k, win, stride, pad, dtype):
     print("case", name, dtype, flush=True)
     mix = Mix([spec], seed=37)
     try:
+        check_form(mix.ctx, name)
         got, _ = mix.run(mix.ctx.sequential())
         x = oops.round_array(mix.x[0], dtype)
         p = OF.prepare_params(spec, mix.raw[0])
@@ -92,6 +112,7 @@ POOLED = [
     ("patch_128x256", 2, 112, 112, 64, 256),
     ("128x64_tap", 4, 64, 64, 64, 128),
     ("64x32_tap", 1, 60, 62, 128, 128),
+    ("64x16_tap_split8", 1, 6, 6, 1536, 264),
 ]
 
 
@@ -106,6 +127,7 @@ def test_pooled_epilogue_of_the_tile_kernels(name, n, h, w, c, k):
     mix = Mix([spec], seed=41)
     try:
         ctx = mix.ctx
+        check_form(ctx, name)
         shape = (n, h // 2, w // 2, k)
         _, tm = mix.run(ctx.sequential(flags=B.MT_SCHED_FUSE_POOL))
         assert tm["n_fused"] == 1

@@ -274,6 +274,31 @@ def test_3x3_layers_on_maps_of_a_few_pixels_have_a_kernel_at_every_batch(c, k):
                 m.close()
 
 
+@pytest.mark.parametrize("dtype,n,hw,c,k,win,form", [
+    ("f16", 1, 14, 256, 256, 3, ("ring_16x16", 16, 16, 1, 1, 8, 0)),
+    ("f16", 1, 4, 1024, 100, 3, ("tile_64x16", 64, 16, 2, 8, 0, 0)),
+    ("f16", 1, 28, 512, 256, 3, ("patch_64x64", 64, 64, 3, 4, 0, 28)),
+    ("f16", 1, 9, 100, 40, 3, ("elements_64x16", 64, 16, 1, 2, 0, 0)),
+    ("f16", 1, 14, 64, 64, 1, ("igemm_pointwise", 0, 0, 0, 1, 0, 0)),
+    ("f16", 1, 96, 64, 64, 1, ("igemm_resident_filters", 0, 0, 0, 1, 0, 0)),
+    ("f32", 1, 41, 32, 70, 3, ("tile_64x16", 64, 16, 2, 1, 0, 0)),
+    ("f32", 1, 57, 16, 24, 3, ("registers_32x16", 32, 16, 0, 1, 0, 0)),
+])
+def test_op_form_names_the_kernel_and_tells_a_split_from_a_ring(dtype, n, hw, c, k, win, form):
+    g = GraphBuilder("t", dtype, n, hw, hw, c)
+    g.conv(0, k, win, pad=win // 2)
+    m = api.Model(g.done())
+    f = m.op_form(0)
+    assert (f.name.decode(), f.tile_channels, f.tile_pixels, f.stage_slices, f.split_k, f.ring_waves, f.panel_columns) == form
+    assert m.op_info(0).split_k == f.split_k
+    tiles = -(-k // max(1, f.tile_channels)) * -(-n * hw * hw // max(1, f.tile_pixels))
+    assert f.workspace_bytes == (0 if f.split_k == 1 else tiles * f.split_k * f.tile_channels * f.tile_pixels * 4 + tiles * 4)
+    out = B.mt_op_form()
+    assert B.load().mt_model_op_form(m.h, 1, C.byref(out)) == B.MT_ERR_INVALID_ARG
+    assert B.load().mt_model_op_form(None, 0, C.byref(out)) == B.MT_ERR_INVALID_ARG
+    m.close()
+
+
 def _model(ops, dtype=B.MT_F16, dims=(1, 8, 8, 8)):
     lib = B.load()
     h = C.c_void_p()

@@ -10,10 +10,23 @@ pytestmark = pytest.mark.gpu
 
 
 def small_split_model(dtype="f16"):
-    """Two 3x3 layers on a 7x7 map and a classifier: every convolution is split along its reduction."""
-    g = GraphBuilder("small_split", dtype, 1, 7, 7, 256)
-    t = g.conv(0, 256, 3, pad=1, bn=True)
+    """Two 3x3 layers on a 4x4 map and a classifier: every convolution is split along its reduction."""
+    g = GraphBuilder("small_split", dtype, 1, 4, 4, 1024)
+    t = g.conv(0, 1024, 3, pad=1, bn=True)
     t = g.conv(t, 512, 3, pad=1, bn=True, res=-1)
+    t = g.gap(t)
+    g.fc(t, 100)
+    return g.done()
+
+
+def wide_split_model(dtype="f16"):
+    """Split layers on a patch (its epilogue can apply the pooling behind it) and on three tiles, and a classifier."""
+    g = GraphBuilder("wide_split", dtype, 1, 28, 28, 512)
+    t = g.conv(0, 256, 3, pad=1, bn=True)
+    t = g.maxpool(t, 2, 2)
+    t = g.conv(t, 512, 5, pad=2, bn=True)
+    t = g.conv(t, 512, 5, pad=2, bn=True)
+    t = g.conv(t, 64, 7, stride=2, pad=3, bn=True)
     t = g.gap(t)
     g.fc(t, 100)
     return g.done()
@@ -30,19 +43,21 @@ def both_ways(mix, sched):
     return ref, got, tm
 
 
-def uses_split(mix):
-    return any(mix.ctx.op_info(t, i).split_k > 1 and B.load().mt_kernel_name(mix.ctx.op_info(t, i).kernel_id) != b"igemm_pointwise"
-               for t in range(len(mix.specs)) for i in range(mix.ctx.lens()[t]))
+def split_forms(mix, tenant):
+    """Kernels of the tenant's convolutions whose partial sums meet in a workspace."""
+    forms = [mix.ctx.op_form(tenant, i) for i in range(mix.ctx.lens()[tenant])]
+    return [f.name.decode() for f in forms if f.split_k > 1 and f.workspace_bytes > 0]
 
 
 def test_static_scratch_pass_equals_mt_run_twice_in_a_row():
     # first call: two tenants with many split layers; second call, right after it: a smaller tenant set, so that the
     # array still holds the first call's partial sums and counter values where the second one works
-    big = Mix([zoo.resnet18("f16", 1), zoo.BUILDERS["mobilenetv2"]("f16", 1)], seed=911)
+    big = Mix([wide_split_model(), zoo.BUILDERS["mobilenetv2"]("f16", 1)], seed=911)
     small = Mix([small_split_model()], seed=912)
     try:
-        assert uses_split(big) and uses_split(small)
-        sb = big.ctx.schedule([[9, 15], [20, 40]], 3)
+        assert split_forms(big, 0) == ["patch_64x64", "tile_64x32", "tile_64x64", "tile_64x16"]
+        assert split_forms(small, 0) == ["tile_64x16", "tile_64x16"]
+        sb = big.ctx.schedule([[2, 4], [20, 40]], 3)
         ss = small.ctx.sequential()
         ref_b, got_b, tm_b = both_ways(big, sb)
         ref_s, got_s, tm_s = both_ways(small, ss)
