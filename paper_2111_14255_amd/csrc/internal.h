@@ -161,10 +161,8 @@ enum TileChoice {
     TILE_NARROW,     // the 64 x 16 tile, whose order of additions the fused 1x1 + depthwise kernels reproduce
     TILE_RING4,      // 16 x 16 tiles whose reduction four waves deal out between them
     TILE_UNSPLIT,    // no partial sums through memory: fp32 (1.5 % of a network's time) and layers that never had a workspace
-    TILE_NO_RING,    // what mt_run_static_scratch's limit is stated in
 };
 bool plan_tile(OpArgs &a, TileChoice choice);
-int reduction_ranges(const OpArgs &a);   // ranges the reduction of an output is cut into, over workgroups and over the waves of a ring
 bool tile_is_narrow(const OpArgs &a);
 void describe_tile(const OpArgs &a, mt_op_form *out);    // all but the workspace
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);

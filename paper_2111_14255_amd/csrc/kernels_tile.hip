@@ -1016,7 +1016,7 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
         const TileForm &t = FORMS[f];
         const TileCost &c = f32 ? t.single : t.half;
         if (c.start == 0) continue;
-        if ((only >= 0 && f != only) || (choice == TILE_NO_RING && t.ring)) continue;
+        if (only >= 0 && f != only) continue;
         if (t.patch_pixels == 0 && a.kernel_id == K_PCONV) continue;
         if (t.bn > 64 && a.K <= t.bn / 2) continue;         // more than half of the tile would be padding
         const int w = panels[f];
@@ -1052,8 +1052,6 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
 
 // One ascending pass over the reduction on 64 x 16 tiles.
 bool tile_is_narrow(const OpArgs &a) { return a.form == FORM_64x16 && a.split_k == 1; }
-
-int reduction_ranges(const OpArgs &a) { return a.split_k * (a.form >= 0 ? std::max(1, FORMS[a.form].ring) : 1); }
 
 void describe_tile(const OpArgs &a, mt_op_form *out) {
     const TileForm &t = FORMS[a.form];

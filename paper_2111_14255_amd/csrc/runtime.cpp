@@ -25,6 +25,10 @@ using namespace mt;
 namespace {
 
 constexpr size_t ALIGN = 256;
+// mt_run_static_scratch: workspaces up to this size come from the fixed array.  A larger one stays in its tenant's arena,
+// where every split operator has one, so that one layer (512 -> 512, stride 2, at batch 64: 31 MiB) does not use up what the other
+// tenants need.
+constexpr size_t SCRATCH_MAX_WORKSPACE = MT_STATIC_SCRATCH_BYTES / 4;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 inline int elt_size(int dtype) { return dtype == MT_F32 ? 4 : 2; }
 
@@ -428,9 +432,10 @@ struct Tenant {
     std::vector<OpArgs> pool_args;   // its arguments for that form (pooled output tensor, quad pixel walk)
     std::vector<uint8_t> short_kernel;   // operator runs on a short, latency-bound kernel (see MT_SCHED_PRIORITIZE_SHORT)
     // mt_run_static_scratch: where each split operator's counters and workspace sit inside the tenant's two blocks of the
-    // fixed scratch array (byte offsets; blocks are laid out per call, counters of all tenants first)
+    // fixed scratch array (byte offsets; the counters of all tenants come first, see place_scratch)
+    std::vector<uint8_t> in_scratch;
     std::vector<size_t> st_cnt_off, st_ws_off;
-    size_t st_cnt_bytes = 0, st_ws_bytes = 0, st_need = 0;
+    size_t st_cnt_bytes = 0, st_ws_bytes = 0;
 };
 
 struct mt_schedule;
@@ -498,7 +503,7 @@ struct mt_schedule {
     int end_stage = -1;             // last stage that launches anything (-1: the schedule launches nothing)
     int n_fused = 0;                // operators that run inside the next operator's launch
     int32_t prio[MT_MAX_TENANTS] = {0};   // wave priority of a tenant's kernels, 0..3; -1: 3 for its short kernels, 0 for the others
-    RunPlan plan[2];                // of mt_run and of mt_run_static_scratch
+    RunPlan plan[2];                // of mt_run, and of mt_run_static_scratch where any operator has its workspace in the fixed array
     // set while the plan of mt_run_static_scratch is written: base of the fixed scratch array and each tenant's blocks in it
     uint8_t *st_base = nullptr;
     size_t st_cnt_base[MT_MAX_TENANTS] = {}, st_ws_base[MT_MAX_TENANTS] = {};
@@ -591,12 +596,13 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
     const int tp = s->prio[it.tenant];
     OpArgs a = patched(t, it.op, inputs[it.tenant], outputs[it.tenant]);
     // partial sums and arrival counters from the fixed scratch array instead of the arena
-    auto redirect = [&](OpArgs &o) {
-        if (!s->st_base || !o.ws) return;
-        o.ws = (float *)(s->st_base + s->st_ws_base[it.tenant] + t.st_ws_off[it.op]);
-        o.counters = (uint32_t *)(s->st_base + s->st_cnt_base[it.tenant] + t.st_cnt_off[it.op]);
+    auto redirect = [&](OpArgs &o, int tenant) {
+        const Tenant &to = *ctx->tenants[tenant];
+        if (!s->st_base || !to.in_scratch[it.op]) return;
+        o.ws = (float *)(s->st_base + s->st_ws_base[tenant] + to.st_ws_off[it.op]);
+        o.counters = (uint32_t *)(s->st_base + s->st_cnt_base[tenant] + to.st_cnt_off[it.op]);
     };
-    redirect(a);
+    redirect(a, it.tenant);
     a.prio = tp >= 0 ? tp : (t.short_kernel[it.op] || it.fuse == 2 || it.fuse == 3) ? 3 : 0;
     if (it.fuse == 2 || it.fuse == 3) {
         OpArgs prev = patched(t, it.op - 1, inputs[it.tenant], outputs[it.tenant]);
@@ -608,12 +614,8 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
         int nm = 0;
         for (int k = 0; k < COISSUE_MAX - 1 && it.mates[k] >= 0; ++k, ++nm) {
             const int m = it.mates[k];
-            const Tenant &tm = *ctx->tenants[m];
-            b[k] = patched(tm, it.op, inputs[m], outputs[m]);
-            if (s->st_base && b[k].ws) {
-                b[k].ws = (float *)(s->st_base + s->st_ws_base[m] + tm.st_ws_off[it.op]);
-                b[k].counters = (uint32_t *)(s->st_base + s->st_cnt_base[m] + tm.st_cnt_off[it.op]);
-            }
+            b[k] = patched(*ctx->tenants[m], it.op, inputs[m], outputs[m]);
+            redirect(b[k], m);
             b[k].prio = a.prio;
         }
         return launch_kernel(a, st, b, nm);
@@ -621,7 +623,7 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
     if (it.fuse == 4) {
         OpArgs b = t.pool_args[it.op];
         b.prio = a.prio;
-        redirect(b);
+        redirect(b, it.tenant);
         if (t.reads_input[it.op]) b.x = inputs[it.tenant];
         if (t.writes_output[it.op + 1]) b.y = outputs[it.tenant];
         return launch_raw(b, st);
@@ -1056,6 +1058,40 @@ bool rebind_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *c
 }
 
 }  // namespace
+
+// Places the tenants' workspaces in the fixed scratch array and sets its address in the schedule.
+int32_t place_scratch(mt_ctx *ctx, mt_schedule *s, size_t *counter_bytes) {
+    size_t cnt_at = 0, ws_at = 0;
+    for (int i = 0; i < s->n_tenants; ++i) ws_at += ctx->tenants[i]->st_cnt_bytes;      // counters of all tenants first: one fill clears them
+    *counter_bytes = ws_at;
+    for (int i = 0; i < s->n_tenants; ++i) {
+        s->st_cnt_base[i] = cnt_at; cnt_at += ctx->tenants[i]->st_cnt_bytes;
+        s->st_ws_base[i] = ws_at; ws_at += ctx->tenants[i]->st_ws_bytes;
+    }
+    if (ws_at > (size_t)MT_STATIC_SCRATCH_BYTES)
+        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(ws_at) +
+                                              " bytes, the fixed scratch array holds " + std::to_string((size_t)MT_STATIC_SCRATCH_BYTES));
+    void *base = nullptr;
+    const int e = static_scratch_address(ctx->device, &base);
+    if (e != 0) return fail(MT_ERR_HIP, std::string("fixed scratch array: ") + hipGetErrorString((hipError_t)e));
+    s->st_base = (uint8_t *)base;
+    return MT_OK;
+}
+
+// Writes the plan of mt_run_static_scratch down ahead of its first call, which then takes no device memory, signals or kernel
+// symbols.  The buffers are not known yet: any address stands for them until the call puts its own in.  A schedule the call
+// refuses has no such plan, and a failure here is left to the call to report.
+void prepare_static_plan(mt_ctx *ctx, mt_schedule *s) {
+    if (s->flags & (MT_SCHED_GRAPH | MT_SCHED_STREAM_GRAPHS | MT_SCHED_PARALLEL_ISSUE)) return;
+    (void)hipSetDevice(ctx->device);
+    size_t counter_bytes = 0;
+    const void *in[MT_MAX_TENANTS];
+    void *out[MT_MAX_TENANTS];
+    for (int i = 0; i < s->n_tenants; ++i) in[i] = out[i] = ctx->tenants[i]->arena;
+    if (place_scratch(ctx, s, &counter_bytes) == MT_OK)
+        (void)build_plan(ctx, s, in, out, s->plan[counter_bytes > 0 ? 1 : 0], true, counter_bytes);
+    s->st_base = nullptr;
+}
 
 // ============================================================================================
 extern "C" {
@@ -1703,21 +1739,13 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
         t->args[i] = a;
         o.w_host.clear(); o.w_host.shrink_to_fit();
     }
+    t->in_scratch.assign(nops, 0);
     t->st_cnt_off.assign(nops, 0);
     t->st_ws_off.assign(nops, 0);
     for (size_t i = 0; i < nops; ++i) {
         const OpRec &o = t->model.ops[i];
-        // The limit of mt_run_static_scratch counts a layer that runs on a ring as the split layer it would be without one: which
-        // sets of tenants are taken does not depend on which form is the fastest.
-        OpArgs split = o.plan;
-        if (o.plan.dtype != MT_F32 && o.plan.split_k == 1 && reduction_ranges(o.plan) > 1 && o.plan.kernel_id != K_IGEMM_PW && o.plan.gemm_k > 256 &&
-            plan_tile(split, TILE_NO_RING) && split.split_k > 1) {
-            size_t tiles = 0, floats = 0;
-            tile_workspace(split, &tiles, &floats);
-            t->st_need += align_up(tiles * split.groups * sizeof(uint32_t)) + align_up(tiles * floats * split.groups * sizeof(float));
-        }
-        if (!t->args[i].ws) continue;
-        t->st_need += align_up(o.cnt_bytes) + align_up(o.ws_bytes);
+        if (!t->args[i].ws || o.ws_bytes > SCRATCH_MAX_WORKSPACE) continue;
+        t->in_scratch[i] = 1;
         t->st_cnt_off[i] = t->st_cnt_bytes; t->st_cnt_bytes += align_up(o.cnt_bytes);
         t->st_ws_off[i] = t->st_ws_bytes; t->st_ws_bytes += align_up(o.ws_bytes);
     }
@@ -1824,9 +1852,9 @@ int32_t mt_tenant_read_tensor(mt_ctx *ctx, int32_t tenant, int32_t tensor_id, vo
 }
 
 // ---- schedule --------------------------------------------------------------------------------
-int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, const int32_t *pointers,
-                           const int32_t *stage_concurrency, const int32_t *cu_share, int32_t order, int32_t flags,
-                           mt_schedule **out) {
+// `for_static`: mt_run_static_scratch may be called on the schedule.
+static int32_t make_schedule(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, const int32_t *pointers, const int32_t *stage_concurrency,
+                             const int32_t *cu_share, const int32_t *prio, int32_t order, int32_t flags, bool for_static, mt_schedule **out) {
     if (!ctx || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     *out = nullptr;
     if (n_tenants != (int)ctx->tenants.size() || n_tenants < 1)
@@ -1863,7 +1891,7 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
     HIP_TRY(hipSetDevice(ctx->device));
     std::unique_ptr<mt_schedule> s(new mt_schedule);
     s->ctx = ctx; s->n_tenants = n_tenants; s->n_stages = n_stages; s->flags = flags;
-    for (int i = 0; i < n_tenants; ++i) s->prio[i] = (flags & MT_SCHED_PRIORITIZE_SHORT) ? -1 : 0;
+    for (int i = 0; i < n_tenants; ++i) s->prio[i] = prio ? prio[i] : (flags & MT_SCHED_PRIORITIZE_SHORT) ? -1 : 0;
     // streams restricted to a share of the units have queues of their own
     const bool per_stage = (flags & MT_SCHED_SHARE_PER_STAGE) != 0;
     std::vector<std::pair<int, int>> units;
@@ -1991,8 +2019,15 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
         s->end_stage = last;
     }
     ctx->live_schedules.insert(s.get());
+    if (for_static) prepare_static_plan(ctx, s.get());
     *out = s.release();
     return MT_OK;
+}
+
+int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, const int32_t *pointers,
+                           const int32_t *stage_concurrency, const int32_t *cu_share, int32_t order, int32_t flags,
+                           mt_schedule **out) {
+    return make_schedule(ctx, n_tenants, n_stages, pointers, stage_concurrency, cu_share, nullptr, order, flags, true, out);
 }
 
 int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio) {
@@ -2000,8 +2035,10 @@ int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio) {
     for (int i = 0; i < s->n_tenants; ++i)
         if (prio[i] < -1 || prio[i] > 3) return fail(MT_ERR_INVALID_ARG, "wave priority must be -1 (by kernel size) or 0..3");
     for (int i = 0; i < s->n_tenants; ++i) s->prio[i] = prio[i];
-    if (s->ctx)
+    if (s->ctx) {
         for (RunPlan &p : s->plan) drop_plan(s->ctx, p);      // its launches carry the old value
+        prepare_static_plan(s->ctx, s);
+    }
     return MT_OK;
 }
 
@@ -2031,24 +2068,9 @@ int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *in
     if (s->flags & (MT_SCHED_GRAPH | MT_SCHED_STREAM_GRAPHS | MT_SCHED_PARALLEL_ISSUE))
         return fail(MT_ERR_INVALID_ARG, "graph replay and parallel issue allocate on their first run: not available without allocation");
     HIP_TRY(hipSetDevice(ctx->device));
-    size_t cnt_total = 0, need = 0;
-    for (int i = 0; i < s->n_tenants; ++i) {
-        cnt_total += ctx->tenants[i]->st_cnt_bytes;
-        need += ctx->tenants[i]->st_need;
-    }
-    if (need > (size_t)MT_STATIC_SCRATCH_BYTES)
-        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(need) +
-                                              " bytes, the fixed scratch array holds " + std::to_string((size_t)MT_STATIC_SCRATCH_BYTES));
-    void *base = nullptr;
-    const int e = static_scratch_address(ctx->device, &base);
-    if (e != 0) return fail(MT_ERR_HIP, std::string("fixed scratch array: ") + hipGetErrorString((hipError_t)e));
-    size_t cnt_at = 0, ws_at = cnt_total;                  // counters of all tenants first: one fill clears them
-    for (int i = 0; i < s->n_tenants; ++i) {
-        s->st_cnt_base[i] = cnt_at; cnt_at += ctx->tenants[i]->st_cnt_bytes;
-        s->st_ws_base[i] = ws_at; ws_at += ctx->tenants[i]->st_ws_bytes;
-    }
-    s->st_base = (uint8_t *)base;
-    const int32_t rc = run_pass(ctx, s, inputs, outputs, tm, true, cnt_total);
+    size_t counter_bytes = 0;
+    int32_t rc = place_scratch(ctx, s, &counter_bytes);
+    if (rc == MT_OK) rc = run_pass(ctx, s, inputs, outputs, tm, true, counter_bytes);
     s->st_base = nullptr;
     return rc;
 }
@@ -2078,7 +2100,7 @@ static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, 
     HIP_TRY(wait_for_default_stream());
     const auto t0 = std::chrono::steady_clock::now();
     LaneDevice *dev = ctx->lanes;
-    RunPlan &plan = s->plan[static_scratch ? 1 : 0];
+    RunPlan &plan = s->plan[static_scratch && counter_bytes > 0 ? 1 : 0];
     bool same = plan.valid;
     for (int i = 0; same && i < s->n_tenants; ++i) same = plan.in[i] == inputs[i] && plan.out[i] == outputs[i];
     if (!same && !(plan.valid && rebind_plan(ctx, s, inputs, outputs, plan))) {
@@ -2180,10 +2202,9 @@ struct ProfileCost {
 double profile_schedule(ProfileCost *pc, const int32_t *pointers, const int32_t *cu_share) {
     if (pc->rc != MT_OK) return 1e30;
     mt_schedule *s = nullptr;
-    pc->rc = mt_schedule_create(pc->ctx, pc->n_tenants, pc->o->n_stages, pointers, pc->conc, cu_share, pc->o->issue_order,
-                                pc->o->flags, &s);
-    if (pc->rc == MT_OK && pc->prio) pc->rc = mt_schedule_set_wave_priority(s, pc->prio);
-    if (pc->rc != MT_OK) { if (s) mt_schedule_destroy(s); return 1e30; }
+    pc->rc = make_schedule(pc->ctx, pc->n_tenants, pc->o->n_stages, pointers, pc->conc, cu_share, pc->prio, pc->o->issue_order,
+                           pc->o->flags, false, &s);
+    if (pc->rc != MT_OK) return 1e30;
     // The profiled latency of a candidate is the median of its timed runs: one preempted run must not decide
     // a comparison between two schedules that differ by a few percent.
     std::vector<double> samples;

@@ -1,6 +1,7 @@
 """mt_run_static_scratch (the pass for callers that cannot allocate) against mt_run, through the C ABI, on the GPU."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2111_14255_amd import binding as B
 from synth import GraphBuilder, zoo
@@ -81,9 +82,80 @@ def test_static_scratch_pass_equals_mt_run_twice_in_a_row():
         small.close()
 
 
-def test_static_scratch_limits_and_flags():
-    mix = Mix([zoo.BUILDERS["vgg16"]("f16", 1), zoo.resnet18("f16", 1)], seed=913)      # needs more than the array holds
+def layers_side_by_side(n, shape, k, win, stride):
+    """n convolutions of one input, each with its own output, and a classifier behind the last."""
+    g = GraphBuilder("side_by_side", "f16", *shape)
+    t = [g.conv(0, k, win, stride, win // 2, bn=True) for _ in range(n)][-1]
+    g.fc(g.gap(t), 10)
+    return g.done()
+
+
+def test_static_scratch_counts_the_workspaces_that_are_used():
+    # VGG-16 splits two layers (6.5 MiB), ResNet-18 none: its rings need no workspace
+    mix = Mix([zoo.BUILDERS["vgg16"]("f16", 1), zoo.resnet18("f16", 1)], seed=913)
     try:
+        forms = [mix.ctx.op_form(t, i) for t in range(2) for i in range(mix.ctx.lens()[t])]
+        assert 0 < sum(f.workspace_bytes for f in forms) < B.MT_STATIC_SCRATCH_BYTES / 2
+        assert any(f.ring_waves for f in forms)
+        ref, got, _ = both_ways(mix, mix.ctx.all_concurrent())
+        for r, g in zip(ref, got):
+            np.testing.assert_array_equal(g, r)
+    finally:
+        mix.close()
+
+
+def test_large_workspaces_stay_in_the_arena():
+    # 14.25 MiB in one layer of each tenant, 0.75 MiB in the other: three tenants would need 45 MiB of the array
+    def net():
+        g = GraphBuilder("large_split", "f16", 12, 14, 14, 512)
+        t = g.conv(0, 512, 3, pad=1, bn=True)
+        g.conv(t, 64, 7, stride=2, pad=3, bn=True)
+        return g.done()
+    mix = Mix([net(), net(), net()], seed=914)
+    try:
+        ctx = mix.ctx
+        sizes = [ctx.op_form(0, i).workspace_bytes for i in range(2)]
+        assert sizes[0] > B.MT_STATIC_SCRATCH_BYTES / 4 and 0 < sizes[1] < B.MT_STATIC_SCRATCH_BYTES / 16
+        ref, _ = mix.run(ctx.sequential())
+        for s in (ctx.all_concurrent(), ctx.schedule([[], [], []], 1, concurrency=[1], flags=B.MT_SCHED_COISSUE), ctx.schedule([[1]] * 3, 2)):
+            for _ in range(2):
+                _, got, _ = both_ways(mix, s)
+                for r, g in zip(ref, got):
+                    np.testing.assert_array_equal(g, r)
+    finally:
+        mix.close()
+
+
+@pytest.mark.parametrize("split", [False, True])
+def test_the_call_takes_no_device_memory(split):
+    # the packets' arguments of a schedule take some 60 KiB, in pieces of 1 MiB: with these many schedules several are taken
+    nets = [zoo.BUILDERS["mobilenetv2"]("f16", 1), wide_split_model() if split else zoo.resnet18("f16", 1)]
+    mix = Mix(nets, seed=915)
+    try:
+        assert bool(split_forms(mix, 1)) == split
+        outs = [mix.ctx.make_output(t) for t in range(2)]
+        keep, taken = [], []
+        for i in range(48):
+            s = mix.ctx.all_concurrent(flags=B.MT_SCHED_FUSE_POOL if i % 2 else 0)
+            if i % 3 == 0:
+                s.set_wave_priority([i % 4, -1])
+            keep.append(s)
+            torch.cuda.synchronize()
+            before = torch.cuda.mem_get_info()[0]
+            mix.ctx.run_static_scratch(s, mix.inputs, outs)
+            torch.cuda.synchronize()
+            taken.append(before - torch.cuda.mem_get_info()[0])
+        assert not any(taken), taken
+        assert all(np.isfinite(mix.ctx.output_to_numpy(t, outs[t])).all() for t in range(2))
+    finally:
+        mix.close()
+
+
+def test_static_scratch_limits_and_flags():
+    # five split layers of 3.25 MiB each: more than the array holds
+    mix = Mix([layers_side_by_side(5, (1, 28, 28, 512), 256, 3, 1), zoo.BUILDERS["tinyC"]("f16", 1)], seed=913)
+    try:
+        assert sum(mix.ctx.op_form(0, i).workspace_bytes for i in range(5)) > B.MT_STATIC_SCRATCH_BYTES
         outs = [mix.ctx.make_output(t) for t in range(2)]
         s = mix.ctx.sequential()
         with pytest.raises(B.MtError) as ei:
