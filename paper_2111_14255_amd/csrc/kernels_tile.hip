@@ -31,8 +31,9 @@
 namespace mt {
 
 // How a row of A is gathered: TG_POINT 1x1 windows without padding and C % 64 == 0 (a row is contiguous), TG_TAP
-// C % 64 == 0 (64 consecutive j lie inside one filter tap), TG_CHUNK C % 8 == 0 (every 16-byte piece has its own tap).
-constexpr int TG_POINT = 0, TG_TAP = 1, TG_CHUNK = 2;
+// C % 64 == 0 (64 consecutive j lie inside one filter tap), TG_CHUNK C % 8 == 0 (every 16-byte piece has its own tap).  Which taps
+// of a window are inside the image is a mask of 15 rows and 16 columns; TG_FAR is TG_CHUNK for larger windows and compares.
+constexpr int TG_POINT = 0, TG_TAP = 1, TG_CHUNK = 2, TG_FAR = 3;
 
 namespace {
 
@@ -385,7 +386,9 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
         ws[i] = (uint32_t)(rg * 8 * a.k_pad + (st0 * KD + kd) * RK) * ES;
     }
     constexpr int NP = KD == 1 ? 1 : XQ;                   // positions along j tracked (loads of one 64-slice share one)
+    constexpr bool PIECEWISE = MODE == TG_CHUNK || MODE == TG_FAR;   // every 16-byte piece has a tap of its own
     uint32_t xoff[XQ], xmask[XQ];
+    int first_row[XQ], first_col[XQ];                      // TG_FAR: first row and column of the window
     int ptap[NP], pch[NP];                                 // tap and channel of each position (TG_TAP: wave-uniform)
     uint32_t xs = (uint32_t)(st0 * KD) * 128u;          // TG_POINT: scalar offset
     const uint32_t x_end = (uint32_t)a.gemm_k * ES;
@@ -396,14 +399,17 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
         const bool ok = m < M;
         int n, ih0, iw0;
         window_origin(a, ok ? (uint32_t)m : 0u, n, ih0, iw0);
-        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (MODE == TG_CHUNK ? 0 : piece * EPP)) * ES;
+        xoff[i] = (uint32_t)(((n * a.H + ih0) * a.W + iw0) * XS + (PIECEWISE ? 0 : piece * EPP)) * ES;
         if constexpr (MODE == TG_POINT) {
             xoff[i] = ok ? xoff[i] + (uint32_t)(kd * 128) : OUT_OF_RANGE;
+        } else if constexpr (MODE == TG_FAR) {
+            first_row[i] = ok ? ih0 : INT32_MIN / 2;            // beyond the last pixel: outside the image at every tap
+            first_col[i] = iw0;
         } else {
             xmask[i] = ok ? window_mask(a, ih0, iw0) : 0u;
         }
         if (MODE != TG_POINT && i < NP) {
-            const int j0 = (st0 * KD + (KD == 1 ? 0 : kd)) * RK + (MODE == TG_CHUNK ? piece * EPP : 0);
+            const int j0 = (st0 * KD + (KD == 1 ? 0 : kd)) * RK + (PIECEWISE ? piece * EPP : 0);
             ptap[i] = j0 / a.C;
             pch[i] = j0 - ptap[i] * a.C;
         }
@@ -425,8 +431,13 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
                 const int tr = a.S == 1 ? ptap[i] : (int)__umulhi((uint32_t)ptap[i], inv_s);
                 const int tc = ptap[i] - tr * a.S;
                 toff[i] = (uint32_t)((tr * a.W + tc) * XS + pch[i]) * ES;
-                trow[i] = (uint32_t)min(tr, 15);           // beyond the window (padding of the reduction): a bit that is never set
-                tcol[i] = (uint32_t)(16 + tc);
+                if constexpr (MODE == TG_FAR) {
+                    trow[i] = (uint32_t)(tr < a.R ? tr : INT32_MIN / 2);   // beyond the window: outside every image
+                    tcol[i] = (uint32_t)tc;
+                } else {
+                    trow[i] = (uint32_t)min(tr, 15);       // beyond the window (padding of the reduction): a bit that is never set
+                    tcol[i] = (uint32_t)(16 + tc);
+                }
                 ptap[i] += adv_t;
                 pch[i] += adv_c;
                 const bool carry = pch[i] >= a.C;
@@ -444,8 +455,10 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
                 load_to_lds(rsrc_x, KD == 1 || xs + slice < x_end ? xoff[i] : OUT_OF_RANGE, xs, dst);
             } else {
                 const int pi = KD == 1 ? 0 : i;
-                const uint32_t off = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u ? xoff[i] + toff[pi] : OUT_OF_RANGE;
-                load_to_lds(rsrc_x, off, 0u, dst);
+                bool inside;
+                if constexpr (MODE == TG_FAR) inside = ((uint32_t)first_row[i] + trow[pi] < (uint32_t)a.H) & ((uint32_t)first_col[i] + tcol[pi] < (uint32_t)a.W);
+                else inside = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u;
+                load_to_lds(rsrc_x, inside ? xoff[i] + toff[pi] : OUT_OF_RANGE, 0u, dst);
             }
         }
         xs += KD * 128;
@@ -936,6 +949,8 @@ constexpr TileForm FORMS[] = {
     {32, 16, 1, 4, 256, 0, 4, {3.35, 0.9, 0.28, 0.25, 0, 0}, {3.3, 0.95, 0.37, 0.4, 0, 0}},
     {16, 16, 1, 4, 256, 0, 4, {3.19, 0.568, 0.193, 0.175, 0, 0}, {3.03, 0.652, 0.259, 0.209, 0, 0}},
 };
+bool far_window(const OpArgs &a) { return a.R > 15 || a.S > 15; }
+bool far_form(int form) { return form >= 1 && form <= 5; }    // built for such windows; few layers have them
 constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]), FORM_64x16 = 5, FORM_RING4 = 14;
 constexpr int MAX_SPLIT = 8, TARGET_WGS = 768, UNITS = 256;
 
@@ -985,14 +1000,16 @@ void set_walk(OpArgs &a) {
 
 }  // namespace
 
-// Form, split and launch shape of a convolution (a fully connected layer is a 1x1 one) with C % 8 == 0 and a window of at
-// most 15 x 15: a pure function of the layer's shape and of `choice` (see TileChoice).
+// Form, split and launch shape of a convolution (a fully connected layer is a 1x1 one) with C % 8 == 0 (fp32: C % 4 == 0 and a
+// window of at most 15 x 15): a pure function of the layer's shape and of `choice` (see TileChoice).
 bool plan_tile(OpArgs &a, TileChoice choice) {
     const int only = choice == TILE_NARROW ? FORM_64x16 : choice == TILE_RING4 ? FORM_RING4 : -1;
     const bool unsplit = choice == TILE_UNSPLIT;
     const bool f32 = a.dtype == MT_F32;
     const int row = f32 ? ROW<float> : TK;
-    if (a.C % (row / 8) != 0 || a.R > 15 || a.S > 15) return false;
+    const bool far = far_window(a);
+    if (a.C % (row / 8) != 0) return false;
+    if (far && (f32 || (int64_t)a.R * a.S * a.S >= (int64_t)1 << 32)) return false;    // the division of a tap by S is exact below
     // fp32 with few output channels: the tiles would be half padding (144 -> 24 on 4 x 56 x 56 7.4 us, 5.7 with operands from
     // memory; 288 -> 32 on 4 x 149 x 149 41 / 37; short reductions are bound by their input: 32 -> 16 on 4 x 112 x 112 7.9 / 20)
     if (f32 && a.K <= 32 && a.gemm_k >= 128) return false;
@@ -1016,7 +1033,7 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
         const TileForm &t = FORMS[f];
         const TileCost &c = f32 ? t.single : t.half;
         if (c.start == 0) continue;
-        if (only >= 0 && f != only) continue;
+        if ((only >= 0 && f != only) || (far && !far_form(f))) continue;
         if (t.patch_pixels == 0 && a.kernel_id == K_PCONV) continue;
         if (t.bn > 64 && a.K <= t.bn / 2) continue;         // more than half of the tile would be padding
         const int w = panels[f];
@@ -1110,6 +1127,25 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
     };
     constexpr bool f32 = std::is_same_v<T, float>;
+    if (far_window(a)) {
+        if constexpr (!f32) {
+            // us, element-wise gather / this: 17x17, 64 -> 64 on 40 x 40 66.7 / 17.5, 1x31, 64 -> 128 on 8 x 56 x 56 75.6 / 24.2, 16x3,
+            // 128 -> 256 on 16 x 28 x 28 213 / 62.7
+            auto far = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
+                MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, TG_FAR>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, TG_FAR>), grid, block, st, a, mate);
+            };
+            switch (a.form) {
+                case 1: far.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+                case 2: far.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
+                case 3: far.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;
+                case 4: far.template operator()<64, 32, 2, 1, 4, 2, 3>(); break;
+                case 5: far.template operator()<64, 16, 4, 1, 1, 2, 3>(); break;
+                default: return (int)hipErrorInvalidValue;
+            }
+            return (int)hipGetLastError();
+        }
+        return (int)hipErrorInvalidValue;
+    }
     switch (a.form) {
         case 2: tile.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
         case 3: tile.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;

@@ -127,7 +127,7 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
     // (64 -> 256 on 56 x 56 takes 5.9 us on it, 4.1 on the tile of least estimate)
     const bool short_1x1 = small && p.R == 1 && p.S == 1 && p.C <= 256;
     if (vec && plan_tile(p, !short_1x1 ? TILE_ANY : beside_depthwise ? TILE_NARROW : TILE_UNSPLIT)) return;
-    // element-wise gather (C % 8 != 0 or a window of more than 15 rows or columns): tiles of the register-staged kernel
+    // element-wise gather (C % 8 != 0): tiles of the register-staged kernel
     p.vec_a = 0;
     p.n_pad = cdiv(Kc, bn) * bn;
     const int tiles = cdiv(M, bm) * (p.n_pad / bn);

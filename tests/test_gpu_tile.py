@@ -40,6 +40,17 @@ CASES = [
     ("64x16_chunk_c24_unaligned_channels", 2, 13, 11, 24, 67, 3, 1, 1),
     ("64x16_one_pixel_split8", 9, 1, 1, 9216, 1000, 1, 1, 0),
     ("ring_16x16_one_pixel", 9, 1, 1, 4096, 520, 1, 1, 0),
+    # windows of more than 15 rows or columns
+    ("64x16_far_1x20_even_window", 3, 17, 9, 16, 32, (1, 20), 1, (0, 10)),
+    ("64x16_far_split8_17x17_wider_than_the_map", 1, 8, 8, 64, 72, 17, 1, 8),
+    ("64x16_far_split8_18x3_stride2", 1, 20, 30, 72, 100, (18, 3), 2, (9, 1)),
+    ("64x32_far_1x17", 1, 60, 60, 64, 72, (1, 17), 1, (0, 8)),
+    ("64x32_far_split4_17x1", 1, 20, 20, 256, 256, (17, 1), 1, (8, 0)),
+    ("64x64_far_1x16_c8", 4, 80, 80, 8, 64, (1, 16), 1, (0, 8)),
+    ("64x64_far_16x5_c24", 2, 40, 40, 24, 136, (16, 5), 1, (8, 2)),
+    ("64x64_far_split7_1x31", 1, 48, 48, 128, 64, (1, 31), 1, (0, 15)),
+    ("128x64_far_3x16_c8", 2, 70, 70, 8, 72, (3, 16), 1, (1, 8)),
+    ("128x64_far_split3_1x31_ragged_channels", 6, 40, 40, 64, 124, (1, 31), 1, (0, 15)),
     ("patch_64x64_panel_of_one_column", 1, 62, 61, 192, 136, 3, 1, 1),
     ("patch_64x64_tiles_span_images", 40, 7, 7, 64, 320, 3, 1, 1),
     ("patch_64x64_split4", 1, 28, 28, 512, 256, 3, 1, 1),
@@ -162,5 +173,50 @@ def test_patch_does_not_carry_non_finite_pixels_into_foreign_windows():
         assert np.array_equal(~np.isfinite(got[0]), bad)
         scale = float(np.abs(ref[~bad]).max())
         assert float(np.abs(got[0][~bad] - ref[~bad]).max()) <= 2e-2 * scale
+    finally:
+        mix.close()
+
+
+def test_far_windows_pooled_co_issued_and_beside_non_finite_pixels():
+    """Windows of more than 15 rows or columns: the pooled epilogue and the launch of two tenants keep the bits, and a pixel that
+    is not finite reaches the windows that hold it only."""
+    n, h, w, c, k, win, pad = 2, 20, 22, 24, 72, (17, 4), (8, 2)
+    g = GraphBuilder("far", "bf16", n, h, w, c)
+    a = g.conv(0, k, win, 1, pad, act="none", bn=False)
+    spec = g.done()
+    g = GraphBuilder("far_pooled", "bf16", n, h, w, c)
+    a = g.conv(0, k, win, 1, (8, 1), act="relu", bn=True)
+    b = g.conv(a, 40, (1, 18), 1, (0, 9), act="relu", bn=True)
+    pl = g.maxpool(b, 2, 2, 0)
+    pooled = g.done()
+    mix = Mix([spec, spec, pooled], seed=44)
+    try:
+        ctx = mix.ctx
+        assert ctx.op_form(0, 0).name.startswith(b"tile_") and ctx.op_form(2, 1).name.startswith(b"tile_")
+        x = mix.x[0]
+        for (i, r, q) in ((0, h - 1, 5), (0, 3, w - 1), (1, 0, 9), (1, 12, 0)):
+            x[i, r, q, 9] = np.nan
+        mix.inputs[0] = ctx.make_input(0, x)
+        plain, tm = mix.run(ctx.sequential())
+        assert tm["n_fused"] == 0
+        for flags, fused in ((B.MT_SCHED_COISSUE, 1), (B.MT_SCHED_FUSE_POOL, 1), (B.MT_SCHED_COISSUE | B.MT_SCHED_FUSE_POOL, 2)):
+            got, tm = mix.run(ctx.schedule([[], [], []], 1, concurrency=[1], flags=flags))
+            assert tm["n_fused"] == fused
+            for p, q in zip(plain, got):
+                np.testing.assert_array_equal(p, q)
+        for t in range(3):
+            xs = oops.round_array(mix.x[t], "bf16")
+            p = OF.prepare_params(mix.specs[t], mix.raw[t])
+            if t < 2:
+                ref = conv_ref(xs, p[0], 1, pad, "none", "bf16")[0].permute(0, 2, 3, 1).contiguous().numpy()
+            else:
+                y, act = conv_ref(xs, p[0], 1, (8, 1), "relu", "bf16")
+                y, act = conv_ref(oops.round_array(act(y).permute(0, 2, 3, 1).contiguous().numpy(), "bf16"), p[1], 1, (0, 9), "relu", "bf16")
+                ref = F.max_pool2d(act(y), 2).permute(0, 2, 3, 1).contiguous().numpy()
+            ref = ref.reshape(n, -1)
+            bad = ~np.isfinite(ref)
+            assert (bad.any() and not bad.all()) == (t == 0)
+            assert np.array_equal(~np.isfinite(plain[t]), bad)
+            assert float(np.abs(plain[t][~bad] - ref[~bad]).max()) <= 2e-2 * float(np.abs(ref[~bad]).max())
     finally:
         mix.close()
