@@ -2,13 +2,8 @@
 // can be named in dispatch packets, and the queues, signals and argument memory those packets use.
 #include "lanes.h"
 
-#include <dlfcn.h>
-#include <elf.h>
-#include <fcntl.h>
+#include <link.h>
 #include <sched.h>
-#include <sys/mman.h>
-#include <sys/stat.h>
-#include <unistd.h>
 
 #include <algorithm>
 #include <cstdio>
@@ -29,51 +24,50 @@ inline void pause_once() {
 
 thread_local LaunchRecorder *recorder_of_thread = nullptr;
 
-// A read-only view of this library's own file.
-struct OwnFile {
-    const uint8_t *p = nullptr;
-    size_t n = 0;
-    OwnFile() {
-        Dl_info info{};
-        if (!dladdr((const void *)&current_recorder, &info) || !info.dli_fname) return;
-        const int fd = open(info.dli_fname, O_RDONLY | O_CLOEXEC);
-        if (fd < 0) return;
-        struct stat st{};
-        if (fstat(fd, &st) == 0 && st.st_size > 0) {
-            void *m = mmap(nullptr, (size_t)st.st_size, PROT_READ, MAP_PRIVATE, fd, 0);
-            if (m != MAP_FAILED) { p = (const uint8_t *)m; n = (size_t)st.st_size; }
+// The read-only segments of this library in memory.
+std::vector<std::pair<const uint8_t *, size_t>> own_segments() {
+    static const char here = 0;
+    struct Find {
+        uintptr_t inside;
+        std::vector<std::pair<const uint8_t *, size_t>> found;
+    } f{(uintptr_t)&here, {}};
+    (void)dl_iterate_phdr([](dl_phdr_info *o, size_t, void *u) {
+        Find *f = (Find *)u;
+        std::vector<std::pair<const uint8_t *, size_t>> segs;
+        bool own = false;
+        for (int i = 0; i < o->dlpi_phnum; ++i) {
+            const ElfW(Phdr) &h = o->dlpi_phdr[i];
+            if (h.p_type != PT_LOAD) continue;
+            const uintptr_t at = (uintptr_t)(o->dlpi_addr + h.p_vaddr);
+            own = own || (f->inside >= at && f->inside < at + h.p_memsz);
+            if ((h.p_flags & PF_R) && !(h.p_flags & PF_W)) segs.push_back({(const uint8_t *)at, (size_t)h.p_filesz});
         }
-        close(fd);
-    }
-};
+        if (own) f->found = std::move(segs);
+        return own ? 1 : 0;
+    }, &f);
+    return f.found;
+}
 
-// The gfx950 code objects inside the library file: its .hip_fatbin section holds one offload bundle per device source,
-// each a table of (offset, size, target) followed by the objects.
+// The gfx950 code objects inside the loaded library: one offload bundle per device source, each a table of (offset, size,
+// target) followed by the objects.  They are read from memory, where they stay while the library is loaded; its file may have
+// been replaced or removed since.
 std::vector<std::pair<const uint8_t *, size_t>> own_code_objects() {
-    static const OwnFile file;                           // stays mapped: the loader reads the objects in place
     std::vector<std::pair<const uint8_t *, size_t>> out;
-    if (file.n < sizeof(Elf64_Ehdr)) return out;
-    const Elf64_Ehdr *eh = (const Elf64_Ehdr *)file.p;
-    if (std::memcmp(eh->e_ident, ELFMAG, SELFMAG) != 0 || eh->e_shoff + (uint64_t)eh->e_shnum * sizeof(Elf64_Shdr) > file.n || eh->e_shstrndx >= eh->e_shnum) return out;
-    const Elf64_Shdr *sh = (const Elf64_Shdr *)(file.p + eh->e_shoff);
-    const char *names = (const char *)(file.p + sh[eh->e_shstrndx].sh_offset);
-    for (int i = 0; i < eh->e_shnum; ++i) {
-        if (std::strcmp(names + sh[i].sh_name, ".hip_fatbin") != 0 || sh[i].sh_offset + sh[i].sh_size > file.n) continue;
-        const uint8_t *base = file.p + sh[i].sh_offset;
-        static const char magic[] = "__CLANG_OFFLOAD_BUNDLE__";
-        for (size_t at = 0; at + 64 < sh[i].sh_size;) {
-            if (std::memcmp(base + at, magic, 24) != 0) { at += 8; continue; }
-            const size_t left = sh[i].sh_size - at;
+    for (auto [base, size] : own_segments()) {
+        for (size_t at = (8 - (uintptr_t)base % 8) % 8; at + 64 < size;) {
+            // the magic in two parts, so that the segment holds it in bundles only
+            if (std::memcmp(base + at, "__CLANG_OFFL", 12) != 0 || std::memcmp(base + at + 12, "OAD_BUNDLE__", 12) != 0) { at += 8; continue; }
+            const size_t left = size - at;
             uint64_t count = 0;
             std::memcpy(&count, base + at + 24, 8);
             size_t pos = 32, end = 32;
             for (uint64_t e = 0; e < count && pos + 24 <= left; ++e) {
                 uint64_t h[3];                           // offset, size, length of the target name
                 std::memcpy(h, base + at + pos, 24);
-                if (pos + 24 + h[2] > left) break;
+                if (h[2] > left - pos - 24) break;
                 const std::string target((const char *)base + at + pos + 24, (size_t)h[2]);
                 pos += 24 + (size_t)h[2];
-                if (h[0] + h[1] <= left) {
+                if (h[0] <= left && h[1] <= left - h[0]) {
                     end = std::max<size_t>(end, (size_t)(h[0] + h[1]));
                     if (h[1] > 0 && target.find("gfx950") != std::string::npos) out.push_back({base + at + h[0], (size_t)h[1]});
                 }
@@ -178,7 +172,7 @@ bool LaneDevice::load_code(std::string *why) {
         }
         code_.push_back(x);
     }
-    if (code_.empty() && why) *why = "no gfx950 code object found in the library file";
+    if (code_.empty() && why) *why = "no gfx950 code object found in the library";
     return !code_.empty();
 }
 

@@ -1,5 +1,9 @@
 """Schedules as queue packets: streams that share a lane, buffers exchanged between runs, passes longer than a queue,
 several contexts at once.  Every output is compared bit for bit with the sequential schedule's."""
+import os
+import shutil
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -133,3 +137,28 @@ def test_a_pass_beside_a_capture_and_after_work_on_the_default_stream(static):
         assert same([mix.ctx.output_to_numpy(t, o) for t, o in enumerate(outs)], ref)
     finally:
         mix.close()
+
+
+def test_library_whose_file_is_gone_since_it_was_loaded(tmp_path):
+    """The kernels named in packets come from the loaded library, not from its file: an installation may be replaced under a
+    running program."""
+    lib = str(tmp_path / "libmtsched_copy.so")
+    shutil.copy(B._build.lib_path(), lib)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    prog = """
+import os, sys
+sys.path[:0] = [%r, %r]
+import torch
+from paper_2111_14255_amd import binding as B
+B.load()
+os.unlink(%r)
+from synth import zoo
+from gpu_harness import Mix, assert_close
+mix = Mix([zoo.BUILDERS["tinyC"]("f16", 1)], seed=3)
+got, _ = mix.run(mix.ctx.sequential())
+assert_close(got[0], mix.oracle()[0], "f16")
+mix.close()
+print("ran without the file")
+""" % (root, os.path.join(root, "tests"), lib)
+    r = subprocess.run([sys.executable, "-c", prog], env=dict(os.environ, MTSCHED_LIB=lib), capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "ran without the file" in r.stdout, r.stdout + r.stderr
