@@ -42,9 +42,10 @@ template <typename T> constexpr int ROW = 128 / (int)sizeof(T);    // the same o
 constexpr int XCDS = 8;
 constexpr uint32_t OUT_OF_RANGE = 0x80000000u;  // beyond any tensor: the load delivers zeros
 
-// 64 lanes x 16 bytes from rsrc + voff (per lane) + soff to LDS at `lds` + 16 * lane.
+// 64 lanes x 16 bytes from rsrc + voff (per lane) + soff to LDS at `lds` + 16 * lane.  The instruction takes the LDS address from m0;
+// the compiler puts it there, so it knows what m0 holds, and the wait state the load needs after that follows.
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 // All but the N youngest loads of this wave have landed, its LDS reads are done, and the other waves got here as well.
