@@ -31,7 +31,7 @@
  *  - One context is used from one host thread at a time (the paper issues all
  *    operators from a single main thread, Sec. III-D).
  *  - mt_run places operators on hardware queues of its own, not on HIP streams: a schedule is turned into queue packets
- *    once, when it is created or on its first run, and every run publishes them.  A "stream" of a schedule is an ordered
+ *    on its first run and the packets are published again by every later one.  A "stream" of a schedule is an ordered
  *    sequence of operators on such a queue.  Up to four streams run on four queues that the chip serves side by side;
  *    further streams share a queue, where they advance together, and streams restricted to a CU share have queues of
  *    their own.  Operators of one tenant that do not depend on each other (parallel branches) may run at the same time.
@@ -351,7 +351,7 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
                            int32_t issue_order, int32_t flags, mt_schedule **out);
 /* Wave priority per tenant (host array of n_tenants entries): 0..3 = every kernel of that tenant raises its waves to
  * that issue priority, -1 = the rule of MT_SCHED_PRIORITIZE_SHORT for that tenant.  Replaces what the flags set;
- * the schedule's packets are written again.  Timing only. */
+ * the schedule's packets are written again on the next run.  Timing only. */
 int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio);
 int32_t mt_schedule_destroy(mt_schedule *s);
 
@@ -376,11 +376,11 @@ int32_t mt_run(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *con
  * MT_STATIC_SCRATCH_BYTES bytes of device memory that the library's code object holds on every GPU it is loaded on,
  * instead of from the tenants' arenas.  An operator that needs more than a quarter of the array (mt_op_form.workspace_bytes)
  * keeps the workspace in its tenant's arena.  The call allocates nothing on the device and makes no HIP call that a capture
- * forbids: what its packets need is taken when the schedule is created and when its wave priorities are set.  The schedule
- * must have been created without MT_SCHED_GRAPH, MT_SCHED_STREAM_GRAPHS and MT_SCHED_PARALLEL_ISSUE: MT_ERR_INVALID_ARG
- * otherwise.  The counters' part of the array is cleared by a fill kernel at the start of each call; workspaces need no
- * clearing.  If the operators in the array together need more than it holds the call fails with MT_ERR_OUT_OF_MEMORY before anything is launched, and
- * mt_last_error states both figures.  Outputs have the bits of mt_run.  All calls on one GPU share the array, which
+ * forbids: what its packets need is taken when the schedule is created, which must have been without MT_SCHED_GRAPH,
+ * MT_SCHED_STREAM_GRAPHS and MT_SCHED_PARALLEL_ISSUE: MT_ERR_INVALID_ARG otherwise.  The counters' part of the array is
+ * cleared by a fill kernel at the start of each call; workspaces need no clearing.  If the operators in the array together
+ * need more than it holds the call fails with MT_ERR_OUT_OF_MEMORY before anything is launched, and mt_last_error states
+ * both figures.  Outputs have the bits of mt_run.  All calls on one GPU share the array, which
  * keeps the last call's contents: two calls that overlap in time on one GPU (from two contexts or two host threads)
  * race on it and must be serialised by the caller.  inputs / outputs / t as for mt_run. */
 #define MT_STATIC_SCRATCH_BYTES (16u << 20)

@@ -188,9 +188,7 @@ int launch_dwpw(const OpArgs &dw, const OpArgs &pw, void *stream);   // depthwis
 bool pwdw_fusable(const OpArgs &pw, const OpArgs &dw);
 int launch_pwdw(const OpArgs &pw, const OpArgs &dw, void *stream);   // 1x1 convolution + the depthwise 3x3 that reads it on a small map, one launch
 int launch_fill_u32(uint32_t *p, size_t n, uint32_t v, void *stream);
-// Device address of the library's fixed scratch array (MT_STATIC_SCRATCH_BYTES bytes) on `device`, which must be the
-// current device; looked up once per device.  Returns a hipError_t as int.
-int static_scratch_address(int device, void **ptr);
+constexpr const char *STATIC_SCRATCH_SYMBOL = "_ZN2mt14static_scratchE";   // kernels_igemm.hip: the fixed array of MT_STATIC_SCRATCH_BYTES bytes
 int launch_probe(uint32_t *out, int n_groups, void *stream);
 int launch_arrive(uint32_t *counter, void *stream);                 // one thread adds 1 to *counter (system scope, release)
 // Diagnostics: a register-only loop of 4 * iters 32x32x16 matrix instructions per wave (sink: n_groups * 256 floats), and

@@ -172,8 +172,15 @@ bool LaneDevice::load_code(std::string *why) {
         }
         code_.push_back(x);
     }
-    if (code_.empty() && why) *why = "no gfx950 code object found in the library";
-    return !code_.empty();
+    for (hsa_executable_t x : code_) {
+        hsa_executable_symbol_t s;
+        uint64_t at = 0;
+        if (hsa_executable_get_symbol_by_name(x, STATIC_SCRATCH_SYMBOL, &gpu_, &s) == HSA_STATUS_SUCCESS &&
+            hsa_executable_symbol_get_info(s, HSA_EXECUTABLE_SYMBOL_INFO_VARIABLE_ADDRESS, &at) == HSA_STATUS_SUCCESS)
+            static_scratch_ = (uint8_t *)at;
+    }
+    if (!static_scratch_ && why) *why = code_.empty() ? "no gfx950 code object found in the library" : "the fixed scratch array is not in the code objects";
+    return static_scratch_ != nullptr;
 }
 
 const KernelCode *LaneDevice::kernel(const void *host_fn) {

@@ -55,6 +55,7 @@ public:
     void destroy_queue(hsa_queue_t *q);
 
     const KernelCode *kernel(const void *host_fn);       // null if the kernel is not in this library's code objects
+    uint8_t *static_scratch() const { return static_scratch_; }
 
     bool alloc_args(size_t bytes, KernargBlock *out);
     void free_args(KernargBlock b);
@@ -80,6 +81,7 @@ private:
     std::vector<hsa_agent_t> access_;                    // agents that touch argument memory: the GPU and the CPUs
     hsa_amd_memory_pool_t vram_{};
     double ms_per_tick_ = 0;
+    uint8_t *static_scratch_ = nullptr;
     hsa_queue_t *plain_[N_LANES] = {};
     std::vector<hsa_executable_t> code_;
     // Held while packets are placed and the doorbell is rung.  Two queues may share one: what a queue waits for is always in its

@@ -467,6 +467,7 @@ struct StagePlan {
     std::vector<IssueItem> items;
     std::vector<int> streams;       // distinct streams used, ascending
     std::vector<std::vector<IssueItem>> by_stream;   // items of each stream (index = tenant that owns the stream), in issue order
+    std::vector<std::vector<int>> level;             // their levels (item_levels)
     int prev_stage = -1;            // latest earlier stage that launched anything (-1: none)
     std::array<hsa_queue_t *, MT_MAX_TENANTS> queue_of{};   // queue of each stream
 };
@@ -485,7 +486,7 @@ struct RunPlan {
     std::vector<const void *> in;
     std::vector<void *> out;
     std::vector<std::vector<LaneSlice>> stages;
-    std::vector<hsa_signal_t> signals;
+    std::vector<hsa_signal_t> signals;               // the schedule's first ones
     KernargBlock args;
     std::vector<RecordedLaunch> launches;
     std::vector<size_t> arg_at;                      // offset of each launch's arguments in `args`
@@ -504,6 +505,11 @@ struct mt_schedule {
     int n_fused = 0;                // operators that run inside the next operator's launch
     int32_t prio[MT_MAX_TENANTS] = {0};   // wave priority of a tenant's kernels, 0..3; -1: 3 for its short kernels, 0 for the others
     RunPlan plan[2];                // of mt_run, and of mt_run_static_scratch where any operator has its workspace in the fixed array
+    std::vector<hsa_signal_t> signals;             // of both plans, which never run at the same time
+    // mt_run_static_scratch: argument memory held for its plan, plan[static_plan] (-1: it refuses the schedule)
+    int static_plan = -1;
+    KernargBlock static_args;
+    RunPlan *static_plan_of() { return static_plan < 0 ? nullptr : &plan[static_plan]; }
     // set while the plan of mt_run_static_scratch is written: base of the fixed scratch array and each tenant's blocks in it
     uint8_t *st_base = nullptr;
     size_t st_cnt_base[MT_MAX_TENANTS] = {}, st_ws_base[MT_MAX_TENANTS] = {};
@@ -867,10 +873,30 @@ std::vector<int> item_levels(const mt_ctx *ctx, const std::vector<IssueItem> &it
     return level;
 }
 
-void drop_plan(mt_ctx *ctx, RunPlan &p) {
-    for (hsa_signal_t s : p.signals) ctx->lanes->return_signal(s);
+// The argument memory of the plan of mt_run_static_scratch goes back to what the schedule holds for it.
+void drop_plan(mt_ctx *ctx, mt_schedule *s, RunPlan &p) {
+    if (&p == s->static_plan_of() && p.args.bytes > s->static_args.bytes) std::swap(p.args, s->static_args);
     ctx->lanes->free_args(p.args);
     p = RunPlan{};
+}
+
+// Everything a schedule has taken from the lanes.
+void release_plans(mt_ctx *ctx, mt_schedule *s) {
+    for (RunPlan &p : s->plan) drop_plan(ctx, s, p);
+    for (hsa_signal_t sg : s->signals) ctx->lanes->return_signal(sg);
+    s->signals.clear();
+    ctx->lanes->free_args(s->static_args);
+    s->static_args = KernargBlock{};
+}
+
+// The schedule's signal number i, taken from the lanes if it has fewer; handle 0 on failure.
+hsa_signal_t schedule_signal(mt_ctx *ctx, mt_schedule *s, size_t i) {
+    while (s->signals.size() <= i) {
+        const hsa_signal_t sg = ctx->lanes->take_signal();
+        if (!sg.handle) return sg;
+        s->signals.push_back(sg);
+    }
+    return s->signals[i];
 }
 
 bool names_caller_buffers(const mt_ctx *ctx, const IssueItem &it) {
@@ -887,8 +913,9 @@ bool names_caller_buffers(const mt_ctx *ctx, const IssueItem &it) {
 // released (its siblings start after it and need no fence of their own); the first packet of a queue acquires at system
 // scope (caller's inputs, argument memory written by the host), and what writes a caller's output releases there.
 int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, RunPlan &plan, bool clear_counters, size_t counter_bytes) {
-    drop_plan(ctx, plan);
+    drop_plan(ctx, s, plan);
     LaneDevice *dev = ctx->lanes;
+    const bool reserved = &plan == s->static_plan_of();
     LaunchRecorder rec;
     rec.dev = dev;
     struct Emit { size_t launch; uint32_t head; int signal; };           // one kernel packet of a slice
@@ -897,7 +924,7 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
     for (int i = 0; i < MT_MAX_TENANTS; ++i) plan.first_op[i] = plan.last_op[i] = -1;
     bool no_signal = false;
     auto new_signal = [&]() {
-        hsa_signal_t sg = dev->take_signal();
+        const hsa_signal_t sg = schedule_signal(ctx, s, plan.signals.size());
         no_signal = no_signal || !sg.handle;
         plan.signals.push_back(sg);
         return (int)plan.signals.size() - 1;
@@ -933,7 +960,7 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
             for (int sm : sp.streams) {
                 if (sp.queue_of[sm] != q) continue;
                 const auto &items = sp.by_stream[sm];
-                const auto level = item_levels(ctx, items);
+                const auto &level = sp.level[sm];
                 for (size_t k = 0; k < items.size() && rc == MT_OK; ++k) {
                     const size_t first = rec.launches.size();
                     const int e = launch_item(ctx, s, items[k], inputs, outputs, nullptr);
@@ -992,10 +1019,10 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
         plan.arg_at.push_back(bytes);
         bytes += ((size_t)l.code->kernarg_bytes + 63) / 64 * 64;
     }
-    if (rc == MT_OK && !dev->alloc_args(bytes, &plan.args)) rc = fail(MT_ERR_OUT_OF_MEMORY, "no device memory for kernel arguments");
+    if (reserved && bytes <= s->static_args.bytes) std::swap(plan.args, s->static_args);
+    else if (rc == MT_OK && !dev->alloc_args(bytes, &plan.args)) rc = fail(MT_ERR_OUT_OF_MEMORY, "no device memory for kernel arguments");
     if (rc != MT_OK) {
-        for (hsa_signal_t sg : plan.signals) dev->return_signal(sg);
-        plan = RunPlan{};
+        drop_plan(ctx, s, plan);
         return rc;
     }
     for (size_t l = 0; l < rec.launches.size(); ++l) write_args(rec.launches[l], rec.args.data() + rec.launches[l].arg_off, plan.args.p + plan.arg_at[l]);
@@ -1059,38 +1086,50 @@ bool rebind_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *c
 
 }  // namespace
 
-// Places the tenants' workspaces in the fixed scratch array and sets its address in the schedule.
-int32_t place_scratch(mt_ctx *ctx, mt_schedule *s, size_t *counter_bytes) {
+// Places the tenants' workspaces in the fixed scratch array, the counters of all tenants first: one fill clears them.  Returns
+// the bytes they take.
+size_t place_scratch(const mt_ctx *ctx, mt_schedule *s, size_t *counter_bytes) {
     size_t cnt_at = 0, ws_at = 0;
-    for (int i = 0; i < s->n_tenants; ++i) ws_at += ctx->tenants[i]->st_cnt_bytes;      // counters of all tenants first: one fill clears them
+    for (int i = 0; i < s->n_tenants; ++i) ws_at += ctx->tenants[i]->st_cnt_bytes;
     *counter_bytes = ws_at;
     for (int i = 0; i < s->n_tenants; ++i) {
         s->st_cnt_base[i] = cnt_at; cnt_at += ctx->tenants[i]->st_cnt_bytes;
         s->st_ws_base[i] = ws_at; ws_at += ctx->tenants[i]->st_ws_bytes;
     }
-    if (ws_at > (size_t)MT_STATIC_SCRATCH_BYTES)
-        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(ws_at) +
-                                              " bytes, the fixed scratch array holds " + std::to_string((size_t)MT_STATIC_SCRATCH_BYTES));
-    void *base = nullptr;
-    const int e = static_scratch_address(ctx->device, &base);
-    if (e != 0) return fail(MT_ERR_HIP, std::string("fixed scratch array: ") + hipGetErrorString((hipError_t)e));
-    s->st_base = (uint8_t *)base;
-    return MT_OK;
+    return ws_at;
 }
 
-// Writes the plan of mt_run_static_scratch down ahead of its first call, which then takes no device memory, signals or kernel
-// symbols.  The buffers are not known yet: any address stands for them until the call puts its own in.  A schedule the call
-// refuses has no such plan, and a failure here is left to the call to report.
-void prepare_static_plan(mt_ctx *ctx, mt_schedule *s) {
+// Takes argument memory and signals for the plan of mt_run_static_scratch, at least as much as it needs, so that its first call
+// takes none.  A schedule the call refuses has no argument memory.
+void reserve_static(mt_ctx *ctx, mt_schedule *s) {
     if (s->flags & (MT_SCHED_GRAPH | MT_SCHED_STREAM_GRAPHS | MT_SCHED_PARALLEL_ISSUE)) return;
-    (void)hipSetDevice(ctx->device);
-    size_t counter_bytes = 0;
-    const void *in[MT_MAX_TENANTS];
-    void *out[MT_MAX_TENANTS];
-    for (int i = 0; i < s->n_tenants; ++i) in[i] = out[i] = ctx->tenants[i]->arena;
-    if (place_scratch(ctx, s, &counter_bytes) == MT_OK)
-        (void)build_plan(ctx, s, in, out, s->plan[counter_bytes > 0 ? 1 : 0], true, counter_bytes);
-    s->st_base = nullptr;
+    size_t counters = 0;
+    if (place_scratch(ctx, s, &counters) > (size_t)MT_STATIC_SCRATCH_BYTES) return;
+    s->static_plan = counters > 0 ? 1 : 0;
+    auto arg_bytes = [](size_t operators) { return (operators + 64 + 256 + 63) / 64 * 64; };   // a few numbers beside them, 256 bytes of implicit arguments
+    size_t bytes = 0, signals = 0;
+    if (counters > 0) { bytes += arg_bytes(0); ++signals; }
+    const int timed = ((s->flags & MT_SCHED_TIME_FIRST_OP) ? 1 : 0) + ((s->flags & MT_SCHED_TIME_TENANTS) ? 1 : 0);
+    signals += (size_t)timed * s->n_tenants;
+    for (const StagePlan &sp : s->stages) {
+        std::map<hsa_queue_t *, std::pair<int, size_t>> ends;            // per queue: latest level, launches in it
+        for (int sm : sp.streams) {
+            const auto &items = sp.by_stream[sm];
+            const auto &level = sp.level[sm];
+            auto &end = ends[sp.queue_of[sm]];
+            for (size_t k = 0; k < items.size(); ++k) {
+                const IssueItem &it = items[k];
+                if (it.fuse == 1) continue;
+                const size_t launches = (size_t)std::max(1, ctx->tenants[it.tenant]->args[it.op].groups);
+                bytes += launches * arg_bytes(it.mates[0] >= 0 ? sizeof(OpArgsPair) : it.fuse == 2 || it.fuse == 3 ? 2 * sizeof(OpArgs) : sizeof(OpArgs));
+                if (end.second == 0 || level[k] > end.first) end = {level[k], launches};
+                else if (level[k] == end.first) end.second += launches;
+            }
+        }
+        for (const auto &[queue, end] : ends) signals += end.second + 1;  // and one for the first kernel of a first stage
+    }
+    (void)ctx->lanes->alloc_args(bytes, &s->static_args);
+    if (signals > 0) (void)schedule_signal(ctx, s, signals - 1);
 }
 
 // ============================================================================================
@@ -1146,7 +1185,7 @@ int32_t mt_destroy(mt_ctx *ctx) {
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
     for (mt_schedule *ls : ctx->live_schedules) {
-        for (RunPlan &p : ls->plan) drop_plan(ctx, p);
+        release_plans(ctx, ls);
         release_masked(ls);
         ls->ctx = nullptr;
     }
@@ -2008,6 +2047,7 @@ static int32_t make_schedule(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, c
         std::sort(sp.streams.begin(), sp.streams.end());
         sp.by_stream.assign(n_tenants, {});
         for (const IssueItem &it : sp.items) sp.by_stream[it.stream].push_back(it);
+        for (const auto &items : sp.by_stream) sp.level.push_back(item_levels(ctx, items));
         for (int sm : sp.streams)
             if (unit_of[st][sm] >= 0) sp.queue_of[sm] = s->masked->queues[unit_of[st][sm]];
         lane_plan(ctx->lanes, sp);
@@ -2019,7 +2059,7 @@ static int32_t make_schedule(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, c
         s->end_stage = last;
     }
     ctx->live_schedules.insert(s.get());
-    if (for_static) prepare_static_plan(ctx, s.get());
+    if (for_static) reserve_static(ctx, s.get());
     *out = s.release();
     return MT_OK;
 }
@@ -2035,17 +2075,15 @@ int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio) {
     for (int i = 0; i < s->n_tenants; ++i)
         if (prio[i] < -1 || prio[i] > 3) return fail(MT_ERR_INVALID_ARG, "wave priority must be -1 (by kernel size) or 0..3");
     for (int i = 0; i < s->n_tenants; ++i) s->prio[i] = prio[i];
-    if (s->ctx) {
-        for (RunPlan &p : s->plan) drop_plan(s->ctx, p);      // its launches carry the old value
-        prepare_static_plan(s->ctx, s);
-    }
+    if (s->ctx)
+        for (RunPlan &p : s->plan) drop_plan(s->ctx, s, p);   // its launches carry the old value
     return MT_OK;
 }
 
 int32_t mt_schedule_destroy(mt_schedule *s) {
     if (!s) return fail(MT_ERR_INVALID_ARG, "schedule is NULL");
     if (s->ctx) {
-        for (RunPlan &p : s->plan) drop_plan(s->ctx, p);
+        release_plans(s->ctx, s);
         release_masked(s);
         s->ctx->live_schedules.erase(s);
     }
@@ -2069,8 +2107,12 @@ int32_t mt_run_static_scratch(mt_ctx *ctx, mt_schedule *s, const void *const *in
         return fail(MT_ERR_INVALID_ARG, "graph replay and parallel issue allocate on their first run: not available without allocation");
     HIP_TRY(hipSetDevice(ctx->device));
     size_t counter_bytes = 0;
-    int32_t rc = place_scratch(ctx, s, &counter_bytes);
-    if (rc == MT_OK) rc = run_pass(ctx, s, inputs, outputs, tm, true, counter_bytes);
+    const size_t need = place_scratch(ctx, s, &counter_bytes);
+    if (need > (size_t)MT_STATIC_SCRATCH_BYTES)
+        return fail(MT_ERR_OUT_OF_MEMORY, "the split workspaces of these tenants need " + std::to_string(need) +
+                                              " bytes, the fixed scratch array holds " + std::to_string((size_t)MT_STATIC_SCRATCH_BYTES));
+    s->st_base = ctx->lanes->static_scratch();
+    const int32_t rc = run_pass(ctx, s, inputs, outputs, tm, true, counter_bytes);
     s->st_base = nullptr;
     return rc;
 }

@@ -1,7 +1,10 @@
 """mt_run_static_scratch (the pass for callers that cannot allocate) against mt_run, through the C ABI, on the GPU."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
-import torch
 
 from paper_2111_14255_amd import binding as B
 from synth import GraphBuilder, zoo
@@ -126,29 +129,44 @@ def test_large_workspaces_stay_in_the_arena():
         mix.close()
 
 
+MEASURE = """
+import sys
+sys.path[:0] = [%r, %r]
+import numpy as np
+import torch
+from paper_2111_14255_amd import binding as B
+from synth import zoo
+from gpu_harness import Mix
+from test_zz_no_alloc import split_forms, wide_split_model
+split = %r
+mix = Mix([zoo.BUILDERS["mobilenetv2"]("f16", 1), wide_split_model() if split else zoo.resnet18("f16", 1)], seed=915)
+assert bool(split_forms(mix, 1)) == split
+outs = [mix.ctx.make_output(t) for t in range(2)]
+keep, taken = [], []
+for i in range(48):
+    co = mix.ctx.schedule([[], []], 1, concurrency=[1 + i %% 2], flags=(B.MT_SCHED_FUSE_POOL, B.MT_SCHED_FUSE_EXPAND, B.MT_SCHED_TIME_TENANTS)[i %% 3])
+    if i %% 5 == 4:
+        mix.ctx.run_static_scratch(co, mix.inputs, outs)
+        co.set_wave_priority([i %% 4, -1])
+    keep.append(co)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    mix.ctx.run_static_scratch(co, mix.inputs, outs)
+    torch.cuda.synchronize()
+    taken.append(before - torch.cuda.mem_get_info()[0])
+assert not any(taken), taken
+assert all(np.isfinite(mix.ctx.output_to_numpy(t, outs[t])).all() for t in range(2))
+print("no memory taken")
+"""
+
+
 @pytest.mark.parametrize("split", [False, True])
 def test_the_call_takes_no_device_memory(split):
-    # the packets' arguments of a schedule take some 60 KiB, in pieces of 1 MiB: with these many schedules several are taken
-    nets = [zoo.BUILDERS["mobilenetv2"]("f16", 1), wide_split_model() if split else zoo.resnet18("f16", 1)]
-    mix = Mix(nets, seed=915)
-    try:
-        assert bool(split_forms(mix, 1)) == split
-        outs = [mix.ctx.make_output(t) for t in range(2)]
-        keep, taken = [], []
-        for i in range(48):
-            s = mix.ctx.all_concurrent(flags=B.MT_SCHED_FUSE_POOL if i % 2 else 0)
-            if i % 3 == 0:
-                s.set_wave_priority([i % 4, -1])
-            keep.append(s)
-            torch.cuda.synchronize()
-            before = torch.cuda.mem_get_info()[0]
-            mix.ctx.run_static_scratch(s, mix.inputs, outs)
-            torch.cuda.synchronize()
-            taken.append(before - torch.cuda.mem_get_info()[0])
-        assert not any(taken), taken
-        assert all(np.isfinite(mix.ctx.output_to_numpy(t, outs[t])).all() for t in range(2))
-    finally:
-        mix.close()
+    """In a process of its own, from its first call on.  The arguments of a schedule's packets take some 60 KiB, in pieces of
+    1 MiB: with these many schedules several are taken, all of them before the calls."""
+    here = os.path.dirname(os.path.abspath(__file__))
+    r = subprocess.run([sys.executable, "-c", MEASURE % (os.path.dirname(here), here, split)], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "no memory taken" in r.stdout, r.stdout + r.stderr
 
 
 def test_static_scratch_limits_and_flags():
