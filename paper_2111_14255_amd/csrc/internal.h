@@ -92,7 +92,7 @@ struct OpArgs {
     int32_t k_pad;               // packed weight row length (multiple of the k tile)
     int32_t n_pad;               // packed weight rows (multiple of the channel tile)
     int32_t split_k;
-    int32_t wk;                  // wave groups that share an output tile (64x64 tile only): 1 or 2; fp32 convolution: its tiling (dconv_f32_plan)
+    int32_t wk;                  // fp32 convolution on operands from memory: its tiling (dconv_f32_plan), 0: another kernel
     int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
     int32_t form;                // tile and staging of the tile kernels (kernels_tile.hip), -1: another kernel
     int32_t panel;               // patch-staged 3x3 layers: columns of a panel (kernels_tile.hip)
@@ -101,7 +101,7 @@ struct OpArgs {
     // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
     uint32_t divq_m, divq_s1, divq_s2, divpq_m, divpq_s1, divpq_s2;
     int32_t tile_order;          // 0: channel tile fastest (an XCD shares activation tiles), 1: pixel tile fastest (shares filter tiles)
-    int32_t vec_a;               // im2col gather mode: 0 element-wise, 1 16-byte chunks (C % 8 == 0), 2 tile inside one tap (C % 64 == 0)
+    int32_t vec_a;               // im2col rows of a 16-bit type: 1 gathered in 16-byte pieces or more (C % 8 == 0), 0 element by element
     int32_t grid_x, grid_y, grid_z, block;
     const void *x;
     const void *w;

@@ -1,9 +1,10 @@
-// Convolutions whose matrix-core operands come straight from memory: no LDS tiles, no barrier in the reduction.
+// fp32 convolutions whose matrix-core operands come straight from memory: no LDS tiles, no barrier in the reduction.  They are the
+// ones the tile kernels (kernels_tile.hip) do not take: channel counts that are no multiple of 4, windows of more than 15 rows
+// or columns, few output channels.
 //
-// A wave owns TN x TM tiles of 16 output channels x 16 pixels.  A reduction step is 64 bytes of a filter row and of an
-// im2col row (32 elements of fp16 / bf16, 16 of fp32): lane l loads the 16 bytes of row l % 16 that start at byte
-// 16 * (l / 16), which is the operand layout of v_mfma_f32_16x16x32 for 16-bit types and feeds four v_mfma_f32_16x16x4_f32
-// for fp32 (instruction e multiplies element e of every 16-byte piece, so the four lane groups hold the reduction
+// A wave owns TN x TM tiles of 16 output channels x 16 pixels.  A reduction step is 16 elements of a filter row and of an
+// im2col row: lane l loads the four elements of row l % 16 that start at 4 * (l / 16), which feed four
+// v_mfma_f32_16x16x4_f32 (instruction e multiplies element e of every 16-byte piece, so the four lane groups hold the reduction
 // elements e, 4 + e, 8 + e, 12 + e: the same for both operands, and any order of the sum is a correct one).  D steps are
 // in flight in registers; the one consumed is refilled at once.  Pixels outside the image and steps beyond the end get
 // an out-of-range offset, for which the buffer load returns zeros.
@@ -11,8 +12,8 @@
 // WK > 1: WK waves share the tile and split the reduction into contiguous ranges; their sums meet in LDS and are added in
 // range order.  That is the form for small maps: the whole reduction of a tile is in flight after one trip to memory.
 //
-// fp32: the matrix cores need 32 cycles per instruction, so operands from the L1 keep up with them; the kernel replaces
-// one thread per output element (MI355X, ResNet-18 + MobileNetV2 at batch 4: 6.59 ms).
+// The matrix cores need 32 cycles per instruction, so operands from the L1 keep up with them; the kernel replaces
+// one thread per output element (MI355X, ResNet-18 + MobileNetV2 at batch 4 with every layer on it: 6609 us before, 552 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,23 +31,14 @@ constexpr int DC_TABLE = 2048;               // reduction elements of the elemen
 
 // How an im2col row is gathered.  Tap-uniform: the channels are a multiple of a step, so a step lies inside one filter
 // tap.  Piecewise: they are a multiple of 16 bytes, every lane group has a tap of its own.  Element-wise: any channel
-// count (first layers), offsets from a table in LDS; fp32 only.
+// count (first layers), offsets from a table in LDS.
 constexpr int DC_ELEMENT = 0, DC_PIECE = 1, DC_UNIFORM = 2;
 
-__device__ __forceinline__ f32x4 dc_mma(u32x4 a, u32x4 b, f32x4 c, f16) { return Mma<f16, 16>::run(a, b, c); }
-__device__ __forceinline__ f32x4 dc_mma(u32x4 a, u32x4 b, f32x4 c, bf16) { return Mma<bf16, 16>::run(a, b, c); }
-__device__ __forceinline__ f32x4 dc_mma(u32x4 a, u32x4 b, f32x4 c, float) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
-    return c;
-}
-
-template <typename T, int TN, int TM, int WN, int WM, int WK, int D, int MODE>
-__device__ __forceinline__ void dconv_body(const OpArgs &a) {
+template <int TN, int TM, int WN, int WM, int WK, int D, int MODE>
+__global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
     set_wave_priority(a.prio);
-    constexpr int ES = sizeof(T), KST = 64 / ES, EPV = 16 / ES;
+    constexpr int ES = 4, KST = 16, EPV = 4;
     constexpr int NW = WN * WM * WK, BN = 16 * TN * WN, BM = 16 * TM * WM, F = TN * TM;
-    static_assert(MODE != DC_ELEMENT || ES == 4, "the element-wise gather exists for fp32");
     __shared__ __attribute__((aligned(16))) f32x4 red[WK > 1 ? NW * F * 64 : 1];
     __shared__ int2 table[MODE == DC_ELEMENT ? DC_TABLE : 1];
 
@@ -84,21 +76,13 @@ __device__ __forceinline__ void dconv_body(const OpArgs &a) {
     for (int j = 0; j < TM; ++j) {
         const int m = m0 + 16 * j + row;
         const bool ok = m < M;
-        // with the pooled epilogue pixels are walked window by window (four consecutive rows are one 2x2 window)
         const uint32_t mm = ok ? (uint32_t)m : 0u;
-        const uint32_t mq = a.pool2 ? mm >> 2 : mm;
-        const uint32_t pqd = a.pool2 ? (uint32_t)((a.P >> 1) * (a.Q >> 1)) : (uint32_t)(a.P * a.Q);
-        const uint32_t qd = a.pool2 ? (uint32_t)(a.Q >> 1) : (uint32_t)a.Q;
-        const uint32_t t1 = __umulhi(a.divpq_m, mq);
-        const int n = (int)((t1 + ((mq - t1) >> a.divpq_s1)) >> a.divpq_s2);
-        const uint32_t rem = mq - (uint32_t)n * pqd;
+        const uint32_t t1 = __umulhi(a.divpq_m, mm);
+        const int n = (int)((t1 + ((mm - t1) >> a.divpq_s1)) >> a.divpq_s2);
+        const uint32_t rem = mm - (uint32_t)n * (uint32_t)(a.P * a.Q);
         const uint32_t t2 = __umulhi(a.divq_m, rem);
-        int p = (int)((t2 + ((rem - t2) >> a.divq_s1)) >> a.divq_s2);
-        int q = (int)(rem - (uint32_t)p * qd);
-        if (a.pool2) {
-            p = 2 * p + (int)((mm >> 1) & 1u);
-            q = 2 * q + (int)(mm & 1u);
-        }
+        const int p = (int)((t2 + ((rem - t2) >> a.divq_s1)) >> a.divq_s2);
+        const int q = (int)(rem - (uint32_t)p * (uint32_t)a.Q);
         ih0[j] = ok ? p * a.sh - a.ph : -0x10000;                      // a pixel beyond the last one is outside the image at every tap
         iw0[j] = q * a.sw - a.pw;
         xbase[j] = ((n * a.H + (ok ? p * a.sh - a.ph : 0)) * a.W + iw0[j]) * a.x_ct * ES + a.x_coff * ES;
@@ -179,51 +163,37 @@ __device__ __forceinline__ void dconv_body(const OpArgs &a) {
 #pragma unroll
                 for (int i = 0; i < TN; ++i)
 #pragma unroll
-                    for (int j = 0; j < TM; ++j) acc[i][j] = dc_mma(fa[d][i], fb[d][j], acc[i][j], T{});
+                    for (int j = 0; j < TM; ++j) acc[i][j] = Mma<float, 16>::run(fa[d][i], fb[d][j], acc[i][j]);
             }
             if (s0 + D < s_end) load_step(s0 + d + D, fa[d], fb[d]);
         }
     }
 
-    // ---- epilogue: bias, residual, activation, one rounding.  A lane holds 4 consecutive channels of one pixel.
-    T *y = (T *)a.y;
-    const T *res = (const T *)a.res;
+    // ---- epilogue: bias, residual, activation.  A lane holds 4 consecutive channels of one pixel.
+    float *y = (float *)a.y;
+    const float *res = (const float *)a.res;
     const bool vec_ok = (a.y_ct % 4 == 0) & (a.y_coff % 4 == 0) & (a.res_ct % 4 == 0);
     auto finish = [&](f32x4 v4, int i, int j) {
         const int m = m0 + 16 * j + row, k = n0 + 16 * i + 4 * grp;
         const bool live = (m < M) & (k < a.K);
         const float4 b = live ? *reinterpret_cast<const float4 *>(a.bias + k) : float4{0.f, 0.f, 0.f, 0.f};    // padded to n_pad
         float v[4] = {v4[0] + b.x, v4[1] + b.y, v4[2] + b.z, v4[3] + b.w};
-        if (a.pool2) {
-            // the four pixels of a window are four neighbouring lanes; activation and rounding are monotonic
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                v[t] = fmaxf(v[t], __shfl_xor(v[t], 1));
-                v[t] = fmaxf(v[t], __shfl_xor(v[t], 2));
-                v[t] = apply_act(v[t], a.act);
-            }
-            if (live && (row & 3) == 0) store_pack<T, 4>(y + (int64_t)(m >> 2) * a.y_ct + a.y_coff + k, v);
-            return;
-        }
         if (!live) return;
         if (vec_ok && k + 4 <= a.K) {
             if (res) {
                 float rv[4];
-                load_pack<T, 4>(res + (int64_t)m * a.res_ct + k, rv);
+                load_pack<float, 4>(res + (int64_t)m * a.res_ct + k, rv);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) v[t] += rv[t];
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-            store_pack<T, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+            store_pack<float, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
         } else {
             for (int t = 0; t < 4 && k + t < a.K; ++t) {
                 float f = v[t];
-                if (res) f += to_f32(res[(int64_t)m * a.res_ct + k + t]);
-                f = apply_act(f, a.act);
-                T o;
-                from_f32(f, o);
-                y[(int64_t)m * a.y_ct + a.y_coff + k + t] = o;
+                if (res) f += res[(int64_t)m * a.res_ct + k + t];
+                y[(int64_t)m * a.y_ct + a.y_coff + k + t] = apply_act(f, a.act);
             }
         }
     };
@@ -253,23 +223,14 @@ __device__ __forceinline__ void dconv_body(const OpArgs &a) {
         }
     }
 }
-template <typename T, int TN, int TM, int WN, int WM, int WK, int D, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
-    dconv_body<T, TN, TM, WN, WM, WK, D, MODE>(a);
-}
-// several operators of equal launch shape in one launch, one per value of blockIdx.y
-template <typename T, int TN, int TM, int WN, int WM, int WK, int D, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK) dconv_pair_kernel(OpArgsPair p) {
-    dconv_body<T, TN, TM, WN, WM, WK, D, MODE>(p.a[blockIdx.y]);
-}
 
-// The fp32 tilings, widest first: channels x pixels of a workgroup, waves along the reduction.
+// The tilings, widest first: channels x pixels of a workgroup, waves along the reduction.
 struct DcTile { int bn, bm, wk, waves; };
 constexpr DcTile DC_F32[] = {{64, 64, 1, 4}, {32, 32, 4, 4}, {32, 16, 4, 4}, {16, 16, 8, 8}};
 
 }  // namespace
 
-// fp32: the tiling of least estimated time, 0 if the element-wise gather's table is too small for the layer (it then
+// The tiling of least estimated time, 0 if the element-wise gather's table is too small for the layer (it then
 // stays with one thread per output).  Estimate in cycles of a compute unit: the matrix instructions of its workgroups, or
 // the operand bytes of its workgroups at 64 per cycle, whichever is longer, plus the exchange of the partial sums.  256
 // units; with fewer workgroups than units the time is that of one workgroup.
@@ -301,10 +262,10 @@ int launch_dconv_f32(const OpArgs &a, void *stream) {
     const dim3 grid(a.grid_x);
     auto go = [&]<int MODE>() {
         switch (a.wk) {
-            case 1: launch((dconv_kernel<float, 2, 2, 2, 2, 1, 4, MODE>), grid, dim3(256), 0, st, a); break;
-            case 2: launch((dconv_kernel<float, 2, 2, 1, 1, 4, 4, MODE>), grid, dim3(256), 0, st, a); break;
-            case 3: launch((dconv_kernel<float, 2, 1, 1, 1, 4, 6, MODE>), grid, dim3(256), 0, st, a); break;
-            default: launch((dconv_kernel<float, 1, 1, 1, 1, 8, 8, MODE>), grid, dim3(512), 0, st, a); break;
+            case 1: launch((dconv_kernel<2, 2, 2, 2, 1, 4, MODE>), grid, dim3(256), 0, st, a); break;
+            case 2: launch((dconv_kernel<2, 2, 1, 1, 4, 4, MODE>), grid, dim3(256), 0, st, a); break;
+            case 3: launch((dconv_kernel<2, 1, 1, 1, 4, 6, MODE>), grid, dim3(256), 0, st, a); break;
+            default: launch((dconv_kernel<1, 1, 1, 1, 8, 8, MODE>), grid, dim3(512), 0, st, a); break;
         }
     };
     if (a.C % 16 == 0) go.template operator()<DC_UNIFORM>();

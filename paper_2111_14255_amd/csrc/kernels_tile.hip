@@ -850,7 +850,6 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
 #pragma unroll
         for (int i = 0; i < XPS; ++i) issue_none();
     }
-    const int ns = nc * SPC;
     auto stage = [&]<int I>(int c) {
         // the stages of a chunk are a multiple of the filter buffers, so stage I of every chunk uses buffer I % NBUF
         const bool last = c + 1 == nc;
@@ -867,7 +866,6 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
         compute(I * KD, I % NBUF, c & 1);
     };
     static_assert(SPC % NBUF == 0 && NBUF == 3, "buffer of a stage");
-    (void)ns;
     for (int c = 0; c < nc; ++c) {
         [&]<int... I>(std::integer_sequence<int, I...>) { (stage.template operator()<I>(c), ...); }(std::make_integer_sequence<int, SPC>{});
         xs += TK * 2;
@@ -1063,7 +1061,6 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     a.tile_order = ((double)a.K * a.gemm_k > (double)a.N * a.H * a.W * a.C) ? 1 : 0;
     a.grid_x = cdiv(pixel_tiles(t, a, panel) * (a.n_pad / t.bn) * split, XCDS) * XCDS;
     a.grid_y = a.grid_z = 1;
-    a.wk = 1;
     set_walk(a);
     return true;
 }

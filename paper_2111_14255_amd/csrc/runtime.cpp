@@ -77,7 +77,6 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
     p.grid_y = p.grid_z = 1;
     p.block = 256;
     p.split_k = 1;
-    p.wk = 1;
     const bool vec = p.vec_a != 0;
     const double macs = (double)M * Kc * gemm_k;
     // Weight streaming on the vector units: they have two products to form per filter element and pixel, which hides under the
@@ -258,8 +257,7 @@ int32_t finalize_model(mt_model *m) {
                 } else {
                     // a fully connected layer is a 1x1 convolution over a 1x1 map with H*W*C channels
                     if (d.kind == MT_FC) { p.H = p.W = 1; p.C = gemm_k; p.x_ct = gemm_k; p.R = p.S = 1; }
-                    // im2col gather mode: 2 = tile inside one tap (C % 64 == 0, at most 64 taps), 1 = 16-byte chunks, 0 = element-wise
-                    p.vec_a = (p.C % IGEMM_BK == 0 && p.R * p.S <= 64) ? 2 : (p.C % 8 == 0) ? 1 : 0;
+                    p.vec_a = p.C % 8 == 0 ? 1 : 0;
                     const int sform = (d.kind == MT_CONV && groups == 1 && in.c == 3 && res_ct == 0 && ctot % 8 == 0 && d.out_c_offset % 8 == 0)
                                           ? stem_form(R, S, sw, in.w, pw, o.out_c) : 0;
                     const StemGeom sg = stem_geom(R, S, sform);
@@ -653,7 +651,6 @@ constexpr int N_PIPES = 4;
 struct PlainPool {
     hipStream_t main_stream = nullptr;
     hipStream_t tenant[MT_MAX_TENANTS] = {};
-    std::vector<hipStream_t> parked;
     std::vector<hipStream_t> rep;                   // one stream of every class, in the order the classes were found
     std::vector<std::vector<hipStream_t>> spare;    // per class: classified streams not handed out yet
 };

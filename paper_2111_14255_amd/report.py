@@ -443,8 +443,8 @@ def report_layers(args):
 def _family_of(kernel_name):
     """The name mt_op_form gives a kernel, from its name in a trace (demangled or not)."""
     import re
-    m = re.search(r"(igemm|tile|patch|ring|dconv)_(?:pair_)?kernel<[^,]+, ([\d, ]+)", kernel_name) or \
-        re.match(r"_ZN2mt\d+(igemm|tile|patch|ring|dconv)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)((?:Li\d+E)+)", kernel_name)
+    m = re.search(r"(igemm|tile|patch|ring|dconv)_(?:pair_)?kernel<(?:[A-Za-z_][^,]*, )?([\d, ]+)", kernel_name) or \
+        re.match(r"_ZN2mt\d+(igemm|tile|patch|ring)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)((?:Li\d+E)+)", kernel_name)
     if m:
         kind, p = m.group(1), [int(v) for v in re.findall(r"\d+", m.group(2))]
         if kind == "ring":

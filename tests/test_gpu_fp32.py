@@ -36,6 +36,9 @@ CASES = [
     ("registers_32x16_pieces_c20", 4, 28, 28, 20, 24, 3, 1, 1, 1),
     ("registers_32x16_elements_c3", 1, 29, 29, 3, 70, 3, 1, 1, 1),
     ("registers_16x16_pieces_c20", 1, 7, 7, 20, 8, 3, 1, 1, 1),
+    ("registers_64x64_uniform_1x17", 8, 60, 60, 16, 64, (1, 17), 1, (0, 8), 1),
+    ("registers_64x64_pieces_c12_17x1", 8, 60, 60, 12, 64, (17, 1), 1, (8, 0), 1),
+    ("registers_32x32_pieces_c20_3x18", 2, 40, 40, 20, 70, (3, 18), 1, (1, 9), 1),
     ("gemv_one_pixel_one_channel", 1, 1, 1, 16, 1, 1, 1, 0, 1),
 ]
 
