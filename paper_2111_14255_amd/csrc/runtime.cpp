@@ -465,7 +465,7 @@ struct StagePlan {
     std::vector<IssueItem> items;
     std::vector<int> streams;       // distinct streams used, ascending
     std::vector<std::vector<IssueItem>> by_stream;   // items of each stream (index = tenant that owns the stream), in issue order
-    std::vector<std::vector<int>> level;             // their levels (item_levels)
+    std::vector<std::vector<int>> level;             // their levels, filled on first use (find_levels)
     int prev_stage = -1;            // latest earlier stage that launched anything (-1: none)
     std::array<hsa_queue_t *, MT_MAX_TENANTS> queue_of{};   // queue of each stream
 };
@@ -870,6 +870,11 @@ std::vector<int> item_levels(const mt_ctx *ctx, const std::vector<IssueItem> &it
     return level;
 }
 
+void find_levels(const mt_ctx *ctx, StagePlan &sp) {
+    if (sp.level.empty())
+        for (const auto &items : sp.by_stream) sp.level.push_back(item_levels(ctx, items));
+}
+
 // The argument memory of the plan of mt_run_static_scratch goes back to what the schedule holds for it.
 void drop_plan(mt_ctx *ctx, mt_schedule *s, RunPlan &p) {
     if (&p == s->static_plan_of() && p.args.bytes > s->static_args.bytes) std::swap(p.args, s->static_args);
@@ -942,8 +947,9 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
     std::set<hsa_queue_t *> seen;
     int first_stage = -1;
     for (int st = 0; st < s->n_stages && rc == MT_OK; ++st) {
-        const StagePlan &sp = s->stages[st];
+        StagePlan &sp = s->stages[st];
         if (sp.items.empty()) continue;
+        find_levels(ctx, sp);
         if (first_stage < 0) first_stage = st;
         std::vector<hsa_queue_t *> queues;
         for (int sm : sp.streams)
@@ -1108,7 +1114,8 @@ void reserve_static(mt_ctx *ctx, mt_schedule *s) {
     if (counters > 0) { bytes += arg_bytes(0); ++signals; }
     const int timed = ((s->flags & MT_SCHED_TIME_FIRST_OP) ? 1 : 0) + ((s->flags & MT_SCHED_TIME_TENANTS) ? 1 : 0);
     signals += (size_t)timed * s->n_tenants;
-    for (const StagePlan &sp : s->stages) {
+    for (StagePlan &sp : s->stages) {
+        find_levels(ctx, sp);
         std::map<hsa_queue_t *, std::pair<int, size_t>> ends;            // per queue: latest level, launches in it
         for (int sm : sp.streams) {
             const auto &items = sp.by_stream[sm];
@@ -2044,7 +2051,6 @@ static int32_t make_schedule(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, c
         std::sort(sp.streams.begin(), sp.streams.end());
         sp.by_stream.assign(n_tenants, {});
         for (const IssueItem &it : sp.items) sp.by_stream[it.stream].push_back(it);
-        for (const auto &items : sp.by_stream) sp.level.push_back(item_levels(ctx, items));
         for (int sm : sp.streams)
             if (unit_of[st][sm] >= 0) sp.queue_of[sm] = s->masked->queues[unit_of[st][sm]];
         lane_plan(ctx->lanes, sp);
