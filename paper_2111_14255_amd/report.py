@@ -2,14 +2,14 @@
 
   search   best-so-far latency against evaluations for coordinate descent and random search, and the wall time of
            the search (the analogues of the paper's search-curve figure and search-overhead table, Sec. IV)
-  issue    breadth-first against depth-first issue of the same schedules, with the host issue time and the stall of
-           every stream behind the main thread (Sec. III-D), and the same schedules replayed as a device graph
+  issue    breadth-first against depth-first issue of the same schedules, with the host issue time and the time to the
+           first operator of every stream (Sec. III-D), stage barriers on the device and on the host
   mixes    sequential, all-concurrent and searched latency of the paper's tenant combinations (Tables I-II)
   fusion   every tenant alone and all tenants together, with and without the fused launches of neighbouring operators
            and with wave priorities (the runtime's additions to the paper's method)
 
   barriers what a stage barrier costs (Sec. III-B "Stage"): the probe of mt_probe_barrier_cost for 1..8 streams and
-           even-split staged schedules of a workload under the event, counter and host-side barriers
+           even-split staged schedules of a workload with barriers on the device and on the host
   layers   per-operator table of one tenant: GEMM shape, kernel, time alone on the GPU, fraction of its own roofline bound
   streams  which streams can run side by side (mt_probe_stream_conflicts: the dispatch pipes), and a workload in one
            stage on 1 .. n streams, with the tenants that share a stream issued one after the other or co-issued
@@ -136,24 +136,23 @@ def report_issue(args):
     print("Command: `python -m paper_2111_14255_amd.report issue --config %s --rounds %d --candidates %d --runs %d`"
           % (cfg.name, args.rounds, args.candidates, args.runs))
     print()
-    print("Median of 40 runs, ms.  `host issue` is the time the issuing thread(s) spend launching one pass.  Under "
-          "depth-first issue the main thread launches all of stream 0, then all of stream 1, ...: stream k cannot start "
-          "before the main thread has issued every operator of the streams before it, which is the stall the paper's "
-          "Fig. 5 measures; breadth-first issue hands every stream its first operator within one round.")
+    print("Median of 40 runs, ms.  `host issue` is the time spent publishing one pass, host-side barriers included.  The paper's "
+          "main thread launches operator by operator: under depth-first issue stream k cannot start before every operator of the "
+          "streams before it is launched, which is the stall its Fig. 5 measures.  Here the packets of a stage are copied queue by "
+          "queue (0.03 us each) in either order, so the orders differ by noise.")
     print()
     print("| schedule | order | mode | makespan | min | p90 | host issue |")
     print("|---|---|---|---|---|---|---|")
     rows = [("all-concurrent (1 stage)", [[] for _ in specs], 1), ("even split", even, cfg.n_stages), ("searched", rho, cfg.n_stages)]
     for label, ptr, ns in rows:
         for order, oname in ((B.MT_ISSUE_BFS, "BFS"), (B.MT_ISSUE_DFS, "DFS")):
-            for flags, mode in ((0, "streams"), (B.MT_SCHED_PARALLEL_ISSUE, "streams, one issuing thread per stream"),
-                                (B.MT_SCHED_PARALLEL_ISSUE | B.MT_SCHED_HOST_BARRIER, "the same, stage barriers on the host"),
-                                (B.MT_SCHED_GRAPH, "graph replay")):
+            for flags, mode in ((0, "stage barriers on the device"),
+                                (B.MT_SCHED_PARALLEL_ISSUE | B.MT_SCHED_HOST_BARRIER, "stage barriers on the host")):
                 r = _time(ctx, ctx.schedule(ptr, ns, order=order, flags=flags), inputs, outputs)
                 print("| %s | %s | %s | %.4f | %.4f | %.4f | %.4f |" % (label, oname, mode, r["median"], r["min"], r["p90"], r["issue"]))
     print()
-    print("Time from the start of a pass to the end of each tenant's first operator, all-concurrent schedule, one issuing "
-          "thread, median of 40 runs, us (the paper's Fig. 5 reports 102.75 -> 51.23 us and 177.27 -> 51.23 us for its second "
+    print("Time from the start of a pass to the end of each tenant's first operator, all-concurrent schedule, "
+          "median of 40 runs, us (the paper's Fig. 5 reports 102.75 -> 51.23 us and 177.27 -> 51.23 us for its second "
           "and third stream on its GPU):")
     print()
     print("| order | " + " | ".join("%s (%d ops)" % (m.name, l) for m, l in zip(specs, lens)) + " |")
@@ -180,11 +179,11 @@ def report_mixes(args):
     print()
     print("Median makespan of 40 runs, ms; speed-up = sequential / schedule, as the paper's tables print it.  "
           "`searched` = coordinate descent over the pointer matrix (4 stages); `+shares` searches the number of streams in "
-          "use per stage and the per-tenant CU shares as well, in the mode it is then run in: one issuing host thread per stream, stage barriers taken on the host.  The paper's own numbers (other GPUs, other kernels) are "
+          "use per stage and the per-tenant CU shares as well, with stage barriers on the host.  The paper's own numbers (other GPUs, other kernels) are "
           "context only: its coordinate-descent speed-ups for these rows are 1.37, 1.49, 1.49, 1.31, 1.37, 1.63, 1.72 on Titan V.")
     print()
-    print("| tenants | launches | sequential | all-concurrent | searched | searched+graph | searched+shares | streams | shares | best speed-up | search s |")
-    print("|---|---|---|---|---|---|---|---|---|---|---|")
+    print("| tenants | launches | sequential | all-concurrent | searched | searched+shares | streams | shares | best speed-up | search s |")
+    print("|---|---|---|---|---|---|---|---|---|---|")
     names = args.only.split(",") if args.only else list(configs.PAPER_MIXES)
     for name in names:
         cfg = configs.ALL[name]
@@ -195,9 +194,6 @@ def report_mixes(args):
         rho, _, _ = ctx.search(inputs, outputs, cfg.n_stages, rounds=args.rounds, candidates=args.candidates, runs=args.runs,
                                warmup=1, seed=cfg.seed)
         s1 = _time(ctx, ctx.schedule(rho, cfg.n_stages), inputs, outputs)
-        rho_g, _, _ = ctx.search(inputs, outputs, cfg.n_stages, rounds=args.rounds, candidates=args.candidates, runs=args.runs,
-                                 warmup=1, seed=cfg.seed, flags=B.MT_SCHED_GRAPH)
-        s2 = _time(ctx, ctx.schedule(rho_g, cfg.n_stages, flags=B.MT_SCHED_GRAPH), inputs, outputs)
         rho_s, _, _, shares, conc = ctx.search(inputs, outputs, cfg.n_stages, rounds=args.rounds, candidates=args.candidates,
                                                runs=args.runs, warmup=1, seed=cfg.seed, cu_share_rounds=2,
                                                search_concurrency=True,
@@ -206,9 +202,9 @@ def report_mixes(args):
         s3 = _time(ctx, ctx.schedule(rho_s, cfg.n_stages, concurrency=conc, cu_share=shares,
                                       flags=B.MT_SCHED_PARALLEL_ISSUE | B.MT_SCHED_HOST_BARRIER),
                    inputs, outputs)
-        best = min(s1["median"], s2["median"], s3["median"])
-        print("| %s | %d | %.4f | %.4f | %.4f | %.4f | %.4f | %d | %s | %.2f | %.1f |" % (
-            " + ".join(cfg.tenants), sum(ctx.lens()), seq["median"], allc["median"], s1["median"], s2["median"], s3["median"],
+        best = min(s1["median"], s3["median"])
+        print("| %s | %d | %.4f | %.4f | %.4f | %.4f | %d | %s | %.2f | %.1f |" % (
+            " + ".join(cfg.tenants), sum(ctx.lens()), seq["median"], allc["median"], s1["median"], s3["median"],
             conc[0], "/".join(str(v) for v in shares), seq["median"] / best, dt))
         sys.stdout.flush()
         ctx.close()
@@ -230,8 +226,8 @@ def report_streams(args):
     print()
     print("Twelve new unmasked streams; every cell: us per round of 16 rounds in which the two streams launch one one-workgroup "
           "kernel each, every stream recording its own end and the host waiting (the diagonal: the stream alone).  A pair at "
-          "twice the single figure is served one stream at a time: the two sit on the same dispatch pipe.  The library "
-          "classifies its tenant streams this way when it creates them and gives tenant index i a stream of class i % 4.")
+          "twice the single figure is served one stream at a time: the two sit on the same dispatch pipe.  Passes run on four "
+          "queues of the library's own, one per pipe; the streams of the barrier probe are classified this way.")
     print()
     m = 12
     single = (C.c_float * m)()
@@ -251,8 +247,8 @@ def report_streams(args):
     print()
     print("## One stage on c streams, tenants of a stream one after the other or co-issued")
     print()
-    print("Median makespan of 30 runs, ms; one issuing host thread per stream.  Co-issue (`MT_SCHED_COISSUE`): two tenants of "
-          "equal architecture on one stream run operator i of both as one launch.  `inside` = operators that ran inside a "
+    print("Median makespan of 30 runs, ms.  More than four streams share the four queues.  Co-issue (`MT_SCHED_COISSUE`): up to four tenants of "
+          "equal architecture on one stream run operator i of all of them as one launch.  `inside` = operators that ran inside a "
           "mate's launch, of %d.  The last column: md5 of all tenants' output bits, which must not change along a row or a column." % sum(ctx.lens()))
     print()
     print("| streams | one after the other | co-issued | inside | ratio | output bits |")
@@ -311,7 +307,7 @@ def report_fusion(args):
         sys.stdout.flush()
         ctx.close()
     print()
-    print("## All tenants concurrent (one stage, one issuing thread per stream, no CU masks)")
+    print("## All tenants concurrent (one stage, no CU masks)")
     print()
     ctx, specs, inputs, outputs = _setup(cfg)
     n = len(specs)
@@ -371,12 +367,11 @@ def report_barriers(args):
     print("## %s (%s, batch %d, %s): even split into 1 / 2 / 4 / 8 stages, median makespan of 21 runs, ms" % (
         cfg.name, " + ".join(cfg.tenants), cfg.batch, cfg.dtype))
     print()
-    print("main thread = the paper's single issuing thread (Sec. III-D); threads = one issuing host thread per stream; host = the "
-          "issuing thread of a stream waits on the host for the events of the stage before.  Outputs are bit-identical in every cell.")
+    print("Device = the queues of a stage hold a packet that waits for the completion signals of the stage before; host = the host "
+          "waits for them and then publishes the stage.  Outputs are bit-identical in every cell.")
     print()
     PI = B.MT_SCHED_PARALLEL_ISSUE
-    forms = (("events, main thread", 0), ("counter, main thread", B.MT_SCHED_COUNTER_BARRIER), ("events, threads", PI),
-             ("counter, threads", PI | B.MT_SCHED_COUNTER_BARRIER), ("host, threads", PI | B.MT_SCHED_HOST_BARRIER))
+    forms = (("device", 0), ("host", PI | B.MT_SCHED_HOST_BARRIER))
     print("| stages | " + " | ".join(f[0] for f in forms) + " |")
     print("|---|" + "---|" * len(forms))
     for ns in (1, 2, 4, 8):
@@ -407,7 +402,7 @@ def report_layers(args):
     print()
     print("Every operator 1 + 20 times back to back on one stream between two events (`mt_profile_ops`), best of 3 passes.  M x N x K = "
           "pixels x output channels x reduction length; bound = max(flops / 2.5 PFLOP/s, bytes / 8 TB/s) of the operator's algorithmic "
-          "work; an empty dependent launch takes about 3.5 us on this machine, which a single short kernel cannot go below.")
+          "work; a launch through HIP costs the host 2.5 to 3 us, which a single short kernel cannot go below here.")
     print()
     print("| op | kind | M | N | K | window | kernel | split | workgroups | us | bound us | frac | TFLOP/s | GB/s |")
     print("|---|---|---|---|---|---|---|---|---|---|---|---|---|---|")
@@ -584,10 +579,9 @@ def report_benchsum(args):
           "`python -m paper_2111_14255_amd.report benchsum --files <their outputs>`.")
     print()
     print("Makespan = mean of the timed steps, ms; img/s from the host's clock around the timed steps.  Rows of one workload that "
-          "share a suffix ran in the same mode: (none) = the headline mode (one issuing host thread per stream, host-side stage "
+          "share a suffix ran in the same mode: (none) = the headline mode (host-side stage "
           "barriers, fused operator pairs; searched = pointers + streams in use + CU shares + wave priorities, leaders re-measured "
-          "in a play-off), +main_thread = the paper's single issuing thread on plain streams (pointer search only), +graph = "
-          "whole-schedule graph replay.  `one stage` = the searched pointer matrix puts every operator into stage 1.")
+          "in a play-off), +plain = one launch per operator, stage barriers on the device (pointer search only).  `one stage` = the searched pointer matrix puts every operator into stage 1.")
     print()
     for f in args.files.split(","):
         d = json.loads(open(f).read().strip().splitlines()[-1])
