@@ -299,6 +299,16 @@ def test_op_form_names_the_kernel_and_tells_a_split_from_a_ring(dtype, n, hw, c,
     m.close()
 
 
+@pytest.mark.parametrize("arch,batch,mib", [("resnet101", 1, 0), ("resnet50", 64, 1.26), ("resnet101", 128, 2.51), ("vgg16", 1, 6.51), ("vgg16", 12, 4.51),
+                                            ("vgg16", 128, 12.02), ("inceptionv3", 48, 0.95), ("alexnet", 6, 10.02), ("mobilenetv2", 1, 0)])
+def test_what_a_tenant_takes_of_the_fixed_scratch_array(arch, batch, mib):
+    """Workspaces of at most a quarter of the array are in it; sets of tenants that used to fit still do."""
+    m = api.Model(zoo.BUILDERS[arch]("f16", batch))
+    sizes = [m.op_form(i).workspace_bytes for i in range(m.num_ops())]
+    m.close()
+    assert sum(v for v in sizes if v <= B.MT_STATIC_SCRATCH_BYTES // 4) <= mib * 2 ** 20
+
+
 def _model(ops, dtype=B.MT_F16, dims=(1, 8, 8, 8)):
     lib = B.load()
     h = C.c_void_p()
