@@ -143,7 +143,7 @@ mix = Mix([zoo.BUILDERS["mobilenetv2"]("f16", 1), wide_split_model() if split el
 assert bool(split_forms(mix, 1)) == split
 outs = [mix.ctx.make_output(t) for t in range(2)]
 keep, taken = [], []
-for i in range(48):
+for i in range(100):
     co = mix.ctx.schedule([[], []], 1, concurrency=[1 + i %% 2], flags=(B.MT_SCHED_FUSE_POOL, B.MT_SCHED_FUSE_EXPAND, B.MT_SCHED_TIME_TENANTS)[i %% 3])
     if i %% 5 == 4:
         mix.ctx.run_static_scratch(co, mix.inputs, outs)
@@ -162,8 +162,8 @@ print("no memory taken")
 
 @pytest.mark.parametrize("split", [False, True])
 def test_the_call_takes_no_device_memory(split):
-    """In a process of its own, from its first call on.  The arguments of a schedule's packets take some 60 KiB, in pieces of
-    1 MiB: with these many schedules several are taken, all of them before the calls."""
+    """In a process of its own, from its first call on.  The arguments of a schedule's packets take some 45 KiB, and device memory
+    is handed out 2 MiB at a time: these many schedules take several such pieces, none of them in a call."""
     here = os.path.dirname(os.path.abspath(__file__))
     r = subprocess.run([sys.executable, "-c", MEASURE % (os.path.dirname(here), here, split)], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "no memory taken" in r.stdout, r.stdout + r.stderr
