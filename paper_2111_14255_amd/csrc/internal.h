@@ -72,44 +72,70 @@ inline bool is_gemm_kernel(int32_t id) {
            id == K_IGEMM_PW || id == K_PCONV;
 }
 
+// Exact unsigned division by d without a divide: n / d = (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); see make_divisor().
+struct Divisor {
+    uint32_t d, m, s1, s2;
+};
+
+// What the workgroups of a tile kernel need to find their tile and operands, worked out when the layer is planned: none of it
+// depends on the workgroup, and a division by a number that is not known at compile time is some 30 dependent instructions.
+struct TileWalk {
+    uint32_t total, per_xcd;     // workgroups with work, and a contiguous range of them per XCD
+    uint32_t pixels;             // N * P * Q
+    uint32_t x_bytes, w_bytes;   // input tensor (all of its channels), packed filter bank of a group
+    uint32_t flat;               // 1: output pixel m reads input pixel m (1x1 windows, stride 1, not walked quad by quad)
+    uint32_t units, per;         // what a split cuts (stages, rows of a ring, 64-channel chunks of a patch), and how many a workgroup takes
+    Divisor split, tiles;        // workgroup -> tile; tile -> (slow, fast) index
+    Divisor pq, q;               // pixel -> (image, row, column); patches: q the panel's columns, pq the map's rows
+    Divisor c;                   // reduction index -> (tap, channel)
+    uint32_t adv_t, adv_c;       // taps and channels from one stage (row of a wave) to the next
+    uint32_t inv_s;              // mulhi(tap, inv_s) = tap / S; 0 for S == 1
+    Divisor panel_tiles;         // patches: pixel tile -> (panel, tile of it)
+    uint32_t inv_pw, inv_h;      // patches: 2^20 over the patch's row and over H + 1, rounded up
+};
+
 // Everything a launcher needs for one operator.  Pointers are resolved per run (the first operator may
 // read the caller's input buffer, the last one writes the caller's output buffer).
 struct OpArgs {
-    int32_t kind, kernel_id, dtype;
-    int32_t N, H, W, C;          // input tensor; for a grouped convolution C is the channel count of one group
+    // What a tile kernel reads before its first load stands together: one trip through the scalar cache brings it.
+    const void *x;
+    const void *w;
+    TileWalk walk;               // tile kernels
+    int32_t tile_order;          // 0: channel tile fastest (an XCD shares activation tiles), 1: pixel tile fastest (shares filter tiles)
+    int32_t pool2;               // 1: the epilogue applies a 2x2 / stride-2 max pooling; pixels are then walked quad by quad and y is the pooled tensor
+    int32_t k_pad;               // packed weight row length (multiple of the k tile)
     int32_t x_ct, x_coff;        // channels per pixel of the input buffer and first channel read (x_ct == C, 0 unless grouped)
-    int32_t groups;              // launches of this operator (grouped convolution), 1 otherwise
-    float lrn_alpha, lrn_beta, lrn_k;
-    int32_t K, R, S;             // output channels written, window
-    int32_t P, Q;                // output spatial size
+    int32_t H, W, C;             // input map; for a grouped convolution C is the channel count of one group
+    int32_t R, S;                // window
     int32_t sh, sw, ph, pw;
+    int32_t N, P, Q;             // images, output map
+    int32_t panel;               // patch-staged 3x3 layers: columns of a panel (kernels_tile.hip)
+    int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
+    // epilogue
+    int32_t split_k;
+    int32_t K;                   // output channels written
     int32_t act;
     int32_t res_ct;              // channel count of the residual tensor (0 = no residual)
     int32_t y_coff, y_ct;        // channel offset / channel count of the output tensor
-    int32_t vec;                 // channels per thread of the channel-wise kernels (1, 4 or 8)
-    // implicit GEMM
-    int32_t gemm_k;              // R*S*C
-    int32_t k_pad;               // packed weight row length (multiple of the k tile)
-    int32_t n_pad;               // packed weight rows (multiple of the channel tile)
-    int32_t split_k;
-    int32_t wk;                  // fp32 convolution on operands from memory: its tiling (dconv_f32_plan), 0: another kernel
-    int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
-    int32_t form;                // tile and staging of the tile kernels (kernels_tile.hip), -1: another kernel
-    int32_t panel;               // patch-staged 3x3 layers: columns of a panel (kernels_tile.hip)
-    int32_t pool2;               // 1: the epilogue applies a 2x2 / stride-2 max pooling; pixels are then walked quad by quad and y is the pooled tensor
-    // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
-    // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
-    uint32_t divq_m, divq_s1, divq_s2, divpq_m, divpq_s1, divpq_s2;
-    int32_t tile_order;          // 0: channel tile fastest (an XCD shares activation tiles), 1: pixel tile fastest (shares filter tiles)
-    int32_t vec_a;               // im2col rows of a 16-bit type: 1 gathered in 16-byte pieces or more (C % 8 == 0), 0 element by element
-    int32_t grid_x, grid_y, grid_z, block;
-    const void *x;
-    const void *w;
     const float *bias;
     const void *res;
     void *y;
     float *ws;                   // split-K partial sums
     uint32_t *counters;          // split-K arrival counters, one per output tile, zero between launches
+    // the other kernels, and the launchers
+    int32_t kind, kernel_id, dtype;
+    int32_t groups;              // launches of this operator (grouped convolution), 1 otherwise
+    float lrn_alpha, lrn_beta, lrn_k;
+    int32_t vec;                 // channels per thread of the channel-wise kernels (1, 4 or 8)
+    int32_t gemm_k;              // R*S*C
+    int32_t n_pad;               // packed weight rows (multiple of the channel tile)
+    int32_t wk;                  // fp32 convolution on operands from memory: its tiling (dconv_f32_plan), 0: another kernel
+    int32_t form;                // tile and staging of the tile kernels (kernels_tile.hip), -1: another kernel
+    // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
+    // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
+    uint32_t divq_m, divq_s1, divq_s2, divpq_m, divpq_s1, divpq_s2;
+    int32_t vec_a;               // im2col rows of a 16-bit type: 1 gathered in 16-byte pieces or more (C % 8 == 0), 0 element by element
+    int32_t grid_x, grid_y, grid_z, block;
 };
 
 // Kernels whose filter bank is packed as [groups][n_pad][k_pad], rows zero padded.
@@ -129,6 +155,12 @@ inline void make_divisor(uint32_t d, uint32_t &m, uint32_t &s1, uint32_t &s2) {
     m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << l) - d)) / d + 1);
     s1 = l < 1 ? l : 1;
     s2 = l > 1 ? l - 1 : 0;
+}
+
+inline Divisor divisor(uint32_t d) {
+    Divisor v{d, 0, 0, 0};
+    make_divisor(d, v.m, v.s1, v.s2);
+    return v;
 }
 
 // Reduction index of the first-layer kernel (K_STEM): per filter row a run of `dummy` (1 in the aligned form, else 0) + 3 * S input elements, padded to
