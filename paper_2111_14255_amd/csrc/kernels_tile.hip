@@ -84,7 +84,113 @@ bool patch_stageable(const OpArgs &a) {
     return a.kind == MT_CONV && a.dtype != MT_F32 && a.groups <= 1 && a.R == 3 && a.S == 3 && a.sh == 1 && a.sw == 1 && a.ph == 1 && a.pw == 1 && a.C % TK == 0 && a.H <= 1024;
 }
 
-// What follows the main loop: the wave groups' partial sums meet, then those of the workgroups that share the tile, then
+// ---- epilogues ----------------------------------------------------------------------------------------------------
+// On small maps the epilogue is a chain of trips: partial sums through LDS to one wave group, from there through LDS to the threads that
+// store, and in between a trip to memory for bias and residual (0.6 to 0.9 of a layer's 4 us).  Here the threads that store add
+// the sums up themselves and asked for bias and residual before the reduction began.  us, before / now: ResNet-18 at one image
+// 108.6 / 105.8, ResNet-101, Inception-v3, MobileNetV2 and AlexNet together 535 / 518, eight ResNet-50 at batch 16 2689 / 2640.
+// Bias and residual of V consecutive channels of one output pixel.
+template <typename T, int V>
+struct Addend {
+    typedef std::conditional_t<sizeof(T) * V == 8, uint64_t, u32x4> Raw;     // V elements; fp32 only ever takes four of them
+    float bias[V];
+    Raw res;
+
+    __device__ __forceinline__ void load(const OpArgs &a, int m, int k, bool vec_ok) {
+#pragma unroll
+        for (int v = 0; v < V; v += 4) *reinterpret_cast<float4 *>(&bias[v]) = *reinterpret_cast<const float4 *>(a.bias + k + v);   // padded to n_pad
+        res = Raw{};
+        if (a.res != nullptr && !a.pool2 && vec_ok && m >= 0 && k < a.K) res = *reinterpret_cast<const Raw *>((const T *)a.res + (int64_t)m * a.res_ct + k);
+    }
+};
+
+// Whether V channels can be loaded and stored in one access: then they are also all inside the layer or all outside.
+template <int V>
+__device__ __forceinline__ bool whole_packs(const OpArgs &a) {
+    return (a.K % V == 0) & (a.y_ct % V == 0) & (a.y_coff % V == 0) & (a.res_ct % V == 0);
+}
+
+// Finished sums of V channels from k on of output pixel m, and of the pixels beside it: bias, residual, activation, one rounding,
+// store.  Pooling: the four pixels of a window are STRIDE lanes apart and m is the pooled pixel of all four.
+template <typename T, int V, int STRIDE>
+__device__ __forceinline__ void finish_pixel(const OpArgs &a, float (&v)[V], const Addend<T, V> &add, int m, int k, bool vec_ok, bool first_of_window) {
+#pragma unroll
+    for (int t = 0; t < V; ++t) v[t] += add.bias[t];
+    if (a.pool2) {
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            v[t] = fmaxf(v[t], -INFINITY);                 // a window without a number has no maximum, as in the pooling kernels
+            v[t] = fmaxf(v[t], __shfl_xor(v[t], STRIDE));
+            v[t] = fmaxf(v[t], __shfl_xor(v[t], 2 * STRIDE));
+        }
+        if (!first_of_window) return;
+    }
+    if (m < 0 || k >= a.K) return;
+    T *y = (T *)a.y + (int64_t)m * a.y_ct + a.y_coff + k;
+    if (vec_ok) {
+        if (a.res != nullptr && !a.pool2) {
+            const Pack<T, V> rp = __builtin_bit_cast(Pack<T, V>, add.res);
+#pragma unroll
+            for (int t = 0; t < V; ++t) v[t] += to_f32(rp.e[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < V; ++t) v[t] = apply_act(v[t], a.act);
+        store_pack<T, V>(y, v);
+    } else {
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            if (k + t >= a.K) continue;
+            float f = v[t];
+            if (a.res != nullptr && !a.pool2) f += to_f32(((const T *)a.res)[(int64_t)m * a.res_ct + k + t]);
+            f = apply_act(f, a.act);
+            T o;
+            from_f32(f, o);
+            y[t] = o;
+        }
+    }
+}
+
+// Place of channels 4 * c .. + 3 of pixel p in a [pixels][BN] block of partial sums in LDS, in floats: written by 16 lanes with
+// consecutive pixels and read by 16 lanes with consecutive channels, both without bank conflicts.
+template <int BN>
+__device__ __forceinline__ uint32_t sum_at(int p, int c) {
+    constexpr int SHARE = BN < 64 ? 64 / BN : 1;           // rows that fill the 64 banks
+    return (uint32_t)(p * BN + ((c ^ ((p / SHARE) & (BN / 4 - 1))) * 4));
+}
+
+// What follows the main loop where WK wave groups share the reduction: every group puts its partial sums into LDS, and the threads
+// that store add them up, in group order, with bias and residual already at hand.  A group's block of sums is BLOCK floats
+// after the one before it.
+template <int BN, int MF, int SUBN, int SUBM, typename Acc, int TN, int TM>
+__device__ __forceinline__ void publish_sums(const Acc (&acc)[TN][TM], float *sums, int wn, int wm, int frow, int fgrp) {
+    constexpr int GROUPS = MF == 32 ? 4 : 1;
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g)
+                *reinterpret_cast<float4 *>(&sums[sum_at<BN>(wm * SUBM + j * MF + frow, (wn * SUBN + i * MF) / 4 + (MF == 32 ? 2 * g + fgrp : fgrp))]) =
+                    make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+}
+
+template <int BN, int V, int WK>
+__device__ __forceinline__ void add_up(const float *sums, int block, int p, int c, float (&v)[V]) {
+    float4 part[WK][V / 4];
+#pragma unroll
+    for (int w = 0; w < WK; ++w)
+#pragma unroll
+        for (int h = 0; h < V / 4; ++h) part[w][h] = *reinterpret_cast<const float4 *>(&sums[w * block + sum_at<BN>(p, c * (V / 4) + h)]);
+#pragma unroll
+    for (int h = 0; h < V / 4; ++h) {
+        float4 s = part[0][h];
+#pragma unroll
+        for (int w = 1; w < WK; ++w) { s.x += part[w][h].x; s.y += part[w][h].y; s.z += part[w][h].z; s.w += part[w][h].w; }
+        v[4 * h] = s.x; v[4 * h + 1] = s.y; v[4 * h + 2] = s.z; v[4 * h + 3] = s.w;
+    }
+}
+
+// What follows the main loop otherwise: the wave groups' partial sums meet, then those of the workgroups that share the tile, then
 // bias, residual, activation, one rounding and the store.  pixel(ml) is the output pixel of tile row ml (the pooled pixel
 // of its window when the epilogue pools), negative for rows without one.
 template <typename T, int BN, int BM, int WN, int WM, int WK, int MF, typename Acc, int TN, int TM, typename Pixel>
@@ -186,13 +292,18 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         constexpr int EP_IT = (BM * CPR + NT - 1) / NT;
         // (16-bit types: a register quad, not a struct, which costs the wide tiles 12 to 32 registers and the tenants beside them 2 %)
         typedef std::conditional_t<sizeof(T) == 2, u32x4, Pack<T, 8>> Raw;
+        static_assert(NT % CPR == 0, "a thread stores the same channels of several pixels");
+        float bias[8];
+        const int k = n0 + (tid % CPR) * 8;
+        *reinterpret_cast<float4 *>(&bias[0]) = *reinterpret_cast<const float4 *>(a.bias + k);     // padded to n_pad
+        *reinterpret_cast<float4 *>(&bias[4]) = *reinterpret_cast<const float4 *>(a.bias + k + 4);
         Raw res_raw[EP_IT];
         const bool add_res = res != nullptr && !a.pool2;
         if (add_res) {
 #pragma unroll
             for (int it = 0; it < EP_IT; ++it) {
                 const int c = tid + it * NT;
-                const int m = pixel(min(c / CPR, BM - 1)), k = n0 + (c % CPR) * 8;
+                const int m = pixel(min(c / CPR, BM - 1));
                 const bool live = (c < BM * CPR) & (m >= 0) & (k < a.K);
                 res_raw[it] = live ? *reinterpret_cast<const Raw *>(res + (int64_t)m * a.res_ct + k) : Raw{};
             }
@@ -207,16 +318,15 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
                     for (int g = 0; g < GROUPS; ++g) {
                         const int ml = wm * SUBM + j * MF + frow;
                         const int kl = wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * fgrp) : (4 * fgrp));
-                        const float4 b = *reinterpret_cast<const float4 *>(a.bias + n0 + kl);
                         *reinterpret_cast<float4 *>(&et[ml * ELD + kl]) =
-                            make_float4(acc[i][j][g * 4 + 0] + b.x, acc[i][j][g * 4 + 1] + b.y, acc[i][j][g * 4 + 2] + b.z, acc[i][j][g * 4 + 3] + b.w);
+                            make_float4(acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
                     }
         }
         __syncthreads();
         if (a.pool2) {
             for (int c = tid; c < (BM / 4) * CPR; c += NT) {
                 const int r4 = c / CPR, col = (c % CPR) * 8;
-                const int m = pixel(r4 * 4), k = n0 + col;
+                const int m = pixel(r4 * 4);
                 if (m < 0 || k >= a.K) continue;
                 float v[8];
 #pragma unroll
@@ -229,7 +339,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
                     v[4] = fmaxf(v[4], hi.x); v[5] = fmaxf(v[5], hi.y); v[6] = fmaxf(v[6], hi.z); v[7] = fmaxf(v[7], hi.w);
                 }
 #pragma unroll
-                for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
+                for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t] + bias[t], a.act);
                 store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
             }
             return;
@@ -238,12 +348,14 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         for (int it = 0; it < EP_IT; ++it) {
             const int c = tid + it * NT;
             const int row = c / CPR, col = (c % CPR) * 8;
-            const int m = pixel(min(row, BM - 1)), k = n0 + col;
+            const int m = pixel(min(row, BM - 1));
             if (c >= BM * CPR || m < 0 || k >= a.K) continue;
             float v[8];
             const float4 lo = *reinterpret_cast<const float4 *>(&et[row * ELD + col]);
             const float4 hi = *reinterpret_cast<const float4 *>(&et[row * ELD + col + 4]);
             v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] += bias[t];
             if (add_res) {
                 const Pack<T, 8> rp = __builtin_bit_cast(Pack<T, 8>, res_raw[it]);
 #pragma unroll
@@ -370,7 +482,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     static_assert(WQ * NW * 8 == KD * BN && XQ * NW * 8 == KD * BM, "the waves share the loads of a stage evenly");
     constexpr int L = WQ + XQ;
     constexpr int W_BYTES = KD * BN * 128, X_BYTES = KD * BM * 128, STAGE = W_BYTES + X_BYTES;
-    constexpr int RED_BYTES = (WK - 1) * BN * BM * 4, ELD = BN + 4, EP_BYTES = BM * ELD * 4;
+    constexpr int RED_BYTES = (WK > 1 ? WK : 0) * BN * BM * 4, ELD = BN + 4, EP_BYTES = BM * ELD * 4;
     constexpr int LDS_BYTES = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES});
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
@@ -379,11 +491,30 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
+    const int frow = lane % MF, fgrp = lane / MF;          // operand row and reduction group of this lane
 
     int tile, z, tn_idx, tm_idx;
     if (!find_tile(a, tile, z, tn_idx, tm_idx)) return;
     const int M = (int)a.walk.pixels;
     const int n0 = tn_idx * BN, m0 = tm_idx * BM;
+
+    // Epilogue of this form: from the accumulators themselves where a wave has one 16 x 16 product, from the sums in LDS where wave groups
+    // share the reduction.  Bias and residual are requested ahead of the operands (in front of them, so that the waits of the
+    // reduction count the same loads) if a thread has one piece of the tile to store.
+    constexpr bool DIRECT = WK == 1 && MF == 16 && TN == 1 && TM == 1, SUMS = WK > 1;
+    constexpr int NT = 64 * NW, V = !DIRECT && ES == 2 && BN * BM >= 8 * NT ? 8 : 4, PIECES = BN / V, STORING = DIRECT ? NT : std::min(NT, BN * BM / V);
+    constexpr int EP_IT = DIRECT ? 1 : BN * BM / V / STORING;
+    constexpr bool AHEAD = DIRECT || (SUMS && EP_IT == 1);
+    const bool unsplit = a.walk.split.d == 1, vec_ok = whole_packs<V>(a), storing = STORING == NT || tid < STORING;
+    auto pixel = [&](int ml) {
+        const int m = m0 + ml;
+        return m < M ? (a.pool2 ? m >> 2 : m) : -1;
+    };
+    auto my_row = [&](int it) { return DIRECT ? frow : (tid + it * NT) / PIECES; };
+    const int my_k = n0 + (DIRECT ? wn * 16 + 4 * fgrp : (tid % PIECES) * V);
+    Addend<T, V> add;
+    if (AHEAD && unsplit && storing) add.load(a, pixel(my_row(0)), my_k, vec_ok);
+
     const int st0 = z * (int)a.walk.per;
     const int ns = min((int)a.walk.units, st0 + (int)a.walk.per) - st0;
 
@@ -493,7 +624,6 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
 #pragma unroll
             for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
 
-    const int frow = lane % MF, fgrp = lane / MF;          // operand row and reduction group of this lane
     struct Frag { u32x4 w[TN], x[TM]; };
     const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), xrow = (uint32_t)(W_BYTES + (wm * SUBM + frow) * 128);
     const uint32_t swz = (uint32_t)((frow >> 1) & 7);
@@ -534,12 +664,34 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
         rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
         ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
     }
+    if constexpr (DIRECT) {
+        if (unsplit) {
+            float v[4] = {acc[0][0][0], acc[0][0][1], acc[0][0][2], acc[0][0][3]};
+            return finish_pixel<T, 4, 1>(a, v, add, pixel(frow), my_k, vec_ok, (frow & 3) == 0);
+        }
+    }
     wait_and_meet<0>();                                    // the tile buffers are free
-
-    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
-        const int m = m0 + ml;
-        return m < M ? (a.pool2 ? m >> 2 : m) : -1;
-    });
+    if constexpr (SUMS) {
+        if (unsplit) {
+            float *sums = reinterpret_cast<float *>(&smem[0]);
+            Addend<T, V> adds[EP_IT];
+            if constexpr (AHEAD) adds[0] = add;
+#pragma unroll
+            for (int it = 0; !AHEAD && it < EP_IT; ++it) adds[it].load(a, pixel(my_row(it)), my_k, vec_ok);
+            publish_sums<BN, MF, SUBN, SUBM>(acc, sums + wk * (BN * BM), wn, wm, frow, fgrp);
+            __syncthreads();
+            if (!storing) return;
+#pragma unroll
+            for (int it = 0; it < EP_IT; ++it) {
+                const int row = my_row(it);
+                float v[V];
+                add_up<BN, V, WK>(sums, BN * BM, row, tid % PIECES, v);
+                finish_pixel<T, V, PIECES>(a, v, adds[it], pixel(row), my_k, vec_ok, (row & 3) == 0);
+            }
+            return;
+        }
+    }
+    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
 }
 
 // Small maps: a workgroup owns BN output channels x 16 pixels and its WK waves deal the rows of the reduction (128 bytes
@@ -559,11 +711,10 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
     set_wave_priority(a.prio);
     constexpr int ES = sizeof(T), RK = ROW<T>, EPP = 16 / ES, BM = 16, TN = BN / 16;
     constexpr int WQ = BN / 8, XQ = BM / 8, L = WQ + XQ;   // loads of a row: 8 operand rows of 128 bytes each
-    constexpr int ROW_BYTES = (BN + BM) * 128, RED_BYTES = (WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
-    constexpr int LDS_BYTES = std::max({WK * D * ROW_BYTES, RED_BYTES, EP_BYTES});
+    constexpr int ROW_BYTES = (BN + BM) * 128;
+    static_assert(D * ROW_BYTES >= BN * BM * 4, "a wave's sums fit its ring");
     typedef typename Mma<T, 16>::Acc Acc;
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
-    __shared__ int s_last;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[WK * D * ROW_BYTES];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -571,7 +722,16 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
     if (!find_tile(a, tile, z, tn_idx, tm_idx)) return;
     const int M = (int)a.walk.pixels;
     const int n0 = tn_idx * BN, m0 = tm_idx * BM;
-    const int first = z * (int)a.walk.per + wave, end = min((int)a.walk.units, (z + 1) * (int)a.walk.per);
+
+    // Four channels of a pixel per storing thread; bias and residual are requested ahead of the operands
+    constexpr int STORING = BN / 16;                       // waves that store
+    const int my_row = (int)threadIdx.x / (BN / 4), my_piece = (int)threadIdx.x % (BN / 4), my_k = n0 + 4 * my_piece;
+    const int my_m = m0 + my_row < M ? (a.pool2 ? (m0 + my_row) >> 2 : m0 + my_row) : -1;
+    const bool vec_ok = whole_packs<4>(a);
+    Addend<T, 4> add;
+    if (wave < STORING) add.load(a, my_m, my_k, vec_ok);
+
+    const int first = wave, end = (int)a.walk.units;
     const int mine = first < end ? (end - first + WK - 1) / WK : 0;    // this wave's rows: first, first + WK, ...
 
     const int XS = a.x_ct;
@@ -677,12 +837,13 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
             for (int i = 0; i < TN; ++i) acc[i][0] = Mma<T, 16>::run(fw[s][i], fx[s], acc[i][0]);
         slot = slot + 1 == D ? 0 : slot + 1;
     }
-    wait_and_meet<0>();                                    // the rings are free
-
-    finish_tile<T, BN, BM, 1, 1, WK, 16>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
-        const int m = m0 + ml;
-        return m < M ? (a.pool2 ? m >> 2 : m) : -1;
-    });
+    // a wave's sums go into its own ring, whose loads have all landed and been read
+    publish_sums<BN, 16, BN, 16>(acc, reinterpret_cast<float *>(&smem[ring]), 0, 0, frow, fgrp);
+    __syncthreads();
+    if (wave >= STORING) return;
+    float v[4];
+    add_up<BN, 4, WK>(reinterpret_cast<const float *>(&smem[0]), D * ROW_BYTES / 4, my_row, my_piece, v);
+    finish_pixel<T, 4, BN / 4>(a, v, add, my_m, my_k, vec_ok, (my_row & 3) == 0);
 }
 
 // 3x3 windows, stride 1, padding 1, C % 64 == 0: the nine taps of a 64-channel chunk read the same input pixels, so those
@@ -710,7 +871,8 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
     constexpr int XPS = (PL + SPC - NBUF + 1) / (SPC - NBUF + 2);
     constexpr int L = WQ + XPS;
     constexpr int W_BYTES = KD * BN * 128, P_BYTES = PC * 128, DUMP = NBUF * W_BYTES + 2 * P_BYTES;
-    constexpr int RED_BYTES = (WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
+    constexpr bool SUMS = WK > 1 && WK * BN * BM * 4 <= DUMP;    // the groups' sums fit the operands' place
+    constexpr int RED_BYTES = (SUMS ? WK : WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
     constexpr int LDS_BYTES = std::max({DUMP + 1024, RED_BYTES, EP_BYTES});
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
@@ -870,16 +1032,41 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
         [&]<int... I>(std::integer_sequence<int, I...>) { (stage.template operator()<I>(c), ...); }(std::make_integer_sequence<int, SPC>{});
         xs += TK * 2;
     }
-    wait_and_meet<0>();
-
-    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, [&](int ml) {
+    auto pixel = [&](int ml) {
         const int i = m0 + ml;
         int row, img, col;
         locate((uint32_t)min(i, ppx - 1), row, img, col);
         const int q = pn * Wt + col;
         if (i >= ppx || q >= a.Q) return -1;
         return a.pool2 ? (img * (a.P >> 1) + (row >> 1)) * (a.Q >> 1) + (q >> 1) : (img * a.P + row) * a.Q + q;
-    });
+    };
+    wait_and_meet<0>();
+    if constexpr (SUMS) {
+        if (a.walk.split.d == 1) {
+            constexpr int NT = 64 * NW, V = BN * BM >= 8 * NT ? 8 : 4, PIECES = BN / V, EP_IT = BN * BM / V / NT;
+            const bool vec_ok = whole_packs<V>(a);
+            const int my_k = n0 + (tid % PIECES) * V;
+            float *sums = reinterpret_cast<float *>(&smem[0]);
+            int m[EP_IT];
+            Addend<T, V> add[EP_IT];
+#pragma unroll
+            for (int it = 0; it < EP_IT; ++it) {
+                m[it] = pixel((tid + it * NT) / PIECES);
+                add[it].load(a, m[it], my_k, vec_ok);
+            }
+            publish_sums<BN, MF, SUBN, SUBM>(acc, sums + wk * (BN * BM), wn, wm, frow, fgrp);
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < EP_IT; ++it) {
+                const int row = (tid + it * NT) / PIECES;
+                float v[V];
+                add_up<BN, V, WK>(sums, BN * BM, row, tid % PIECES, v);
+                finish_pixel<T, V, PIECES>(a, v, add[it], m[it], my_k, vec_ok, (row & 3) == 0);
+            }
+            return;
+        }
+    }
+    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>

@@ -92,3 +92,27 @@ def test_pooled_epilogue_of_the_rings(name, n, h, w, c, k):
         np.testing.assert_array_equal(fused.view(np.uint32), mix.ctx.read_tensor(0, pl, shape).view(np.uint32))
     finally:
         mix.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,h,w,c,k,win,pad", [(2, 15, 17, 192, 100, 3, 1), (1, 29, 27, 128, 132, 3, 1), (1, 41, 39, 64, 92, 5, 2), (1, 60, 60, 512, 76, 1, 0),
+                                               (1, 30, 31, 64, 4, 3, 1), (3, 40, 41, 64, 68, 3, 1)])
+def test_residual_of_channels_in_fours(n, h, w, c, k, win, pad, dtype):
+    """Channel counts and offsets that are multiples of 4 but not of 8 are stored, and the residual is read, in packs of four."""
+    g = GraphBuilder("t", dtype, n, h, w, c)
+    a = g.conv(0, k, win, 1, pad, act="none", bn=True)
+    d = g.new_tensor()
+    g.conv(0, k, win, 1, pad, act="relu", bn=True, res=a, dst=d, c_off=4, c_tot=k + 4)
+    g.conv(0, 4, win, 1, pad, act="none", dst=d, c_off=0, c_tot=k + 4)
+    spec = g.done()
+    print("case", n, h, w, c, k, win, dtype, flush=True)
+    mix = Mix([spec], seed=49)
+    try:
+        x = oops.round_array(mix.x[0], dtype)
+        p = OF.prepare_params(spec, mix.raw[0])
+        t0 = torch.from_numpy(oops.round_array(conv_ref(x, p[0], 1, pad, 1).float().contiguous().numpy(), dtype)).double()
+        ref = torch.cat([conv_ref(x, p[2], 1, pad, 1), ACT["relu"](conv_ref(x, p[1], 1, pad, 1) + t0)], dim=3).float().numpy()
+        got, _ = mix.run(mix.ctx.sequential())
+        assert_close(got[0], ref.reshape(n, -1), dtype, "residual")
+    finally:
+        mix.close()
