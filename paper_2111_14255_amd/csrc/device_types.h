@@ -38,6 +38,11 @@ __device__ __forceinline__ void set_wave_priority(int p) {
     else if (p == 3) __builtin_amdgcn_s_setprio(3);
 }
 
+__device__ __forceinline__ uint32_t divide(uint32_t n, const Divisor &v) {
+    const uint32_t t = __umulhi(v.m, n);
+    return (t + ((n - t) >> v.s1)) >> v.s2;
+}
+
 // Launches K1 with the operator's arguments, or, when `mate` points to n_mates (1 .. 3) further operators of equal
 // launch shape, K2 (the several-operator form of the same kernel) on a grid of 1 + n_mates times the workgroups,
 // blockIdx.y naming the operator.

@@ -77,8 +77,9 @@ struct Divisor {
     uint32_t d, m, s1, s2;
 };
 
-// What the workgroups of a tile kernel need to find their tile and operands, worked out when the layer is planned: none of it
+// What the workgroups of a kernel need to find their tile and operands, worked out when the layer is planned: none of it
 // depends on the workgroup, and a division by a number that is not known at compile time is some 30 dependent instructions.
+// (The members are described as the tile kernels use them; plan_channelwise and the others say what the other kernels keep in them.)
 struct TileWalk {
     uint32_t total, per_xcd;     // workgroups with work, and a contiguous range of them per XCD
     uint32_t pixels;             // N * P * Q
@@ -100,7 +101,7 @@ struct OpArgs {
     // What a tile kernel reads before its first load stands together: one trip through the scalar cache brings it.
     const void *x;
     const void *w;
-    TileWalk walk;               // tile kernels
+    TileWalk walk;
     int32_t tile_order;          // 0: channel tile fastest (an XCD shares activation tiles), 1: pixel tile fastest (shares filter tiles)
     int32_t pool2;               // 1: the epilogue applies a 2x2 / stride-2 max pooling; pixels are then walked quad by quad and y is the pooled tensor
     int32_t k_pad;               // packed weight row length (multiple of the k tile)
@@ -209,6 +210,11 @@ int dconv_f32_plan(int M, int K, int gemm_k, int C);
 void dconv_f32_tile(int form, int *channels, int *pixels);
 int dconv_f32_grid(int form, int M, int K);
 int launch_dconv_f32(const OpArgs &a, void *stream);
+
+// Fill OpArgs::walk of the channel-wise kernels (kernels_direct.hip) the resident-filter kernels and fp32 convolutions on
+// operands from memory.
+void plan_channelwise(OpArgs &a);
+void plan_dconv_f32(OpArgs &a);
 
 // Launchers (defined in the .hip files).  Return a hipError_t as int.
 int launch_direct(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);

@@ -47,19 +47,16 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
     const int wk = wave / (WN * WM), wn = wave % WN, wm = (wave / WN) % WM;
     const int row = lane & 15, grp = lane >> 4;
 
-    const int M = a.N * a.P * a.Q;
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
-    const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + 7) / 8;
-    const int vid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;       // each XCD's L2 serves a contiguous tile range
-    if (vid >= total) return;                                          // the whole workgroup
-    const int tn_idx = a.tile_order ? vid / tiles_m : vid % tiles_n;
-    const int tm_idx = a.tile_order ? vid % tiles_m : vid / tiles_n;
+    const int M = (int)a.walk.pixels;
+    const uint32_t vid = (blockIdx.x % 8) * a.walk.per_xcd + blockIdx.x / 8;   // each XCD's L2 serves a contiguous tile range
+    if (vid >= a.walk.total) return;                                   // the whole workgroup
+    const int slow = (int)divide(vid, a.walk.tiles), fast = (int)(vid - (uint32_t)slow * a.walk.tiles.d);
+    const int tn_idx = a.tile_order ? slow : fast, tm_idx = a.tile_order ? fast : slow;
     const int n0 = tn_idx * BN + wn * 16 * TN, m0 = tm_idx * BM + wm * 16 * TM;
 
     if constexpr (MODE == DC_ELEMENT) {
         for (int j = tid; j < a.k_pad; j += 64 * NW) {
-            const int rs = j / a.C, c = j - rs * a.C, r = rs / a.S, s = rs - r * a.S;
+            const int rs = (int)divide((uint32_t)j, a.walk.c), c = j - rs * a.C, r = (int)divide((uint32_t)rs, a.walk.split), s = rs - r * a.S;
             table[j] = j < a.gemm_k ? int2{((r * a.W + s) * a.x_ct + c) * ES, r << 16 | s} : int2{0, 0x7fff << 16};
         }
         __syncthreads();
@@ -98,14 +95,14 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
     // position of the next step to load: tap and channel of its first element
     int u_r = 0, u_s = 0, u_c = 0;
     if constexpr (MODE == DC_UNIFORM) {
-        const int j0 = s_begin * KST, rs = j0 / a.C;
+        const int j0 = s_begin * KST, rs = (int)divide((uint32_t)j0, a.walk.c);
         u_c = j0 - rs * a.C;
-        u_r = rs / a.S;
+        u_r = (int)divide((uint32_t)rs, a.walk.split);
         u_s = rs - u_r * a.S;
     } else if constexpr (MODE == DC_PIECE) {
-        const int j0 = s_begin * KST + grp * EPV, rs = j0 / a.C;
+        const int j0 = s_begin * KST + grp * EPV, rs = (int)divide((uint32_t)j0, a.walk.c);
         u_c = j0 - rs * a.C;
-        u_r = rs / a.S;
+        u_r = (int)divide((uint32_t)rs, a.walk.split);
         u_s = rs - u_r * a.S;
     }
     u32x4 fa[D][TN], fb[D][TM];
@@ -255,6 +252,19 @@ void dconv_f32_tile(int form, int *channels, int *pixels) {
 int dconv_f32_grid(int form, int M, int K) {
     const DcTile &t = DC_F32[form - 1];
     return (((M + t.bm - 1) / t.bm) * ((K + t.bn - 1) / t.bn) + 7) / 8 * 8;
+}
+
+// walk.tiles: workgroup -> (slow, fast) tile index; walk.c, split: divisors of the reduction index by the channels and of a tap by S.
+void plan_dconv_f32(OpArgs &a) {
+    const DcTile &t = DC_F32[a.wk - 1];
+    TileWalk &w = a.walk;
+    w.pixels = (uint32_t)(a.N * a.P * a.Q);
+    const uint32_t tiles_m = (w.pixels + (uint32_t)t.bm - 1) / (uint32_t)t.bm, tiles_n = (uint32_t)((a.K + t.bn - 1) / t.bn);
+    w.total = tiles_m * tiles_n;
+    w.per_xcd = (w.total + 7) / 8;
+    w.tiles = divisor(a.tile_order ? tiles_m : tiles_n);
+    w.c = divisor((uint32_t)a.C);
+    w.split = divisor((uint32_t)a.S);
 }
 
 int launch_dconv_f32(const OpArgs &a, void *stream) {

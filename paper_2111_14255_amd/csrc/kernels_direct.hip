@@ -8,23 +8,33 @@
 
 namespace mt {
 
-// Linear element index -> (channel vector, column, row, image).  Tensors stay below 2^31 elements (checked when a
-// model is finalised), so the index arithmetic is 32-bit: a 64-bit division costs several hundred instructions,
-// which is a large part of a kernel that otherwise makes one memory round trip.
+// Linear element index -> (channel vector, column, row, image).  Tensors stay below 2^31 bytes (checked when a
+// model is finalised), so the index arithmetic is 32-bit, and it divides by multiplying (plan_channelwise): divisions would be a
+// large part of a kernel that otherwise makes one memory round trip.  us with divisions and with arguments read one after the other /
+// this, the 1x1 kernels of small maps alike: two fp32 networks at batch 4 (17 depthwise layers) 401 / 388, ResNet-18, VGG-16 and
+// MobileNetV2 at one image 254 / 247, four networks at one image 518 / 502.
 struct ElemIdx {
     int cv, q, p, n;
     uint32_t m;       // pixel index (n * P + p) * Q + q
 };
-__device__ inline ElemIdx split_index(uint32_t g, int CV, int Q, int P) {
+__device__ __forceinline__ ElemIdx split_index(uint32_t g, const TileWalk &w) {
     ElemIdx e;
-    e.m = g / (uint32_t)CV;
-    e.cv = (int)(g - e.m * (uint32_t)CV);
-    const uint32_t t = e.m / (uint32_t)Q;
-    e.q = (int)(e.m - t * (uint32_t)Q);
-    const uint32_t n = t / (uint32_t)P;
-    e.p = (int)(t - n * (uint32_t)P);
+    e.m = divide(g, w.c);
+    e.cv = (int)(g - e.m * w.c.d);
+    const uint32_t t = divide(e.m, w.q);
+    e.q = (int)(e.m - t * w.q.d);
+    const uint32_t n = divide(t, w.pq);
+    e.p = (int)(t - n * w.pq.d);
     e.n = (int)n;
     return e;
+}
+
+// Everything a channel-wise kernel needs, asked for in one trip through the scalar cache.
+__device__ __forceinline__ void fetch_channelwise(const OpArgs &a) {
+    const TileWalk &w = a.walk;
+    asm volatile("" ::"s"(a.x), "s"(a.w), "s"(w.total), "s"(w.c.d), "s"(w.c.m), "s"(w.c.s1), "s"(w.c.s2), "s"(w.q.d), "s"(w.q.m), "s"(w.q.s1), "s"(w.q.s2), "s"(w.pq.d),
+                 "s"(w.pq.m), "s"(w.pq.s1), "s"(w.pq.s2), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.prio), "s"(a.act), "s"(a.y_coff),
+                 "s"(a.y_ct), "s"(a.bias), "s"(a.y));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -36,7 +46,7 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(OpArgs a) {
     const uint32_t total = (uint32_t)a.N * a.P * a.Q * a.K;
     const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= total) return;
-    const ElemIdx e = split_index(gid, a.K, a.Q, a.P);
+    const ElemIdx e = split_index(gid, a.walk);
     const int k = e.cv, q = e.q, p = e.p, n = e.n;
     const int64_t m = e.m;
     const T *x = (const T *)a.x;
@@ -82,12 +92,11 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(OpArgs a) {
 // that the weight vector of a tap is one contiguous load, shared by every pixel through the caches.
 template <typename T, int V>
 __device__ __forceinline__ void dwconv_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const ElemIdx e = split_index(gid, CV, a.Q, a.P);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const ElemIdx e = split_index(gid, a.walk);
     const int cv = e.cv, q = e.q, p = e.p, n = e.n;
     const int64_t m = e.m;
     const int c0 = cv * V;
@@ -133,12 +142,11 @@ __global__ void __launch_bounds__(256) dwconv_pair_kernel(OpArgsPair p) {
 // one before it; taps in the padding halo are masked afterwards.  Tap order of the sums is the same (r, s).
 template <typename T, int V, int KS>
 __device__ __forceinline__ void dwconv_fixed_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const ElemIdx e = split_index(gid, CV, a.Q, a.P);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const ElemIdx e = split_index(gid, a.walk);
     const int cv = e.cv, q = e.q, p = e.p, n = e.n;
     const int64_t m = e.m;
     const int c0 = cv * V;
@@ -153,8 +161,8 @@ __device__ __forceinline__ void dwconv_fixed_kernel_body(const OpArgs &a) {
             const int ih = p * a.sh - a.ph + r, iw = q * a.sw - a.pw + s;
             ok[r * KS + s] = ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W);
             const int ihc = min(max(ih, 0), a.H - 1), iwc = min(max(iw, 0), a.W - 1);
-            load_pack<T, V>(x + ((int64_t)ihc * a.W + iwc) * a.C, xv[r * KS + s]);
-            load_pack<T, V>(w + (int64_t)(r * KS + s) * a.C, wv[r * KS + s]);
+            load_pack<T, V>(x + (uint32_t)((ihc * a.W + iwc) * a.C), xv[r * KS + s]);
+            load_pack<T, V>(w + (uint32_t)((r * KS + s) * a.C), wv[r * KS + s]);
         }
     // the bias vector always exists (zeros when the layer has none): loaded with the taps, not after the sum
 #pragma unroll
@@ -195,15 +203,15 @@ __global__ void __launch_bounds__(256) dwconv_fixed_pair_kernel(OpArgsPair p) {
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 
 template <typename T, int ST>
-__device__ __forceinline__ void dwconv3_rows_kernel_body(const OpArgs &a, int rows, int bands) {
+__device__ __forceinline__ void dwconv3_rows_kernel_body(const OpArgs &a) {
     static_assert(sizeof(T) == 2, "16-byte vectors of 8 channels");
     constexpr int V = 8;
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * bands * a.Q * CV;
-    const uint32_t gid0 = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = gid0 < total;
-    const ElemIdx e = split_index(live ? gid0 : total - 1, CV, a.Q, bands);
+    const int CV = (int)a.walk.c.d, rows = (int)a.walk.per;
+    const uint32_t gid0 = blockIdx.x * 256u + threadIdx.x;
+    const bool live = gid0 < a.walk.total;
+    const ElemIdx e = split_index(live ? gid0 : a.walk.total - 1, a.walk);
     const int cv = e.cv, q = e.q, band = e.p, n = e.n;
     const int lane = threadIdx.x & 63;
     const int c0 = cv * V;
@@ -284,13 +292,13 @@ __device__ __forceinline__ void dwconv3_rows_kernel_body(const OpArgs &a, int ro
     }
 }
 template <typename T, int ST>
-__global__ void __launch_bounds__(256) dwconv3_rows_kernel(OpArgs a, int rows, int bands) {
-    dwconv3_rows_kernel_body<T, ST>(a, rows, bands);
+__global__ void __launch_bounds__(256) dwconv3_rows_kernel(OpArgs a) {
+    dwconv3_rows_kernel_body<T, ST>(a);
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int ST>
-__global__ void __launch_bounds__(256) dwconv3_rows_pair_kernel(OpArgsPair p, int rows, int bands) {
-    dwconv3_rows_kernel_body<T, ST>(p.a[blockIdx.y], rows, bands);
+__global__ void __launch_bounds__(256) dwconv3_rows_pair_kernel(OpArgsPair p) {
+    dwconv3_rows_kernel_body<T, ST>(p.a[blockIdx.y]);
 }
 
 // Output rows per thread of the banded 3x3 depthwise kernel: 1 (the one-pixel kernel) unless the map is large enough
@@ -303,12 +311,11 @@ static int dwconv_band_rows(const OpArgs &a) {
 
 template <typename T, int V, bool IS_MAX, int KS>
 __device__ __forceinline__ void pool_fixed_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const ElemIdx e = split_index(gid, CV, a.Q, a.P);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const ElemIdx e = split_index(gid, a.walk);
     const int cv = e.cv, q = e.q, p = e.p, n = e.n;
     const int64_t m = e.m;
     const int c0 = cv * V;
@@ -322,7 +329,7 @@ __device__ __forceinline__ void pool_fixed_kernel_body(const OpArgs &a) {
             const int ih = p * a.sh - a.ph + r, iw = q * a.sw - a.pw + s;
             ok[r * KS + s] = ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W);
             const int ihc = min(max(ih, 0), a.H - 1), iwc = min(max(iw, 0), a.W - 1);
-            load_pack<T, V>(x + ((int64_t)ihc * a.W + iwc) * a.C, xv[r * KS + s]);
+            load_pack<T, V>(x + (uint32_t)((ihc * a.W + iwc) * a.C), xv[r * KS + s]);
         }
     float acc[V];
 #pragma unroll
@@ -355,12 +362,11 @@ __global__ void __launch_bounds__(256) pool_fixed_pair_kernel(OpArgsPair p) {
 // Window pooling: one thread per (output pixel, V-channel vector).
 template <typename T, int V, bool IS_MAX>
 __device__ __forceinline__ void pool_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const ElemIdx e = split_index(gid, CV, a.Q, a.P);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const ElemIdx e = split_index(gid, a.walk);
     const int cv = e.cv, q = e.q, p = e.p, n = e.n;
     const int64_t m = e.m;
     const int c0 = cv * V;
@@ -403,17 +409,17 @@ __global__ void __launch_bounds__(256) pool_pair_kernel(OpArgsPair p) {
 // arranged as LANES_HW spatial slices x LANES_C channel vectors; each lane sums its slice in order and
 // the slices are combined by a fixed butterfly of wavefront shuffles, so the sum order is fixed.
 template <typename T, int V>
-__device__ __forceinline__ void gap_kernel_body(const OpArgs &a, int lanes_c) {
+__device__ __forceinline__ void gap_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
     const int CV = a.C / V;
-    const int lanes_hw = 64 / lanes_c;
-    const int groups = (CV + lanes_c - 1) / lanes_c;            // wave tasks per image
-    const int wave = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    const int lanes_c = (int)a.walk.per, lanes_hw = 64 >> (lanes_c >> 1);                // 1, 2 or 4 channel vectors beside each other
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    if (wave >= a.N * groups) return;                            // whole wave exits together
-    const int n = wave / groups;
-    const int cv = (wave % groups) * lanes_c + (lane % lanes_c);
-    const int slice = lane / lanes_c;
+    if (wave >= a.walk.total) return;                            // whole wave exits together
+    const int n = (int)divide(wave, a.walk.q);                   // q: wave tasks per image
+    const int cv = (int)(wave - (uint32_t)n * a.walk.q.d) * lanes_c + (lane & (lanes_c - 1));
+    const int slice = lane >> (lanes_c >> 1);
     const int HW = a.H * a.W;
     const bool cv_ok = cv < CV;
     const T *x = (const T *)a.x + (int64_t)n * HW * a.C + (cv_ok ? cv : 0) * V;
@@ -446,13 +452,13 @@ __device__ __forceinline__ void gap_kernel_body(const OpArgs &a, int lanes_c) {
     }
 }
 template <typename T, int V>
-__global__ void __launch_bounds__(256) gap_kernel(OpArgs a, int lanes_c) {
-    gap_kernel_body<T, V>(a, lanes_c);
+__global__ void __launch_bounds__(256) gap_kernel(OpArgs a) {
+    gap_kernel_body<T, V>(a);
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V>
-__global__ void __launch_bounds__(256) gap_pair_kernel(OpArgsPair p, int lanes_c) {
-    gap_kernel_body<T, V>(p.a[blockIdx.y], lanes_c);
+__global__ void __launch_bounds__(256) gap_pair_kernel(OpArgsPair p) {
+    gap_kernel_body<T, V>(p.a[blockIdx.y]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -461,13 +467,13 @@ __global__ void __launch_bounds__(256) gap_pair_kernel(OpArgsPair p, int lanes_c
 // reaches at most 7 channels to either side, V >= 8 for the vector form), all before any arithmetic.
 template <typename T, int V>
 __device__ __forceinline__ void lrn_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const uint32_t m = gid / (uint32_t)CV;
-    const int cv = (int)(gid - m * (uint32_t)CV);
+    const int CV = (int)a.walk.c.d;
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const uint32_t m = divide(gid, a.walk.c);
+    const int cv = (int)(gid - m * a.walk.c.d);
     const int c0 = cv * V;
     const int half = a.R / 2;
     const T *x = (const T *)a.x + (int64_t)m * a.C;
@@ -526,13 +532,12 @@ __global__ void __launch_bounds__(256) lrn_pair_kernel(OpArgsPair p) {
 // Element-wise sum of two tensors of the same shape, activation, one rounding.
 template <typename T, int V>
 __device__ __forceinline__ void add_kernel_body(const OpArgs &a) {
+    fetch_channelwise(a);
     set_wave_priority(a.prio);
-    const int CV = a.C / V;
-    const uint32_t total = (uint32_t)a.N * a.P * a.Q * CV;
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const uint32_t m = gid / (uint32_t)CV;
-    const int c0 = (int)(gid - m * (uint32_t)CV) * V;
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= a.walk.total) return;
+    const uint32_t m = divide(gid, a.walk.c);
+    const int c0 = (int)(gid - m * a.walk.c.d) * V;
     float u[V], v[V];
     load_pack<T, V>((const T *)a.x + (int64_t)m * a.C + c0, u);
     load_pack<T, V>((const T *)a.res + (int64_t)m * a.res_ct + c0, v);
@@ -574,6 +579,33 @@ __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
+// walk.total: threads with work (global average pooling: waves); walk.c, q, pq: divisors by the channel vectors of a pixel, the columns
+// and the rows of the output (banded depthwise layers: the bands); walk.per: output rows of a thread of those.  Global average
+// pooling: walk.q the wave tasks of an image, walk.per its channel vectors beside each other.
+void plan_channelwise(OpArgs &a) {
+    TileWalk &w = a.walk;
+    // the fp32 forms of normalisation and add take one channel per thread, a convolution without a better kernel one output
+    const int vec = (a.kernel_id == K_LRN || a.kernel_id == K_ADD) && a.dtype == MT_F32 ? 1 : a.vec;
+    const uint32_t cv = (uint32_t)(a.kernel_id == K_CONV_DIRECT ? a.K : a.C / vec);
+    if (a.kernel_id == K_GAP) {
+        w.per = 1;
+        while (w.per < 4 && w.per < cv) w.per <<= 1;             // at least 16 spatial slices per wave
+        w.q = divisor((cv + w.per - 1) / w.per);
+        w.total = (uint32_t)a.N * w.q.d;
+        return;
+    }
+    uint32_t rows = (uint32_t)a.P;
+    w.per = 1;
+    if (a.kernel_id == K_DWCONV) {
+        w.per = (uint32_t)dwconv_band_rows(a);
+        rows = (rows + w.per - 1) / w.per;
+    }
+    w.total = (uint32_t)((uint64_t)a.N * rows * a.Q * cv);
+    w.c = divisor(cv);
+    w.q = divisor((uint32_t)a.Q);
+    w.pq = divisor(rows);
+}
+
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int n_mates) {
@@ -586,14 +618,11 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
             break;
         case K_DWCONV: {
             if (a.vec == VMAX) {
-                const int64_t th = (int64_t)a.N * a.P * a.Q * (a.C / VMAX);
-                const int rows = dwconv_band_rows(a);
+                const int64_t th = a.walk.total;
                 if constexpr (sizeof(T) == 2) {
-                    if (rows > 1) {
-                        const int bands = (a.P + rows - 1) / rows;
-                        const int64_t tb = (int64_t)a.N * bands * a.Q * (a.C / VMAX);
-                        if (a.sh == 1) MT_LAUNCH((dwconv3_rows_kernel<T, 1>), (dwconv3_rows_pair_kernel<T, 1>), blocks(tb), block, st, a, mate, rows, bands);
-                        else MT_LAUNCH((dwconv3_rows_kernel<T, 2>), (dwconv3_rows_pair_kernel<T, 2>), blocks(tb), block, st, a, mate, rows, bands);
+                    if (a.walk.per > 1) {
+                        if (a.sh == 1) MT_LAUNCH((dwconv3_rows_kernel<T, 1>), (dwconv3_rows_pair_kernel<T, 1>), blocks(th), block, st, a, mate);
+                        else MT_LAUNCH((dwconv3_rows_kernel<T, 2>), (dwconv3_rows_pair_kernel<T, 2>), blocks(th), block, st, a, mate);
                         break;
                     }
                 }
@@ -631,16 +660,11 @@ static int launch_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate, int
             break;
         }
         case K_GAP: {
-            const int V = a.vec == VMAX ? VMAX : 1;
-            const int CV = a.C / V;
-            int lanes_c = 1;
-            while (lanes_c < 4 && lanes_c < CV) lanes_c <<= 1;     // at least 16 spatial slices per wave
-            const int groups = (CV + lanes_c - 1) / lanes_c;
-            const int64_t th = (int64_t)a.N * groups * 64;
-            if (V == VMAX)
-                MT_LAUNCH((gap_kernel<T, VMAX>), (gap_pair_kernel<T, VMAX>), blocks(th), block, st, a, mate, lanes_c);
+            const int64_t th = (int64_t)a.walk.total * 64;
+            if (a.vec == VMAX)
+                MT_LAUNCH((gap_kernel<T, VMAX>), (gap_pair_kernel<T, VMAX>), blocks(th), block, st, a, mate);
             else
-                launch((gap_kernel<T, 1>), blocks(th), block, 0, st, a, lanes_c);
+                launch((gap_kernel<T, 1>), blocks(th), block, 0, st, a);
             break;
         }
         case K_LRN:

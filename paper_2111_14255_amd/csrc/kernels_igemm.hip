@@ -623,15 +623,18 @@ __global__ void __launch_bounds__(256) gemv_pair_kernel(OpArgsPair p) {
 // ascending order into one accumulator (the arithmetic of the 64x16 tile kernel, bit for bit).
 template <typename T>
 __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
+    asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.walk.total), "s"(a.walk.tiles.d), "s"(a.walk.tiles.m), "s"(a.walk.tiles.s1), "s"(a.walk.tiles.s2), "s"(a.k_pad), "s"(a.x_ct), "s"(a.x_coff),
+                 "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.sh), "s"(a.sw), "s"(a.N), "s"(a.P), "s"(a.Q), "s"(a.prio), "s"(a.K), "s"(a.act), "s"(a.bias), "s"(a.res), "s"(a.n_pad),
+                 "s"(a.divq_m), "s"(a.divq_s1), "s"(a.divpq_m), "s"(a.divpq_s1));
     set_wave_priority(a.prio);
     typedef typename Mma<T, 16>::Acc Acc;
     constexpr int CH = 8;                                // reduction steps whose loads are in flight together
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.N * a.P * a.Q;
-    const int tiles_m = (M + 15) / 16, tiles_n = (a.K + 15) / 16;
-    const int tile = (int)blockIdx.x * 4 + wave;
-    if (tile >= tiles_m * tiles_n) return;               // a whole wave, and no barrier follows
-    const int tn = tile % tiles_n, tm = tile / tiles_n;  // neighbouring waves share the pixel tile
+    const uint32_t tile = blockIdx.x * 4u + (uint32_t)wave;
+    if (tile >= a.walk.total) return;                    // a whole wave, and no barrier follows
+    const int tm = (int)divide(tile, a.walk.tiles), tn = (int)(tile - (uint32_t)tm * a.walk.tiles.d);    // neighbouring waves share the pixel tile
     const int nsteps = a.k_pad / 32;
     const int frag_row = lane & 15, frag_k = (lane >> 4) * 8;
 
@@ -972,8 +975,16 @@ int launch_dwpw(const OpArgs &dw, const OpArgs &pw, void *stream) {
 // runs the depthwise filter over the LDS copy with the operation sequence of the stand-alone depthwise kernel.  Both
 // halves therefore produce the bits of the two separate launches.
 // MT: 16-pixel tiles per wave (a band reads at most 64 * MT pixels), KS: 32-deep reduction steps (k_pad <= 32 * KS).
+struct PwdwWalk {
+    Divisor chunks, bands, q;    // workgroup -> (band and image, chunk of channels); that -> (image, band); output pixel -> row
+    int32_t pb;                  // output rows of a band
+};
 template <typename T, int MT, int KS, int HC>
-__global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands) {
+__global__ void __launch_bounds__(256) pwdw_kernel(PwdwWalk w, OpArgs e, OpArgs d) {
+    // all arguments in one trip through the scalar cache
+    asm volatile("" ::"s"(w.chunks.d), "s"(w.chunks.m), "s"(w.chunks.s1), "s"(w.chunks.s2), "s"(w.bands.d), "s"(w.bands.m), "s"(w.bands.s1), "s"(w.bands.s2), "s"(w.q.m),
+                 "s"(w.q.s1), "s"(w.q.s2), "s"(w.pb), "s"(e.x), "s"(e.w), "s"(e.k_pad), "s"(e.C), "s"(e.N), "s"(e.K), "s"(e.bias), "s"(e.n_pad), "s"(e.act), "s"(d.H), "s"(d.W),
+                 "s"(d.P), "s"(d.sh), "s"(d.sw), "s"(d.prio), "s"(d.w), "s"(d.bias), "s"(d.C));
     set_wave_priority(d.prio);
     constexpr int NI = HC / 16;                          // MFMA tiles along the channels
     constexpr int CPP = HC / 8;                          // 8-channel chunks per pixel
@@ -983,12 +994,11 @@ __global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands
     __shared__ __attribute__((aligned(16))) uint16_t Wd[9 * HC];
     __shared__ float Bd[HC];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int chunks = (e.K + HC - 1) / HC;
-    const int c0 = (blockIdx.x % chunks) * HC;
-    const int band = (blockIdx.x / chunks) % bands;
-    const int img = blockIdx.x / (chunks * bands);
+    const uint32_t across = divide(blockIdx.x, w.chunks);
+    const int c0 = (int)(blockIdx.x - across * w.chunks.d) * HC;
+    const int img = (int)divide(across, w.bands), bands = (int)w.bands.d, band = (int)across - img * bands;
     const int W = d.W, Min = d.H * d.W;                  // the widened map has the pixels of the input map (1x1, stride 1)
-    const int PB = (d.P + bands - 1) / bands;
+    const int PB = w.pb;
     const int p_lo = band * PB, p_hi = min(d.P, p_lo + PB);               // output rows of this band
     const int r_lo = max(0, p_lo * d.sh - 1), r_hi = min(d.H - 1, (p_hi - 1) * d.sh + 1);   // widened rows it reads
     const int px0 = r_lo * W, Mb = (r_hi - r_lo + 1) * W;
@@ -1071,7 +1081,7 @@ __global__ void __launch_bounds__(256) pwdw_kernel(OpArgs e, OpArgs d, int bands
     for (int it = tid; it < (p_hi - p_lo) * d.Q * CPP; it += 256) {
         const int ol = it / CPP, c8 = it - ol * CPP;
         const int c = c0 + c8 * 8;
-        const int pl = ol / d.Q;
+        const int pl = (int)divide((uint32_t)ol, w.q);
         const int p = p_lo + pl, q = ol - pl * d.Q;
         float acc[8];
 #pragma unroll
@@ -1135,10 +1145,11 @@ int launch_pwdw(const OpArgs &pw, const OpArgs &dw, void *stream) {
     if (!pwdw_plan(pw, dw, &variant, &bands)) return (int)hipErrorInvalidValue;
     constexpr int HC = PWDW_HC;
     const dim3 grid(pw.N * bands * ((pw.K + HC - 1) / HC)), block(256);
+    const PwdwWalk w{divisor((uint32_t)((pw.K + HC - 1) / HC)), divisor((uint32_t)bands), divisor((uint32_t)dw.Q), (dw.P + bands - 1) / bands};
     auto go = [&]<typename T>() {
-        if (variant == 0) launch((pwdw_kernel<T, 8, 2, HC>), grid, block, 0, st, pw, dw, bands);
-        else if (variant == 1) launch((pwdw_kernel<T, 4, 4, HC>), grid, block, 0, st, pw, dw, bands);
-        else launch((pwdw_kernel<T, 1, 8, HC>), grid, block, 0, st, pw, dw, bands);
+        if (variant == 0) launch((pwdw_kernel<T, 8, 2, HC>), grid, block, 0, st, w, pw, dw);
+        else if (variant == 1) launch((pwdw_kernel<T, 4, 4, HC>), grid, block, 0, st, w, pw, dw);
+        else launch((pwdw_kernel<T, 1, 8, HC>), grid, block, 0, st, w, pw, dw);
     };
     if (pw.dtype == MT_F16) go.template operator()<f16>();
     else go.template operator()<bf16>();

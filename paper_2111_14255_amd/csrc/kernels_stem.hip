@@ -209,7 +209,7 @@ __device__ __forceinline__ void stem_kernel_body(const OpArgs &a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
 
-    const int stride = gridDim.x * 4;
+    const int stride = (int)a.walk.per;      // tiles from one of a wave's to the next
     int tile = blockIdx.x * 4 + wave;
     u32x4 b[KS];
     uint32_t vm = 0;

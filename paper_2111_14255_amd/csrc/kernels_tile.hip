@@ -405,11 +405,6 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         }
 }
 
-__device__ __forceinline__ uint32_t divide(uint32_t n, const Divisor &v) {
-    const uint32_t t = __umulhi(v.m, n);
-    return (t + ((n - t) >> v.s1)) >> v.s2;
-}
-
 // Image and top left input pixel of the window of output pixel m (walked window by window when the epilogue pools).
 __device__ __forceinline__ void window_origin(const OpArgs &a, uint32_t m, int &n, int &ih0, int &iw0) {
     const uint32_t mq = a.pool2 ? m >> 2 : m;
@@ -444,7 +439,7 @@ __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
                  "s"(w.split.d), "s"(w.split.m), "s"(w.tiles.d), "s"(w.tiles.m), "s"(w.tiles.s1), "s"(w.tiles.s2), "s"(w.pq.d), "s"(w.pq.m), "s"(w.pq.s1), "s"(w.pq.s2),
                  "s"(w.q.d), "s"(w.q.m), "s"(w.q.s1), "s"(w.q.s2), "s"(a.tile_order), "s"(a.pool2), "s"(a.k_pad), "s"(a.x_ct), "s"(a.x_coff), "s"(a.H));
     asm volatile("" ::"s"(w.c.d), "s"(w.c.m), "s"(w.c.s1), "s"(w.c.s2), "s"(w.adv_t), "s"(w.adv_c), "s"(w.inv_s), "s"(a.W), "s"(a.C), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw),
-                 "s"(a.ph), "s"(a.pw), "s"(a.N), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio));
+                 "s"(a.ph), "s"(a.pw), "s"(a.N), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio), "s"(a.K), "s"(a.res_ct), "s"(a.y_coff), "s"(a.y_ct), "s"(a.bias), "s"(a.res));
 }
 
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.

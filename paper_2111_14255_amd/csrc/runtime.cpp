@@ -105,6 +105,8 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
             if (slices && plan_tile(p, TILE_RING4)) return;
             p.n_pad = cdiv(Kc, 64) * 64;
             p.grid_x = cdiv(tiles, 4);
+            p.walk.total = (uint32_t)tiles;
+            p.walk.tiles = divisor((uint32_t)cdiv(Kc, 16));
             make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
             make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);
             return;
@@ -337,6 +339,10 @@ int32_t finalize_model(mt_model *m) {
             default:
                 return bad("unknown operator kind");
         }
+        if (d.kind != MT_CONV && d.kind != MT_FC) plan_channelwise(p);
+        else if (p.kernel_id == K_CONV_DIRECT && p.form < 0 && p.wk == 0) plan_channelwise(p);
+        else if (p.kernel_id == K_STEM) p.walk.per = (uint32_t)p.grid_x * 4;
+        else if (p.kernel_id == K_CONV_DIRECT && p.form < 0) plan_dconv_f32(p);
     }
     if (m->ops.empty()) return fail(MT_ERR_SHAPE_MISMATCH, "model has no operators");
     m->final_tensor = m->ops.back().d.out_tensor;
