@@ -79,7 +79,7 @@ struct Divisor {
 
 // What the workgroups of a kernel need to find their tile and operands, worked out when the layer is planned: none of it
 // depends on the workgroup, and a division by a number that is not known at compile time is some 30 dependent instructions.
-// (The members are described as the tile kernels use them; plan_channelwise and the others say what the other kernels keep in them.)
+// (The members are described as the tile kernels use them; plan_channelwise and plan_rowb say what the other kernels keep in them.)
 struct TileWalk {
     uint32_t total, per_xcd;     // workgroups with work, and a contiguous range of them per XCD
     uint32_t pixels;             // N * P * Q
@@ -214,6 +214,7 @@ int launch_dconv_f32(const OpArgs &a, void *stream);
 // Fill OpArgs::walk of the channel-wise kernels (kernels_direct.hip) the resident-filter kernels and fp32 convolutions on
 // operands from memory.
 void plan_channelwise(OpArgs &a);
+void plan_rowb(OpArgs &a);
 void plan_dconv_f32(OpArgs &a);
 
 // Launchers (defined in the .hip files).  Return a hipError_t as int.

@@ -281,7 +281,7 @@ int32_t finalize_model(mt_model *m) {
                     }
                     const int M = m->batch * o.out_h * o.out_w;
                     const int rw = (d.kind == MT_CONV && groups == 1 && ph < R && (R == 3 || (ph == 0 && pw == 0))) ? rowb_waves(R, S, in.c, o.out_c) : 0;
-                    if (rw > 0 && res_ct % 8 == 0 && ctot % 8 == 0 && d.out_c_offset % 8 == 0 && M >= ROWB_MIN_PIXELS &&
+                    if (rw > 0 && res_ct % 8 == 0 && ctot % 8 == 0 && d.out_c_offset % 8 == 0 && M >= ROWB_MIN_PIXELS && (int64_t)M * res_ct * 2 < (int64_t)1 << 31 &&
                         (R == 1 || M <= ROWB_MAX_PIXELS_3X3 || (sh == 1 && sw == 1))) {
                         // few output channels or a short reduction on a large map: filters resident in LDS, one wave per 32 pixels
                         p.kernel_id = K_ROWB;
@@ -341,6 +341,7 @@ int32_t finalize_model(mt_model *m) {
         }
         if (d.kind != MT_CONV && d.kind != MT_FC) plan_channelwise(p);
         else if (p.kernel_id == K_CONV_DIRECT && p.form < 0 && p.wk == 0) plan_channelwise(p);
+        else if (p.kernel_id == K_ROWB) plan_rowb(p);
         else if (p.kernel_id == K_STEM) p.walk.per = (uint32_t)p.grid_x * 4;
         else if (p.kernel_id == K_CONV_DIRECT && p.form < 0) plan_dconv_f32(p);
     }
