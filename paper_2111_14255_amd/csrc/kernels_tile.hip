@@ -48,6 +48,11 @@ __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t 
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
+// The same with 4 bytes a lane.
+__device__ __forceinline__ void load_words_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+    asm volatile("s_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
 // All but the N youngest loads of this wave have landed, its LDS reads are done, and the other waves got here as well.
 template <int N>
 __device__ __forceinline__ void wait_and_meet() {
@@ -190,6 +195,213 @@ __device__ __forceinline__ void add_up(const float *sums, int block, int p, int 
     }
 }
 
+// Split reduction: publishes this workgroup's partial sums; the last workgroup of the tile to arrive adds them in split order into acc, the
+// others are done (false).  GT threads (the owners) hold the sums.  Device-coherent 16-byte accesses (sc1).
+template <int BN, int BM, int GT, typename Acc, int TN, int TM>
+__device__ __forceinline__ bool meet_splits(const OpArgs &a, Acc (&acc)[TN][TM], int *s_last, int tile, int z, bool owner, int gtid) {
+    if (a.walk.split.d == 1) return true;
+    constexpr int GROUPS = sizeof(Acc) / 16, SC1 = 16;
+    const int parts = a.split_k;
+    const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(a.ws + (int64_t)tile * parts * (BN * BM), 0, parts * (BN * BM * 4), 0x00027000);
+    if (owner) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int g = 0; g < GROUPS; ++g) {
+                    const f32x4 v{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ws, gtid * 16, z * (BN * BM * 4) + ((i * TM + j) * GROUPS + g) * (GT * 16), SC1);
+                }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned old = __hip_atomic_fetch_add(&a.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_last = (old == (unsigned)parts - 1u);
+    }
+    __syncthreads();
+    if (!*s_last) return false;
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = Acc{};
+    constexpr int AT_ONCE = TN * TM * GROUPS <= 4 ? 4 : 1; // parts whose loads are in flight together
+    for (int z0 = 0; owner && z0 < parts; z0 += AT_ONCE) {
+        u32x4 part[AT_ONCE][TN][TM][GROUPS];
+#pragma unroll
+        for (int b = 0; b < AT_ONCE; ++b)
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int g = 0; g < GROUPS; ++g)
+                        part[b][i][j][g] = __builtin_amdgcn_raw_buffer_load_b128(ws, gtid * 16, min(z0 + b, parts - 1) * (BN * BM * 4) + ((i * TM + j) * GROUPS + g) * (GT * 16), SC1);
+#pragma unroll
+        for (int b = 0; b < AT_ONCE; ++b) {
+            if (z0 + b >= parts) continue;
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc[i][j][4 * g + t] += __uint_as_float(part[b][i][j][g][t]);
+        }
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(&a.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// Bias, residual, activation and store straight from the accumulators, for channel counts and offsets that 16-byte pieces do not fit.
+// k0: first channel of the wave's products; m: output pixel of this lane in each of them, negative for none.
+template <typename T, int MF, typename Acc, int TN, int TM>
+__device__ __forceinline__ void store_lanes(const OpArgs &a, const Acc (&acc)[TN][TM], int k0, const int (&m)[TM], int fgrp) {
+    T *y = (T *)a.y;
+    const T *res = (const T *)a.res;
+    const bool vec_ok = (a.y_ct % 4 == 0) && (a.y_coff % 4 == 0) && (a.res_ct % 4 == 0);
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            if (m[j] < 0) continue;
+#pragma unroll
+            for (int g = 0; g < (MF == 32 ? 4 : 1); ++g) {
+                const int k = k0 + i * MF + ((MF == 32) ? (8 * g + 4 * fgrp) : (4 * fgrp));
+                if (k >= a.K) continue;
+                const float4 b = *reinterpret_cast<const float4 *>(a.bias + k);    // padded to n_pad
+                float v[4] = {acc[i][j][g * 4] + b.x, acc[i][j][g * 4 + 1] + b.y, acc[i][j][g * 4 + 2] + b.z, acc[i][j][g * 4 + 3] + b.w};
+                if (vec_ok && k + 4 <= a.K) {
+                    if (res) {
+                        float rv[4];
+                        load_pack<T, 4>(res + (int64_t)m[j] * a.res_ct + k, rv);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) v[t] += rv[t];
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
+                    store_pack<T, 4>(y + (int64_t)m[j] * a.y_ct + a.y_coff + k, v);
+                } else {
+                    for (int t = 0; t < 4 && k + t < a.K; ++t) {
+                        float f = v[t];
+                        if (res) f += to_f32(res[(int64_t)m[j] * a.res_ct + k + t]);
+                        f = apply_act(f, a.act);
+                        T o;
+                        from_f32(f, o);
+                        y[(int64_t)m[j] * a.y_ct + a.y_coff + k + t] = o;
+                    }
+                }
+            }
+        }
+}
+
+// The wide forms of the 16-bit types: a wave finishes its CT x TM products of 32 channels x 32 pixels by itself.  Bias, residual and
+// activation in the layout of the accumulators, one rounding, and 32 pixels at a time through a block of LDS of its own, so that
+// every store is a row of channels; no barrier.  The residual takes the same way in the other direction.  Through an fp32 tile in LDS that
+// all waves write and read, with bias and residual fetched in between and a branch on pooling and residual at every four channels, this took
+// 2.3 to 4.2 us of a workgroup's time and 200 to 234 registers; 1.1 us (2 with a residual) and 171 here.  ResNet-50 at batch 64 1412 -> 1387 us,
+// eight at batch 16 2610 -> 2572, on disjoint eighths of the units 6135 -> 6010, ResNet-101 with three others at one image 514 -> 501.
+// m_lane: output pixel of row lane % 32 of each 32 pixels, negative for rows without one; pooling: the pooled pixel.
+template <typename T, int CT, int TM>
+struct WaveTile {
+    static constexpr int COLS = 32 * CT, SLD = COLS + 8, LPR = COLS / 8, RPI = 64 / LPR, IT = 32 / RPI;   // staging row; lanes a row; rows and accesses
+    static constexpr int BYTES = 32 * SLD * 2;
+    int m_lane[TM];
+    uint32_t k;                               // channel of this lane's 16-byte piece
+    u32x4 res[TM][IT];
+
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void *p, uint32_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+    }
+    __device__ __forceinline__ void load_res(const OpArgs &a, int lane) {
+        const __amdgpu_buffer_rsrc_t r = buffer(a.res, a.walk.pixels * (uint32_t)a.res_ct * 2u);
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int m = __shfl(m_lane[j], lane / LPR + RPI * it);
+                res[j][it] = __builtin_amdgcn_raw_buffer_load_b128(r, m >= 0 && k < (uint32_t)a.K ? ((uint32_t)m * (uint32_t)a.res_ct + k) * 2u : OUT_OF_RANGE, 0, 0);
+            }
+    }
+    static __device__ __forceinline__ void fence() {      // the block is the wave's own and LDS serves its accesses in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // Residual and pooling are decided once: a branch at every four channels keeps the compiler from having several accesses to LDS under way.
+    template <bool RES, bool POOL, typename Acc>
+    __device__ __forceinline__ void finish_as(const OpArgs &a, const Acc (&acc)[CT][TM], uint16_t *sg, const float *bias, int lane) {
+        const int frow = lane & 31, fgrp = lane >> 5, srow = lane / LPR, scol = (lane % LPR) * 8;
+        const __amdgpu_buffer_rsrc_t out = buffer(a.y, (POOL ? a.walk.pixels / 4 : a.walk.pixels) * (uint32_t)a.y_ct * 2u);
+        auto store = [&](int row, int m) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(&sg[row * SLD + scol]);
+            __builtin_amdgcn_raw_buffer_store_b128(v, out, m >= 0 && k < (uint32_t)a.K ? ((uint32_t)m * (uint32_t)a.y_ct + (uint32_t)a.y_coff + k) * 2u : OUT_OF_RANGE, 0, 0);
+        };
+        float4 b[CT][4];
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) b[i][g] = *reinterpret_cast<const float4 *>(&bias[i * 32 + 8 * g + 4 * fgrp]);
+        uint16_t *mine = &sg[(POOL ? frow >> 2 : frow) * SLD + 4 * fgrp];
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            Pack<T, 4> r[CT][4];
+            if (RES) {
+#pragma unroll
+                for (int it = 0; it < IT; ++it) *reinterpret_cast<u32x4 *>(&sg[(srow + RPI * it) * SLD + scol]) = res[j][it];
+                fence();
+#pragma unroll
+                for (int i = 0; i < CT; ++i)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) r[i][g] = *reinterpret_cast<const Pack<T, 4> *>(&mine[i * 32 + 8 * g]);
+            }
+            Pack<T, 4> o[CT][4];
+#pragma unroll
+            for (int i = 0; i < CT; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float v[4] = {acc[i][j][g * 4] + b[i][g].x, acc[i][j][g * 4 + 1] + b[i][g].y, acc[i][j][g * 4 + 2] + b[i][g].z, acc[i][j][g * 4 + 3] + b[i][g].w};
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        if (RES) v[t] += to_f32(r[i][g].e[t]);
+                        if (POOL) {                        // the maximum over the four lanes of a window; without a number there is none
+                            v[t] = fmaxf(v[t], -INFINITY);
+                            v[t] = fmaxf(v[t], __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v[t]), 0xB1, 0xf, 0xf, true)));
+                            v[t] = fmaxf(v[t], __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v[t]), 0x4E, 0xf, 0xf, true)));
+                        }
+                        from_f32(apply_act(v[t], a.act), o[i][g].e[t]);
+                    }
+                }
+            if (!POOL || (frow & 3) == 0) {
+#pragma unroll
+                for (int i = 0; i < CT; ++i)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) *reinterpret_cast<Pack<T, 4> *>(&mine[i * 32 + 8 * g]) = o[i][g];
+            }
+            fence();
+            if (POOL) {
+                const int m = __shfl(m_lane[j], (srow & 7) * 4);
+                if (RPI == 8 || srow < 8) store(srow, m);
+            } else {
+#pragma unroll
+                for (int it = 0; it < IT; ++it) store(srow + RPI * it, __shfl(m_lane[j], srow + RPI * it));
+            }
+            fence();
+        }
+    }
+    template <typename Acc>
+    __device__ __forceinline__ void finish(const OpArgs &a, const Acc (&acc)[CT][TM], uint16_t *sg, const float *bias, int lane) {
+        if (a.pool2) finish_as<false, true>(a, acc, sg, bias, lane);
+        else if (a.res != nullptr) {
+            load_res(a, lane);
+            finish_as<true, false>(a, acc, sg, bias, lane);
+        }
+        else finish_as<false, false>(a, acc, sg, bias, lane);
+    }
+};
+
 // What follows the main loop otherwise: the wave groups' partial sums meet, then those of the workgroups that share the tile, then
 // bias, residual, activation, one rounding and the store.  pixel(ml) is the output pixel of tile row ml (the pooled pixel
 // of its window when the epilogue pools), negative for rows without one.
@@ -232,55 +444,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         }
     }
 
-    // ---- split reduction: publish partial sums; the last workgroup of the tile adds them in split order
-    if (a.split_k > 1) {
-        float *wsp = a.ws + ((int64_t)tile * a.split_k + z) * (BN * BM);
-        if (owner) {
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-#pragma unroll
-                    for (int v = 0; v < ACC; ++v)
-                        __hip_atomic_store(&wsp[((i * TM + j) * ACC + v) * GT + gtid], acc[i][j][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) {
-            const unsigned old = __hip_atomic_fetch_add(&a.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *s_last = (old == (unsigned)a.split_k - 1u);
-        }
-        __syncthreads();
-        if (!*s_last) return;
-        const float *wsr = a.ws + (int64_t)tile * a.split_k * (BN * BM);
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
-        constexpr int RB = (NACC <= 16) ? 4 : 1;
-        for (int zz0 = 0; owner && zz0 < a.split_k; zz0 += RB) {
-            float part[RB][NACC];
-#pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                const float *p = wsr + (int64_t)min(zz0 + b, a.split_k - 1) * (BN * BM);
-#pragma unroll
-                for (int e = 0; e < NACC; ++e) part[b][e] = __hip_atomic_load(&p[e * GT + gtid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int b = 0; b < RB; ++b)
-                if (zz0 + b < a.split_k) {
-#pragma unroll
-                    for (int i = 0; i < TN; ++i)
-#pragma unroll
-                        for (int j = 0; j < TM; ++j)
-#pragma unroll
-                            for (int v = 0; v < ACC; ++v) acc[i][j][v] += part[b][(i * TM + j) * ACC + v];
-                }
-        }
-        if (tid == 0) __hip_atomic_store(&a.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (!meet_splits<BN, BM, GT>(a, acc, s_last, tile, z, owner, gtid)) return;
 
     // ---- epilogue: bias, residual, activation, one rounding, NHWC store
     T *y = (T *)a.y;
@@ -368,41 +532,10 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
         return;
     }
     if (!owner) return;
-    const bool vec_ok = (a.y_ct % 4 == 0) && (a.y_coff % 4 == 0) && (a.res_ct % 4 == 0);
+    int m[TM];
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) {
-            const int m = pixel(wm * SUBM + j * MF + frow);
-            if (m < 0) continue;
-#pragma unroll
-            for (int g = 0; g < GROUPS; ++g) {
-                const int k = n0 + wn * SUBN + i * MF + ((MF == 32) ? (8 * g + 4 * fgrp) : (4 * fgrp));
-                if (k >= a.K) continue;
-                const float4 b = *reinterpret_cast<const float4 *>(a.bias + k);    // padded to n_pad
-                float v[4] = {acc[i][j][g * 4] + b.x, acc[i][j][g * 4 + 1] + b.y, acc[i][j][g * 4 + 2] + b.z, acc[i][j][g * 4 + 3] + b.w};
-                if (vec_ok && k + 4 <= a.K) {
-                    if (res) {
-                        float rv[4];
-                        load_pack<T, 4>(res + (int64_t)m * a.res_ct + k, rv);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) v[t] += rv[t];
-                    }
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-                    store_pack<T, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
-                } else {
-                    for (int t = 0; t < 4 && k + t < a.K; ++t) {
-                        float f = v[t];
-                        if (res) f += to_f32(res[(int64_t)m * a.res_ct + k + t]);
-                        f = apply_act(f, a.act);
-                        T o;
-                        from_f32(f, o);
-                        y[(int64_t)m * a.y_ct + a.y_coff + k + t] = o;
-                    }
-                }
-            }
-        }
+    for (int j = 0; j < TM; ++j) m[j] = pixel(wm * SUBM + j * MF + frow);
+    store_lanes<T, MF>(a, acc, n0 + wn * SUBN, m, fgrp);
 }
 
 // Image and top left input pixel of the window of output pixel m (walked window by window when the epilogue pools).
@@ -477,8 +610,9 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     static_assert(WQ * NW * 8 == KD * BN && XQ * NW * 8 == KD * BM, "the waves share the loads of a stage evenly");
     constexpr int L = WQ + XQ;
     constexpr int W_BYTES = KD * BN * 128, X_BYTES = KD * BM * 128, STAGE = W_BYTES + X_BYTES;
-    constexpr int RED_BYTES = (WK > 1 ? WK : 0) * BN * BM * 4, ELD = BN + 4, EP_BYTES = BM * ELD * 4;
-    constexpr int LDS_BYTES = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES});
+    constexpr bool WIDE = ES == 2 && MF == 32 && WK == 1;  // every wave finishes its own part of the tile
+    constexpr int RED_BYTES = (WK > 1 ? WK : 0) * BN * BM * 4, EP_BYTES = WIDE ? NW * WaveTile<T, TN, TM>::BYTES : BM * (BN + 4) * 4;
+    constexpr int BIAS = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
     __shared__ int s_last;
@@ -509,6 +643,9 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const int my_k = n0 + (DIRECT ? wn * 16 + 4 * fgrp : (tid % PIECES) * V);
     Addend<T, V> add;
     if (AHEAD && unsplit && storing) add.load(a, pixel(my_row(0)), my_k, vec_ok);
+    if (WIDE && wave < BN / 64)
+        load_words_to_lds(raw_buffer(a.bias, (uint32_t)a.n_pad * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u,
+                          (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem + BIAS + (uint32_t)wave * 256u);
 
     const int st0 = z * (int)a.walk.per;
     const int ns = min((int)a.walk.units, st0 + (int)a.walk.per) - st0;
@@ -666,6 +803,16 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
         }
     }
     wait_and_meet<0>();                                    // the tile buffers are free
+    if constexpr (WIDE) {
+        if (!meet_splits<BN, BM, NT>(a, acc, &s_last, tile, z, true, tid)) return;
+        WaveTile<T, TN, TM> mine;
+        mine.k = (uint32_t)(n0 + wn * SUBN + (lane % mine.LPR) * 8);
+#pragma unroll
+        for (int j = 0; j < TM; ++j) mine.m_lane[j] = pixel(wm * SUBM + j * 32 + frow);
+        if (whole_packs<8>(a)) mine.finish(a, acc, reinterpret_cast<uint16_t *>(&smem[wave * mine.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + wn * SUBN, lane);
+        else store_lanes<T, MF>(a, acc, n0 + wn * SUBN, mine.m_lane, fgrp);
+        return;
+    }
     if constexpr (SUMS) {
         if (unsplit) {
             float *sums = reinterpret_cast<float *>(&smem[0]);
@@ -686,7 +833,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
             return;
         }
     }
-    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
+    if constexpr (!WIDE) finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
 }
 
 // Small maps: a workgroup owns BN output channels x 16 pixels and its WK waves deal the rows of the reduction (128 bytes
@@ -866,9 +1013,11 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
     constexpr int XPS = (PL + SPC - NBUF + 1) / (SPC - NBUF + 2);
     constexpr int L = WQ + XPS;
     constexpr int W_BYTES = KD * BN * 128, P_BYTES = PC * 128, DUMP = NBUF * W_BYTES + 2 * P_BYTES;
-    constexpr bool SUMS = WK > 1 && WK * BN * BM * 4 <= DUMP;    // the groups' sums fit the operands' place
-    constexpr int RED_BYTES = (SUMS ? WK : WK - 1) * BN * BM * 4, EP_BYTES = BM * (BN + 4) * 4;
-    constexpr int LDS_BYTES = std::max({DUMP + 1024, RED_BYTES, EP_BYTES});
+    constexpr bool WIDE = MF == 32 && (WK == 1 || (WK == 2 && TN == 2));     // every wave finishes its own part of the tile (two groups: half of it)
+    constexpr bool SUMS = WK > 1 && !WIDE;
+    static_assert(!SUMS || WK * BN * BM * 4 <= DUMP, "the groups' sums fit the operands' place");
+    constexpr int RED_BYTES = WIDE ? 0 : WK * BN * BM * 4, EP_BYTES = WIDE ? 0 : BM * (BN + 4) * 4;
+    constexpr int BIAS = std::max({DUMP + 1024, RED_BYTES, EP_BYTES}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
     __shared__ int s_last;
@@ -998,6 +1147,8 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
         }
     };
 
+    if (WIDE && wave < BN / 64)
+        load_words_to_lds(raw_buffer(a.bias, (uint32_t)a.n_pad * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u, lds0 + BIAS + (uint32_t)wave * 256u);
 #pragma unroll
     for (int i = 0; i < PL; ++i) issue_patch(i, 0);
     xs += TK * 2;
@@ -1036,6 +1187,49 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
         return a.pool2 ? (img * (a.P >> 1) + (row >> 1)) * (a.Q >> 1) + (q >> 1) : (img * a.P + row) * a.Q + q;
     };
     wait_and_meet<0>();
+    if constexpr (WIDE) {
+        constexpr int CT = WK == 2 ? 1 : TN, XCH = WK == 2 ? NW * TM * 4096 : 0;
+        static_assert(XCH + NW * WaveTile<T, CT, TM>::BYTES <= BIAS, "exchanged sums and staging blocks fit");
+        const int c0 = wn * SUBN + (WK == 2 ? wk * 32 : 0);
+        auto complete = [&](Acc (&sums)[CT][TM]) {
+            if (!meet_splits<BN, BM, 64 * NW>(a, sums, &s_last, tile, z, true, tid)) return;
+            WaveTile<T, CT, TM> mine;
+            mine.k = (uint32_t)(n0 + c0 + (lane % mine.LPR) * 8);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) mine.m_lane[j] = pixel(wm * SUBM + j * 32 + frow);
+            if (whole_packs<8>(a)) mine.finish(a, sums, reinterpret_cast<uint16_t *>(&smem[XCH + wave * mine.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + c0, lane);
+            else store_lanes<T, MF>(a, sums, n0 + c0, mine.m_lane, fgrp);
+        };
+        if constexpr (WK == 2) {
+            // two groups: each hands the other the sums of 32 of its 64 channels and finishes the other 32
+            float4 *xch = reinterpret_cast<float4 *>(&smem[0]);
+            Acc kept[1][TM];
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float4 v;
+                    v.x = acc[1][j][4 * g]; v.y = acc[1][j][4 * g + 1]; v.z = acc[1][j][4 * g + 2]; v.w = acc[1][j][4 * g + 3];
+                    if (wk == 1) { v.x = acc[0][j][4 * g]; v.y = acc[0][j][4 * g + 1]; v.z = acc[0][j][4 * g + 2]; v.w = acc[0][j][4 * g + 3]; }
+                    xch[((wave * TM + j) * 4 + g) * 64 + lane] = v;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) kept[0][j][4 * g + t] = wk == 1 ? acc[1][j][4 * g + t] : acc[0][j][4 * g + t];
+                }
+            __syncthreads();
+            const int other = wave ^ (WN * WM);
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 v = xch[((other * TM + j) * 4 + g) * 64 + lane];
+                    kept[0][j][4 * g] += v.x; kept[0][j][4 * g + 1] += v.y; kept[0][j][4 * g + 2] += v.z; kept[0][j][4 * g + 3] += v.w;
+                }
+            complete(kept);
+        } else {
+            complete(acc);
+        }
+        return;
+    }
     if constexpr (SUMS) {
         if (a.walk.split.d == 1) {
             constexpr int NT = 64 * NW, V = BN * BM >= 8 * NT ? 8 : 4, PIECES = BN / V, EP_IT = BN * BM / V / NT;
@@ -1061,16 +1255,18 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
             return;
         }
     }
-    finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
+    if constexpr (!WIDE) finish_tile<T, BN, BM, WN, WM, WK, MF>(a, acc, smem, &s_last, n0, tile, z, pixel);
 }
 
+// Waves per SIMD the registers have to leave room for: two workgroups per compute unit of the widest tile, whose LDS fits twice.
+constexpr int tile_waves_per_simd(int bn, int bm) { return bn * bm >= 128 * 128 ? 2 : 1; }
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK) tile_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM)) tile_kernel(OpArgs a) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a);
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK) tile_pair_kernel(OpArgsPair p) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM)) tile_pair_kernel(OpArgsPair p) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y]);
 }
 
