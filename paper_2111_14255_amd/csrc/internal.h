@@ -17,6 +17,7 @@ struct IssueItem {
     int32_t stream, tenant, op;
     int32_t mates[3] = {-1, -1, -1};   // runtime only: tenants whose operator of the same index runs in this item's launch (co-issue), -1 = none
     int32_t group = -1;    // runtime only: items of a stream that carry different groups run one group after the other
+    bool alone = false;    // runtime only: no other launch of the stage can run at the same time
     int32_t fuse = 0;      // runtime only: 1 = issued as part of a neighbour's launch, 2 / 3 = launches the pair (op - 1, op): depthwise + 1x1 / 1x1 + depthwise, 4 = convolution launched with the pooling operator op + 1 in its epilogue (that operator then carries 1)
 };
 int32_t validate_pointers(int32_t n_tenants, const int32_t *lens, int32_t n_stages, const int32_t *pointers);
@@ -43,7 +44,7 @@ constexpr int IGEMM_BK = 64;   // reduction elements per implicit-GEMM tile; pac
 inline bool is_gemm_kernel(int32_t id);
 
 // ---- kernel families -------------------------------------------------------------------
-// The kernel and tile of an operator are a pure function of its shape and storage type, never of the
+// The kernel, tile and order of additions of an operator are a pure function of its shape and storage type, never of the
 // stream, CU share or stage it runs in; that is what makes outputs bit-identical across schedules.
 // For the implicit GEMMs it names the size class of the layer (the output tile of which the layer has enough to fill the
 // chip); the tile, staging and split that run it are OpArgs::form, panel and split_k.
@@ -135,6 +136,7 @@ struct OpArgs {
     // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
     // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
     uint32_t divq_m, divq_s1, divq_s2, divpq_m, divpq_s1, divpq_s2;
+    int32_t alone;               // 1: nothing else runs beside this launch (set per launch from the schedule; changes no result)
     int32_t vec_a;               // im2col rows of a 16-bit type: 1 gathered in 16-byte pieces or more (C % 8 == 0), 0 element by element
     int32_t grid_x, grid_y, grid_z, block;
 };

@@ -1259,14 +1259,14 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
 }
 
 // Waves per SIMD the registers have to leave room for: two workgroups per compute unit of the widest tile, whose LDS fits twice.
-constexpr int tile_waves_per_simd(int bn, int bm) { return bn * bm >= 128 * 128 ? 2 : 1; }
+constexpr int tile_waves_per_simd(int bn, int bm, int nbuf) { return bn * bm >= 128 * 128 && nbuf == 2 ? 2 : 1; }
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM)) tile_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_kernel(OpArgs a) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a);
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM)) tile_pair_kernel(OpArgsPair p) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_pair_kernel(OpArgsPair p) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y]);
 }
 
@@ -1524,8 +1524,16 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         };
         by_gather(go);
     };
+    // The widest tiles have two stages of LDS, so that two workgroups, or another tenant's, fit beside them; a launch that has the chip to
+    // itself and at most one workgroup per unit waits for memory at every stage that way (0.75 us, matrix instructions 0.2) and takes four.
+    // The order of the sums is the same.  us, two / four: ResNet-50 alone at batch 16, 32, 64 619 / 607, 903 / 862,
+    // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
+    const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
+    };
+    auto wide = [&]<int BN, int BM>() {
+        by_gather([&]<int MODE>() { launch((tile_kernel<T, BN, BM, 2, 2, 1, 1, 4, MODE>), grid, block, 0, st, a); });
     };
     constexpr bool f32 = std::is_same_v<T, float>;
     if (far_window(a)) {
@@ -1561,8 +1569,8 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
                 tile.template operator()<32, 32, 2, 2, 2, 2, 4>();
             } else {
                 switch (a.form) {
-                    case 0: tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
-                    case 1: tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+                    case 0: if (deep) wide.template operator()<128, 128>(); else tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
+                    case 1: if (deep) wide.template operator()<128, 64>(); else tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
                     case 6: patch.template operator()<128, 256, 2, 4, 1, 1, 384>(); break;
                     case 7: patch.template operator()<128, 128, 2, 2, 2, 1, 256>(); break;
                     case 8: patch.template operator()<128, 64, 2, 2, 2, 1, 192>(); break;

@@ -614,6 +614,7 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
         o.counters = (uint32_t *)(s->st_base + s->st_cnt_base[tenant] + to.st_cnt_off[it.op]);
     };
     redirect(a, it.tenant);
+    a.alone = it.alone ? 1 : 0;
     a.prio = tp >= 0 ? tp : (t.short_kernel[it.op] || it.fuse == 2 || it.fuse == 3) ? 3 : 0;
     if (it.fuse == 2 || it.fuse == 3) {
         OpArgs prev = patched(t, it.op - 1, inputs[it.tenant], outputs[it.tenant]);
@@ -634,6 +635,7 @@ int launch_item(const mt_ctx *ctx, const mt_schedule *s, const IssueItem &it, co
     if (it.fuse == 4) {
         OpArgs b = t.pool_args[it.op];
         b.prio = a.prio;
+        b.alone = a.alone;
         redirect(b, it.tenant);
         if (t.reads_input[it.op]) b.x = inputs[it.tenant];
         if (t.writes_output[it.op + 1]) b.y = outputs[it.tenant];
@@ -971,9 +973,13 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
                 if (sp.queue_of[sm] != q) continue;
                 const auto &items = sp.by_stream[sm];
                 const auto &level = sp.level[sm];
+                std::map<int, int> in_level;
+                for (size_t k = 0; k < items.size(); ++k) in_level[level[k]] += items[k].fuse == 1 ? 0 : 1;
                 for (size_t k = 0; k < items.size() && rc == MT_OK; ++k) {
                     const size_t first = rec.launches.size();
-                    const int e = launch_item(ctx, s, items[k], inputs, outputs, nullptr);
+                    IssueItem item = items[k];
+                    item.alone = sp.streams.size() == 1 && !s->masked && in_level[level[k]] == 1 && item.mates[0] < 0;
+                    const int e = launch_item(ctx, s, item, inputs, outputs, nullptr);
                     if (e != 0 || rec.error != 0)
                         rc = fail(MT_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString((hipError_t)(e ? e : rec.error)));
                     if (rec.launches.size() == first) continue;
@@ -983,7 +989,7 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
                         if (op + 1 == (int)ctx->tenants[t]->model.ops.size()) pc.ends_tenant[t] = true;
                         if (ctx->tenants[t]->writes_output[op]) pc.output = true;
                     }
-                    if (names_caller_buffers(ctx, items[k])) plan.io.push_back(RunPlan::IoSite{items[k], pc.first, pc.count});
+                    if (names_caller_buffers(ctx, item)) plan.io.push_back(RunPlan::IoSite{item, pc.first, pc.count});
                     top = std::max(top, pc.level);
                     pieces.push_back(pc);
                 }

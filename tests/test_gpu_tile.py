@@ -220,3 +220,28 @@ def test_far_windows_pooled_co_issued_and_beside_non_finite_pixels():
             assert float(np.abs(plain[t][~bad] - ref[~bad]).max()) <= 2e-2 * float(np.abs(ref[~bad]).max())
     finally:
         mix.close()
+
+
+@pytest.mark.parametrize("name,n,h,w,c,k,win,stride,pad", [
+    ("128x64_one_stage", 16, 28, 28, 64, 512, 1, 2, 0), ("128x128_two_stages", 16, 14, 14, 128, 1024, 1, 1, 0), ("128x64_three_stages", 15, 14, 13, 192, 520, 1, 1, 0),
+    ("128x128_four_stages", 16, 14, 14, 256, 1024, 1, 1, 0), ("128x64_five_stages", 16, 14, 14, 320, 512, 1, 1, 0), ("128x128_chunk_ragged", 16, 28, 27, 72, 252, 3, 1, 1)])
+def test_a_launch_that_has_the_chip_to_itself_keeps_the_bits(name, n, h, w, c, k, win, stride, pad):
+    """The widest tiles stage more of the reduction ahead when nothing else runs: alone, beside another tenant, and on new buffers."""
+    g = GraphBuilder("t", "bf16", n, h, w, c)
+    g.conv(0, k, win, stride, pad, act="relu", bn=True)
+    spec = g.done()
+    print("case", name, flush=True)
+    mix = Mix([spec, spec], seed=45)
+    try:
+        ctx = mix.ctx
+        check_form(ctx, name)
+        alone = ctx.schedule([[], []], 1, concurrency=[1])
+        first, _ = mix.run(alone)
+        beside, _ = mix.run(ctx.all_concurrent())
+        again, _ = mix.run(alone)                        # other output buffers: the arguments are written again
+        for p, q, r in zip(first, beside, again):
+            assert np.isfinite(p).all()
+            np.testing.assert_array_equal(p, q)
+            np.testing.assert_array_equal(p, r)
+    finally:
+        mix.close()
