@@ -478,3 +478,17 @@ def test_wave_priority_descent_matches_oracle_and_finds_a_separable_optimum():
     assert [best[0], best[1]] == [1, 2] and bc.value == 1.0 and len(n) == 8
     bad = (I32 * 2)(0, 4)
     assert B.load().mt_search_wave_priority(2, 1, fn, None, bad, C.byref(bc)) != 0
+
+
+@pytest.mark.parametrize("h,w,c,k,resident", [
+    (80, 102, 128, 256, False), (128, 64, 128, 256, True), (128, 80, 256, 64, True), (128, 81, 256, 64, False), (250, 200, 256, 512, False),
+    (128, 80, 64, 256, True), (10241, 1, 64, 256, False), (13333, 3, 64, 256, False), (200, 200, 64, 256, True), (200, 200, 64, 64, True),
+    (450, 450, 128, 128, False)])
+def test_1x1_layers_take_the_resident_filter_kernel_in_its_pixel_ranges(h, w, c, k, resident):
+    g = GraphBuilder("t", "bf16", 1, h, w, c)
+    g.conv(0, k, 1)
+    m = api.Model(g.done())
+    name = m.op_form(0).name.decode()
+    assert (name == "igemm_resident_filters") == resident, name
+    assert resident or name.startswith("tile_") or name.startswith("ring_")
+    m.close()
