@@ -17,6 +17,7 @@ struct IssueItem {
     int32_t stream, tenant, op;
     int32_t mates[3] = {-1, -1, -1};   // runtime only: tenants whose operator of the same index runs in this item's launch (co-issue), -1 = none
     int32_t group = -1;    // runtime only: items of a stream that carry different groups run one group after the other
+    int32_t units = 0;     // runtime only: compute units of the queue where queues of the stage share a dispatch pipe, 0: grids need not fit
     bool alone = false;    // runtime only: no other launch of the stage can run at the same time
     int32_t fuse = 0;      // runtime only: 1 = issued as part of a neighbour's launch, 2 / 3 = launches the pair (op - 1, op): depthwise + 1x1 / 1x1 + depthwise, 4 = convolution launched with the pooling operator op + 1 in its epilogue (that operator then carries 1)
 };
@@ -93,6 +94,7 @@ struct TileWalk {
     uint32_t adv_t, adv_c;       // taps and channels from one stage (row of a wave) to the next
     uint32_t inv_s;              // mulhi(tap, inv_s) = tap / S; 0 for S == 1
     Divisor panel_tiles;         // patches: pixel tile -> (panel, tile of it)
+    uint32_t step;               // slots from one tile of a workgroup to its next, where a workgroup takes several (set per launch)
     uint32_t inv_pw, inv_h;      // patches: 2^20 over the patch's row and over H + 1, rounded up
 };
 
@@ -136,6 +138,7 @@ struct OpArgs {
     // Exact unsigned division by Q and by P*Q without a divide (multiply-high, two shifts): n / d =
     // (t + ((n - t) >> s1)) >> s2 with t = mulhi(m, n); filled by make_divisor().
     uint32_t divq_m, divq_s1, divq_s2, divpq_m, divpq_s1, divpq_s2;
+    int32_t units;               // grids beyond what this many compute units hold at once are walked by as many workgroups as fit, 0: no such limit
     int32_t alone;               // 1: nothing else runs beside this launch (set per launch from the schedule; changes no result)
     int32_t vec_a;               // im2col rows of a 16-bit type: 1 gathered in 16-byte pieces or more (C % 8 == 0), 0 element by element
     int32_t grid_x, grid_y, grid_z, block;

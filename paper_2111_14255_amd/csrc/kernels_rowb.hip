@@ -17,6 +17,8 @@
 // activation, one rounding, and the way back through the same block to 16-byte stores.  fp32 accumulation in step order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "device_types.h"
 #include "mfma.h"
@@ -418,9 +420,19 @@ void plan_rowb(OpArgs &a) {
     }
 }
 
-int launch_rowb(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates) {
+int launch_rowb(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates) {
     if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
+    OpArgs a = op;
+    if (a.units > 0 && !mate) {
+        // no more workgroups than the queue's units hold at once (see tile_walk_kernel): two a unit where the filters are small
+        const int slices = (int)a.walk.tiles.d, room = a.units * (!rowb_patch_form(a) && a.C <= 128 && a.R == 1 ? 2 : 1);
+        const int chunks = std::max(1, room / slices);
+        if (chunks * slices < a.grid_x) {
+            a.grid_x = chunks * slices;
+            a.walk.per = (uint32_t)(chunks * (a.block / 64));
+        }
+    }
     const dim3 grid(a.grid_x), block(a.block);
     const int nta = rowb_tiles(a.R, a.S, a.C, a.n_pad);
     if (nta == 0 || (int)block.x != 64 * rowb_waves(a.R, a.S, a.C, a.n_pad)) return (int)hipErrorInvalidValue;

@@ -22,6 +22,8 @@
 // consecutive channels (full cache lines per pixel).  fp32 accumulation in step order t = 0 .. KS-1.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "device_types.h"
 #include "mfma.h"
@@ -249,9 +251,14 @@ int stem_form(int R, int S, int sw, int W, int pw, int channels) {
     return (sw % 2 == 0 && W % 2 == 0 && ((3 * pw) & 1)) ? 1 : 2;
 }
 
-int launch_stem(const OpArgs &a, void *stream, const OpArgs *mate, int n_mates) {
+int launch_stem(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates) {
     if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
+    OpArgs a = op;
+    if (a.units > 0 && !mate) {                          // as many workgroups as the queue's units hold at once
+        a.grid_x = std::min(a.grid_x, a.units * (a.R == 7 && a.n_pad == 64 ? 3 : 6));
+        a.walk.per = (uint32_t)a.grid_x * 4;
+    }
     const dim3 grid(a.grid_x), block(256);
     const int tn = a.n_pad / 32;
     const int form = stem_form(a.R, a.S, a.sw, a.W, a.pw, a.n_pad);

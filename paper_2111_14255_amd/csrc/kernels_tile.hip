@@ -48,9 +48,10 @@ __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t 
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
-// The same with 4 bytes a lane.
+// The same with 4 bytes a lane.  Once per tile: its descriptor may come out of vector registers (v_readlane) just before, and the five wait
+// states between a vector instruction that writes scalar registers and a load that reads them are not added inside inline assembly.
 __device__ __forceinline__ void load_words_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    asm volatile("s_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 // All but the N youngest loads of this wave have landed, its LDS reads are done, and the other waves got here as well.
@@ -576,9 +577,10 @@ __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
 }
 
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.
-__device__ __forceinline__ bool find_tile(const OpArgs &a, int &tile, int &z, int &tn_idx, int &tm_idx) {
+// slot: position in the XCD's range of tiles.
+__device__ __forceinline__ bool find_tile(const OpArgs &a, uint32_t slot, int &tile, int &z, int &tn_idx, int &tm_idx) {
     const TileWalk &w = a.walk;
-    const uint32_t vid = (blockIdx.x % XCDS) * w.per_xcd + blockIdx.x / XCDS;
+    const uint32_t vid = (blockIdx.x % XCDS) * w.per_xcd + slot;
     if (vid >= w.total) return false;
     const uint32_t t = w.split.d == 1 ? vid : divide(vid, w.split);
     z = (int)(vid - t * w.split.d);
@@ -592,7 +594,7 @@ __device__ __forceinline__ bool find_tile(const OpArgs &a, int &tile, int &z, in
 // BN output channels x BM pixels per workgroup; WN x WM waves over the tile, WK such groups that share the reduction;
 // KD 64-deep slices of the reduction per stage, NBUF stages in LDS.
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__device__ __forceinline__ void tile_body(const OpArgs &a) {
+__device__ __forceinline__ void tile_body(const OpArgs &a, uint32_t slot) {
     fetch_walk(a);
     set_wave_priority(a.prio);
     constexpr int NW = WN * WM * WK;
@@ -623,7 +625,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a) {
     const int frow = lane % MF, fgrp = lane / MF;          // operand row and reduction group of this lane
 
     int tile, z, tn_idx, tm_idx;
-    if (!find_tile(a, tile, z, tn_idx, tm_idx)) return;
+    if (!find_tile(a, slot, tile, z, tn_idx, tm_idx)) return;
     const int M = (int)a.walk.pixels;
     const int n0 = tn_idx * BN, m0 = tm_idx * BM;
 
@@ -861,7 +863,7 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, z, tn_idx, tm_idx;
-    if (!find_tile(a, tile, z, tn_idx, tm_idx)) return;
+    if (!find_tile(a, blockIdx.x / XCDS, tile, z, tn_idx, tm_idx)) return;
     const int M = (int)a.walk.pixels;
     const int n0 = tn_idx * BN, m0 = tm_idx * BM;
 
@@ -995,7 +997,7 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
 // panel + 2 pixels wide, with an empty row between two images; what lies outside an image is loaded out of range, i.e. zero.
 // The filter bank is [n_pad][chunk][tap][64].
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
-__device__ __forceinline__ void patch_body(const OpArgs &a) {
+__device__ __forceinline__ void patch_body(const OpArgs &a, uint32_t slot) {
     fetch_walk(a);
     set_wave_priority(a.prio);
     constexpr int NW = WN * WM * WK, NBUF = 3;
@@ -1028,7 +1030,7 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
 
     const int Wt = a.panel, PW = Wt + 2;
     int tile, z, tn_idx, tm_idx;
-    if (!find_tile(a, tile, z, tn_idx, tm_idx)) return;
+    if (!find_tile(a, slot, tile, z, tn_idx, tm_idx)) return;
     const int ppx = a.N * a.P * Wt;                        // pixels of a panel
     const int pn = (int)divide((uint32_t)tm_idx, a.walk.panel_tiles);
     const int n0 = tn_idx * BN, m0 = (tm_idx - pn * (int)a.walk.panel_tiles.d) * BM;
@@ -1262,12 +1264,27 @@ __device__ __forceinline__ void patch_body(const OpArgs &a) {
 constexpr int tile_waves_per_simd(int bn, int bm, int nbuf) { return bn * bm >= 128 * 128 && nbuf == 2 ? 2 : 1; }
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_kernel(OpArgs a) {
-    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a);
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, blockIdx.x / XCDS);
+}
+
+// The same with fewer workgroups than tiles: a workgroup takes every walk.step-th tile of its XCD's range.  Where two queues share a dispatch
+// pipe the pipe is taken until the last workgroup of a launch has found room: launches that fit their queue's units at once let
+// the other queue's run beside them.  Queues on 32 units each, two to a pipe, us a kernel (four queues in brackets): 37 us of short workgroups 89 (39),
+// 50 us of resident ones 86 (54).  Eight ResNet-50 on disjoint eighths of the units, us: batch 4 3397 / 2972, 16 5452 / 3979
+// (in eight stages 5988 / 4464), 64 13997 / 9700; four and fewer have a pipe each and run the kernel above.
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_walk_kernel(OpArgs a) {
+    for (uint32_t slot = blockIdx.x / XCDS;;) {
+        tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, slot);
+        slot += a.walk.step;
+        if (slot >= a.walk.per_xcd) return;
+        __syncthreads();                                   // every wave is done with the tile's LDS
+    }
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_pair_kernel(OpArgsPair p) {
-    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y]);
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y], blockIdx.x / XCDS);
 }
 
 template <typename T, int BN, int WK, int D, int MODE>
@@ -1282,12 +1299,22 @@ __global__ void __launch_bounds__(64 * WK) ring_pair_kernel(OpArgsPair p) {
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a);
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, blockIdx.x / XCDS);
+}
+
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+__global__ void __launch_bounds__(64 * WN * WM * WK) patch_walk_kernel(OpArgs a) {
+    for (uint32_t slot = blockIdx.x / XCDS;;) {
+        patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, slot);
+        slot += a.walk.step;
+        if (slot >= a.walk.per_xcd) return;
+        __syncthreads();
+    }
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPair p) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(p.a[blockIdx.y]);
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(p.a[blockIdx.y], blockIdx.x / XCDS);
 }
 
 // ---- choice of form -----------------------------------------------------------------------------------------------
@@ -1510,8 +1537,21 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         else if (a.R == 1 && a.S == 1 && a.ph == 0 && a.pw == 0) go.template operator()<TG_POINT>();
         else go.template operator()<TG_TAP>();
     };
+    // Workgroups of a launch that has to fit a.units compute units at once, `room` of them per unit; 0: it fits, or need not
+    OpArgs walked = a;
+    auto walkers = [&](int room) {
+        const uint32_t fit = (uint32_t)(a.units * room) / XCDS;
+        if (a.units == 0 || mate || fit >= a.walk.per_xcd) return 0u;
+        walked.walk.step = fit;
+        return fit * XCDS;
+    };
     auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
         auto go = [&]<int MODE>() {
+            if constexpr (sizeof(T) == 2 && (MODE == TG_POINT || MODE == TG_TAP) && BM > 16) {
+                // workgroups a unit holds: by LDS (three of up to 53 KB, two of up to 80 KB)
+                if (const uint32_t g = walkers(NBUF * KD * (BN + BM) <= 416 ? 3 : NBUF * KD * (BN + BM) <= 600 ? 2 : 1))
+                    return launch((tile_walk_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), dim3(g), block, 0, st, walked);
+            }
             if constexpr (std::is_same_v<T, float>) launch((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, 0, st, a);
             else MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, st, a, mate);
         };
@@ -1530,6 +1570,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
     const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
+        if (const uint32_t g = walkers(BM == 32 ? 2 : 1)) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, KD, PC>), dim3(g), block, 0, st, walked);
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
     };
     auto wide = [&]<int BN, int BM>() {

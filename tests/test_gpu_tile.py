@@ -245,3 +245,43 @@ def test_a_launch_that_has_the_chip_to_itself_keeps_the_bits(name, n, h, w, c, k
             np.testing.assert_array_equal(p, r)
     finally:
         mix.close()
+
+
+@pytest.mark.parametrize("dtype,share", [("bf16", 32), ("f16", 40), ("bf16", 8)])
+def test_workgroups_that_walk_several_tiles_keep_the_bits(dtype, share):
+    """More queues with a share of the units than dispatch pipes: launches larger than a share holds at once are walked by as many
+    workgroups as fit.  Every form that has such a kernel, tiles that do not divide evenly among them, and a split reduction."""
+    layers = [("128x128_tap_split3_stride2", 12, 56, 56, 256, 256, 3, 2, 1), ("128x64_c192", 15, 14, 13, 192, 520, 1, 1, 0), ("64x64_point", 3, 77, 91, 128, 136, 1, 1, 0),
+              ("64x64_deep_tap_stride2", 5, 56, 57, 64, 200, 3, 2, 1), ("64x32_point", 1, 60, 60, 512, 72, 1, 1, 0), ("128x128_point", 3, 70, 70, 320, 200, 1, 1, 0),
+              ("patch_64x64_split4", 1, 28, 28, 512, 256, 3, 1, 1), ("patch_64x32_odd_map", 2, 17, 17, 192, 512, 3, 1, 1), ("patch_128x64_wide_panel", 1, 100, 66, 128, 256, 3, 1, 1),
+              ("patch_128x128_last_panel_partial", 2, 66, 97, 128, 256, 3, 1, 1), ("patch_128x256", 2, 112, 112, 64, 256, 3, 1, 1)]
+    specs = []
+    for name, n, h, w, c, k, win, stride, pad in layers:
+        g = GraphBuilder(name, dtype, n, h, w, c)
+        g.conv(0, k, win, stride, pad, act="relu", bn=True)
+        specs.append(g.done())
+    g = GraphBuilder("resident", dtype, 5, 112, 112, 64)                 # the resident-filter and first-layer kernels walk by themselves
+    g.conv(g.conv(0, 256, 1, 1, 0, act="relu", bn=True), 64, 1, 1, 0, act="none", bn=True)
+    g.conv(0, 64, 3, 1, 1, act="relu", bn=True)
+    specs.append(g.done())
+    g = GraphBuilder("first", dtype, 6, 224, 224, 3)
+    g.conv(0, 64, 7, 2, 3, act="relu", bn=True)
+    specs.append(g.done())
+    for first in range(0, len(specs), 8):
+        group = specs[first:first + 8] if len(specs) - first >= 8 else specs[-8:]
+        mix = Mix(group, seed=46)
+        try:
+            ctx = mix.ctx
+            for t, spec in enumerate(group):
+                if re.match(r"(patch_)?\d+x", spec.name):
+                    assert ctx.op_form(t, 0).name.decode().endswith(re.search(r"\d+x\d+", spec.name).group(0))
+            print("case", dtype, share, [s.name for s in group], flush=True)
+            plain, _ = mix.run(ctx.sequential())
+            shared = ctx.schedule([[] for _ in group], 1, cu_share=[share] * len(group))
+            for _ in range(2):
+                got, _ = mix.run(shared)
+                for p, q in zip(plain, got):
+                    assert np.isfinite(p).all()
+                    np.testing.assert_array_equal(p, q)
+        finally:
+            mix.close()
