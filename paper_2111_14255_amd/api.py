@@ -159,6 +159,12 @@ class Schedule:
         arr = (C.c_int32 * len(prio))(*prio)
         B.check(B.load().mt_schedule_set_wave_priority(self.h, arr))
 
+    def launch_forms(self):
+        """(launches of the latest run whose grids were cut to a share of the units, launches that stage four steps ahead)"""
+        walked, deep = C.c_int32(), C.c_int32()
+        B.check(B.load().mt_schedule_launch_forms(self.h, C.byref(walked), C.byref(deep)))
+        return walked.value, deep.value
+
     def close(self):
         if self.h:
             B.load().mt_schedule_destroy(self.h)

@@ -120,6 +120,7 @@ SIGNATURES = {
     "mt_schedule_create": (_i32, [_vp, _i32, _i32, _pi32, _pi32, _pi32, _i32, _i32, C.POINTER(_vp)]),
     "mt_release_idle_streams": (_i32, [_vp]),
     "mt_schedule_set_wave_priority": (_i32, [_vp, C.POINTER(C.c_int32)]),
+    "mt_schedule_launch_forms": (_i32, [_vp, _pi32, _pi32]),
     "mt_schedule_destroy": (_i32, [_vp]),
     "mt_expand_pointers": (_i32, [_i32, _pi32, _i32, _pi32, _pi32]),
     "mt_issue_order_of_stage": (_i32, [_i32, _pi32, _i32, _i32, _pi32, _pi32]),

@@ -429,6 +429,7 @@ int launch_rowb(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates)
         const int slices = (int)a.walk.tiles.d, room = a.units * (!rowb_patch_form(a) && a.C <= 128 && a.R == 1 ? 2 : 1);
         const int chunks = std::max(1, room / slices);
         if (chunks * slices < a.grid_x) {
+            count_launch(&LaunchRecorder::walked);
             a.grid_x = chunks * slices;
             a.walk.per = (uint32_t)(chunks * (a.block / 64));
         }

@@ -255,8 +255,9 @@ int launch_stem(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates)
     if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
     OpArgs a = op;
-    if (a.units > 0 && !mate) {                          // as many workgroups as the queue's units hold at once
-        a.grid_x = std::min(a.grid_x, a.units * (a.R == 7 && a.n_pad == 64 ? 3 : 6));
+    if (const int fit = a.units * (a.R == 7 && a.n_pad == 64 ? 3 : 6); a.units > 0 && !mate && fit < a.grid_x) {   // as many workgroups as the queue's units hold at once
+        count_launch(&LaunchRecorder::walked);
+        a.grid_x = fit;
         a.walk.per = (uint32_t)a.grid_x * 4;
     }
     const dim3 grid(a.grid_x), block(256);

@@ -1543,6 +1543,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         const uint32_t fit = (uint32_t)(a.units * room) / XCDS;
         if (a.units == 0 || mate || fit >= a.walk.per_xcd) return 0u;
         walked.walk.step = fit;
+        count_launch(&LaunchRecorder::walked);
         return fit * XCDS;
     };
     auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
@@ -1574,6 +1575,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
     };
     auto wide = [&]<int BN, int BM>() {
+        count_launch(&LaunchRecorder::deep);
         by_gather([&]<int MODE>() { launch((tile_kernel<T, BN, BM, 2, 2, 1, 1, 4, MODE>), grid, block, 0, st, a); });
     };
     constexpr bool f32 = std::is_same_v<T, float>;

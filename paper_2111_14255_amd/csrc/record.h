@@ -32,11 +32,16 @@ struct LaunchRecorder {
     LaneDevice *dev = nullptr;
     std::vector<RecordedLaunch> launches;
     std::vector<uint8_t> args;
+    int walked = 0, deep = 0;            // launches cut to a share of the units, and staged deep (mt_schedule_launch_forms)
     int error = 0;                       // hipError_t of the first launch that could not be written down
     void add(const void *host_fn, dim3 grid, dim3 block, size_t lds, const void *packed, size_t bytes);
 };
 
 LaunchRecorder *&current_recorder();     // of the calling thread, null = launch for real
+
+inline void count_launch(int LaunchRecorder::*what) {
+    if (LaunchRecorder *r = current_recorder()) ++(r->*what);
+}
 
 template <typename... P, typename... A>
 inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, const A &...args) {

@@ -508,6 +508,7 @@ struct RunPlan {
     struct IoSite { IssueItem item; size_t first, count; };
     std::vector<IoSite> io;                          // launches whose arguments name the caller's buffers
     int first_op[MT_MAX_TENANTS], last_op[MT_MAX_TENANTS];   // signals of the timed operators, -1: none
+    int walked = 0, deep = 0;                        // see mt_schedule_launch_forms
 };
 
 struct mt_schedule {
@@ -521,6 +522,7 @@ struct mt_schedule {
     int32_t prio[MT_MAX_TENANTS] = {0};   // wave priority of a tenant's kernels, 0..3; -1: 3 for its short kernels, 0 for the others
     RunPlan plan[2];                // of mt_run, and of mt_run_static_scratch where any operator has its workspace in the fixed array
     std::vector<hsa_signal_t> signals;             // of both plans, which never run at the same time
+    int last_plan = 0;                             // the one that ran last
     // mt_run_static_scratch: argument memory held for its plan, plan[static_plan] (-1: it refuses the schedule)
     int static_plan = -1;
     KernargBlock static_args;
@@ -1079,6 +1081,8 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
         for (Pending &p : pending[st]) plan.stages[st].push_back(finish(p));
     }
     plan.launches = std::move(rec.launches);
+    plan.walked = rec.walked;
+    plan.deep = rec.deep;
     plan.in.assign(inputs, inputs + s->n_tenants);
     plan.out.assign(outputs, outputs + s->n_tenants);
     plan.valid = true;
@@ -2116,6 +2120,13 @@ int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio) {
     return MT_OK;
 }
 
+int32_t mt_schedule_launch_forms(const mt_schedule *s, int32_t *n_walked, int32_t *n_deep) {
+    if (!s || !n_walked || !n_deep) return fail(MT_ERR_INVALID_ARG, "NULL argument");
+    *n_walked = s->plan[s->last_plan].walked;
+    *n_deep = s->plan[s->last_plan].deep;
+    return MT_OK;
+}
+
 int32_t mt_schedule_destroy(mt_schedule *s) {
     if (!s) return fail(MT_ERR_INVALID_ARG, "schedule is NULL");
     if (s->ctx) {
@@ -2178,7 +2189,8 @@ static int32_t run_pass(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, 
     HIP_TRY(wait_for_default_stream());
     const auto t0 = std::chrono::steady_clock::now();
     LaneDevice *dev = ctx->lanes;
-    RunPlan &plan = s->plan[static_scratch && counter_bytes > 0 ? 1 : 0];
+    s->last_plan = static_scratch && counter_bytes > 0 ? 1 : 0;
+    RunPlan &plan = s->plan[s->last_plan];
     bool same = plan.valid;
     for (int i = 0; same && i < s->n_tenants; ++i) same = plan.in[i] == inputs[i] && plan.out[i] == outputs[i];
     if (!same && !(plan.valid && rebind_plan(ctx, s, inputs, outputs, plan))) {

@@ -236,9 +236,12 @@ def test_a_launch_that_has_the_chip_to_itself_keeps_the_bits(name, n, h, w, c, k
         ctx = mix.ctx
         check_form(ctx, name)
         alone = ctx.schedule([[], []], 1, concurrency=[1])
+        both = ctx.all_concurrent()
+        assert alone.launch_forms() == (0, 0)            # nothing has run yet
         first, _ = mix.run(alone)
-        beside, _ = mix.run(ctx.all_concurrent())
+        beside, _ = mix.run(both)
         again, _ = mix.run(alone)                        # other output buffers: the arguments are written again
+        assert alone.launch_forms() == (0, 2) and both.launch_forms() == (0, 0)
         for p, q, r in zip(first, beside, again):
             assert np.isfinite(p).all()
             np.testing.assert_array_equal(p, q)
@@ -276,10 +279,14 @@ def test_workgroups_that_walk_several_tiles_keep_the_bits(dtype, share):
                 if re.match(r"(patch_)?\d+x", spec.name):
                     assert ctx.op_form(t, 0).name.decode().endswith(re.search(r"\d+x\d+", spec.name).group(0))
             print("case", dtype, share, [s.name for s in group], flush=True)
-            plain, _ = mix.run(ctx.sequential())
+            alone, four = ctx.sequential(), ctx.schedule([[] for _ in group], 1, cu_share=[share] * 4 + [0] * (len(group) - 4), concurrency=[4])
+            plain, _ = mix.run(alone)
+            mix.run(four)                                # four queues have a dispatch pipe each
+            assert alone.launch_forms()[0] == 0 and four.launch_forms() == (0, 0)
             shared = ctx.schedule([[] for _ in group], 1, cu_share=[share] * len(group))
             for _ in range(2):
                 got, _ = mix.run(shared)
+                assert shared.launch_forms() == (sum(len(spec.ops) for spec in group), 0)      # all of them are larger than their share
                 for p, q in zip(plain, got):
                     assert np.isfinite(p).all()
                     np.testing.assert_array_equal(p, q)
