@@ -1267,14 +1267,31 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM,
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, blockIdx.x / XCDS);
 }
 
+// Workgroups of a walking kernel that a compute unit holds, by LDS (three of up to 53 KB, two of up to 80 KB); the kernels' launch bounds have
+// the compiler leave registers for as many.
+constexpr int tile_room(int bn, int bm, int kd, int nbuf) { return nbuf * kd * (bn + bm) <= 416 ? 3 : nbuf * kd * (bn + bm) <= 600 ? 2 : 1; }
+constexpr int patch_room(int bm) { return bm == 32 ? 2 : 1; }
+
+// The OpArgs a kernel was launched with, as its only parameter.  What is read through one call is not kept for the next.
+__device__ __forceinline__ const OpArgs &kernel_arguments() {
+    typedef const OpArgs __attribute__((address_space(4))) InConstant;
+    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const OpArgs *)(InConstant *)at;
+}
+
 // The same with fewer workgroups than tiles: a workgroup takes every walk.step-th tile of its XCD's range.  Where two queues share a dispatch
 // pipe the pipe is taken until the last workgroup of a launch has found room: launches that fit their queue's units at once let
 // the other queue's run beside them.  Queues on 32 units each, two to a pipe, us a kernel (four queues in brackets): 37 us of short workgroups 89 (39),
 // 50 us of resident ones 86 (54).  Eight ResNet-50 on disjoint eighths of the units, us: batch 4 3397 / 2972, 16 5452 / 3979
 // (in eight stages 5988 / 4464), 64 13997 / 9700; four and fewer have a pipe each and run the kernel above.
+// The arguments are read anew for every tile: kept across the loop they are more scalars than there are, and the compiler puts 70 to 146 of them
+// into lanes of vector registers (f16 64x32 tile: 129 registers, one more than two workgroups leave each; 126 to 128 so).  Eight ResNet-50 at
+// batch 16 in eight stages 4597 / 4500 us, runs of one side 4 % apart.
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_walk_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD, NBUF) * WN * WM * WK / 4) tile_walk_kernel(OpArgs) {
     for (uint32_t slot = blockIdx.x / XCDS;;) {
+        const OpArgs &a = kernel_arguments();
         tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) return;
@@ -1303,8 +1320,9 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
-__global__ void __launch_bounds__(64 * WN * WM * WK) patch_walk_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * WK / 4) patch_walk_kernel(OpArgs) {
     for (uint32_t slot = blockIdx.x / XCDS;;) {
+        const OpArgs &a = kernel_arguments();
         patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) return;
@@ -1549,8 +1567,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
         auto go = [&]<int MODE>() {
             if constexpr (sizeof(T) == 2 && (MODE == TG_POINT || MODE == TG_TAP) && BM > 16) {
-                // workgroups a unit holds: by LDS (three of up to 53 KB, two of up to 80 KB)
-                if (const uint32_t g = walkers(NBUF * KD * (BN + BM) <= 416 ? 3 : NBUF * KD * (BN + BM) <= 600 ? 2 : 1))
+                if (const uint32_t g = walkers(tile_room(BN, BM, KD, NBUF)))
                     return launch((tile_walk_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), dim3(g), block, 0, st, walked);
             }
             if constexpr (std::is_same_v<T, float>) launch((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, 0, st, a);
@@ -1571,7 +1588,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
     const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
-        if (const uint32_t g = walkers(BM == 32 ? 2 : 1)) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, KD, PC>), dim3(g), block, 0, st, walked);
+        if (const uint32_t g = walkers(patch_room(BM))) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, KD, PC>), dim3(g), block, 0, st, walked);
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
     };
     auto wide = [&]<int BN, int BM>() {

@@ -10,6 +10,7 @@ import pytest
 from paper_2111_14255_amd import binding as B, api
 from oracle import schedule as S, fold as ofold, ops as oops
 from synth import GraphBuilder, zoo, weights
+import code_objects
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 I32 = C.c_int32
@@ -492,3 +493,13 @@ def test_1x1_layers_take_the_resident_filter_kernel_in_its_pixel_ranges(h, w, c,
     assert (name == "igemm_resident_filters") == resident, name
     assert resident or name.startswith("tile_") or name.startswith("ring_")
     m.close()
+
+
+def test_a_unit_holds_as_many_walking_workgroups_as_their_launches_count_on():
+    """Launches cut to a share of the units count on as many workgroups per unit as the LDS holds, three at most: registers have to leave room for
+    them.  None of these kernels keeps scalars in vector registers (the loads to LDS take theirs without the compiler's wait states)."""
+    walking = {name: k for name, k in code_objects.kernels().items() if "_walk_kernel" in name}
+    assert len(walking) == 30
+    for name, k in walking.items():
+        assert code_objects.held_by_registers(k) >= min(3, 160 * 1024 // k[".group_segment_fixed_size"]), name
+        assert k[".sgpr_spill_count"] == 0 and k[".vgpr_spill_count"] == 0, name
