@@ -43,7 +43,10 @@ constexpr int XCDS = 8;
 constexpr uint32_t OUT_OF_RANGE = 0x80000000u;  // beyond any tensor: the load delivers zeros
 
 // 64 lanes x 16 bytes from rsrc + voff (per lane) + soff to LDS at `lds` + 16 * lane.  The instruction takes the LDS address from m0;
-// the compiler puts it there, so it knows what m0 holds, and the wait state the load needs after that follows.
+// the compiler puts it there, so it knows what m0 holds, and the wait state the load needs after that follows.  It needs five after a vector
+// instruction that writes one of its scalars (v_readlane, v_readfirstlane), which nothing adds inside inline assembly: the scalars come from
+// arguments and scalar arithmetic, none of the kernels spills any, and the host tests look for such a pair in the built kernels.  (Five states
+// in front of every load make ResNet-50 at batch 64 0.5 %, Inception-v3 and AlexNet at batch 5 1 % slower.)
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }

@@ -1,6 +1,8 @@
 """What the compiler says about the kernels of the built library: the metadata of its gfx950 code objects, read from the file."""
 import os
+import re
 import struct
+import subprocess
 
 import msgpack
 
@@ -44,3 +46,49 @@ def held_by_registers(kernel):
     """Workgroups of a kernel whose registers a compute unit holds: 512 per lane of each of four SIMDs, given out in eights."""
     waves = kernel[".max_flat_workgroup_size"] // 64
     return 512 // ((kernel[".vgpr_count"] + 7) // 8 * 8) * 4 // waves
+
+
+def listings():
+    """Assembly of the code objects, kernel by kernel: (name, [(address, mnemonic, operands)])."""
+    for elf in objects():
+        text = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", "--mcpu=gfx950", "-"], input=elf, capture_output=True, check=True).stdout.decode()
+        for part in re.split(r"\n(?=[0-9a-f]+ <)", text)[1:]:
+            head, _, body = part.partition("\n")
+            yield head, [(int(a, 16), m, [o.strip() for o in ops.split(",")]) for m, ops, a in re.findall(r"^\t(\S+) ?(.*?)\s*// ([0-9A-F]+):", body, re.M)]
+
+
+def scalars(operand):
+    """Scalar registers an operand names: s7, s[4:7], vcc, m0."""
+    m = re.match(r"(?:s\[(\d+):(\d+)\]|s(\d+)$)", operand)
+    if m:
+        return set(range(int(m[1]), int(m[2]) + 1)) if m[1] else {int(m[3])}
+    return {operand} if operand in ("vcc", "m0") else set()
+
+
+def early_lds_loads(code, states=5):
+    """Loads to LDS that read a scalar register which a vector instruction wrote fewer than `states` wait states before, on any path."""
+    at = {a: i for i, (a, _, _) in enumerate(code)}
+    came_from = [[] for _ in code]
+    for i, (a, m, ops) in enumerate(code):
+        if m not in ("s_branch", "s_endpgm", "s_setpc_b64") and i + 1 < len(code):
+            came_from[i + 1].append(i)
+        if m.startswith(("s_branch", "s_cbranch")):
+            offset = int(re.match(r"\d+", ops[0])[0])
+            came_from[at[a + 4 + 4 * (offset - 65536 if offset > 32767 else offset)]].append(i)
+    found = []
+    for i, (a, m, ops) in enumerate(code):
+        if not (m.startswith("buffer_load") and ops[-1].split()[-1] == "lds"):
+            continue
+        reads = scalars(ops[1]) | scalars(ops[2].split()[0]) | {"m0"}
+        todo = [(j, states) for j in came_from[i]]
+        while todo:
+            j, left = todo.pop()
+            _, mj, oj = code[j]
+            # results: the first operand, of additions with carry, divisions and 64-bit multiply-adds the second as well
+            results = scalars(oj[0]) | (scalars(oj[1]) if re.search("_co_|div_scale|mad_[iu]64", mj) else set())
+            if mj.startswith("v_") and results & reads:
+                found.append((hex(a), mj))
+            left -= int(oj[0], 0) + 1 if mj == "s_nop" else 1
+            if left > 0:
+                todo += [(k, left) for k in came_from[j]]
+    return found

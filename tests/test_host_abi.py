@@ -503,3 +503,22 @@ def test_a_unit_holds_as_many_walking_workgroups_as_their_launches_count_on():
     for name, k in walking.items():
         assert code_objects.held_by_registers(k) >= min(3, 160 * 1024 // k[".group_segment_fixed_size"]), name
         assert k[".sgpr_spill_count"] == 0 and k[".vgpr_spill_count"] == 0, name
+
+
+def test_loads_to_lds_keep_their_distance_from_vector_instructions_that_write_scalars():
+    """The tile kernels' loads to LDS are inline assembly, in which the compiler does not add the five wait states that a load needs after a
+    vector instruction has written a scalar register it reads.  Shown on small listings, then in every kernel of the library."""
+    load = (8, "buffer_load_dwordx4", ["v4", "s[20:23]", "s14 offen lds"])
+    end = (16, "s_endpgm", [""])
+    for op, early in ((("v_readlane_b32", ["s22", "v1", "3"]), True), (("v_readfirstlane_b32", ["s14", "v1"]), True), (("v_readlane_b32", ["m0", "v1", "3"]), True),
+                      (("v_add_co_u32_e64", ["v2", "s[14:15]", "v1", "v3"]), True), (("v_readlane_b32", ["s24", "v1", "3"]), False), (("s_mov_b32", ["s22", "s1"]), False)):
+        assert bool(code_objects.early_lds_loads([(0, *op), (4, "s_nop", ["3"]), load, end])) == early, op
+        assert not code_objects.early_lds_loads([(0, *op), (4, "s_nop", ["4"]), load, end])
+    # behind the jump back to the head of a loop
+    loop = [(0, "s_nop", ["4"]), load, (16, "v_readlane_b32", ["s14", "v1", "3"]), (24, "s_cbranch_scc1", ["65531"]), (28, "s_endpgm", [""])]
+    assert code_objects.early_lds_loads(loop)
+    n = 0
+    for name, code in code_objects.listings():
+        n += sum(1 for _, m, ops in code if m.startswith("buffer_load") and ops[-1].endswith(" lds"))
+        assert not code_objects.early_lds_loads(code), name
+    assert n > 1000
