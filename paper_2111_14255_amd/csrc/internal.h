@@ -184,6 +184,11 @@ inline StemGeom stem_geom(int R, int S, int form) {
     g.ksteps = (g.ng + 1) / 2;
     return g;
 }
+// Workgroups of an instantiation that a compute unit holds: what the launch bounds have the compiler leave registers for (7x7 145, 3x3 on 64 channels 85, on 32
+// 63).  A grid of more waits for room, and on a queue that shares a dispatch pipe the other queue with it.  us a layer, six per unit
+// / this: 3x3 -> 64 on 224 x 224 at batch 4, 8, 16, 64 10.6 / 9.9, 15.8 / 14.7, 24.4 / 24.0, 105.7 / 100.5; 7x7 / 2 -> 32 at batch 16 and 64 10.8 /
+// 10.0, 24.9 / 23.9; with one more per unit (3x3 -> 64: 5) within 2 % of this.
+constexpr int stem_room(int R, int channels) { return R == 7 ? 3 : channels == 64 ? 4 : 6; }
 int stem_form(int R, int S, int sw, int W, int pw, int channels);    // 0: none, 1: aligned form (one dummy element per run), 2: general form
 int launch_stem(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int n_mates = 0);
 // K_ROWB: waves per workgroup of the instantiation for this window / channel counts, 0 if there is none.  Its packed

@@ -233,12 +233,12 @@ __device__ __forceinline__ void stem_kernel_body(const OpArgs &a) {
     }
 }
 template <typename T, int R, int S, int DUMMY, int TN, bool ALIGNED>
-__global__ void __launch_bounds__(256) stem_kernel(OpArgs a) {
+__global__ void __launch_bounds__(256, stem_room(R, 32 * TN)) stem_kernel(OpArgs a) {
     stem_kernel_body<T, R, S, DUMMY, TN, ALIGNED>(a);
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int R, int S, int DUMMY, int TN, bool ALIGNED>
-__global__ void __launch_bounds__(256) stem_pair_kernel(OpArgsPair p) {
+__global__ void __launch_bounds__(256, stem_room(R, 32 * TN)) stem_pair_kernel(OpArgsPair p) {
     stem_kernel_body<T, R, S, DUMMY, TN, ALIGNED>(p.a[blockIdx.y]);
 }
 
@@ -255,7 +255,7 @@ int launch_stem(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates)
     if (mate && (n_mates < 1 || n_mates >= COISSUE_MAX)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
     OpArgs a = op;
-    if (const int fit = a.units * (a.R == 7 && a.n_pad == 64 ? 3 : 6); a.units > 0 && !mate && fit < a.grid_x) {   // as many workgroups as the queue's units hold at once
+    if (const int fit = a.units * stem_room(a.R, a.n_pad); a.units > 0 && !mate && fit < a.grid_x) {   // as many workgroups as the queue's units hold at once
         count_launch(&LaunchRecorder::walked);
         a.grid_x = fit;
         a.walk.per = (uint32_t)a.grid_x * 4;

@@ -280,9 +280,8 @@ int32_t finalize_model(mt_model *m) {
                         p.n_pad = o.out_c;
                         p.k_pad = sg.ksteps * 16;
                         const int n_tiles = (m->batch * o.out_h * o.out_w + 31) / 32;
-                                                // as many workgroups as stay resident (3 per compute unit for the 7x7 window with 64 channels, by
-                        // registers and LDS; 6 or more for the lighter forms); the waves walk the tiles with a grid stride
-                        p.grid_x = std::min((n_tiles + 3) / 4, (R == 7 && o.out_c == 64) ? 768 : 1536);
+                        // as many workgroups as stay resident; the waves walk the tiles with a grid stride
+                        p.grid_x = std::min((n_tiles + 3) / 4, 256 * stem_room(R, o.out_c));
                         p.grid_y = p.grid_z = 1;
                         make_divisor((uint32_t)p.Q, p.divq_m, p.divq_s1, p.divq_s2);
                         make_divisor((uint32_t)p.P * (uint32_t)p.Q, p.divpq_m, p.divpq_s1, p.divpq_s2);

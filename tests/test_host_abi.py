@@ -522,3 +522,17 @@ def test_loads_to_lds_keep_their_distance_from_vector_instructions_that_write_sc
         n += sum(1 for _, m, ops in code if m.startswith("buffer_load") and ops[-1].endswith(" lds"))
         assert not code_objects.early_lds_loads(code), name
     assert n > 1000
+
+
+@pytest.mark.parametrize("win,stride,k", [(7, 2, 64), (7, 2, 32), (3, 1, 64), (3, 2, 32)])
+def test_a_unit_holds_as_many_first_layer_workgroups_as_their_grids_count_on(win, stride, k):
+    """The grids of first layers, also those cut to a share of the units, are a number of workgroups per unit that registers and LDS have room for."""
+    g = GraphBuilder("t", "f16", 64, 224, 224, 3)
+    g.conv(0, k, win, stride, win // 2)
+    m = api.Model(g.done())
+    per_unit = m.op_info(0).grid_blocks / 256
+    m.close()
+    forms = [kern for name, kern in code_objects.kernels().items() if "11stem_kernel" in name and "Li%dELi%dELi" % (win, win) in name and "Li%dELb" % (k // 32) in name]
+    assert len(forms) == 4                               # two types, aligned and general
+    for kern in forms:
+        assert per_unit <= code_objects.held_by_registers(kern) and per_unit * kern[".group_segment_fixed_size"] <= 160 * 1024
