@@ -17,7 +17,7 @@ struct IssueItem {
     int32_t stream, tenant, op;
     int32_t mates[3] = {-1, -1, -1};   // runtime only: tenants whose operator of the same index runs in this item's launch (co-issue), -1 = none
     int32_t group = -1;    // runtime only: items of a stream that carry different groups run one group after the other
-    int32_t units = 0;     // runtime only: compute units of the queue where queues of the stage share a dispatch pipe, 0: grids need not fit
+    int32_t units = 0;     // runtime only: compute units of the queue in a stage of more queues than dispatch pipes, 0: grids need not fit
     bool alone = false;    // runtime only: no other launch of the stage can run at the same time
     int32_t fuse = 0;      // runtime only: 1 = issued as part of a neighbour's launch, 2 / 3 = launches the pair (op - 1, op): depthwise + 1x1 / 1x1 + depthwise, 4 = convolution launched with the pooling operator op + 1 in its epilogue (that operator then carries 1)
 };

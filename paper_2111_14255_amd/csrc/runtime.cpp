@@ -991,9 +991,12 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
                 for (size_t k = 0; k < items.size() && rc == MT_OK; ++k) {
                     const size_t first = rec.launches.size();
                     IssueItem item = items[k];
-                    // Queues that share a dispatch pipe: grids as large as their units hold at once (tile_walk_kernel).  An XCD deals workgroups
-                    // to its four shader engines in turn and waits where one is full, so of units that the 8 x 4 engines do not
-                    // share evenly only the even part counts (six ResNet-50 on 40 units each 5112 us, counted as 32 3560).
+                    // More queues than dispatch pipes: grids as large as their units hold at once (tile_walk_kernel), also on queues that have their
+                    // pipe alone, which end sooner so as well.  us to the end of the lone queues' tenants, uncut / cut: five ResNet-50 at batch 16 on 48
+                    // units each 2300 / 2265, seven on 32 2580 / 2485, three ResNet-18 on 32 beside two tenants that share a pipe 1078 / 992 (and
+                    // ResNet-50 on 64 units 1040 / 1053).  An XCD deals workgroups to its four shader engines in turn and waits where one is full, so
+                    // of units that the 8 x 4 engines do not share evenly only the even part counts (six ResNet-50 on 40 units each 5112 us,
+                    // counted as 32 3560).
                     const int own = sp.units_of[sm];
                     item.units = queues.size() > (size_t)N_LANES && item.mates[0] < 0 ? (own >= 32 ? own / 32 * 32 : own) : 0;
                     item.alone = sp.streams.size() == 1 && !s->masked && in_level[level[k]] == 1 && item.mates[0] < 0;
