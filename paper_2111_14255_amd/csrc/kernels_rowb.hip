@@ -1,4 +1,4 @@
-// Convolutions whose whole filter bank fits in LDS (1x1 and 3x3 windows on 64 .. 256 input channels, up to 72 KB of
+// Convolutions whose whole filter bank fits in LDS (1x1 and 3x3 windows on 64 input channels, up to 72 KB of
 // filters), with the activations going from memory straight into the MFMA operand registers.
 //
 // The tile kernel stages both operands of every 64-deep reduction tile in LDS and synchronises the workgroup once per
@@ -8,7 +8,7 @@
 // channels 16 * (t % SPT) + 0..7 of tap t / SPT of their pixel and lanes 32..63 the next 8, one 16-byte buffer load each
 // (a tap outside the image gets an out-of-range offset and reads zeros).  No activation tile in LDS, no workgroup
 // barrier after the prologue, waves progress independently.
-//   * Short reductions (at most 16 steps: 1x1 windows) keep all operand registers of the pixel tile and walk the
+//   * Short reductions (four steps: 1x1 windows) keep all operand registers of the pixel tile and walk the
 //     output channels in groups of 64 (the activations are read once).
 //   * Long reductions (3x3 on 64 channels: 36 steps, 64 output channels) keep a window of 12 loads in flight: the
 //     register of step t is refilled with step t + 12 as soon as its matrix instructions are issued.
@@ -205,18 +205,16 @@ __device__ __forceinline__ void rowb_kernel_body(const OpArgs &a) {
         tile = next;
     }
 }
-// Waves per SIMD the registers have to leave room for: two workgroups per compute unit where their filters and staging blocks fit.
-// (16 steps of operands alone are 64 registers: two workgroups would spill.)
-constexpr int rowb_waves_per_simd(int steps, int nta, int nw) {
-    return steps <= 8 && 2 * (steps * nta * 1024 + nw * 32 * 72 * 2 + nta * 128) <= 160 * 1024 ? nw / 2 : 1;
-}
+// Workgroups a compute unit holds, by LDS: two of the short reductions (45 and 71 KB), one of the long one (111 KB, 154 KB in the patch form);
+// the launch bounds have the compiler leave registers for as many.
+constexpr int rowb_room(int R) { return R == 1 ? 2 : 1; }
 template <typename T, int R, int S, int SPT, int NTA, int NW>
-__global__ void __launch_bounds__(64 * NW, rowb_waves_per_simd(R * S * SPT, NTA, NW)) rowb_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * NW, rowb_room(R) * NW / 4) rowb_kernel(OpArgs a) {
     rowb_kernel_body<T, R, S, SPT, NTA, NW>(a);
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int R, int S, int SPT, int NTA, int NW>
-__global__ void __launch_bounds__(64 * NW, rowb_waves_per_simd(R * S * SPT, NTA, NW)) rowb_pair_kernel(OpArgsPair p) {
+__global__ void __launch_bounds__(64 * NW, rowb_room(R) * NW / 4) rowb_pair_kernel(OpArgsPair p) {
     rowb_kernel_body<T, R, S, SPT, NTA, NW>(p.a[blockIdx.y]);
 }
 
@@ -388,10 +386,7 @@ int rowb_tiles(int R, int S, int C, int channels) {
     if (R != S) return 0;
     if (R == 3) return (C == 64 && channels == 64) ? 2 : 0;
     if (R != 1) return 0;
-    if (C == 64) return channels % 256 == 0 ? 8 : channels % 64 == 0 ? 2 : 0;
-    if (C == 128) return channels % 128 == 0 ? 4 : 0;
-    if (C == 256) return channels % 128 == 0 ? 4 : channels % 64 == 0 ? 2 : 0;
-    return 0;
+    return C == 64 && channels % 256 == 0 ? 8 : C == 64 && channels % 64 == 0 ? 2 : 0;
 }
 
 // The 3x3 layers of stride 1 take the patch form (rowp_kernel); its grid walks 4 x 8 pixel tiles, not runs of 32 pixels.
@@ -425,8 +420,8 @@ int launch_rowb(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates)
     hipStream_t st = (hipStream_t)stream;
     OpArgs a = op;
     if (a.units > 0 && !mate) {
-        // no more workgroups than the queue's units hold at once (see tile_walk_kernel): two a unit where the filters are small
-        const int slices = (int)a.walk.tiles.d, room = a.units * (!rowb_patch_form(a) && a.C <= 128 && a.R == 1 ? 2 : 1);
+        // no more workgroups than the queue's units hold at once (see tile_walk_kernel)
+        const int slices = (int)a.walk.tiles.d, room = a.units * rowb_room(a.R);
         const int chunks = std::max(1, room / slices);
         if (chunks * slices < a.grid_x) {
             count_launch(&LaunchRecorder::walked);
@@ -440,11 +435,8 @@ int launch_rowb(const OpArgs &op, void *stream, const OpArgs *mate, int n_mates)
     auto go = [&]<typename T>() {
         if (a.R == 3 && rowb_patch_form(a)) MT_LAUNCH((rowp_kernel<T>), (rowp_pair_kernel<T>), grid, block, st, a, mate);
         else if (a.R == 3) MT_LAUNCH((rowb_kernel<T, 3, 3, 4, 2, 8>), (rowb_pair_kernel<T, 3, 3, 4, 2, 8>), grid, block, st, a, mate);
-        else if (a.C == 64 && nta == 2) MT_LAUNCH((rowb_kernel<T, 1, 1, 4, 2, 8>), (rowb_pair_kernel<T, 1, 1, 4, 2, 8>), grid, block, st, a, mate);
-        else if (a.C == 64) MT_LAUNCH((rowb_kernel<T, 1, 1, 4, 8, 8>), (rowb_pair_kernel<T, 1, 1, 4, 8, 8>), grid, block, st, a, mate);
-        else if (a.C == 128) MT_LAUNCH((rowb_kernel<T, 1, 1, 8, 4, 8>), (rowb_pair_kernel<T, 1, 1, 8, 4, 8>), grid, block, st, a, mate);
-        else if (nta == 2) MT_LAUNCH((rowb_kernel<T, 1, 1, 16, 2, 8>), (rowb_pair_kernel<T, 1, 1, 16, 2, 8>), grid, block, st, a, mate);
-        else MT_LAUNCH((rowb_kernel<T, 1, 1, 16, 4, 8>), (rowb_pair_kernel<T, 1, 1, 16, 4, 8>), grid, block, st, a, mate);
+        else if (nta == 2) MT_LAUNCH((rowb_kernel<T, 1, 1, 4, 2, 8>), (rowb_pair_kernel<T, 1, 1, 4, 2, 8>), grid, block, st, a, mate);
+        else MT_LAUNCH((rowb_kernel<T, 1, 1, 4, 8, 8>), (rowb_pair_kernel<T, 1, 1, 4, 8, 8>), grid, block, st, a, mate);
     };
     if (a.dtype == MT_F16) go.template operator()<f16>();
     else go.template operator()<bf16>();

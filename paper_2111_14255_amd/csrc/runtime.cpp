@@ -65,16 +65,14 @@ namespace {
 // Pixel ranges of the resident-filter kernel.  3x3: from where there are enough 32-pixel wave tiles to fill the chip; with stride 2 it
 // reads every input line nine times through the L1, which bounds it on large maps (64 -> 64 on 56x56 at batch 16 / 128: 12.1 /
 // 70.4 us against 15.0 / 65.7 us on the tile kernel).
-// 1x1: since the tile kernels finish a tile by the wave they are the faster ones on 128 and 256 input channels, and on 64 below some 40000
-// pixels.  us, resident filters / tiles, bf16: 256 -> 64 on 12544 pixels 7.6 / 4.0, on 50176 9.3 / 7.2, on 200704 28.1 / 20.5; 256 -> 1024 with
-// residual on 12544 24.3 / 17.3; 128 -> 512 with residual on 12544 9.6 / 7.6, on 50176 28.4 / 25.0; 64 -> 256 with residual on 25088 11.1 /
-// 7.1, on 50176 12.8 / 13.3, on 100352 20.1 / 23.0; 64 -> 64 on 25088 4.3 / 3.7, on 50176 4.9 / 5.2.  (On 8192 to 10240 pixels it is
-// behind as well, 256 -> 64 on 8464 7.7 / 3.9; there the ragged, strided and sliced forms of the kernel are pinned by its tests.)
-constexpr int ROWB_MIN_PIXELS = 8192, ROWB_MAX_PIXELS_3X3 = 131072, ROWB_1X1_SMALL = 10240, ROWB_1X1_LARGE = 40000;
-bool rowb_range(int R, int C, int M, bool unit_stride) {
-    if (M < ROWB_MIN_PIXELS) return false;
-    if (R == 1) return M <= ROWB_1X1_SMALL || (C == 64 && M >= ROWB_1X1_LARGE);
-    return M <= ROWB_MAX_PIXELS_3X3 || unit_stride;
+// 1x1, 64 input channels: from some 40000 pixels on; below, and on more channels at any size, the tile kernels are the faster ones.  us,
+// resident filters / tiles, bf16: 64 -> 256 with residual on 25088 pixels 11.1 / 7.1, on 50176 12.8 / 13.3, on 100352 20.1 / 23.0; 64 -> 64 on
+// 25088 4.3 / 3.7, on 50176 4.9 / 5.2; 128 -> 512 with residual on 12544 9.6 / 7.6, on 50176 28.4 / 25.0; 256 -> 64 on 8464 7.7 / 3.9, on 12544
+// 7.6 / 4.0, on 50176 9.3 / 7.2, on 200704 28.1 / 20.5; 256 -> 1024 with residual on 12544 24.3 / 17.3.
+constexpr int ROWB_MIN_PIXELS_3X3 = 8192, ROWB_MAX_PIXELS_3X3 = 131072, ROWB_MIN_PIXELS_1X1 = 40000;
+bool rowb_range(int R, int M, bool unit_stride) {
+    if (R == 1) return M >= ROWB_MIN_PIXELS_1X1;
+    return M >= ROWB_MIN_PIXELS_3X3 && (M <= ROWB_MAX_PIXELS_3X3 || unit_stride);
 }
 
 bool needs_weights(int kind) { return kind == MT_CONV || kind == MT_DWCONV || kind == MT_FC; }
@@ -290,7 +288,7 @@ int32_t finalize_model(mt_model *m) {
                     const int M = m->batch * o.out_h * o.out_w;
                     const int rw = (d.kind == MT_CONV && groups == 1 && ph < R && (R == 3 || (ph == 0 && pw == 0))) ? rowb_waves(R, S, in.c, o.out_c) : 0;
                     if (rw > 0 && res_ct % 8 == 0 && ctot % 8 == 0 && d.out_c_offset % 8 == 0 && (int64_t)M * res_ct * 2 < (int64_t)1 << 31 &&
-                        rowb_range(R, in.c, M, sh == 1 && sw == 1)) {
+                        rowb_range(R, M, sh == 1 && sw == 1)) {
                         // few output channels or a short reduction on a large map: filters resident in LDS, one wave per 32 pixels
                         p.kernel_id = K_ROWB;
                         p.n_pad = o.out_c;

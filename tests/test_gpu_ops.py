@@ -79,22 +79,33 @@ CONV_CASES = [
     ("stem_3x3_k64", dict(n=1, h=224, w=224, c=3, k=64, r=3, stride=2, pad=1), STEM),
     ("stem_3x3_all_border", dict(n=3, h=2, w=4, c=3, k=32, r=3, stride=2, pad=1), STEM),
     ("stem_7x7_concat", dict(n=1, h=36, w=36, c=3, k=64, r=7, stride=2, pad=3, coff=64, ctot=136), STEM),
-    # filters resident in LDS, activations straight from memory: 1x1 / 3x3 on 64 or 256 channels, maps of 8192 pixels or more
-    ("rowb_1x1_c64_n64", dict(n=1, h=96, w=96, c=64, k=64, r=1), ROWB),
-    ("rowb_1x1_c64_n256_res", dict(n=1, h=92, w=92, c=64, k=256, r=1, res=True), ROWB),
-    ("rowb_1x1_c256_n64_ragged", dict(n=1, h=91, w=93, c=256, k=64, r=1, act="relu6"), ROWB),
-    ("rowb_1x1_c256_n128", dict(n=2, h=66, w=66, c=256, k=128, r=1, act="none", bn=False), ROWB),
-    ("rowb_1x1_stride2", dict(n=4, h=100, w=100, c=64, k=256, r=1, stride=2), ROWB),
+    # filters resident in LDS, activations straight from memory: 1x1 on 64 channels and maps of 40000 pixels or more, 3x3 on 64 -> 64 and 8192 or more
+    ("rowb_1x1_c64_n64", dict(n=1, h=200, w=200, c=64, k=64, r=1), ROWB),
+    ("rowb_1x1_c64_n256_res", dict(n=1, h=200, w=201, c=64, k=256, r=1, res=True), ROWB),
+    ("rowb_1x1_c64_n64_ragged", dict(n=1, h=201, w=203, c=64, k=64, r=1, act="relu6"), ROWB),
+    ("rowb_1x1_c64_n128", dict(n=2, h=142, w=143, c=64, k=128, r=1, act="none", bn=False), ROWB),
+    ("rowb_1x1_stride2", dict(n=4, h=202, w=202, c=64, k=256, r=1, stride=2), ROWB),
     ("rowb_3x3_res_ragged", dict(n=1, h=95, w=97, c=64, k=64, r=3, pad=1, res=True), ROWB),
     ("rowb_3x3_patch_three_images", dict(n=3, h=60, w=52, c=64, k=64, r=3, pad=1, act="relu6"), ROWB),
     ("rowb_3x3_patch_grid_stride", dict(n=5, h=112, w=112, c=64, k=64, r=3, pad=1, res=True), ROWB),
     ("rowb_3x3_stride2", dict(n=3, h=120, w=116, c=64, k=64, r=3, stride=2, pad=1), ROWB),
     ("rowb_3x3_no_padding", dict(n=1, h=100, w=100, c=64, k=64, r=3), ROWB),
-    ("rowb_1x1_c128_n512_sliced_res", dict(n=1, h=92, w=92, c=128, k=512, r=1, res=True), ROWB),
-    ("rowb_1x1_c256_n512_stride2", dict(n=4, h=100, w=100, c=256, k=512, r=1, stride=2), ROWB),
-    ("rowb_1x1_c64_n128_two_slices", dict(n=1, h=96, w=96, c=64, k=128, r=1, act="none"), ROWB),
-    ("rowb_1x1_c256_n192_three_slices", dict(n=1, h=91, w=93, c=256, k=192, r=1), ROWB),
-    ("rowb_concat", dict(n=1, h=96, w=96, c=64, k=64, r=1, coff=64, ctot=192), ROWB),
+    ("rowb_1x1_c64_n512_sliced_res", dict(n=1, h=201, w=200, c=64, k=512, r=1, res=True), ROWB),
+    ("rowb_1x1_c64_n512_stride2", dict(n=4, h=201, w=202, c=64, k=512, r=1, stride=2), ROWB),
+    ("rowb_1x1_c64_n128_two_slices", dict(n=1, h=200, w=200, c=64, k=128, r=1, act="none"), ROWB),
+    ("rowb_1x1_c64_n192_three_slices", dict(n=1, h=201, w=203, c=64, k=192, r=1), ROWB),
+    ("rowb_concat", dict(n=1, h=200, w=200, c=64, k=64, r=1, coff=64, ctot=192), ROWB),
+    # 1x1 on maps between those of the small classes and the resident filters
+    ("map9216_1x1_c64_n64", dict(n=1, h=96, w=96, c=64, k=64, r=1), IG64),
+    ("map8464_1x1_c64_n256_res", dict(n=1, h=92, w=92, c=64, k=256, r=1, res=True), IG128x64),
+    ("map8463_1x1_c256_n64_ragged", dict(n=1, h=91, w=93, c=256, k=64, r=1, act="relu6"), IG64),
+    ("map8712_1x1_c256_n128", dict(n=2, h=66, w=66, c=256, k=128, r=1, act="none", bn=False), IG64),
+    ("map10000_1x1_stride2", dict(n=4, h=100, w=100, c=64, k=256, r=1, stride=2), IG128x64),
+    ("map8464_1x1_c128_n512_sliced_res", dict(n=1, h=92, w=92, c=128, k=512, r=1, res=True), IG128x64),
+    ("map10000_1x1_c256_n512_stride2", dict(n=4, h=100, w=100, c=256, k=512, r=1, stride=2), IG128x64),
+    ("map9216_1x1_c64_n128_two_slices", dict(n=1, h=96, w=96, c=64, k=128, r=1, act="none"), IG64),
+    ("map8463_1x1_c256_n192_three_slices", dict(n=1, h=91, w=93, c=256, k=192, r=1), IG128x64),
+    ("map9216_concat", dict(n=1, h=96, w=96, c=64, k=64, r=1, coff=64, ctot=192), IG64),
     # 3x3 / stride 1 / padding 1 on 64 k channels, 150 or more 64x64 tiles: activations staged as an input patch
     ("pconv_w56_two_channel_tiles", dict(n=2, h=56, w=56, c=64, k=128, r=3, pad=1), PCONV),
     ("pconv_w31_res_ragged", dict(n=3, h=27, w=31, c=128, k=256, r=3, pad=1, res=True), PCONV),
