@@ -292,3 +292,44 @@ def test_workgroups_that_walk_several_tiles_keep_the_bits(dtype, share):
                     np.testing.assert_array_equal(p, q)
         finally:
             mix.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_walking_workgroups_with_residuals_pooling_and_channels_in_fours(dtype):
+    """The epilogues of launches cut to a share: a residual, channel counts that are multiples of 4 only, 2x2 max pooling, a split reduction that pools; and
+    a fused 1x1 + depthwise pair, which is never cut, beside them."""
+    residual = [("tile_128x128", 3, 70, 70, 320, 196, 1), ("tile_128x64", 15, 14, 13, 192, 516, 1), ("tile_64x64", 3, 77, 91, 128, 140, 1),
+                ("tile_64x32", 1, 60, 60, 512, 76, 1), ("patch_64x32", 1, 28, 28, 256, 508, 3), ("patch_128x128", 2, 66, 98, 128, 252, 3)]
+    pooled = [("patch_128x256", 2, 112, 112, 64, 256, 3), ("patch_64x64", 1, 28, 28, 512, 256, 3), ("patch_128x64", 1, 56, 56, 64, 512, 3), ("tile_128x128", 2, 70, 70, 320, 256, 1)]
+    specs = []
+    for form, n, h, w, c, k, win in residual + pooled:
+        g = GraphBuilder(form, dtype, n, h, w, c)
+        if len(specs) < len(residual):
+            g.conv(0, k, win, 1, win // 2, act="relu", bn=True, res=g.conv(0, k, win, 1, win // 2, act="none", bn=True))
+        else:
+            g.maxpool(g.conv(0, k, win, 1, win // 2, act="relu", bn=True), 2, 2, 0)
+        specs.append(g.done())
+    g = GraphBuilder("pair", dtype, 2, 28, 28, 64)
+    g.dwconv(g.conv(0, 384, 1, 1, 0, act="relu6", bn=True), 3, 1, 1, act="relu6", bn=True)
+    specs.append(g.done())
+    fused = B.MT_SCHED_FUSE_POOL | B.MT_SCHED_FUSE_EXPAND
+    for group in (specs[:len(residual)] + specs[-1:], specs[len(residual):]):
+        mix = Mix(group, seed=47)
+        try:
+            ctx = mix.ctx
+            print("case", dtype, [s.name for s in group], flush=True)
+            for t, spec in enumerate(group[:-1]):
+                assert ctx.op_form(t, 0).name.decode() == spec.name
+            plain, tm = mix.run(ctx.sequential())
+            assert tm["n_fused"] == 0
+            convs = sum(op.kind == "conv" for spec in group[:-1] for op in spec.ops)
+            for flags, n_fused in ((0, 0), (fused, 1 + sum(op.kind == "maxpool" for spec in group for op in spec.ops))):
+                shared = ctx.schedule([[] for _ in group], 1, cu_share=[32] * len(group), flags=flags)
+                for _ in range(2):
+                    got, tm = mix.run(shared)
+                    assert tm["n_fused"] == n_fused and shared.launch_forms()[0] >= convs
+                    for p, q in zip(plain, got):
+                        assert np.isfinite(p).all()
+                        np.testing.assert_array_equal(p, q)
+        finally:
+            mix.close()
