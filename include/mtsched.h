@@ -354,8 +354,8 @@ int32_t mt_schedule_create(mt_ctx *ctx, int32_t n_tenants, int32_t n_stages, con
  * the schedule's packets are written again on the next run.  Timing only. */
 int32_t mt_schedule_set_wave_priority(mt_schedule *s, const int32_t *prio);
 /* How the launches of the schedule's latest run differ from the ones its operators get in a schedule without shares and with
- * several streams (never in their results): *n_walked had their grids cut to the compute units of a share whose queue takes turns
- * with another one, *n_deep stage the widest tiles four steps ahead because nothing runs beside them.  Both 0 before the first run. */
+ * several streams (never in their results): *n_walked had their grids cut to the compute units of a share, in a stage of more than four
+ * queues, *n_deep stage the widest tiles four steps ahead because nothing runs beside them.  Both 0 before the first run. */
 int32_t mt_schedule_launch_forms(const mt_schedule *s, int32_t *n_walked, int32_t *n_deep);
 int32_t mt_schedule_destroy(mt_schedule *s);
 

@@ -305,8 +305,9 @@ __device__ __forceinline__ void store_lanes(const OpArgs &a, const Acc (&acc)[TN
 // activation in the layout of the accumulators, one rounding, and 32 pixels at a time through a block of LDS of its own, so that
 // every store is a row of channels; no barrier.  The residual takes the same way in the other direction.  Through an fp32 tile in LDS that
 // all waves write and read, with bias and residual fetched in between and a branch on pooling and residual at every four channels, this took
-// 2.3 to 4.2 us of a workgroup's time and 200 to 234 registers; 1.1 us (2 with a residual) and 171 here.  ResNet-50 at batch 64 1412 -> 1387 us,
-// eight at batch 16 2610 -> 2572, on disjoint eighths of the units 6135 -> 6010, ResNet-101 with three others at one image 514 -> 501.
+// 2.3 to 4.2 us of a workgroup's time and 200 to 234 registers; 1.1 us (2 with a residual) here, and 171 registers on the 128x128 tile, 184 and
+// 230 on the 128-wide patches.  ResNet-50 at batch 64 1412 -> 1387 us, eight at batch 16 2610 -> 2572, on disjoint eighths of the units
+// 6135 -> 6010, ResNet-101 with three others at one image 514 -> 501.
 // m_lane: output pixel of row lane % 32 of each 32 pixels, negative for rows without one; pooling: the pooled pixel.
 template <typename T, int CT, int TM>
 struct WaveTile {
@@ -1345,7 +1346,9 @@ namespace {
 // split if the reduction is split over workgroups (16-bit types only, and rings never are: a split costs them more than it gives); n: workgroups per compute unit, ns: stages of a workgroup.  Fitted to timings of the
 // distinct convolutions and classifiers of nine networks at batches 1 to 64 (fp32: 1 to 8), launch gap included.  Sum over
 // those layers, us, without the ring forms / picking by the estimate / the fastest measured form of every layer: bf16 at batch 1
-// 593 / 531 / 519, batch 5 839 / 805 / 767.  fp32, operands from memory to registers (kernels_dconv.hip) / picking here /
+// 593 / 531 / 519, batch 5 839 / 805 / 767.  The timings are of the kernels before TileWalk and WaveTile, which took up to 1.25 us from every start and 1 to
+// 2 us from the wide forms; sums and numbers have not been fitted again (a fit to launches that have the chip to themselves picked forms that
+// made tenants beside each other slower, and was not kept).  fp32, operands from memory to registers (kernels_dconv.hip) / picking here /
 // fastest: batch 1 1219 / 930 / 900, batch 4 1526 / 1220 / 1160.
 struct TileCost {
     double start, wave, stage, crowd, split_once, split_each;
@@ -1472,7 +1475,7 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
         patch_fits = patch_fits || (panels[f] > 0 && FORMS[f].bm >= 64);
     }
     // Layers of K_PCONV's size run on a patch wherever one of 64 pixels or more fits: the estimate, fitted to all layers,
-    // sometimes puts another tile first there, and it is the slower one.  us, patch / tile of least estimate: 8 x 28 x 28
+    // sometimes puts another tile first there, and it is the slower one.  us, measured with the kernels the estimate was fitted to, patch / tile of least estimate: 8 x 28 x 28
     // 128 -> 128 7.6 / 8.7, 56 x 56 128 -> 256 7.5 / 8.7, 112 x 112 64 -> 128 7.8 / 8.1, 5 x 35 x 35 64 -> 96 6.2 / 6.8, 40 x 7 x 7
     // 64 -> 320 6.2 / 6.7, 60 x 7 x 7 128 -> 256 7.7 / 8.6.  On maps of a few pixels a tile touches more images than such a patch
     // holds, and the estimate chooses among all forms (700 x 2 x 2, 512 -> 512: 64 x 32 patch 33.0, 128 x 64 tile 27.8).
@@ -1558,7 +1561,8 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         else if (a.R == 1 && a.S == 1 && a.ph == 0 && a.pw == 0) go.template operator()<TG_POINT>();
         else go.template operator()<TG_TAP>();
     };
-    // Workgroups of a launch that has to fit a.units compute units at once, `room` of them per unit; 0: it fits, or need not
+    // Workgroups of a launch that has to fit a.units compute units at once, `room` of them per unit; 0: it fits, or need not.  Rings and 64x16 tiles, rows
+    // gathered by 16-byte pieces (C not a multiple of 64, windows over 15), fp32 and launches of several tenants have no such form.
     OpArgs walked = a;
     auto walkers = [&](int room) {
         const uint32_t fit = (uint32_t)(a.units * room) / XCDS;

@@ -103,7 +103,7 @@ void plan_igemm(OpArgs &p, int M, int Kc, int gemm_k, bool beside_depthwise) {
     // output tile.  Its waves share nothing, so it is only level with the 64 x 16 tile where there are few of them or the
     // reduction is one LDS row deep: 32 -> 192 on 1568 pixels 4.3 / 4.4 us, but 256 -> 1024 on 196 pixels 4.9 / 3.6.  Longer reductions
     // on few tiles: four waves deal them out between them (960 -> 160 on 49 pixels 3.9 us, 2048 -> 192 on 64 pixels 4.5, against 4.5 and
-    // 6.5 with four contiguous ranges loaded to registers).
+    // 6.5 with four contiguous ranges loaded to registers; all with the kernels before TileWalk).
     if (small && vec && p.kind == MT_CONV && p.R == 1 && p.S == 1 && p.ph == 0 && p.pw == 0) {
         const int tiles = cdiv(M, 16) * cdiv(Kc, 16);
         const bool slices = p.k_pad / 32 > 8;
@@ -300,7 +300,7 @@ int32_t finalize_model(mt_model *m) {
                         const int slices = o.out_c / (32 * rowb_tiles(R, S, in.c, o.out_c));
                         p.grid_x = slices * std::max(1, std::min((n_tiles + rw - 1) / rw, 512 / slices));
                         if (rowb_patch_form(p)) {
-                            // 4 x 8 pixel tiles, eight per workgroup, one workgroup per compute unit (143 KB of LDS)
+                            // 4 x 8 pixel tiles, eight per workgroup, one workgroup per compute unit (154 KB of LDS)
                             const int t2 = m->batch * ((o.out_h + 3) / 4) * ((o.out_w + 7) / 8);
                             p.grid_x = std::max(1, std::min((t2 + rw - 1) / rw, 256));
                         }
