@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
     }
 
     // ---- epilogue: bias, residual, activation.  A lane holds 4 consecutive channels of one pixel.
-    float *y = (float *)a.y;
+    const Results y = results_in(a.y);
     const float *res = (const float *)a.res;
     const bool vec_ok = (a.y_ct % 4 == 0) & (a.y_coff % 4 == 0) & (a.res_ct % 4 == 0);
     auto finish = [&](f32x4 v4, int i, int j) {
@@ -185,12 +185,12 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-            store_pack<float, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+            store_pack<float, 4>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
         } else {
             for (int t = 0; t < 4 && k + t < a.K; ++t) {
                 float f = v[t];
                 if (res) f += res[(int64_t)m * a.res_ct + k + t];
-                y[(int64_t)m * a.y_ct + a.y_coff + k + t] = apply_act(f, a.act);
+                store_one<float>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k + t), apply_act(f, a.act));
             }
         }
     };
@@ -219,6 +219,7 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
             finish(v, f / TM, f % TM);
         }
     }
+    results_stored();
 }
 
 // The tilings, widest first: channels x pixels of a workgroup, waves along the reduction.

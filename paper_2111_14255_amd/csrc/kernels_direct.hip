@@ -82,9 +82,8 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(OpArgs a) {
     if (a.bias) acc += a.bias[k];
     if (a.res) acc += to_f32(((const T *)a.res)[m * a.res_ct + k]);
     acc = apply_act(acc, a.act);
-    T o;
-    from_f32(acc, o);
-    ((T *)a.y)[m * a.y_ct + a.y_coff + k] = o;
+    store_one<T>(results_in(a.y), (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), acc);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -124,16 +123,18 @@ __device__ __forceinline__ void dwconv_kernel_body(const OpArgs &a) {
         if (a.bias) acc[i] += a.bias[c0 + i];
         acc[i] = apply_act(acc[i], a.act);
     }
-    store_pack<T, V>((T *)a.y + m * a.y_ct + a.y_coff + c0, acc);
+    store_pack<T, V>(results_in(a.y), (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), acc);
 }
 template <typename T, int V>
 __global__ void __launch_bounds__(256) dwconv_kernel(OpArgs a) {
     dwconv_kernel_body<T, V>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V>
 __global__ void __launch_bounds__(256) dwconv_pair_kernel(OpArgsPair p) {
     dwconv_kernel_body<T, V>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -179,16 +180,18 @@ __device__ __forceinline__ void dwconv_fixed_kernel_body(const OpArgs &a) {
         for (int i = 0; i < V; ++i) acc[i] = ok[t] ? fmaf(xv[t][i], wv[t][i], acc[i]) : acc[i];
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = apply_act(acc[i] + bv[i], a.act);
-    store_pack<T, V>((T *)a.y + m * a.y_ct + a.y_coff + c0, acc);
+    store_pack<T, V>(results_in(a.y), (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), acc);
 }
 template <typename T, int V, int KS>
 __global__ void __launch_bounds__(256) dwconv_fixed_kernel(OpArgs a) {
     dwconv_fixed_kernel_body<T, V, KS>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V, int KS>
 __global__ void __launch_bounds__(256) dwconv_fixed_pair_kernel(OpArgsPair p) {
     dwconv_fixed_kernel_body<T, V, KS>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // 3x3 depthwise convolution with padding 1 on a large map: a thread owns one (column, channel vector) of a band of
@@ -278,7 +281,7 @@ __device__ __forceinline__ void dwconv3_rows_kernel_body(const OpArgs &a) {
             }
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[i] = apply_act(acc[i] + bv[i], a.act);
-        if (live) store_pack<T, V>((T *)a.y + ((int64_t)(n * a.P + p) * a.Q + q) * a.y_ct + a.y_coff + c0, acc);
+        if (live) store_pack<T, V>(results_in(a.y), (uint32_t)((n * a.P + p) * a.Q + q) * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), acc);
         if constexpr (ST == 1) {
 #pragma unroll
             for (int sx = 0; sx < 3; ++sx) { win[0][sx] = win[1][sx]; win[1][sx] = win[2][sx]; }
@@ -294,11 +297,13 @@ __device__ __forceinline__ void dwconv3_rows_kernel_body(const OpArgs &a) {
 template <typename T, int ST>
 __global__ void __launch_bounds__(256) dwconv3_rows_kernel(OpArgs a) {
     dwconv3_rows_kernel_body<T, ST>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int ST>
 __global__ void __launch_bounds__(256) dwconv3_rows_pair_kernel(OpArgsPair p) {
     dwconv3_rows_kernel_body<T, ST>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // Output rows per thread of the banded 3x3 depthwise kernel: 1 (the one-pixel kernel) unless the map is large enough
@@ -346,16 +351,18 @@ __device__ __forceinline__ void pool_fixed_kernel_body(const OpArgs &a) {
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[i] = acc[i] / (float)cnt;
     }
-    store_pack<T, V>((T *)a.y + m * a.y_ct + a.y_coff + c0, acc);
+    store_pack<T, V>(results_in(a.y), (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), acc);
 }
 template <typename T, int V, bool IS_MAX, int KS>
 __global__ void __launch_bounds__(256) pool_fixed_kernel(OpArgs a) {
     pool_fixed_kernel_body<T, V, IS_MAX, KS>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V, bool IS_MAX, int KS>
 __global__ void __launch_bounds__(256) pool_fixed_pair_kernel(OpArgsPair p) {
     pool_fixed_kernel_body<T, V, IS_MAX, KS>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -392,16 +399,18 @@ __device__ __forceinline__ void pool_kernel_body(const OpArgs &a) {
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[i] = acc[i] / (float)cnt;
     }
-    store_pack<T, V>((T *)a.y + m * a.y_ct + a.y_coff + c0, acc);
+    store_pack<T, V>(results_in(a.y), (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), acc);
 }
 template <typename T, int V, bool IS_MAX>
 __global__ void __launch_bounds__(256) pool_kernel(OpArgs a) {
     pool_kernel_body<T, V, IS_MAX>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V, bool IS_MAX>
 __global__ void __launch_bounds__(256) pool_pair_kernel(OpArgsPair p) {
     pool_kernel_body<T, V, IS_MAX>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -448,17 +457,19 @@ __device__ __forceinline__ void gap_kernel_body(const OpArgs &a) {
     if (slice == 0 && cv_ok) {
 #pragma unroll
         for (int j = 0; j < V; ++j) acc[j] = acc[j] / (float)HW;
-        store_pack<T, V>((T *)a.y + (int64_t)n * a.y_ct + a.y_coff + cv * V, acc);
+        store_pack<T, V>(results_in(a.y), (uint32_t)n * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + cv * V), acc);
     }
 }
 template <typename T, int V>
 __global__ void __launch_bounds__(256) gap_kernel(OpArgs a) {
     gap_kernel_body<T, V>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V>
 __global__ void __launch_bounds__(256) gap_pair_kernel(OpArgsPair p) {
     gap_kernel_body<T, V>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -517,16 +528,18 @@ __device__ __forceinline__ void lrn_kernel_body(const OpArgs &a) {
         }
         out[0] = win[1] / powf(a.lrn_k + a.lrn_alpha * ssq, a.lrn_beta);
     }
-    store_pack<T, V>((T *)a.y + (int64_t)m * a.y_ct + a.y_coff + c0, out);
+    store_pack<T, V>(results_in(a.y), m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), out);
 }
 template <typename T, int V>
 __global__ void __launch_bounds__(256) lrn_kernel(OpArgs a) {
     lrn_kernel_body<T, V>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V>
 __global__ void __launch_bounds__(256) lrn_pair_kernel(OpArgsPair p) {
     lrn_kernel_body<T, V>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // Element-wise sum of two tensors of the same shape, activation, one rounding.
@@ -543,16 +556,18 @@ __device__ __forceinline__ void add_kernel_body(const OpArgs &a) {
     load_pack<T, V>((const T *)a.res + (int64_t)m * a.res_ct + c0, v);
 #pragma unroll
     for (int i = 0; i < V; ++i) u[i] = apply_act(u[i] + v[i], a.act);
-    store_pack<T, V>((T *)a.y + (int64_t)m * a.y_ct + a.y_coff + c0, u);
+    store_pack<T, V>(results_in(a.y), m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + c0), u);
 }
 template <typename T, int V>
 __global__ void __launch_bounds__(256) add_kernel(OpArgs a) {
     add_kernel_body<T, V>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int V>
 __global__ void __launch_bounds__(256) add_pair_kernel(OpArgsPair p) {
     add_kernel_body<T, V>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // Records the hardware id registers of the compute unit each one-wavefront workgroup runs on, then keeps the unit

@@ -376,7 +376,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
     }
 
     // ---- epilogue: bias, residual, activation, one rounding, NHWC store -------------------------
-    T *y = (T *)a.y;
+    const Results y = results_in(a.y);
     const T *res = (const T *)a.res;
     // Coalesced form (channel counts and offsets multiples of 8): the accumulators plus bias go through LDS as an
     // fp32 [pixel][channel] tile, then every thread finishes 8 consecutive channels of one pixel: one 16-byte residual
@@ -442,7 +442,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
                 }
 #pragma unroll
                 for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
-                store_pack<T, 8>(y + (int64_t)(m >> 2) * a.y_ct + a.y_coff + k, v);
+                store_pack<T, 8>(y, (uint32_t)(m >> 2) * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
             }
             return;
         }
@@ -463,7 +463,7 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
             }
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
-            store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+            store_pack<T, 8>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
         }
         return;
     }
@@ -494,15 +494,13 @@ __device__ __forceinline__ void igemm_body(const OpArgs &a) {
                     }
 #pragma unroll
                     for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-                    store_pack<T, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+                    store_pack<T, 4>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
                 } else {
                     for (int t = 0; t < 4 && k + t < a.K; ++t) {
                         float f = v[t];
                         if (res) f += to_f32(res[(int64_t)m * a.res_ct + k + t]);
                         f = apply_act(f, a.act);
-                        T o;
-                        from_f32(f, o);
-                        y[(int64_t)m * a.y_ct + a.y_coff + k + t] = o;
+                        store_one<T>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k + t), f);
                     }
                 }
             }
@@ -585,7 +583,7 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
             acc[r][m] = v;
         }
     if (lane == 0) {
-        T *y = (T *)a.y;
+        const Results y = results_in(a.y);
         const T *res = (const T *)a.res;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
@@ -597,9 +595,7 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
                 float f = acc[r][m] + bias_k[r];
                 if (res) f += to_f32(res[(int64_t)m * a.res_ct + k]);
                 f = apply_act(f, a.act);
-                T o;
-                from_f32(f, o);
-                y[(int64_t)m * a.y_ct + a.y_coff + k] = o;
+                store_one<T>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), f);
             }
         }
     }
@@ -607,11 +603,13 @@ __device__ __forceinline__ void gemv_kernel_body(const OpArgs &a) {
 template <typename T, int MB, int ROWS, bool STREAM_W>
 __global__ void __launch_bounds__(256) gemv_kernel(OpArgs a) {
     gemv_kernel_body<T, MB, ROWS, STREAM_W>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int MB, int ROWS, bool STREAM_W>
 __global__ void __launch_bounds__(256) gemv_pair_kernel(OpArgsPair p) {
     gemv_kernel_body<T, MB, ROWS, STREAM_W>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -675,7 +673,7 @@ __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
     }
 
     // epilogue: bias, residual, activation, one rounding
-    T *y = (T *)a.y;
+    const Results y = results_in(a.y);
     const T *res = (const T *)a.res;
     const int k = tn * 16 + 4 * (lane >> 4);
     if (m >= M || k >= a.K) return;
@@ -690,31 +688,32 @@ __device__ __forceinline__ void pw_direct_kernel_body(const OpArgs &a) {
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-        store_pack<T, 4>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+        store_pack<T, 4>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
     } else {
         for (int t = 0; t < 4 && k + t < a.K; ++t) {
             float f = v[t];
             if (res) f += to_f32(res[(int64_t)m * a.res_ct + k + t]);
             f = apply_act(f, a.act);
-            T o;
-            from_f32(f, o);
-            y[(int64_t)m * a.y_ct + a.y_coff + k + t] = o;
+            store_one<T>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k + t), f);
         }
     }
 }
 template <typename T>
 __global__ void __launch_bounds__(256) pw_direct_kernel(OpArgs a) {
     pw_direct_kernel_body<T>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T>
 __global__ void __launch_bounds__(256) pw_direct_pair_kernel(OpArgsPair p) {
     pw_direct_kernel_body<T>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int MF>
 __global__ void __launch_bounds__(256) igemm_kernel(OpArgs a) {
     igemm_body<T, BN, BM, WN, WM, MF>(a);
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int MF>
@@ -764,7 +763,7 @@ static int launch_igemm_typed(const OpArgs &a, hipStream_t st, const OpArgs *mat
 // tensor, which stays valid).  The MFMA sequence, tile and reduction order are those of the 64x16 implicit-GEMM
 // instantiation, so the output bits equal those of the two separate launches.
 template <typename T>
-__global__ void __launch_bounds__(256) dwpw_kernel(OpArgs a, OpArgs d) {
+__device__ __forceinline__ void dwpw_body(const OpArgs &a, const OpArgs &d) {
     set_wave_priority(a.prio);
     constexpr int BN = 64, BM = 16;
     constexpr int G = 3;                                 // channel chunks of a thread whose tap loads are in flight together
@@ -881,7 +880,7 @@ __global__ void __launch_bounds__(256) dwpw_kernel(OpArgs a, OpArgs d) {
                 from_f32(ch_ok ? v : 0.f, o.e[i]);
             }
             *reinterpret_cast<Pack<T, 8> *>(&Xf[px * XLD + c0]) = o;
-            if (tn == 0 && ch_ok) *reinterpret_cast<Pack<T, 8> *>((T *)d.y + (int64_t)m * d.y_ct + d.y_coff + c0) = o;
+            if (tn == 0 && ch_ok) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), results_in(d.y), ((uint32_t)m * (uint32_t)d.y_ct + (uint32_t)(d.y_coff + c0)) * 2u, 0, THROUGH);
         }
     }
 
@@ -910,7 +909,7 @@ __global__ void __launch_bounds__(256) dwpw_kernel(OpArgs a, OpArgs d) {
     }
 
     // epilogue of the 1x1 layer: bias, residual, activation, one rounding
-    T *y = (T *)a.y;
+    const Results y = results_in(a.y);
     const T *res = (const T *)a.res;
     const int mo = m0 + frag_row, k = n0 + wn * 16 + 4 * (lane >> 4);
     if (mo >= M || k >= a.K) return;
@@ -925,17 +924,20 @@ __global__ void __launch_bounds__(256) dwpw_kernel(OpArgs a, OpArgs d) {
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-        store_pack<T, 4>(y + (int64_t)mo * a.y_ct + a.y_coff + k, v);
+        store_pack<T, 4>(y, (uint32_t)mo * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
     } else {
         for (int t = 0; t < 4 && k + t < a.K; ++t) {
             float f = v[t];
             if (res) f += to_f32(res[(int64_t)mo * a.res_ct + k + t]);
             f = apply_act(f, a.act);
-            T o;
-            from_f32(f, o);
-            y[(int64_t)mo * a.y_ct + a.y_coff + k + t] = o;
+            store_one<T>(y, (uint32_t)mo * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k + t), f);
         }
     }
+}
+template <typename T>
+__global__ void __launch_bounds__(256) dwpw_kernel(OpArgs a, OpArgs d) {
+    dwpw_body<T>(a, d);
+    results_stored();
 }
 
 static size_t dwpw_lds_bytes(int k_pad) { return (size_t)k_pad * (18 + 4) + (size_t)16 * (k_pad + 8) * 2; }
@@ -1068,12 +1070,12 @@ __global__ void __launch_bounds__(256) pwdw_kernel(PwdwWalk w, OpArgs e, OpArgs 
     __syncthreads();
 
     // ---- the rows of the widened tensor this band owns, to memory, 16 bytes per thread ------------------------
-    T *ey = (T *)e.y;
+    const Results ey = results_in(e.y);
     for (int it = (own_lo - r_lo) * W * CPP + tid; it < (own_hi - r_lo) * W * CPP; it += 256) {
         const int px = it / CPP, c8 = it - px * CPP;
         const int c = c0 + c8 * 8;
         if (c < e.K)
-            *reinterpret_cast<u32x4 *>(ey + (int64_t)(img * Min + px0 + px) * e.y_ct + e.y_coff + c) = *reinterpret_cast<const u32x4 *>(&Es[px * ELD + c8 * 8]);
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(&Es[px * ELD + c8 * 8]), ey, ((uint32_t)(img * Min + px0 + px) * (uint32_t)e.y_ct + (uint32_t)(e.y_coff + c)) * 2u, 0, THROUGH);
     }
     // ---- the depthwise layer over the LDS copy: four channels a thread, so that all four waves have work at the usual band (a
     // thread with eight does 290 vector instructions in a row while half of the workgroup waits: 1.35 to 2.2 us of the pair's 4.2, 0.65 to 1.1 here; MobileNetV2 at one image 179 -> 162, with
@@ -1081,7 +1083,7 @@ __global__ void __launch_bounds__(256) pwdw_kernel(PwdwWalk w, OpArgs e, OpArgs 
     // A thread's channels are the same for all of its pixels: their filters are read once.
     constexpr int QPP = HC / 4;                          // 4-channel pieces per pixel
     static_assert(256 % QPP == 0, "a thread keeps its channels");
-    T *dy = (T *)d.y;
+    const Results dy = results_in(d.y);
     const int Mout = d.P * d.Q;
     const int c4 = (tid % QPP) * 4, cd = c0 + c4;
     Pack<T, 4> wt[9];
@@ -1110,9 +1112,10 @@ __global__ void __launch_bounds__(256) pwdw_kernel(PwdwWalk w, OpArgs e, OpArgs 
         if (cd < d.C) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[i] = apply_act(acc[i] + Bd[c4 + i], d.act);
-            store_pack<T, 4>(dy + (int64_t)(img * Mout + p * d.Q + q) * d.y_ct + d.y_coff + cd, acc);
+            store_pack<T, 4>(dy, (uint32_t)(img * Mout + p * d.Q + q) * (uint32_t)d.y_ct + (uint32_t)(d.y_coff + cd), acc);
         }
     }
+    results_stored();
 }
 
 // Launch shape of the fused pair: the kernel variant (pixels a band may read, by reduction depth) and the number of

@@ -196,7 +196,7 @@ __device__ __forceinline__ void rowb_kernel_body(const OpArgs &a) {
             for (int j = 0; j < 4; ++j) {
                 const int row = srow + 8 * j;
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(&sg[row * SLD + scol]);
-                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_y, (uint32_t)((tile * 32 + row) * a.y_ct + a.y_coff + kslice + kb + scol) * 2u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_y, (uint32_t)((tile * 32 + row) * a.y_ct + a.y_coff + kslice + kb + scol) * 2u, 0, THROUGH);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -211,11 +211,13 @@ constexpr int rowb_room(int R) { return R == 1 ? 2 : 1; }
 template <typename T, int R, int S, int SPT, int NTA, int NW>
 __global__ void __launch_bounds__(64 * NW, rowb_room(R) * NW / 4) rowb_kernel(OpArgs a) {
     rowb_kernel_body<T, R, S, SPT, NTA, NW>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int R, int S, int SPT, int NTA, int NW>
 __global__ void __launch_bounds__(64 * NW, rowb_room(R) * NW / 4) rowb_pair_kernel(OpArgsPair p) {
     rowb_kernel_body<T, R, S, SPT, NTA, NW>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 // 3x3 window, stride 1, 64 -> 64 channels: the activations go through LDS once, as the input patch of the wave's pixel
@@ -256,7 +258,7 @@ __device__ __forceinline__ void rowp_kernel_body(const OpArgs &a) {
 
     const int n_tiles = (int)a.walk.total;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)a.walk.x_bytes, 0x00027000);
-    T *y = reinterpret_cast<T *>(a.y);
+    const Results y = results_in(a.y);
     const T *res = reinterpret_cast<const T *>(a.res);
     uint16_t *pt = patch[wave];
     const int srow = lane >> 3, scol = (lane & 7) * 8;
@@ -364,18 +366,20 @@ __device__ __forceinline__ void rowp_kernel_body(const OpArgs &a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const u32x4 v = *reinterpret_cast<const u32x4 *>(&pt[(srow + 8 * j) * SLD + scol]);
-            if (mrow[j] >= 0) *reinterpret_cast<u32x4 *>(y + (int64_t)mrow[j] * a.y_ct + a.y_coff + scol) = v;
+            if (mrow[j] >= 0) __builtin_amdgcn_raw_buffer_store_b128(v, y, ((uint32_t)mrow[j] * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + scol)) * 2u, 0, THROUGH);
         }
     }
 }
 template <typename T>
 __global__ void __launch_bounds__(512) rowp_kernel(OpArgs a) {
     rowp_kernel_body<T>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T>
 __global__ void __launch_bounds__(512) rowp_pair_kernel(OpArgsPair p) {
     rowp_kernel_body<T>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 }  // namespace

@@ -61,7 +61,7 @@ __device__ __forceinline__ void stem_kernel_body(const OpArgs &a) {
     const int rowbytes = a.W * 3 * 2;
     const int size = a.N * a.H * rowbytes;    // < 2 GiB by construction of the model
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, size, 0x00027000);
-    T *y = reinterpret_cast<T *>(a.y);
+    const Results y = results_in(a.y);
 
     // Requests the KS groups of this lane for its pixel of `tile`; vm = bit e set when element e of a run is a real
     // element of a column inside the image (the same for every filter row of the pixel).
@@ -204,7 +204,7 @@ __device__ __forceinline__ void stem_kernel_body(const OpArgs &a) {
             const int row = c / CPR, col = (c % CPR) * 8;
             const int m = tile * 32 + row;
             const u32x4 v = *reinterpret_cast<const u32x4 *>(&sg[row * SLD + col]);
-            if (m < M && col < a.K) *reinterpret_cast<u32x4 *>(y + (int64_t)m * a.y_ct + a.y_coff + col) = v;
+            if (m < M && col < a.K) __builtin_amdgcn_raw_buffer_store_b128(v, y, ((uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + col)) * 2u, 0, THROUGH);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -235,11 +235,13 @@ __device__ __forceinline__ void stem_kernel_body(const OpArgs &a) {
 template <typename T, int R, int S, int DUMMY, int TN, bool ALIGNED>
 __global__ void __launch_bounds__(256, stem_room(R, 32 * TN)) stem_kernel(OpArgs a) {
     stem_kernel_body<T, R, S, DUMMY, TN, ALIGNED>(a);
+    results_stored();
 }
 // two operators of equal launch shape in one launch, one per value of blockIdx.y
 template <typename T, int R, int S, int DUMMY, int TN, bool ALIGNED>
 __global__ void __launch_bounds__(256, stem_room(R, 32 * TN)) stem_pair_kernel(OpArgsPair p) {
     stem_kernel_body<T, R, S, DUMMY, TN, ALIGNED>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 }  // namespace

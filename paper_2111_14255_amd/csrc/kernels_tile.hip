@@ -135,7 +135,8 @@ __device__ __forceinline__ void finish_pixel(const OpArgs &a, float (&v)[V], con
         if (!first_of_window) return;
     }
     if (m < 0 || k >= a.K) return;
-    T *y = (T *)a.y + (int64_t)m * a.y_ct + a.y_coff + k;
+    const Results y = results_in(a.y);
+    const uint32_t at = (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k);
     if (vec_ok) {
         if (a.res != nullptr && !a.pool2) {
             const Pack<T, V> rp = __builtin_bit_cast(Pack<T, V>, add.res);
@@ -144,17 +145,14 @@ __device__ __forceinline__ void finish_pixel(const OpArgs &a, float (&v)[V], con
         }
 #pragma unroll
         for (int t = 0; t < V; ++t) v[t] = apply_act(v[t], a.act);
-        store_pack<T, V>(y, v);
+        store_pack<T, V>(y, at, v);
     } else {
 #pragma unroll
         for (int t = 0; t < V; ++t) {
             if (k + t >= a.K) continue;
             float f = v[t];
             if (a.res != nullptr && !a.pool2) f += to_f32(((const T *)a.res)[(int64_t)m * a.res_ct + k + t]);
-            f = apply_act(f, a.act);
-            T o;
-            from_f32(f, o);
-            y[t] = o;
+            store_one<T>(y, at + (uint32_t)t, apply_act(f, a.act));
         }
     }
 }
@@ -263,7 +261,7 @@ __device__ __forceinline__ bool meet_splits(const OpArgs &a, Acc (&acc)[TN][TM],
 // k0: first channel of the wave's products; m: output pixel of this lane in each of them, negative for none.
 template <typename T, int MF, typename Acc, int TN, int TM>
 __device__ __forceinline__ void store_lanes(const OpArgs &a, const Acc (&acc)[TN][TM], int k0, const int (&m)[TM], int fgrp) {
-    T *y = (T *)a.y;
+    const Results y = results_in(a.y);
     const T *res = (const T *)a.res;
     const bool vec_ok = (a.y_ct % 4 == 0) && (a.y_coff % 4 == 0) && (a.res_ct % 4 == 0);
 #pragma unroll
@@ -286,15 +284,12 @@ __device__ __forceinline__ void store_lanes(const OpArgs &a, const Acc (&acc)[TN
                     }
 #pragma unroll
                     for (int t = 0; t < 4; ++t) v[t] = apply_act(v[t], a.act);
-                    store_pack<T, 4>(y + (int64_t)m[j] * a.y_ct + a.y_coff + k, v);
+                    store_pack<T, 4>(y, (uint32_t)m[j] * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
                 } else {
                     for (int t = 0; t < 4 && k + t < a.K; ++t) {
                         float f = v[t];
                         if (res) f += to_f32(res[(int64_t)m[j] * a.res_ct + k + t]);
-                        f = apply_act(f, a.act);
-                        T o;
-                        from_f32(f, o);
-                        y[(int64_t)m[j] * a.y_ct + a.y_coff + k + t] = o;
+                        store_one<T>(y, (uint32_t)m[j] * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k + t), apply_act(f, a.act));
                     }
                 }
             }
@@ -342,7 +337,7 @@ struct WaveTile {
         const __amdgpu_buffer_rsrc_t out = buffer(a.y, (POOL ? a.walk.pixels / 4 : a.walk.pixels) * (uint32_t)a.y_ct * 2u);
         auto store = [&](int row, int m) {
             const u32x4 v = *reinterpret_cast<const u32x4 *>(&sg[row * SLD + scol]);
-            __builtin_amdgcn_raw_buffer_store_b128(v, out, m >= 0 && k < (uint32_t)a.K ? ((uint32_t)m * (uint32_t)a.y_ct + (uint32_t)a.y_coff + k) * 2u : OUT_OF_RANGE, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, out, m >= 0 && k < (uint32_t)a.K ? ((uint32_t)m * (uint32_t)a.y_ct + (uint32_t)a.y_coff + k) * 2u : OUT_OF_RANGE, 0, THROUGH);
         };
         float4 b[CT][4];
 #pragma unroll
@@ -452,7 +447,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
     if (!meet_splits<BN, BM, GT>(a, acc, s_last, tile, z, owner, gtid)) return;
 
     // ---- epilogue: bias, residual, activation, one rounding, NHWC store
-    T *y = (T *)a.y;
+    const Results y = results_in(a.y);
     const T *res = (const T *)a.res;
     const bool vec8_ok = (a.K % 8 == 0) && (a.y_ct % 8 == 0) && (a.y_coff % 8 == 0) && (a.res_ct % 8 == 0);
     if (vec8_ok) {
@@ -509,7 +504,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
                 }
 #pragma unroll
                 for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t] + bias[t], a.act);
-                store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+                store_pack<T, 8>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
             }
             return;
         }
@@ -532,7 +527,7 @@ __device__ __forceinline__ void finish_tile(const OpArgs &a, Acc (&acc)[TN][TM],
             }
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = apply_act(v[t], a.act);
-            store_pack<T, 8>(y + (int64_t)m * a.y_ct + a.y_coff + k, v);
+            store_pack<T, 8>(y, (uint32_t)m * (uint32_t)a.y_ct + (uint32_t)(a.y_coff + k), v);
         }
         return;
     }
@@ -1269,6 +1264,7 @@ constexpr int tile_waves_per_simd(int bn, int bm, int nbuf) { return bn * bm >= 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_kernel(OpArgs a) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, blockIdx.x / XCDS);
+    results_stored();
 }
 
 // Workgroups of a walking kernel that a compute unit holds, by LDS (three of up to 53 KB, two of up to 80 KB); the kernels' launch bounds have
@@ -1298,29 +1294,34 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD, NBUF)
         const OpArgs &a = kernel_arguments();
         tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, slot);
         slot += a.walk.step;
-        if (slot >= a.walk.per_xcd) return;
+        if (slot >= a.walk.per_xcd) break;
         __syncthreads();                                   // every wave is done with the tile's LDS
     }
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_pair_kernel(OpArgsPair p) {
     tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y], blockIdx.x / XCDS);
+    results_stored();
 }
 
 template <typename T, int BN, int WK, int D, int MODE>
 __global__ void __launch_bounds__(64 * WK) ring_kernel(OpArgs a) {
     ring_body<T, BN, WK, D, MODE>(a);
+    results_stored();
 }
 
 template <typename T, int BN, int WK, int D, int MODE>
 __global__ void __launch_bounds__(64 * WK) ring_pair_kernel(OpArgsPair p) {
     ring_body<T, BN, WK, D, MODE>(p.a[blockIdx.y]);
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
     patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, blockIdx.x / XCDS);
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
@@ -1329,14 +1330,16 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * 
         const OpArgs &a = kernel_arguments();
         patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, slot);
         slot += a.walk.step;
-        if (slot >= a.walk.per_xcd) return;
+        if (slot >= a.walk.per_xcd) break;
         __syncthreads();
     }
+    results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPair p) {
     patch_body<T, BN, BM, WN, WM, WK, KD, PC>(p.a[blockIdx.y], blockIdx.x / XCDS);
+    results_stored();
 }
 
 // ---- choice of form -----------------------------------------------------------------------------------------------

@@ -932,8 +932,9 @@ bool names_caller_buffers(const mt_ctx *ctx, const IssueItem &it) {
 // Writes the whole schedule down as packets.  Within a queue the packets of a level follow each other without a barrier
 // bit and run together; the first packet of a level carries it and starts when everything before it is complete.  Streams
 // that share a lane are merged level by level.  Fences: a level's first packet acquires at agent scope what earlier levels
-// released (its siblings start after it and need no fence of their own); the first packet of a queue acquires at system
-// scope (caller's inputs, argument memory written by the host), and what writes a caller's output releases there.
+// stored (its siblings start after it and need no fence of their own); the first packet of a queue acquires at system
+// scope (caller's inputs, argument memory written by the host), and what writes a caller's output releases there.  No other
+// packet releases: every kernel stores its results through to memory before its waves end (results_stored).
 int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void *const *outputs, RunPlan &plan, bool clear_counters, size_t counter_bytes) {
     drop_plan(ctx, s, plan);
     LaneDevice *dev = ctx->lanes;
@@ -1033,7 +1034,7 @@ int32_t build_plan(mt_ctx *ctx, mt_schedule *s, const void *const *inputs, void 
                             if (pc.ends_tenant[t] && (s->flags & MT_SCHED_TIME_TENANTS)) plan.last_op[t] = need();
                         }
                     const RecordedLaunch &rl = rec.launches[l];
-                    p.emits.push_back(Emit{l, dispatch_head(opens, acquire, system ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_AGENT,
+                    p.emits.push_back(Emit{l, dispatch_head(opens, acquire, system ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_NONE,
                                                             rl.grid[2] * rl.block[2] > 1 ? 3 : rl.grid[1] * rl.block[1] > 1 ? 2 : 1), signal});
                     first_packet = false;
                 }

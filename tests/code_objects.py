@@ -65,8 +65,8 @@ def scalars(operand):
     return {operand} if operand in ("vcc", "m0") else set()
 
 
-def early_lds_loads(code, states=5):
-    """Loads to LDS that read a scalar register which a vector instruction wrote fewer than `states` wait states before, on any path."""
+def predecessors(code):
+    """For every instruction the ones that may run just before it."""
     at = {a: i for i, (a, _, _) in enumerate(code)}
     came_from = [[] for _ in code]
     for i, (a, m, ops) in enumerate(code):
@@ -75,6 +75,30 @@ def early_lds_loads(code, states=5):
         if m.startswith(("s_branch", "s_cbranch")):
             offset = int(re.match(r"\d+", ops[0])[0])
             came_from[at[a + 4 + 4 * (offset - 65536 if offset > 32767 else offset)]].append(i)
+    return came_from
+
+
+def held_back_stores(code):
+    """Stores to memory that stop at the XCD's L2 (no sc1), and stores that a wave may end without waiting for."""
+    came_from = predecessors(code)
+    stores = lambda m: re.match(r"(buffer|global|flat)_store", m)
+    found = [(hex(a), m) for a, m, ops in code if stores(m) and "sc1" not in ops[-1].split()]
+    seen, todo = set(), [i for i, (_, m, _) in enumerate(code) if m == "s_endpgm"]
+    while todo:
+        for j in came_from[todo.pop()]:
+            a, m, ops = code[j]
+            if j in seen or (m == "s_waitcnt" and "vmcnt(0)" in " ".join(ops)):
+                continue
+            seen.add(j)
+            if stores(m):
+                found.append((hex(a), m))
+            todo.append(j)
+    return found
+
+
+def early_lds_loads(code, states=5):
+    """Loads to LDS that read a scalar register which a vector instruction wrote fewer than `states` wait states before, on any path."""
+    came_from = predecessors(code)
     found = []
     for i, (a, m, ops) in enumerate(code):
         if not (m.startswith("buffer_load") and ops[-1].split()[-1] == "lds"):

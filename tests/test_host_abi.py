@@ -525,6 +525,26 @@ def test_loads_to_lds_keep_their_distance_from_vector_instructions_that_write_sc
     assert n > 1000
 
 
+def test_kernels_end_with_their_results_in_memory():
+    """Packets between dependent launches release nothing, so every store of an operator's kernel goes through to memory (sc1) and no wave
+    ends before its stores have arrived there.  Shown on small listings, then in every kernel of the library but the probes."""
+    through, held = (8, "buffer_store_dwordx4", ["v[0:3]", "v4", "s[20:23]", "0 offen sc1"]), (8, "global_store_dword", ["v1", "v2", "s[4:5]"])
+    wait, end = (16, "s_waitcnt", ["vmcnt(0) lgkmcnt(0)"]), (28, "s_endpgm", [""])
+    assert not code_objects.held_back_stores([through, wait, end])
+    assert code_objects.held_back_stores([held, wait, end]) and code_objects.held_back_stores([through, end])
+    assert code_objects.held_back_stores([through, (16, "s_waitcnt", ["vmcnt(1)"]), end])
+    # a way round the wait
+    assert code_objects.held_back_stores([through, (12, "s_cbranch_execz", ["2"]), wait, (20, "s_nop", ["0"]), (24, "s_nop", ["0"]), end])
+    n = 0
+    for name, code in code_objects.listings():
+        if any(p in name for p in ("peak_", "probe_kernel", "arrive_kernel", "fill_u32_kernel")) or "_kernel" not in name:
+            continue
+        n += 1
+        assert any("store" in m and "sc1" in ops[-1] for _, m, ops in code), name
+        assert not code_objects.held_back_stores(code), name
+    assert n > 250
+
+
 @pytest.mark.parametrize("win,stride,k", [(7, 2, 64), (7, 2, 32), (3, 1, 64), (3, 2, 32)])
 def test_a_unit_holds_as_many_first_layer_workgroups_as_their_grids_count_on(win, stride, k):
     """The grids of first layers, also those cut to a share of the units, are a number of workgroups per unit that registers and LDS have room for."""
