@@ -113,7 +113,7 @@ struct OpArgs {
     int32_t R, S;                // window
     int32_t sh, sw, ph, pw;
     int32_t N, P, Q;             // images, output map
-    int32_t panel;               // patch-staged 3x3 layers: columns of a panel (kernels_tile.hip)
+    int32_t panel;               // patch-staged 3x3 layers: columns of a panel; rings of 3x3 layers: -8 or -4, tiles are rectangles of as many columns (kernels_tile.hip)
     int32_t prio;                // issue priority of the kernel's waves, 0 (default) .. 3; set per launch from the schedule
     // epilogue
     int32_t split_k;
@@ -197,7 +197,8 @@ int launch_stem(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int
 int rowb_waves(int R, int S, int C, int channels);
 int rowb_tiles(int R, int S, int C, int channels);   // 32-channel tiles per slice of output channels (a workgroup holds one slice's filters)
 // Tile kernels (kernels_tile.hip): choice of form, its split workspace (tiles, floats per tile), the pooled plan, launch.
-// The filter bank is [n_pad][k_pad]; a patch-staged layer (panel > 0) orders the reduction index (64-channel chunk, tap, channel).
+// The filter bank is [n_pad][k_pad]; a patch-staged layer (panel > 0) orders the reduction index (64-channel chunk, tap, channel), a ring on
+// rectangles (panel < 0) packs it in operand order.
 bool patch_stageable(const OpArgs &a);
 enum TileChoice {
     TILE_ANY,        // whatever the estimate says

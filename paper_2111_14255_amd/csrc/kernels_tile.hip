@@ -575,6 +575,16 @@ __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
                  "s"(a.ph), "s"(a.pw), "s"(a.N), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio), "s"(a.K), "s"(a.res_ct), "s"(a.y_coff), "s"(a.y_ct), "s"(a.bias), "s"(a.res));
 }
 
+// The same for ring_patch_body: fewer, so that they are one trip there too (with the ones above the compiler ran out of scalar registers
+// and asked for the epilogue's in a second trip, 0.1 us).
+__device__ __forceinline__ void fetch_rect_walk(const OpArgs &a) {
+    const TileWalk &w = a.walk;
+    asm volatile("" ::"s"(a.x), "s"(a.w), "s"(w.total), "s"(w.per_xcd), "s"(w.x_bytes), "s"(w.w_bytes), "s"(w.units), "s"(w.tiles.d), "s"(w.tiles.m), "s"(w.tiles.s1), "s"(w.tiles.s2),
+                 "s"(w.pq.d), "s"(w.pq.m), "s"(w.pq.s1), "s"(w.pq.s2), "s"(w.q.d), "s"(w.q.m), "s"(w.q.s1), "s"(w.q.s2), "s"(a.tile_order), "s"(a.pool2), "s"(a.x_ct), "s"(a.x_coff), "s"(a.H),
+                 "s"(a.W), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio));
+    asm volatile("" ::"s"(a.K), "s"(a.res_ct), "s"(a.y_coff), "s"(a.y_ct), "s"(a.bias), "s"(a.res));
+}
+
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.
 // slot: position in the XCD's range of tiles.
 __device__ __forceinline__ bool find_tile(const OpArgs &a, uint32_t slot, int &tile, int &z, int &tn_idx, int &tm_idx) {
@@ -989,6 +999,140 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
     finish_pixel<T, 4, BN / 4>(a, v, add, my_m, my_k, vec_ok, (my_row & 3) == 0);
 }
 
+// 3x3 windows, stride 1, padding 1 on the rings: a wave's part of the reduction is not rows of 64 elements but chunks of 64 bytes of channels with
+// all nine taps.  The tile is a rectangle of 2 x 8 or 4 x 4 pixels, so a wave copies the 4 x 10 or 6 x 6 input pixels of a chunk to LDS once
+// and every tap reads its operand there, and the filters, packed in operand order ([channel tile][chunk][tap][lane][16 bytes]), go straight to
+// registers, a kilobyte a load.  Two chunks of a wave are in flight after one trip to memory.
+//
+// What bounds it: a compute unit copies 64 bytes a cycle, and ring_body copies every input pixel nine times: 147 KB and 5200 cycles for 16 channels
+// x 16 pixels of 256 channels, of which 4300 wait for copies.  98 KB here, and a third to two thirds of the LDS.  us a layer, ring_body / this, f16 at one
+// image: 128 -> 128 on 28 x 28 4.0 / 3.4, 256 -> 256 on 14 x 14 4.0 / 3.6, 512 -> 512 on 14 x 14 7.2 / 5.6, on 7 x 7 5.2 / 4.3; ResNet-18 98.4 / 95.0,
+// ResNet-101, Inception-v3, MobileNetV2 and AlexNet together 458 / 446.
+template <typename T, int TN, int WK>
+__device__ __forceinline__ void ring_patch_body(const OpArgs &a) {
+    fetch_rect_walk(a);
+    set_wave_priority(a.prio);
+    constexpr int ES = sizeof(T), BN = 16 * TN, D = 2;
+    constexpr int PIXELS = 48, PATCH = PIXELS * 64, XL = PIXELS / 16;  // a load covers 16 pixels of 64 bytes
+    constexpr int REGION = std::max(D * PATCH, BN * 16 * 4);           // LDS of a wave: its patches, then its sums
+    typedef typename Mma<T, 16>::Acc Acc;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[WK * REGION];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int tile, z, tn_idx, tm_idx;
+    if (!find_tile(a, blockIdx.x / XCDS, tile, z, tn_idx, tm_idx)) return;
+    const int rect = -a.panel, PW = rect + 2;              // columns of the rectangle and of its patch
+    const bool wide = rect == 8;
+    const int n0 = tn_idx * BN;
+    const int img = (int)divide((uint32_t)tm_idx, a.walk.pq), in_img = tm_idx - img * (int)a.walk.pq.d;
+    const int trow = (int)divide((uint32_t)in_img, a.walk.q), tcol = in_img - trow * (int)a.walk.q.d;
+    const int p0 = trow * (wide ? 2 : 4), q0 = tcol * rect;
+
+    // Place of tile row j in the rectangle: four consecutive rows are a 2 x 2 window, so that the epilogue can pool.
+    auto place = [&](int j, int &dy, int &dx) {
+        dy = (wide ? 0 : 2 * (j >> 3)) + ((j >> 1) & 1);
+        dx = 2 * (wide ? j >> 2 : (j >> 2) & 1) + (j & 1);
+    };
+    // Four channels of a pixel per storing thread; bias and residual are requested ahead of the operands
+    constexpr int STORING = BN / 16;                       // waves that store
+    const int my_row = (int)threadIdx.x / (BN / 4), my_piece = (int)threadIdx.x % (BN / 4), my_k = n0 + 4 * my_piece;
+    int my_m = -1;
+    {
+        int dy, dx;
+        place(my_row, dy, dx);
+        const int p = p0 + dy, q = q0 + dx;
+        if (a.pool2) my_m = (p >> 1) < (a.P >> 1) && (q >> 1) < (a.Q >> 1) ? (img * (a.P >> 1) + (p >> 1)) * (a.Q >> 1) + (q >> 1) : -1;
+        else my_m = p < a.P && q < a.Q ? (img * a.P + p) * a.Q + q : -1;
+    }
+    const bool vec_ok = whole_packs<4>(a);
+    Addend<T, 4> add;
+    if (wave < STORING) add.load(a, my_m, my_k, vec_ok);
+
+    const T *x = (const T *)a.x + a.x_coff;
+    const u32x4 rsrc_x = raw_buffer(x, a.walk.x_bytes - (uint32_t)a.x_coff * ES);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)a.walk.w_bytes, 0x00027000);
+    const uint32_t region = (uint32_t)wave * REGION;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem + region;
+
+    // Lane l of load i delivers 16-byte column l % 4 of patch pixel 16 i + l / 4; column c of pixel r holds piece c ^ (r / 4 % 4).
+    uint32_t xoff[XL];
+    const int need = (wide ? 4 : 6) * PW;
+    const uint32_t inv = wide ? 6554u : 10923u;            // 2^16 over PW, rounded up
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+        const int r = i * 16 + (lane >> 2), pr = (int)(((uint32_t)r * inv) >> 16), pc = r - pr * PW;
+        const int ih = p0 - 1 + pr, iw = q0 - 1 + pc, piece = (lane ^ (r >> 2)) & 3;
+        const bool ok = (r < need) & ((uint32_t)ih < (uint32_t)a.H) & ((uint32_t)iw < (uint32_t)a.W);
+        xoff[i] = ok ? (uint32_t)(((img * a.H + ih) * a.W + iw) * a.x_ct) * ES + (uint32_t)piece * 16u : OUT_OF_RANGE;
+    }
+    const int chunks = (int)a.walk.units;
+    uint32_t wtile[TN];                                    // filters of a channel tile
+#pragma unroll
+    for (int i = 0; i < TN; ++i) wtile[i] = (uint32_t)((tn_idx * TN + i) * chunks) * 9216u;
+
+    const int frow = lane & 15, fgrp = lane >> 4;
+    int dy, dx;
+    place(frow, dy, dx);
+    const int first_pixel = dy * PW + dx;                  // patch pixel of tap (0, 0)
+
+    Acc acc[TN][1];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][0][v] = 0.f;
+
+    u32x4 w[D][9][TN];
+    auto copy_patch = [&](int c, int d) {
+#pragma unroll
+        for (int i = 0; i < XL; ++i) load_to_lds(rsrc_x, xoff[i], (uint32_t)c * 64u, lds0 + (uint32_t)(d * PATCH + i * 1024));
+    };
+    auto load_filters = [&](int c, int d) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+                w[d][t][i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (uint32_t)lane * 16u + (uint32_t)(t % 3) * 1024u, wtile[i] + (uint32_t)c * 9216u + (uint32_t)(t / 3) * 3072u, 0);
+    };
+    auto multiply = [&](int d) {
+        u32x4 fx[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const uint32_t r = (uint32_t)(first_pixel + (t / 3) * PW + t % 3);
+            fx[t] = *reinterpret_cast<const u32x4 *>(&smem[region + (uint32_t)(d * PATCH) + r * 64u + (((uint32_t)fgrp ^ (r >> 2)) & 3u) * 16u]);
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int i = 0; i < TN; ++i) acc[i][0] = Mma<T, 16>::run(w[d][t][i], fx[t], acc[i][0]);
+    };
+    // This wave's chunks: wave, wave + WK, ...
+    for (int c = wave; c < chunks; c += D * WK) {
+        const bool two = c + WK < chunks;
+        if (c != wave) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the patches have been read: their place can be filled again
+        copy_patch(c, 0);
+        if (two) {
+            copy_patch(c + WK, 1);
+            load_filters(c, 0);
+            load_filters(c + WK, 1);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(D * 9 * TN) : "memory");
+            multiply(0);
+            multiply(1);
+        } else {
+            load_filters(c, 0);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(9 * TN) : "memory");
+            multiply(0);
+        }
+    }
+    // a wave's sums go into its own region, whose patches have all landed and been read
+    publish_sums<BN, 16, BN, 16>(acc, reinterpret_cast<float *>(&smem[region]), 0, 0, frow, fgrp);
+    __syncthreads();
+    if (wave >= STORING) return;
+    float v[4];
+    add_up<BN, 4, WK>(reinterpret_cast<const float *>(&smem[0]), REGION / 4, my_row, my_piece, v);
+    finish_pixel<T, 4, BN / 4>(a, v, add, my_m, my_k, vec_ok, (my_row & 3) == 0);
+}
+
 // 3x3 windows, stride 1, padding 1, C % 64 == 0: the nine taps of a 64-channel chunk read the same input pixels, so those
 // are staged once per chunk as a patch and every tap reads its operand rows at a shifted position.
 // The map is cut into panels of `panel` columns; inside a panel pixels are numbered row by row through all images, and a
@@ -1318,6 +1462,18 @@ __global__ void __launch_bounds__(64 * WK) ring_pair_kernel(OpArgsPair p) {
     results_stored();
 }
 
+template <typename T, int TN, int WK>
+__global__ void __launch_bounds__(64 * WK) ring_patch_kernel(OpArgs a) {
+    ring_patch_body<T, TN, WK>(a);
+    results_stored();
+}
+
+template <typename T, int TN, int WK>
+__global__ void __launch_bounds__(64 * WK) ring_patch_pair_kernel(OpArgsPair p) {
+    ring_patch_body<T, TN, WK>(p.a[blockIdx.y]);
+    results_stored();
+}
+
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
     patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, blockIdx.x / XCDS);
@@ -1416,8 +1572,20 @@ int patch_panel(int N, int P, int Q, int BM, int PC, bool pool) {
     return best;
 }
 
-// Pixel tiles of a form: over the flattened map, or per panel.
+// Columns of the rectangles a ring's tiles are for this layer: the shape of which fewer cover the map; 0: tiles of consecutive pixels.  Rectangles
+// that stick out at the edges are work for nothing, and a tenant beside it pays for that: where they are 14 and 23 % more than tiles of consecutive
+// pixels (14 x 14 and 7 x 7 maps at batch 4) the layer alone is 1.5 to 5 us faster, but ResNet-18 + MobileNetV2 in fp32 take 388 us instead of 376,
+// four networks at batch 8 842 instead of 836.  At one image (14 x 14: 8 % more) both gain.
+int ring_rect(const OpArgs &a) {
+    const int chunk = 64 / (a.dtype == MT_F32 ? 4 : 2);
+    if (a.kind != MT_CONV || a.groups > 1 || a.R != 3 || a.S != 3 || a.sh != 1 || a.sw != 1 || a.ph != 1 || a.pw != 1 || a.C % chunk != 0) return 0;
+    const int flat = cdiv(a.N * a.P * a.Q, 16), wide = a.N * cdiv(a.P, 2) * cdiv(a.Q, 8), square = a.N * cdiv(a.P, 4) * cdiv(a.Q, 4);
+    if (10 * std::min(wide, square) > 11 * flat) return 0;
+    return wide < square ? 8 : 4;
+}
+// Pixel tiles of a form: over the flattened map, per panel, or rectangles (panel < 0).
 int pixel_tiles(const TileForm &f, const OpArgs &a, int panel) {
+    if (panel < 0) return a.N * cdiv(a.P, 16 / -panel) * cdiv(a.Q, -panel);
     if (f.patch_pixels == 0) return cdiv(a.N * a.P * a.Q, f.bm);
     return cdiv(a.Q, panel) * cdiv(a.N * a.P * panel, f.bm);
 }
@@ -1435,12 +1603,12 @@ void set_walk(OpArgs &a) {
     w.x_bytes = (uint32_t)((uint64_t)a.N * a.H * a.W * a.x_ct * es);
     w.w_bytes = (uint32_t)((uint64_t)a.n_pad * a.k_pad * es);
     w.flat = a.R == 1 && a.S == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0 && !a.pool2;
-    w.units = t.patch_pixels > 0 ? (uint32_t)(a.C / TK) : (uint32_t)a.k_pad / (row * (uint32_t)t.kd);
+    w.units = a.panel < 0 ? (uint32_t)a.C / (row / 2) : t.patch_pixels > 0 ? (uint32_t)(a.C / TK) : (uint32_t)a.k_pad / (row * (uint32_t)t.kd);
     w.per = (w.units + (uint32_t)a.split_k - 1) / (uint32_t)a.split_k;
     w.split = divisor((uint32_t)a.split_k);
     w.tiles = divisor(a.tile_order ? tiles_m : tiles_n);
-    w.q = divisor(q);
-    w.pq = divisor(a.panel > 0 ? p : p * q);
+    w.q = divisor(a.panel < 0 ? (uint32_t)cdiv(a.Q, -a.panel) : q);
+    w.pq = divisor(a.panel < 0 ? (uint32_t)(cdiv(a.Q, -a.panel) * cdiv(a.P, 16 / -a.panel)) : a.panel > 0 ? p : p * q);
     a.divq_m = w.q.m; a.divq_s1 = w.q.s1; a.divq_s2 = w.q.s2;            // for the fused 1x1 + depthwise kernels
     a.divpq_m = w.pq.m; a.divpq_s1 = w.pq.s1; a.divpq_s2 = w.pq.s2;
     w.c = divisor((uint32_t)a.C);
@@ -1508,11 +1676,11 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     if (form < 0) return false;
     const TileForm &t = FORMS[form];
     a.form = form;
-    a.panel = panel;
+    a.panel = panel = t.ring ? -ring_rect(a) : panel;
     a.split_k = split;
     a.block = t.threads;
     a.n_pad = cdiv(a.K, t.bn) * t.bn;
-    a.k_pad = t.patch_pixels > 0 ? a.gemm_k : cdiv(a.gemm_k, row * t.kd) * row * t.kd;
+    a.k_pad = t.patch_pixels > 0 || panel < 0 ? a.gemm_k : cdiv(a.gemm_k, row * t.kd) * row * t.kd;
     // Consecutive tiles run on one XCD: they walk the channel tiles of one pixel tile when the activations are the larger
     // operand, the pixel tiles of one channel tile otherwise.
     a.tile_order = ((double)a.K * a.gemm_k > (double)a.N * a.H * a.W * a.C) ? 1 : 0;
@@ -1532,7 +1700,7 @@ void describe_tile(const OpArgs &a, mt_op_form *out) {
     out->tile_pixels = t.bm;
     out->stage_slices = t.kd;
     out->ring_waves = t.ring;
-    out->panel_columns = a.panel;
+    out->panel_columns = std::max(a.panel, 0);
 }
 
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats) {
@@ -1586,6 +1754,11 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         by_gather(go);
     };
     auto ring = [&]<int BN, int WK, int D>() {
+        if (a.panel < 0) {
+            if constexpr (std::is_same_v<T, float>) launch((ring_patch_kernel<T, BN / 16, WK>), grid, block, 0, st, a);
+            else MT_LAUNCH((ring_patch_kernel<T, BN / 16, WK>), (ring_patch_pair_kernel<T, BN / 16, WK>), grid, block, st, a, mate);
+            return;
+        }
         auto go = [&]<int MODE>() {
             if constexpr (std::is_same_v<T, float>) launch((ring_kernel<T, BN, WK, D, MODE>), grid, block, 0, st, a);
             else MT_LAUNCH((ring_kernel<T, BN, WK, D, MODE>), (ring_pair_kernel<T, BN, WK, D, MODE>), grid, block, st, a, mate);

@@ -1754,6 +1754,17 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
                             }
                         }
                 src = packed.data();
+            } else if (a.panel < 0) {
+                // [K][tap][C] -> [16 channels][chunk of 64 bytes][tap][lane][16 bytes]: lane l holds piece l / 16 of output channel l % 16
+                packed.assign((size_t)a.n_pad * a.k_pad * es, 0);
+                const int chunk = 64 / es, ncc = a.C / chunk;
+                for (int k = 0; k < a.K; ++k)
+                    for (int cc = 0; cc < ncc; ++cc)
+                        for (int tap = 0; tap < 9; ++tap)
+                            for (int p = 0; p < 4; ++p)
+                                std::memcpy(packed.data() + (((((size_t)(k / 16) * ncc + cc) * 9 + tap) * 64) + p * 16 + k % 16) * 16,
+                                            src + ((size_t)k * a.gemm_k + (size_t)tap * a.C + cc * chunk) * es + p * 16, 16);
+                src = packed.data();
             } else if (a.panel > 0) {
                 // [K][tap][C] -> [n_pad][chunk of 64 channels][tap][64], zero padded rows
                 packed.assign((size_t)a.n_pad * a.k_pad * es, 0);
