@@ -35,7 +35,11 @@ constexpr int DC_TABLE = 2048;               // reduction elements of the elemen
 constexpr int DC_ELEMENT = 0, DC_PIECE = 1, DC_UNIFORM = 2;
 
 template <int TN, int TM, int WN, int WM, int WK, int D, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs a) {
+__global__ void __launch_bounds__(64 * WN * WM * WK) dconv_kernel(OpArgs args) {
+    OpArgs a = args;
+    hold(a.x, a.w, a.walk.total, a.walk.per_xcd, a.walk.pixels, a.N, a.walk.tiles.d, a.walk.tiles.m, a.walk.tiles.s1, a.walk.tiles.s2, a.walk.split.d, a.walk.split.m,
+         a.walk.split.s1, a.walk.split.s2, a.walk.c.d, a.walk.c.m, a.walk.c.s1, a.walk.c.s2, a.tile_order, a.k_pad, a.x_ct, a.x_coff, a.H, a.W, a.C, a.S, a.sh, a.sw, a.ph, a.pw, a.P, a.Q, a.prio, a.K,
+         a.act, a.res_ct, a.y_coff, a.y_ct, a.bias, a.res, a.y, a.gemm_k, a.n_pad, a.divq_m, a.divq_s1, a.divq_s2, a.divpq_m, a.divpq_s1, a.divpq_s2);
     set_wave_priority(a.prio);
     constexpr int ES = 4, KST = 16, EPV = 4;
     constexpr int NW = WN * WM * WK, BN = 16 * TN * WN, BM = 16 * TM * WM, F = TN * TM;

@@ -562,10 +562,10 @@ __device__ __forceinline__ uint32_t window_mask(const OpArgs &a, int ih0, int iw
     return range(ih0, a.H, a.R) | range(iw0, a.W, a.S) << 16;
 }
 
-// Asks for everything a workgroup needs before its first load in one go: read where it is first used, the arguments come in four
-// or five trips through the scalar cache, one after the other.  With that and the divisors of TileWalk a workgroup requests its
-// first operands after 180 instructions instead of 600 (1.25 us, of which 0.35 the arguments): ResNet-18 at one image 119.8 -> 108.6 us,
-// ResNet-101, Inception-v3, MobileNetV2 and AlexNet together 587 -> 535, eight ResNet-50 at batch 16 2756 -> 2689.
+// A workgroup's arguments, all in one trip.  fetch_walk only asks for them together, which is enough for the kernels of one operator with
+// narrow tiles, and leaves the compiler free to keep what it likes; held, they are two trips there (the scalar registers run out).
+// us, asked for together / held: 64 -> 128 on 112 x 112 (128 x 64 patch) 6.6 / 6.3, eight ResNet-50 at batch 16, two to a launch, 2520 / 2469; but 256 -> 256 on
+// 14 x 14 (ring) 3.5 / 3.6, 64 -> 96 on 5 x 35 x 35 (64 x 64 patch) 5.2 / 5.4.
 __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
     const TileWalk &w = a.walk;
     asm volatile("" ::"s"(a.x), "s"(a.w), "s"(w.total), "s"(w.per_xcd), "s"(w.pixels), "s"(w.x_bytes), "s"(w.w_bytes), "s"(w.flat), "s"(w.units), "s"(w.per),
@@ -574,7 +574,6 @@ __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
     asm volatile("" ::"s"(w.c.d), "s"(w.c.m), "s"(w.c.s1), "s"(w.c.s2), "s"(w.adv_t), "s"(w.adv_c), "s"(w.inv_s), "s"(a.W), "s"(a.C), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw),
                  "s"(a.ph), "s"(a.pw), "s"(a.N), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio), "s"(a.K), "s"(a.res_ct), "s"(a.y_coff), "s"(a.y_ct), "s"(a.bias), "s"(a.res));
 }
-
 // The same for ring_patch_body: fewer, so that they are one trip there too (with the ones above the compiler ran out of scalar registers
 // and asked for the epilogue's in a second trip, 0.1 us).
 __device__ __forceinline__ void fetch_rect_walk(const OpArgs &a) {
@@ -583,6 +582,15 @@ __device__ __forceinline__ void fetch_rect_walk(const OpArgs &a) {
                  "s"(w.pq.d), "s"(w.pq.m), "s"(w.pq.s1), "s"(w.pq.s2), "s"(w.q.d), "s"(w.q.m), "s"(w.q.s1), "s"(w.q.s2), "s"(a.tile_order), "s"(a.pool2), "s"(a.x_ct), "s"(a.x_coff), "s"(a.H),
                  "s"(a.W), "s"(a.P), "s"(a.Q), "s"(a.panel), "s"(a.prio));
     asm volatile("" ::"s"(a.K), "s"(a.res_ct), "s"(a.y_coff), "s"(a.y_ct), "s"(a.bias), "s"(a.res));
+}
+// TAPS: the window has more than one tap, or the map is walked image by image
+template <bool TAPS>
+__device__ __forceinline__ void hold_walk(OpArgs &a) {
+    TileWalk &w = a.walk;
+    hold(a.x, a.w, w.total, w.per_xcd, w.pixels, w.x_bytes, w.w_bytes, w.flat, w.units, w.per, w.split.d, w.split.m, w.split.s1, w.split.s2, w.tiles.d, w.tiles.m, w.tiles.s1, w.tiles.s2,
+         w.pq.d, w.pq.m, w.pq.s1, w.pq.s2, w.q.d, w.q.m, w.q.s1, w.q.s2, a.tile_order, a.pool2, a.k_pad, a.x_ct, a.x_coff, a.H, a.W, a.sh, a.sw, a.ph, a.pw, a.prio, a.K, a.res_ct, a.y_coff, a.y_ct, a.bias, a.res);
+    if constexpr (TAPS) hold(w.c.d, w.c.m, w.c.s1, w.c.s2, w.adv_t, w.adv_c, w.inv_s, a.C, a.R, a.S);
+    else hold(a.gemm_k);
 }
 
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.
@@ -602,9 +610,11 @@ __device__ __forceinline__ bool find_tile(const OpArgs &a, uint32_t slot, int &t
 
 // BN output channels x BM pixels per workgroup; WN x WM waves over the tile, WK such groups that share the reduction;
 // KD 64-deep slices of the reduction per stage, NBUF stages in LDS.
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__device__ __forceinline__ void tile_body(const OpArgs &a, uint32_t slot) {
-    fetch_walk(a);
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE, bool HELD>
+__device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
+    OpArgs a = args;
+    if constexpr (HELD) hold_walk<MODE != TG_POINT>(a);
+    else fetch_walk(a);
     set_wave_priority(a.prio);
     constexpr int NW = WN * WM * WK;
     constexpr int SUBN = BN / WN, SUBM = BM / WM;
@@ -655,7 +665,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &a, uint32_t slot) {
     Addend<T, V> add;
     if (AHEAD && unsplit && storing) add.load(a, pixel(my_row(0)), my_k, vec_ok);
     if (WIDE && wave < BN / 64)
-        load_words_to_lds(raw_buffer(a.bias, (uint32_t)a.n_pad * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u,
+        load_words_to_lds(raw_buffer(a.bias, (uint32_t)(n0 + BN) * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u,
                           (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem + BIAS + (uint32_t)wave * 256u);
 
     const int st0 = z * (int)a.walk.per;
@@ -858,9 +868,11 @@ __device__ __forceinline__ void tile_body(const OpArgs &a, uint32_t slot) {
 // 1x1 1024 -> 256 on 14 x 14 4.9 / 3.9; 2048 -> 192 on 8 x 8 with waves that load to registers 6.5, 4.6 here.
 // Rings hold 64 to 72 KB, not what fits: with 128 to 144 KB a layer alone is up to 0.6 us faster, but its workgroups wait for an empty
 // compute unit when other tenants run (ResNet-101, Inception-v3, MobileNetV2 and AlexNet together: 665 us, 587 with these).
-template <typename T, int BN, int WK, int D, int MODE>
-__device__ __forceinline__ void ring_body(const OpArgs &a) {
-    fetch_walk(a);
+template <typename T, int BN, int WK, int D, int MODE, bool HELD>
+__device__ __forceinline__ void ring_body(const OpArgs &args) {
+    OpArgs a = args;
+    if constexpr (HELD) hold_walk<MODE != TG_POINT>(a);
+    else fetch_walk(a);
     set_wave_priority(a.prio);
     constexpr int ES = sizeof(T), RK = ROW<T>, EPP = 16 / ES, BM = 16, TN = BN / 16;
     constexpr int WQ = BN / 8, XQ = BM / 8, L = WQ + XQ;   // loads of a row: 8 operand rows of 128 bytes each
@@ -1008,9 +1020,14 @@ __device__ __forceinline__ void ring_body(const OpArgs &a) {
 // x 16 pixels of 256 channels, of which 4300 wait for copies.  98 KB here, and a third to two thirds of the LDS.  us a layer, ring_body / this, f16 at one
 // image: 128 -> 128 on 28 x 28 4.0 / 3.4, 256 -> 256 on 14 x 14 4.0 / 3.6, 512 -> 512 on 14 x 14 7.2 / 5.6, on 7 x 7 5.2 / 4.3; ResNet-18 98.4 / 95.0,
 // ResNet-101, Inception-v3, MobileNetV2 and AlexNet together 458 / 446.
-template <typename T, int TN, int WK>
-__device__ __forceinline__ void ring_patch_body(const OpArgs &a) {
-    fetch_rect_walk(a);
+template <typename T, int TN, int WK, bool HELD>
+__device__ __forceinline__ void ring_patch_body(const OpArgs &args) {
+    OpArgs a = args;
+    if constexpr (HELD)
+        hold(a.x, a.w, a.walk.total, a.walk.per_xcd, a.walk.x_bytes, a.walk.w_bytes, a.walk.units, a.walk.tiles.d, a.walk.tiles.m, a.walk.tiles.s1, a.walk.tiles.s2, a.walk.pq.d, a.walk.pq.m,
+             a.walk.pq.s1, a.walk.pq.s2, a.walk.q.d, a.walk.q.m, a.walk.q.s1, a.walk.q.s2, a.tile_order, a.pool2, a.x_ct, a.x_coff, a.H, a.W, a.P, a.Q, a.panel, a.prio, a.K, a.res_ct, a.y_coff,
+             a.y_ct, a.bias, a.res);
+    else fetch_rect_walk(a);
     set_wave_priority(a.prio);
     constexpr int ES = sizeof(T), BN = 16 * TN, D = 2;
     constexpr int PIXELS = 48, PATCH = PIXELS * 64, XL = PIXELS / 16;  // a load covers 16 pixels of 64 bytes
@@ -1139,9 +1156,15 @@ __device__ __forceinline__ void ring_patch_body(const OpArgs &a) {
 // tile is BM consecutive ones.  Its patch holds the rows from the one above its first to the one below its last, each
 // panel + 2 pixels wide, with an empty row between two images; what lies outside an image is loaded out of range, i.e. zero.
 // The filter bank is [n_pad][chunk][tap][64].
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
-__device__ __forceinline__ void patch_body(const OpArgs &a, uint32_t slot) {
-    fetch_walk(a);
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC, bool HELD>
+__device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
+    OpArgs a = args;
+    if constexpr (HELD)
+        hold(a.x, a.w, a.walk.total, a.walk.per_xcd, a.walk.x_bytes, a.walk.w_bytes, a.walk.units, a.walk.per, a.walk.split.d, a.walk.split.m, a.walk.split.s1, a.walk.split.s2, a.walk.tiles.d,
+             a.walk.tiles.m, a.walk.tiles.s1, a.walk.tiles.s2, a.walk.pq.d, a.walk.pq.m, a.walk.pq.s1, a.walk.pq.s2, a.walk.q.d, a.walk.q.m, a.walk.q.s1, a.walk.q.s2, a.walk.panel_tiles.d,
+             a.walk.panel_tiles.m, a.walk.panel_tiles.s1, a.walk.panel_tiles.s2, a.walk.inv_pw, a.walk.inv_h, a.tile_order, a.pool2, a.k_pad, a.x_ct, a.x_coff, a.H, a.W, a.N, a.P, a.Q, a.panel, a.prio, a.K, a.res_ct, a.y_coff,
+             a.y_ct, a.bias, a.res);
+    else fetch_walk(a);
     set_wave_priority(a.prio);
     constexpr int NW = WN * WM * WK, NBUF = 3;
     constexpr int SUBN = BN / WN, SUBM = BM / WM;
@@ -1293,7 +1316,7 @@ __device__ __forceinline__ void patch_body(const OpArgs &a, uint32_t slot) {
     };
 
     if (WIDE && wave < BN / 64)
-        load_words_to_lds(raw_buffer(a.bias, (uint32_t)a.n_pad * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u, lds0 + BIAS + (uint32_t)wave * 256u);
+        load_words_to_lds(raw_buffer(a.bias, (uint32_t)(n0 + BN) * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u, lds0 + BIAS + (uint32_t)wave * 256u);
 #pragma unroll
     for (int i = 0; i < PL; ++i) issue_patch(i, 0);
     xs += TK * 2;
@@ -1407,7 +1430,7 @@ __device__ __forceinline__ void patch_body(const OpArgs &a, uint32_t slot) {
 constexpr int tile_waves_per_simd(int bn, int bm, int nbuf) { return bn * bm >= 128 * 128 && nbuf == 2 ? 2 : 1; }
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_kernel(OpArgs a) {
-    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, blockIdx.x / XCDS);
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE, sizeof(T) == 2 && BM / WM >= 32 && WK == 1>(a, blockIdx.x / XCDS);
     results_stored();
 }
 
@@ -1436,7 +1459,7 @@ template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, 
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD, NBUF) * WN * WM * WK / 4) tile_walk_kernel(OpArgs) {
     for (uint32_t slot = blockIdx.x / XCDS;;) {
         const OpArgs &a = kernel_arguments();
-        tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(a, slot);
+        tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE, true>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) break;
         __syncthreads();                                   // every wave is done with the tile's LDS
@@ -1446,37 +1469,37 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD, NBUF)
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
 __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM, NBUF)) tile_pair_kernel(OpArgsPair p) {
-    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>(p.a[blockIdx.y], blockIdx.x / XCDS);
+    tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE, true>(p.a[blockIdx.y], blockIdx.x / XCDS);
     results_stored();
 }
 
 template <typename T, int BN, int WK, int D, int MODE>
 __global__ void __launch_bounds__(64 * WK) ring_kernel(OpArgs a) {
-    ring_body<T, BN, WK, D, MODE>(a);
+    ring_body<T, BN, WK, D, MODE, false>(a);
     results_stored();
 }
 
 template <typename T, int BN, int WK, int D, int MODE>
 __global__ void __launch_bounds__(64 * WK) ring_pair_kernel(OpArgsPair p) {
-    ring_body<T, BN, WK, D, MODE>(p.a[blockIdx.y]);
+    ring_body<T, BN, WK, D, MODE, true>(p.a[blockIdx.y]);
     results_stored();
 }
 
 template <typename T, int TN, int WK>
 __global__ void __launch_bounds__(64 * WK) ring_patch_kernel(OpArgs a) {
-    ring_patch_body<T, TN, WK>(a);
+    ring_patch_body<T, TN, WK, false>(a);
     results_stored();
 }
 
 template <typename T, int TN, int WK>
 __global__ void __launch_bounds__(64 * WK) ring_patch_pair_kernel(OpArgsPair p) {
-    ring_patch_body<T, TN, WK>(p.a[blockIdx.y]);
+    ring_patch_body<T, TN, WK, true>(p.a[blockIdx.y]);
     results_stored();
 }
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, blockIdx.x / XCDS);
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC, BN == 128>(a, blockIdx.x / XCDS);
     results_stored();
 }
 
@@ -1484,7 +1507,7 @@ template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * WK / 4) patch_walk_kernel(OpArgs) {
     for (uint32_t slot = blockIdx.x / XCDS;;) {
         const OpArgs &a = kernel_arguments();
-        patch_body<T, BN, BM, WN, WM, WK, KD, PC>(a, slot);
+        patch_body<T, BN, BM, WN, WM, WK, KD, PC, true>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) break;
         __syncthreads();
@@ -1494,7 +1517,7 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * 
 
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPair p) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC>(p.a[blockIdx.y], blockIdx.x / XCDS);
+    patch_body<T, BN, BM, WN, WM, WK, KD, PC, true>(p.a[blockIdx.y], blockIdx.x / XCDS);
     results_stored();
 }
 
