@@ -1155,8 +1155,23 @@ __device__ __forceinline__ void ring_patch_body(const OpArgs &args) {
 // The map is cut into panels of `panel` columns; inside a panel pixels are numbered row by row through all images, and a
 // tile is BM consecutive ones.  Its patch holds the rows from the one above its first to the one below its last, each
 // panel + 2 pixels wide, with an empty row between two images; what lies outside an image is loaded out of range, i.e. zero.
-// The filter bank is [n_pad][chunk][tap][64].
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC, bool HELD>
+// The filter bank is packed in operand order ([32 channels][chunk][tap][16 elements][lane][16 bytes]) and goes straight to registers, a kilobyte a
+// load and DW steps ahead, so LDS holds only the patches and the waves meet once per chunk.
+//
+// What bounds it: matrix instructions (with loads of both operands left out a 128x128 tile of 512 channels takes 25.5 us, with them 31.6) and,
+// at short reductions, the first patch and the finish.  Filters that pass through LDS, as they did before, are two thirds of the bytes written to it and half of
+// those read, with a barrier per tap, and their three stages kept a second workgroup from the unit: 64x64 and 128x64 tiles now leave room for one.
+// The wave groups divide the four steps of a tap such that no filter is loaded twice on 64 channels (two waves, four groups) and on the 128x64
+// tile (four waves, two groups); on the wider ones two waves load the same filters, the second from the L1, which costs nothing (two waves and four
+// groups on the 128x128 tile: 31.6 / 32.4 us).  us a layer, filters through LDS / this, f16, 3x3:
+//   128x64   128 -> 128 on 16 x 28 x 28  8.25 / 7.56     512 -> 512 on 64 x 7 x 7   22.3 / 19.5     64 -> 128 on 112 x 112  6.19 / 5.80
+//   64x64    256 -> 256 on 16 x 14 x 14  8.94 / 7.85     512 -> 512 on 8 x 14 x 14  13.9 / 12.0     256 -> 256 on 56 x 56   9.02 / 7.93
+//   64x32    256 -> 512 on 28 x 28       7.90 / 6.20
+//   128x128  256 -> 256 on 64 x 14 x 14  18.8 / 17.5     512 -> 512 on 8 x 28 x 28  32.6 / 31.6
+//   128x256  256 -> 256 on 8 x 56 x 56   30.2 / 30.3     128 -> 128 on 8 x 112 x 112  35.5 / 34.7
+// Passes: ResNet-18, VGG-16 and MobileNetV2 225 / 217, four networks at batch 8 844 / 806, eight ResNet-50 at batch 16 2447 / 2326, on shares of the
+// units in eight stages 4341 / 4164.
+template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC, bool HELD, int ROOM = 0>
 __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     OpArgs a = args;
     if constexpr (HELD)
@@ -1166,31 +1181,27 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
              a.y_ct, a.bias, a.res);
     else fetch_walk(a);
     set_wave_priority(a.prio);
-    constexpr int NW = WN * WM * WK, NBUF = 3;
-    constexpr int SUBN = BN / WN, SUBM = BM / WM;
-    constexpr int MF = (SUBN % 32 == 0 && SUBM % 32 == 0) ? 32 : 16;
-    constexpr int TN = SUBN / MF, TM = SUBM / MF;
-    constexpr int KS = MF == 32 ? 16 : 32, PPS = KS / 8;
-    constexpr int STEPS = KD * TK / KS, MY_STEPS = STEPS / WK;
-    static_assert(STEPS % WK == 0 && 9 % KD == 0, "stages are whole taps, shared evenly by the wave groups");
-    constexpr int ACC = MF == 32 ? 16 : 4;
-    constexpr int SPC = 9 / KD;                            // stages per chunk
-    constexpr int WQ = KD * BN / 8 / NW, PL = PC / 8 / NW; // loads of a wave per stage / per patch
-    static_assert(WQ * NW * 8 == KD * BN && PL * NW * 8 == PC, "the waves share the loads evenly");
-    // The next chunk's patch is requested during this chunk's stages, early enough to have landed with the wait of its first
-    constexpr int XPS = (PL + SPC - NBUF + 1) / (SPC - NBUF + 2);
-    constexpr int L = WQ + XPS;
-    constexpr int W_BYTES = KD * BN * 128, P_BYTES = PC * 128, DUMP = NBUF * W_BYTES + 2 * P_BYTES;
-    constexpr bool WIDE = MF == 32 && (WK == 1 || (WK == 2 && TN == 2));     // every wave finishes its own part of the tile (two groups: half of it)
-    constexpr bool SUMS = WK > 1 && !WIDE;
-    static_assert(!SUMS || WK * BN * BM * 4 <= DUMP, "the groups' sums fit the operands' place");
-    constexpr int RED_BYTES = WIDE ? 0 : WK * BN * BM * 4, EP_BYTES = WIDE ? 0 : BM * (BN + 4) * 4;
-    constexpr int BIAS = std::max({DUMP + 1024, RED_BYTES, EP_BYTES}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
+    constexpr int NW = WN * WM * WK, MF = 32;
+    constexpr int SUBN = BN / WN, SUBM = BM / WM, TN = SUBN / MF, TM = SUBM / MF;
+    static_assert(TN >= 1 && TM >= 1 && 4 % WK == 0, "the wave groups share the four 16-element steps of a tap");
+    constexpr int ACC = 16, MY = 4 / WK, SPC = 9 * MY;     // a wave's steps per tap and per chunk
+    static_assert(SPC % DW == 0, "registers of a step");
+    constexpr int PL = PC / 8 / NW;                        // loads of a wave per patch
+    static_assert(PL * NW * 8 == PC && PL < SPC, "the waves share a patch evenly, and it is requested during a chunk's steps");
+    constexpr int P_BYTES = PC * 128;
+    constexpr bool WIDE = WK == 2, SUMS = !WIDE;           // two groups: every wave finishes half of its part of the tile
+    constexpr int OWN = WIDE ? TN * TM / WK : 1;           // products of 32 x 32 in it: a row of them
+    static_assert(!WIDE || (TN * TM % WK == 0 && TM % OWN == 0), "the half is 32 channels x OWN * 32 pixels");
+    constexpr int XCH = NW * OWN * 4096, RED_BYTES = WIDE ? XCH + NW * WaveTile<T, 1, OWN>::BYTES : WK * BN * BM * 4, EP_BYTES = WIDE ? 0 : BM * (BN + 4) * 4;
+    constexpr int COUNTED = ROOM > 0 ? 160 * 1024 / (ROOM + 1) + 1 : 0;      // a compute unit holds no more workgroups than are counted on
+    constexpr int BIAS = std::max({2 * P_BYTES, RED_BYTES, EP_BYTES, COUNTED + 15 & ~15}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
     __shared__ int s_last;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x;
+    if (ROOM > 0) asm volatile("" : "+v"(tid));            // what a lane's place decides is worked out for every tile: kept, it is more registers than there are
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
 
@@ -1223,20 +1234,16 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     const int XS = a.x_ct;
     const T *x = (const T *)a.x + a.x_coff;
     const u32x4 rsrc_x = raw_buffer(x, a.walk.x_bytes - (uint32_t)a.x_coff * 2u);
-    const u32x4 rsrc_w = raw_buffer(a.w, a.walk.w_bytes);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)a.walk.w_bytes, 0x00027000);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
     // Columns of the LDS rows as in tile_body; a patch row's key is its pixel's number without the two border columns of the
     // rows above it, so that 16 consecutive pixels of a tile have 16 consecutive keys wherever a map row ends among them.
     static_assert(NW % 2 == 0 && BN % 16 == 0, "a wave's row groups have one parity");
     const int lrow = lane >> 3;
 
-    const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + ((lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1))) * 8) * 2u;
-    uint32_t ws[WQ];
+    uint32_t wtile[TN];                                    // this wave's part of the filters of 32 channels, chunk by chunk
 #pragma unroll
-    for (int i = 0; i < WQ; ++i) {
-        const int q = i * NW + wave, kd = q / (BN / 8), rg = q % (BN / 8);
-        ws[i] = (uint32_t)(rg * 8 * a.k_pad + (c_begin * 9 + kd) * TK) * 2u;
-    }
+    for (int i = 0; i < TN; ++i) wtile[i] = (((uint32_t)(n0 / 32 + wn * TN + i) * a.walk.units + (uint32_t)c_begin) * 36u + (uint32_t)(wk * MY)) * 1024u;
     uint32_t xoff[PL];
     const uint32_t inv_pw = a.walk.inv_pw, inv_h = a.walk.inv_h;
 #pragma unroll
@@ -1253,16 +1260,15 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     uint32_t xs = (uint32_t)(c_begin * TK) * 2u;           // channel offset of the patch requested next
 
     auto issue_patch = [&](int i, int buf) {
-        load_to_lds(rsrc_x, xoff[i], xs, lds0 + (uint32_t)(NBUF * W_BYTES + buf * P_BYTES + (i * NW + wave) * 1024));
+        load_to_lds(rsrc_x, xoff[i], xs, lds0 + (uint32_t)(buf * P_BYTES + (i * NW + wave) * 1024));
     };
-    auto issue_w = [&](int buf) {
+    // Step j of a chunk: 16 elements of tap j / MY
+    u32x4 w[DW][TN];
+    auto load_filters = [&](int c, int j) {
 #pragma unroll
-        for (int i = 0; i < WQ; ++i) {
-            load_to_lds(rsrc_w, wv, ws[i], lds0 + (uint32_t)(buf * W_BYTES + (i * NW + wave) * 1024));
-            ws[i] += KD * TK * 2;
-        }
+        for (int i = 0; i < TN; ++i)
+            w[j % DW][i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (uint32_t)lane * 16u + (uint32_t)(j % MY) * 1024u, wtile[i] + (uint32_t)c * 36864u + (uint32_t)(j / MY) * 4096u, 0);
     };
-    auto issue_none = [&]() { load_to_lds(rsrc_x, OUT_OF_RANGE, 0u, lds0 + DUMP); };   // keeps the number of loads per stage the same
 
     Acc acc[TN][TM];
 #pragma unroll
@@ -1273,8 +1279,6 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
             for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
 
     const int frow = lane % MF, fgrp = lane / MF;
-    struct Frag { u32x4 w[TN], x[TM]; };
-    const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), wswz = (uint32_t)((frow >> 1) & 7);
     int ppos[TM], prow[TM];                                          // patch pixel of tap (0, 0) for this lane's pixels
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
@@ -1284,34 +1288,15 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
         ppos[j] = prow[j] * PW + col;
     }
 
-    // one stage: taps tap0 .. tap0 + KD - 1, filters in buffer wb, patch in buffer pb
-    auto compute = [&](int tap0, int wb, int pb) {
-        Frag f[2];
-        const int s0 = wk * MY_STEPS;
-        auto load_frag = [&](int s, Frag &fr) {
-            const int kd = s / (TK / KS), c0 = (s % (TK / KS)) * PPS;
-            const int tap = tap0 + kd;
-            const uint32_t wcol = ((uint32_t)(c0 + fgrp) ^ wswz) * 16u;
+    u32x4 fx[2][TM];
+    auto load_pixels = [&](int j, int pb, u32x4 (&x)[TM]) {
+        const int tap = j / MY, c0 = (wk * MY + j % MY) * 2;
+        const int shift = (tap / 3) * PW + tap % 3;
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
-                fr.w[i] = *reinterpret_cast<const u32x4 *>(&smem[(uint32_t)(wb * W_BYTES + kd * BN * 128 + i * MF * 128) + wrow + wcol]);
-            const int shift = (tap / 3) * PW + tap % 3;
-#pragma unroll
-            for (int j = 0; j < TM; ++j) {
-                const uint32_t rr = (uint32_t)(ppos[j] + shift);
-                const uint32_t col = ((uint32_t)(c0 + fgrp) ^ (((rr >> 1) - (uint32_t)(prow[j] + tap / 3)) & 7u)) * 16u;
-                fr.x[j] = *reinterpret_cast<const u32x4 *>(&smem[(uint32_t)(NBUF * W_BYTES) + (uint32_t)(pb * P_BYTES) + rr * 128u + col]);
-            }
-        };
-        load_frag(s0, f[0]);
-#pragma unroll
-        for (int s = 0; s < MY_STEPS; ++s) {
-            if (s + 1 < MY_STEPS) load_frag(s0 + s + 1, f[(s + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);             // the next step's operands are requested before this one multiplies
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(f[s & 1].w[i], f[s & 1].x[j], acc[i][j]);
+        for (int i = 0; i < TM; ++i) {
+            const uint32_t rr = (uint32_t)(ppos[i] + shift);
+            const uint32_t col = ((uint32_t)(c0 + fgrp) ^ (((rr >> 1) - (uint32_t)(prow[i] + tap / 3)) & 7u)) * 16u;
+            x[i] = *reinterpret_cast<const u32x4 *>(&smem[(uint32_t)(pb * P_BYTES) + rr * 128u + col]);
         }
     };
 
@@ -1319,32 +1304,37 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
         load_words_to_lds(raw_buffer(a.bias, (uint32_t)(n0 + BN) * 4u), (uint32_t)(n0 + lane) * 4u, (uint32_t)wave * 256u, lds0 + BIAS + (uint32_t)wave * 256u);
 #pragma unroll
     for (int i = 0; i < PL; ++i) issue_patch(i, 0);
-    xs += TK * 2;
 #pragma unroll
-    for (int s = 0; s < NBUF - 1; ++s) {
-        issue_w(s);
-#pragma unroll
-        for (int i = 0; i < XPS; ++i) issue_none();
-    }
-    auto stage = [&]<int I>(int c) {
-        // the stages of a chunk are a multiple of the filter buffers, so stage I of every chunk uses buffer I % NBUF
-        const bool last = c + 1 == nc;
-        if (I == SPC - 1 && last) wait_and_meet<0>();
-        else wait_and_meet<L>();
-        if (!(last && I + NBUF - 1 >= SPC)) {
-            issue_w((I + NBUF - 1) % NBUF);
-#pragma unroll
-            for (int i = 0; i < XPS; ++i) {
-                if (I * XPS + i < PL && !last) issue_patch(I * XPS + i < PL ? I * XPS + i : 0, (c + 1) & 1);
-                else issue_none();
-            }
-        }
-        compute(I * KD, I % NBUF, c & 1);
-    };
-    static_assert(SPC % NBUF == 0 && NBUF == 3, "buffer of a stage");
+    for (int j = 0; j < DW; ++j) load_filters(0, j);
+    wait_and_meet<DW * TN>();
+    load_pixels(0, 0, fx[0]);
     for (int c = 0; c < nc; ++c) {
-        [&]<int... I>(std::integer_sequence<int, I...>) { (stage.template operator()<I>(c), ...); }(std::make_integer_sequence<int, SPC>{});
+        const bool last = c + 1 == nc;
         xs += TK * 2;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(ppos[i]));     // the addresses of all steps, kept from chunk to chunk, are more registers than there are
+#pragma unroll
+        for (int j = 0; j < SPC; ++j) {
+            if (j < PL && !last) issue_patch(j, (c + 1) & 1);
+            if (j + 1 < SPC) {
+                load_pixels(j + 1, c & 1, fx[(j + 1) & 1]);
+            } else if (!last) {
+                wait_and_meet<(SPC - PL) * TN>();          // the filters requested after the last piece of the patch may be under way
+                load_pixels(0, (c + 1) & 1, fx[(j + 1) & 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);             // the next step's operands are requested before this one multiplies
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int m = 0; m < TM; ++m) acc[i][m] = Mma<T, MF>::run(w[j % DW][i], fx[j & 1][m], acc[i][m]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j + DW < SPC) load_filters(c, j + DW);
+            else if (!last) load_filters(c + 1, j + DW - SPC);
+        }
+        if constexpr (SPC % 2 != 0) {
+#pragma unroll
+            for (int m = 0; m < TM; ++m) fx[0][m] = fx[1][m];
+        }
     }
     auto pixel = [&](int ml) {
         const int i = m0 + ml;
@@ -1356,46 +1346,36 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     };
     wait_and_meet<0>();
     if constexpr (WIDE) {
-        constexpr int CT = WK == 2 ? 1 : TN, XCH = WK == 2 ? NW * TM * 4096 : 0;
-        static_assert(XCH + NW * WaveTile<T, CT, TM>::BYTES <= BIAS, "exchanged sums and staging blocks fit");
-        const int c0 = wn * SUBN + (WK == 2 ? wk * 32 : 0);
-        auto complete = [&](Acc (&sums)[CT][TM]) {
-            if (!meet_splits<BN, BM, 64 * NW>(a, sums, &s_last, tile, z, true, tid)) return;
-            WaveTile<T, CT, TM> mine;
-            mine.k = (uint32_t)(n0 + c0 + (lane % mine.LPR) * 8);
+        // each group hands the other the sums of half of its products and finishes the other half
+        float *xch = reinterpret_cast<float *>(&smem[0]) + lane * 4;
+        const int other = wave ^ (WN * WM);
+        Acc mine[1][OWN];
 #pragma unroll
-            for (int j = 0; j < TM; ++j) mine.m_lane[j] = pixel(wm * SUBM + j * 32 + frow);
-            if (whole_packs<8>(a)) mine.finish(a, sums, reinterpret_cast<uint16_t *>(&smem[XCH + wave * mine.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + c0, lane);
-            else store_lanes<T, MF>(a, sums, n0 + c0, mine.m_lane, fgrp);
-        };
-        if constexpr (WK == 2) {
-            // two groups: each hands the other the sums of 32 of its 64 channels and finishes the other 32
-            float4 *xch = reinterpret_cast<float4 *>(&smem[0]);
-            Acc kept[1][TM];
+        for (int q = 0; q < 4 * OWN; ++q) {
+            const Acc &low = acc[0][q / 4], &high = acc[(OWN + q / 4) / TM][(OWN + q / 4) % TM];
+            const int e = 4 * (q % 4);
+            float4 v = make_float4(high[e], high[e + 1], high[e + 2], high[e + 3]);
+            if (wk == 1) v = make_float4(low[e], low[e + 1], low[e + 2], low[e + 3]);
+            *reinterpret_cast<float4 *>(&xch[(wave * OWN * 4 + q) * 256]) = v;
 #pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float4 v;
-                    v.x = acc[1][j][4 * g]; v.y = acc[1][j][4 * g + 1]; v.z = acc[1][j][4 * g + 2]; v.w = acc[1][j][4 * g + 3];
-                    if (wk == 1) { v.x = acc[0][j][4 * g]; v.y = acc[0][j][4 * g + 1]; v.z = acc[0][j][4 * g + 2]; v.w = acc[0][j][4 * g + 3]; }
-                    xch[((wave * TM + j) * 4 + g) * 64 + lane] = v;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) kept[0][j][4 * g + t] = wk == 1 ? acc[1][j][4 * g + t] : acc[0][j][4 * g + t];
-                }
-            __syncthreads();
-            const int other = wave ^ (WN * WM);
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 v = xch[((other * TM + j) * 4 + g) * 64 + lane];
-                    kept[0][j][4 * g] += v.x; kept[0][j][4 * g + 1] += v.y; kept[0][j][4 * g + 2] += v.z; kept[0][j][4 * g + 3] += v.w;
-                }
-            complete(kept);
-        } else {
-            complete(acc);
+            for (int t = 0; t < 4; ++t) mine[0][q / 4][e + t] = wk == 1 ? high[e + t] : low[e + t];
         }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4 * OWN; ++q) {
+            const float4 v = *reinterpret_cast<const float4 *>(&xch[(other * OWN * 4 + q) * 256]);
+            Acc &to = mine[0][q / 4];
+            to[4 * (q % 4)] += v.x; to[4 * (q % 4) + 1] += v.y; to[4 * (q % 4) + 2] += v.z; to[4 * (q % 4) + 3] += v.w;
+        }
+        if (!meet_splits<BN, BM, 64 * NW>(a, mine, &s_last, tile, z, true, tid)) return;
+        WaveTile<T, 1, OWN> part;
+        static_assert(XCH + NW * part.BYTES <= BIAS, "exchanged sums and staging blocks fit");
+        const int c0 = wn * SUBN + wk * OWN / TM * 32, p0 = wm * SUBM + wk * OWN % TM * 32;
+        part.k = (uint32_t)(n0 + c0 + (lane % part.LPR) * 8);
+#pragma unroll
+        for (int j = 0; j < OWN; ++j) part.m_lane[j] = pixel(p0 + j * 32 + frow);
+        if (whole_packs<8>(a)) part.finish(a, mine, reinterpret_cast<uint16_t *>(&smem[XCH + wave * part.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + c0, lane);
+        else store_lanes<T, MF>(a, mine, n0 + c0, part.m_lane, fgrp);
         return;
     }
     if constexpr (SUMS) {
@@ -1437,7 +1417,7 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM,
 // Workgroups of a walking kernel that a compute unit holds, by LDS (three of up to 53 KB, two of up to 80 KB); the kernels' launch bounds have
 // the compiler leave registers for as many.
 constexpr int tile_room(int bn, int bm, int kd, int nbuf) { return nbuf * kd * (bn + bm) <= 416 ? 3 : nbuf * kd * (bn + bm) <= 600 ? 2 : 1; }
-constexpr int patch_room(int bm) { return bm == 32 ? 2 : 1; }
+constexpr int patch_room(int bn, int bm) { return bn * bm <= 128 * 64 ? 2 : 1; }
 
 // The OpArgs a kernel was launched with, as its only parameter.  What is read through one call is not kept for the next.
 __device__ __forceinline__ const OpArgs &kernel_arguments() {
@@ -1497,17 +1477,18 @@ __global__ void __launch_bounds__(64 * WK) ring_patch_pair_kernel(OpArgsPair p) 
     results_stored();
 }
 
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC, BN == 128>(a, blockIdx.x / XCDS);
+    patch_body<T, BN, BM, WN, WM, WK, DW, PC, BN == 128>(a, blockIdx.x / XCDS);
     results_stored();
 }
 
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
-__global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * WK / 4) patch_walk_kernel(OpArgs) {
+template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC>
+__global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BN, BM) * WN * WM * WK / 4) patch_walk_kernel(OpArgs) {
+    constexpr int AHEAD = BN == 64 && BM == 64 ? 3 : BM == 256 ? 2 : DW;     // filters further ahead are more registers than there are
     for (uint32_t slot = blockIdx.x / XCDS;;) {
         const OpArgs &a = kernel_arguments();
-        patch_body<T, BN, BM, WN, WM, WK, KD, PC, true>(a, slot);
+        patch_body<T, BN, BM, WN, WM, WK, AHEAD, PC, true, patch_room(BN, BM)>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) break;
         __syncthreads();
@@ -1515,9 +1496,9 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BM) * WN * WM * 
     results_stored();
 }
 
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int PC>
+template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK) patch_pair_kernel(OpArgsPair p) {
-    patch_body<T, BN, BM, WN, WM, WK, KD, PC, true>(p.a[blockIdx.y], blockIdx.x / XCDS);
+    patch_body<T, BN, BM, WN, WM, WK, DW, PC, true>(p.a[blockIdx.y], blockIdx.x / XCDS);
     results_stored();
 }
 
@@ -1793,9 +1774,9 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     // The order of the sums is the same.  us, two / four: ResNet-50 alone at batch 16, 32, 64 619 / 607, 903 / 862,
     // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
     const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
-    auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int PC>() {
-        if (const uint32_t g = walkers(patch_room(BM))) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, KD, PC>), dim3(g), block, 0, st, walked);
-        MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, KD, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, KD, PC>), grid, block, st, a, mate);
+    auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int DW, int PC>() {
+        if (const uint32_t g = walkers(patch_room(BN, BM))) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, DW, PC>), dim3(g), block, 0, st, walked);
+        MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, DW, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, DW, PC>), grid, block, st, a, mate);
     };
     auto wide = [&]<int BN, int BM>() {
         count_launch(&LaunchRecorder::deep);
@@ -1837,11 +1818,11 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
                 switch (a.form) {
                     case 0: if (deep) wide.template operator()<128, 128>(); else tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
                     case 1: if (deep) wide.template operator()<128, 64>(); else tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
-                    case 6: patch.template operator()<128, 256, 2, 4, 1, 1, 384>(); break;
-                    case 7: patch.template operator()<128, 128, 2, 2, 2, 1, 256>(); break;
-                    case 8: patch.template operator()<128, 64, 2, 2, 2, 1, 192>(); break;
-                    case 9: patch.template operator()<64, 64, 2, 2, 2, 3, 192>(); break;
-                    case 10: patch.template operator()<64, 32, 2, 1, 4, 1, 128>(); break;
+                    case 6: patch.template operator()<128, 256, 2, 2, 2, 3, 384>(); break;
+                    case 7: patch.template operator()<128, 128, 2, 2, 2, 6, 256>(); break;
+                    case 8: patch.template operator()<128, 64, 4, 1, 2, 9, 192>(); break;
+                    case 9: patch.template operator()<64, 64, 2, 1, 4, 9, 192>(); break;
+                    case 10: patch.template operator()<64, 32, 2, 1, 4, 9, 128>(); break;
                     default: return (int)hipErrorInvalidValue;
                 }
             }

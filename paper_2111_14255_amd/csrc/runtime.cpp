@@ -1766,14 +1766,16 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
                                             src + ((size_t)k * a.gemm_k + (size_t)tap * a.C + cc * chunk) * es + p * 16, 16);
                 src = packed.data();
             } else if (a.panel > 0) {
-                // [K][tap][C] -> [n_pad][chunk of 64 channels][tap][64], zero padded rows
+                // [K][tap][C] -> [32 channels][chunk of 64 channels][tap][16 elements][lane][8]: lane l of a step holds elements 8 * (l / 32) .. + 7 of
+                // output channel l % 32
                 packed.assign((size_t)a.n_pad * a.k_pad * es, 0);
                 const int ncc = a.C / 64;
                 for (int k = 0; k < a.K; ++k)
                     for (int cc = 0; cc < ncc; ++cc)
                         for (int tap = 0; tap < 9; ++tap)
-                            std::memcpy(packed.data() + ((size_t)k * a.k_pad + ((size_t)cc * 9 + tap) * 64) * es,
-                                        src + ((size_t)k * a.gemm_k + (size_t)tap * a.C + cc * 64) * es, (size_t)64 * es);
+                            for (int p = 0; p < 8; ++p)
+                                std::memcpy(packed.data() + ((((((size_t)(k / 32) * ncc + cc) * 9 + tap) * 4 + p / 2) * 64) + (p % 2) * 32 + k % 32) * 16,
+                                            src + ((size_t)k * a.gemm_k + (size_t)tap * a.C + cc * 64 + p * 8) * es, 16);
                 src = packed.data();
             } else if (a.kernel_id == K_ROWB) {
                 // [K][gemm_k] -> [slice][step][channel tile][lane][8]: lane l of a step holds elements 16 * step + 8 * (l / 32)
