@@ -208,6 +208,7 @@ enum TileChoice {
 };
 bool plan_tile(OpArgs &a, TileChoice choice);
 bool tile_is_narrow(const OpArgs &a);
+bool tile_packs_filters(const OpArgs &a);   // the filter bank is [groups][32 channels][16 elements][lane][8]
 void describe_tile(const OpArgs &a, mt_op_form *out);    // all but the workspace
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);
 bool plan_tile_pooled(OpArgs &a);

@@ -593,6 +593,14 @@ __device__ __forceinline__ void hold_walk(OpArgs &a) {
     else hold(a.gemm_k);
 }
 
+// Tiles of the 16-bit types whose filters are packed in operand order and go straight to registers, a kilobyte a load and as many stages ahead as
+// pixels; waves share a tile such that no filter is loaded twice.  With both operands in LDS these tiles spend three to four times as many cycles on LDS
+// as on matrix instructions and leave room for one or two workgroups a unit.  us, both in LDS / this, f16: 128x64 1x1 256 -> 1024 on 64 x 14 x 14
+// 14.7 / 12.4, 2048 -> 512 on 64 x 7 x 7 17.2 / 15.8; 64x64 1x1 1024 -> 256 on 16 x 14 x 14 alone 5.9 / 6.5, but eight ResNet-50 at batch 16, us a pass: 2326
+// with both in LDS, 2279 with the 128x64 tile like this, 2198 with both.  The others lose: 64x32 (Inception-v3 and AlexNet at batch 5 639 / 670), 64x64 of
+// short reductions (64 -> 256 on 56 x 56 3.1 / 3.6), 128x128 (ResNet-50 at batch 64 1287 / 1346, eight at batch 16 2198 / 2272).
+constexpr bool filters_packed(int bn, int bm, int kd) { return (bn == 128 && bm == 64) || (bn == 64 && bm == 64 && kd == 2); }
+
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.
 // slot: position in the XCD's range of tiles.
 __device__ __forceinline__ bool find_tile(const OpArgs &a, uint32_t slot, int &tile, int &z, int &tn_idx, int &tm_idx) {
@@ -610,7 +618,7 @@ __device__ __forceinline__ bool find_tile(const OpArgs &a, uint32_t slot, int &t
 
 // BN output channels x BM pixels per workgroup; WN x WM waves over the tile, WK such groups that share the reduction;
 // KD 64-deep slices of the reduction per stage, NBUF stages in LDS.
-template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE, bool HELD>
+template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE, bool HELD, int ROOM = 0>
 __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
     OpArgs a = args;
     if constexpr (HELD) hold_walk<MODE != TG_POINT>(a);
@@ -627,18 +635,24 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
     static_assert(STEPS % WK == 0, "the wave groups share a stage evenly");
     constexpr int MY_STEPS = STEPS / WK;
     constexpr int ACC = MF == 32 ? 16 : 4;
-    constexpr int WQ = KD * BN / 8 / NW, XQ = KD * BM / 8 / NW;   // loads of a wave per stage: 8 rows of 128 bytes each
-    static_assert(WQ * NW * 8 == KD * BN && XQ * NW * 8 == KD * BM, "the waves share the loads of a stage evenly");
-    constexpr int L = WQ + XQ;
-    constexpr int W_BYTES = KD * BN * 128, X_BYTES = KD * BM * 128, STAGE = W_BYTES + X_BYTES;
+    constexpr bool PACKED = ES == 2 && filters_packed(BN, BM, KD);     // filters go straight to registers
+    constexpr int W = MY_STEPS * TN, SETS = NBUF - 1;      // such loads of a wave per stage, stages of them in registers
+    constexpr int WQ = PACKED ? 0 : KD * BN / 8 / NW, XQ = KD * BM / 8 / NW;   // loads of a wave to LDS per stage: 8 rows of 128 bytes each
+    static_assert((PACKED || WQ * NW * 8 == KD * BN) && XQ * NW * 8 == KD * BM, "the waves share the loads of a stage evenly");
+    static_assert(!PACKED || WM == 1, "no filter is loaded twice");
+    constexpr int L = PACKED ? W + XQ : WQ + XQ;
+    constexpr int W_BYTES = PACKED ? 0 : KD * BN * 128, X_BYTES = KD * BM * 128, STAGE = W_BYTES + X_BYTES;
     constexpr bool WIDE = ES == 2 && MF == 32 && WK == 1;  // every wave finishes its own part of the tile
     constexpr int RED_BYTES = (WK > 1 ? WK : 0) * BN * BM * 4, EP_BYTES = WIDE ? NW * WaveTile<T, TN, TM>::BYTES : BM * (BN + 4) * 4;
-    constexpr int BIAS = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
+    constexpr int COUNTED = ROOM > 0 ? 160 * 1024 / (ROOM + 1) + 1 : 0;      // a compute unit holds no more workgroups than are counted on
+    constexpr int BIAS = std::max({NBUF * STAGE, RED_BYTES, EP_BYTES, COUNTED + 15 & ~15}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
     typedef typename Mma<T, MF>::Acc Acc;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
     __shared__ int s_last;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x;
+    if (ROOM > 0) asm volatile("" : "+v"(tid));            // what a lane's place decides is worked out for every tile: kept, it is more registers than there are
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave / (WN * WM), wn = (wave % (WN * WM)) % WN, wm = (wave % (WN * WM)) / WN;
     const int frow = lane % MF, fgrp = lane / MF;          // operand row and reduction group of this lane
@@ -684,12 +698,25 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
     const int lrow = lane >> 3, piece = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
 
     const uint32_t wv = (uint32_t)((n0 + lrow) * a.k_pad + piece * EPP) * ES;
-    uint32_t ws[WQ];                                       // scalar part of each filter load
+    uint32_t ws[std::max(WQ, 1)];                          // scalar part of each filter load
 #pragma unroll
     for (int i = 0; i < WQ; ++i) {
         const int q = i * NW + wave, kd = q / (BN / 8), rg = q % (BN / 8);
         ws[i] = (uint32_t)(rg * 8 * a.k_pad + (st0 * KD + kd) * RK) * ES;
     }
+    // Packed filters: [32 channels][row of 64 elements][16 elements][lane][16 bytes]
+    const __amdgpu_buffer_rsrc_t packed = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)a.walk.w_bytes, 0x00027000);
+    uint32_t wtile[TN];                                    // this wave's part of the stage requested next, per 32 channels
+#pragma unroll
+    for (int i = 0; i < TN; ++i) wtile[i] = (uint32_t)(((n0 / 32 + wn * TN + i) * (a.k_pad / TK) + st0 * KD) * 4 + wk * MY_STEPS) * 1024u;
+    u32x4 w[PACKED ? SETS : 1][MY_STEPS][TN];
+    auto load_filters = [&](int set, int step, uint32_t voff) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+            w[set][step][i] = __builtin_amdgcn_raw_buffer_load_b128(packed, voff + (uint32_t)(step % 4) * 1024u, wtile[i] + (uint32_t)(step / 4) * 4096u, 0);
+            if (step == MY_STEPS - 1) wtile[i] += KD * 4096;
+        }
+    };
     constexpr int NP = KD == 1 ? 1 : XQ;                   // positions along j tracked (loads of one 64-slice share one)
     constexpr bool PIECEWISE = MODE == TG_CHUNK || MODE == TG_FAR;   // every 16-byte piece has a tap of its own
     uint32_t xoff[XQ], xmask[XQ];
@@ -722,7 +749,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
     const int adv_t = (int)a.walk.adv_t, adv_c = (int)a.walk.adv_c;
     const uint32_t inv_s = a.walk.inv_s;
 
-    auto issue = [&](int buf) {
+    auto issue = [&](int buf, bool some = true) {           // some: false for a stage beyond the reduction
         const uint32_t base = lds0 + (uint32_t)(buf * STAGE);
 #pragma unroll
         for (int i = 0; i < WQ; ++i) {
@@ -757,13 +784,13 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
                 // Slices of the last stage that lie beyond the reduction (C is not a multiple of KD rows) hold the next pixel's channels:
                 // the filters are zero there, but zero times infinity or NaN is NaN
                 const uint32_t slice = (uint32_t)((i * NW + wave) / (BM / 8) * 128);
-                load_to_lds(rsrc_x, KD == 1 || xs + slice < x_end ? xoff[i] : OUT_OF_RANGE, xs, dst);
+                load_to_lds(rsrc_x, some && (KD == 1 || xs + slice < x_end) ? xoff[i] : OUT_OF_RANGE, xs, dst);
             } else {
                 const int pi = KD == 1 ? 0 : i;
                 bool inside;
                 if constexpr (MODE == TG_FAR) inside = ((uint32_t)first_row[i] + trow[pi] < (uint32_t)a.H) & ((uint32_t)first_col[i] + tcol[pi] < (uint32_t)a.W);
                 else inside = (xmask[i] >> trow[pi]) & (xmask[i] >> tcol[pi]) & 1u;
-                load_to_lds(rsrc_x, inside ? xoff[i] + toff[pi] : OUT_OF_RANGE, 0u, dst);
+                load_to_lds(rsrc_x, some && inside ? xoff[i] + toff[pi] : OUT_OF_RANGE, 0u, dst);
             }
         }
         xs += KD * 128;
@@ -777,20 +804,21 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
 #pragma unroll
             for (int v = 0; v < ACC; ++v) acc[i][j][v] = 0.f;
 
-    struct Frag { u32x4 w[TN], x[TM]; };
+    struct Frag { u32x4 w[PACKED ? 1 : TN], x[TM]; };
     const uint32_t wrow = (uint32_t)((wn * SUBN + frow) * 128), xrow = (uint32_t)(W_BYTES + (wm * SUBM + frow) * 128);
     const uint32_t swz = (uint32_t)((frow >> 1) & 7);
     auto load_frag = [&](uint32_t buf, int s, Frag &f) {   // s: step of the stage
         const int kd = s / (8 / PPS), c0 = (s % (8 / PPS)) * PPS;
         const uint32_t col = ((uint32_t)(c0 + fgrp) ^ swz) * 16u;
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
-            f.w[i] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BN * 128 + i * MF * 128) + wrow + col]);
+        for (int i = 0; !PACKED && i < TN; ++i)
+            f.w[PACKED ? 0 : i] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BN * 128 + i * MF * 128) + wrow + col]);
 #pragma unroll
         for (int j = 0; j < TM; ++j)
             f.x[j] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BM * 128 + j * MF * 128) + xrow + col]);
     };
-    auto compute = [&](int buf) {
+    // One stage; SET: where its packed filters are.  Those of the stage NBUF - 1 ahead, at voff, take their place step by step.
+    auto compute = [&]<int SET>(int buf, uint32_t voff) {
         const uint32_t b = (uint32_t)(buf * STAGE);
         Frag f[2];
         const int s0 = wk * MY_STEPS;
@@ -802,20 +830,51 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
 #pragma unroll
             for (int i = 0; i < TN; ++i)
 #pragma unroll
-                for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(f[s & 1].w[i], f[s & 1].x[j], acc[i][j]);
+                for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(PACKED ? w[SET][s][i] : f[s & 1].w[PACKED ? 0 : i], f[s & 1].x[j], acc[i][j]);
+            if constexpr (PACKED) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_filters(SET, s, voff);
+            }
         }
     };
 
-    for (int s = 0; s < NBUF - 1; ++s)
-        if (s < ns) issue(s);
     int rbuf = 0, ibuf = NBUF - 1;
-    for (int t = 0; t < ns; ++t) {
-        // stages issued after stage t: NBUF - 2 of them, fewer at the end
-        wait_for_stage<L, NBUF - 2>(min(ns - 1 - t, NBUF - 2));
-        if (t + NBUF - 1 < ns) issue(ibuf);
-        compute(rbuf);
-        rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
-        ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
+    if constexpr (PACKED) {
+        // Stages beyond the reduction are requested out of range: with a branch around a request the compiler would not know how many are under way and
+        // wait for all of them (ResNet-50 at batch 64 1294 / 1288 us, Inception-v3 and AlexNet at batch 5 639 / 635).
+        auto filters_at = [&](int t) { return t < ns ? (uint32_t)lane * 16u : OUT_OF_RANGE; };
+        [&]<int... S>(std::integer_sequence<int, S...>) {
+            auto request = [&]<int SET>() {
+                issue(SET, SET < ns);
+#pragma unroll
+                for (int s = 0; s < MY_STEPS; ++s) {
+                    load_filters(SET, s, filters_at(SET));
+                    __builtin_amdgcn_sched_barrier(0);     // in the order in which they are waited for
+                }
+            };
+            (request.template operator()<S>(), ...);
+            int t = 0;
+            auto stage = [&]<int SET>() {                  // false: that was the last one
+                wait_and_meet<(NBUF - 2) * L + W>();       // requested after this stage's pixels: its filters, and NBUF - 2 stages
+                issue(ibuf, t + NBUF - 1 < ns);
+                compute.template operator()<SET>(rbuf, filters_at(t + NBUF - 1));
+                rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
+                ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
+                return ++t < ns;
+            };
+            while ((stage.template operator()<S>() && ...)) {}
+        }(std::make_integer_sequence<int, SETS>{});
+    } else {
+        for (int s = 0; s < NBUF - 1; ++s)
+            if (s < ns) issue(s);
+        for (int t = 0; t < ns; ++t) {
+            // stages issued after stage t: NBUF - 2 of them, fewer at the end
+            wait_for_stage<L, NBUF - 2>(min(ns - 1 - t, NBUF - 2));
+            if (t + NBUF - 1 < ns) issue(ibuf);
+            compute.template operator()<0>(rbuf, 0u);
+            rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
+            ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
+        }
     }
     if constexpr (DIRECT) {
         if (unsplit) {
@@ -1414,9 +1473,9 @@ __global__ void __launch_bounds__(64 * WN * WM * WK, tile_waves_per_simd(BN, BM,
     results_stored();
 }
 
-// Workgroups of a walking kernel that a compute unit holds, by LDS (three of up to 53 KB, two of up to 80 KB); the kernels' launch bounds have
-// the compiler leave registers for as many.
-constexpr int tile_room(int bn, int bm, int kd, int nbuf) { return nbuf * kd * (bn + bm) <= 416 ? 3 : nbuf * kd * (bn + bm) <= 600 ? 2 : 1; }
+// Workgroups of a walking kernel that a compute unit holds: by LDS (made to hold no more) and by registers, which the launch bounds have the
+// compiler leave for as many.
+constexpr int tile_room(int bn, int bm, int kd) { return kd == 1 && bn * bm <= 128 * 64 ? 3 : kd == 2 && bm == 64 ? 1 : 2; }
 constexpr int patch_room(int bn, int bm) { return bn * bm <= 128 * 64 ? 2 : 1; }
 
 // The OpArgs a kernel was launched with, as its only parameter.  What is read through one call is not kept for the next.
@@ -1436,10 +1495,10 @@ __device__ __forceinline__ const OpArgs &kernel_arguments() {
 // into lanes of vector registers (f16 64x32 tile: 129 registers, one more than two workgroups leave each; 126 to 128 so).  Eight ResNet-50 at
 // batch 16 in eight stages 4597 / 4500 us, runs of one side 4 % apart.
 template <typename T, int BN, int BM, int WN, int WM, int WK, int KD, int NBUF, int MODE>
-__global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD, NBUF) * WN * WM * WK / 4) tile_walk_kernel(OpArgs) {
+__global__ void __launch_bounds__(64 * WN * WM * WK, tile_room(BN, BM, KD) * WN * WM * WK / 4) tile_walk_kernel(OpArgs) {
     for (uint32_t slot = blockIdx.x / XCDS;;) {
         const OpArgs &a = kernel_arguments();
-        tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE, true>(a, slot);
+        tile_body<T, BN, BM, WN, WM, WK, KD, NBUF, MODE, true, tile_room(BN, BM, KD)>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) break;
         __syncthreads();                                   // every wave is done with the tile's LDS
@@ -1694,6 +1753,10 @@ bool plan_tile(OpArgs &a, TileChoice choice) {
     return true;
 }
 
+bool tile_packs_filters(const OpArgs &a) {
+    return a.form >= 0 && a.dtype != MT_F32 && a.panel == 0 && FORMS[a.form].ring == 0 && filters_packed(FORMS[a.form].bn, FORMS[a.form].bm, FORMS[a.form].kd);
+}
+
 // One ascending pass over the reduction on 64 x 16 tiles.
 bool tile_is_narrow(const OpArgs &a) { return a.form == FORM_64x16 && a.split_k == 1; }
 
@@ -1749,7 +1812,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     auto tile = [&]<int BN, int BM, int WN, int WM, int WK, int KD, int NBUF>() {
         auto go = [&]<int MODE>() {
             if constexpr (sizeof(T) == 2 && (MODE == TG_POINT || MODE == TG_TAP) && BM > 16) {
-                if (const uint32_t g = walkers(tile_room(BN, BM, KD, NBUF)))
+                if (const uint32_t g = walkers(tile_room(BN, BM, KD)))
                     return launch((tile_walk_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), dim3(g), block, 0, st, walked);
             }
             if constexpr (std::is_same_v<T, float>) launch((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, MODE>), grid, block, 0, st, a);
@@ -1778,9 +1841,9 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         if (const uint32_t g = walkers(patch_room(BN, BM))) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, DW, PC>), dim3(g), block, 0, st, walked);
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, DW, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, DW, PC>), grid, block, st, a, mate);
     };
-    auto wide = [&]<int BN, int BM>() {
+    auto wide = [&]<int BN, int BM, int WN, int WM, int NBUF>() {
         count_launch(&LaunchRecorder::deep);
-        by_gather([&]<int MODE>() { launch((tile_kernel<T, BN, BM, 2, 2, 1, 1, 4, MODE>), grid, block, 0, st, a); });
+        by_gather([&]<int MODE>() { launch((tile_kernel<T, BN, BM, WN, WM, 1, 1, NBUF, MODE>), grid, block, 0, st, a); });
     };
     constexpr bool f32 = std::is_same_v<T, float>;
     if (far_window(a)) {
@@ -1791,9 +1854,9 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
                 MT_LAUNCH((tile_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, TG_FAR>), (tile_pair_kernel<T, BN, BM, WN, WM, WK, KD, NBUF, TG_FAR>), grid, block, st, a, mate);
             };
             switch (a.form) {
-                case 1: far.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+                case 1: far.template operator()<128, 64, 4, 1, 1, 1, 3>(); break;
                 case 2: far.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
-                case 3: far.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;
+                case 3: far.template operator()<64, 64, 2, 1, 4, 2, 4>(); break;
                 case 4: far.template operator()<64, 32, 2, 1, 4, 2, 3>(); break;
                 case 5: far.template operator()<64, 16, 4, 1, 1, 2, 3>(); break;
                 default: return (int)hipErrorInvalidValue;
@@ -1804,7 +1867,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     }
     switch (a.form) {
         case 2: tile.template operator()<64, 64, 2, 2, 1, 1, 3>(); break;
-        case 3: tile.template operator()<64, 64, 2, 2, 2, 2, 3>(); break;
+        case 3: if constexpr (f32) tile.template operator()<64, 64, 2, 2, 2, 2, 3>(); else tile.template operator()<64, 64, 2, 1, 4, 2, 4>(); break;
         case 4: tile.template operator()<64, 32, 2, 1, 4, 2, 3>(); break;
         case 5: tile.template operator()<64, 16, 4, 1, 1, 2, 3>(); break;
         case 12: ring.template operator()<16, 8, 2>(); break;
@@ -1816,8 +1879,8 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
                 tile.template operator()<32, 32, 2, 2, 2, 2, 4>();
             } else {
                 switch (a.form) {
-                    case 0: if (deep) wide.template operator()<128, 128>(); else tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
-                    case 1: if (deep) wide.template operator()<128, 64>(); else tile.template operator()<128, 64, 2, 2, 1, 1, 2>(); break;
+                    case 0: if (deep) wide.template operator()<128, 128, 2, 2, 4>(); else tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
+                    case 1: if (deep) wide.template operator()<128, 64, 4, 1, 5>(); else tile.template operator()<128, 64, 4, 1, 1, 1, 3>(); break;
                     case 6: patch.template operator()<128, 256, 2, 2, 2, 3, 384>(); break;
                     case 7: patch.template operator()<128, 128, 2, 2, 2, 6, 256>(); break;
                     case 8: patch.template operator()<128, 64, 4, 1, 2, 9, 192>(); break;

@@ -1777,6 +1777,16 @@ int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t a
                                 std::memcpy(packed.data() + ((((((size_t)(k / 32) * ncc + cc) * 9 + tap) * 4 + p / 2) * 64) + (p % 2) * 32 + k % 32) * 16,
                                             src + ((size_t)k * a.gemm_k + (size_t)tap * a.C + cc * 64 + p * 8) * es, 16);
                 src = packed.data();
+            } else if (tile_packs_filters(a)) {
+                // [groups][K][gemm_k] -> [groups][32 channels][64 elements][16 elements][lane][8]: lane l of a step holds elements 8 * (l / 32) .. + 7 of output
+                // channel l % 32; zeros where the bank is padded
+                packed.assign((size_t)a.groups * a.n_pad * a.k_pad * es, 0);
+                for (int g = 0; g < a.groups; ++g)
+                    for (int k = 0; k < a.K; ++k)
+                        for (int j = 0; j < a.gemm_k; j += 8)
+                            std::memcpy(packed.data() + ((size_t)g * a.n_pad * a.k_pad + ((((size_t)(k / 32) * (a.k_pad / 16) + j / 16) * 64 + j / 8 % 2 * 32 + k % 32) * 8)) * es,
+                                        src + (((size_t)g * a.K + k) * a.gemm_k + j) * es, 16);
+                src = packed.data();
             } else if (a.kernel_id == K_ROWB) {
                 // [K][gemm_k] -> [slice][step][channel tile][lane][8]: lane l of a step holds elements 16 * step + 8 * (l / 32)
                 // .. + 7 of output channel 32 * (slice * tiles + tile) + l % 32
