@@ -14,6 +14,7 @@ HOST_SOURCES = ["sched_core.cpp", "lanes.cpp", "runtime.cpp"]
 COMMON = ["-O3", "-fPIC", "-std=c++20", "-Wall", "-Wno-unused-function"]
 # packed-fp32 code generation is switched off for all device code
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+HOST_FLAGS = ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"]
 
 
 def _hipcc():
@@ -50,7 +51,7 @@ def build(verbose=False, lib=None, sanitize=False):
         LIB = lib
     obj_dir = OBJ + ("_asan" if sanitize else "")
     os.makedirs(obj_dir, exist_ok=True)
-    host_extra = ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"] + (SANITIZE_HOST if sanitize else [])
+    host_extra = HOST_FLAGS + (SANITIZE_HOST if sanitize else [])
     jobs = [(s, DEVICE_FLAGS, obj_dir) for s in DEVICE_SOURCES] + [(s, host_extra, obj_dir) for s in HOST_SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda j: _compile(*j), jobs))

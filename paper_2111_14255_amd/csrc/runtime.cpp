@@ -1171,6 +1171,35 @@ void reserve_static(mt_ctx *ctx, mt_schedule *s) {
     if (signals > 0) (void)schedule_signal(ctx, s, signals - 1);
 }
 
+namespace {
+// Filters [groups][K][taps][row of channels] in operand order: [groups][ROWS output channels][RUN bytes of a tap][tap][16 bytes of the run][output channel], zeros
+// where the bank is padded.  Block after block of ROWS * RUN bytes, which stay in the first-level cache while the pieces of a run spread over them: output channel
+// by output channel the pieces of a line of the bank were written far apart, and the whole bank was cleared first (us a bank of 512 -> 512 3x3 filters, f16:
+// 1061, 446 this way).
+template <int ROWS, int RUN>
+void pack_operands(std::vector<uint8_t> &packed, const uint8_t *src, const OpArgs &a, int taps, int es) {
+    const size_t group = (size_t)a.n_pad * a.k_pad * es, filter = (size_t)a.gemm_k * es, tap_bytes = filter / taps;
+    const size_t runs = (size_t)a.k_pad * es / taps / RUN;
+    packed.resize(group * a.groups);
+    if (a.n_pad != a.K || a.k_pad != a.gemm_k) std::memset(packed.data(), 0, packed.size());
+    for (int g = 0; g < a.groups; ++g)
+        for (int k0 = 0; k0 < a.K; k0 += ROWS)
+            for (size_t run = 0; run * RUN < tap_bytes; ++run)      // what lies beyond is padding
+                for (int tap = 0; tap < taps; ++tap) {
+                    uint8_t *block = packed.data() + g * group + ((k0 / ROWS * runs + run) * taps + tap) * ROWS * RUN;
+                    const size_t at = run * RUN, held = std::min<size_t>(RUN, tap_bytes - at);      // the last run of a padded bank may be shorter
+                    const uint8_t *from = src + ((size_t)g * a.K + k0) * filter + tap * tap_bytes + at;
+                    for (int k = 0; k < std::min(ROWS, a.K - k0); ++k, from += filter) {
+                        if (held == RUN) {
+                            for (int p = 0; p < RUN / 16; ++p) std::memcpy(block + (p * ROWS + k) * 16, from + p * 16, 16);
+                        } else {
+                            for (size_t p = 0; p < held / 16; ++p) std::memcpy(block + (p * ROWS + k) * 16, from + p * 16, 16);
+                        }
+                    }
+                }
+}
+}  // namespace
+
 // ============================================================================================
 extern "C" {
 
@@ -1696,33 +1725,6 @@ int32_t mt_round_to_storage(const float *src, int64_t n, int32_t dtype, void *ds
 }
 
 // ---- registration ----------------------------------------------------------------------------
-// Filters [groups][K][taps][row of channels] in operand order: [groups][ROWS output channels][RUN bytes of a tap][tap][16 bytes of the run][output channel], zeros
-// where the bank is padded.  Block after block of ROWS * RUN bytes, which stay in the first-level cache while the pieces of a run spread over them: output channel
-// by output channel the pieces of a line of the bank were written far apart, and the whole bank was cleared first (us a bank of 512 -> 512 3x3 filters, f16:
-// 1061, 446 this way).
-template <int ROWS, int RUN>
-void pack_operands(std::vector<uint8_t> &packed, const uint8_t *src, const OpArgs &a, int taps, int es) {
-    const size_t group = (size_t)a.n_pad * a.k_pad * es, filter = (size_t)a.gemm_k * es, tap_bytes = filter / taps;
-    const size_t runs = (size_t)a.k_pad * es / taps / RUN;
-    packed.resize(group * a.groups);
-    if (a.n_pad != a.K || a.k_pad != a.gemm_k) std::memset(packed.data(), 0, packed.size());
-    for (int g = 0; g < a.groups; ++g)
-        for (int k0 = 0; k0 < a.K; k0 += ROWS)
-            for (size_t run = 0; run * RUN < tap_bytes; ++run)      // what lies beyond is padding
-                for (int tap = 0; tap < taps; ++tap) {
-                    uint8_t *block = packed.data() + g * group + ((k0 / ROWS * runs + run) * taps + tap) * ROWS * RUN;
-                    const size_t at = run * RUN, held = std::min<size_t>(RUN, tap_bytes - at);      // the last run of a padded bank may be shorter
-                    const uint8_t *from = src + ((size_t)g * a.K + k0) * filter + tap * tap_bytes + at;
-                    for (int k = 0; k < std::min(ROWS, a.K - k0); ++k, from += filter) {
-                        if (held == RUN) {
-                            for (int p = 0; p < RUN / 16; ++p) std::memcpy(block + (p * ROWS + k) * 16, from + p * 16, 16);
-                        } else {
-                            for (size_t p = 0; p < held / 16; ++p) std::memcpy(block + (p * ROWS + k) * 16, from + p * 16, 16);
-                        }
-                    }
-                }
-}
-
 int32_t mt_register(mt_ctx *ctx, const mt_model *m, void *device_arena, size_t arena_bytes, int32_t *out_tenant) {
     if (!ctx || !m || !out_tenant) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     if (!m->finalized) return fail(MT_ERR_NOT_FINALIZED, "model is not finalised");
