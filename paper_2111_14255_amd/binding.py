@@ -139,13 +139,20 @@ _lib = None
 
 
 def load():
-    """Loads the built library (building it first only if it has never been built)."""
+    """Loads the built library (building it first only if there is none).  A library of other sources than those beside it is refused."""
     global _lib
     if _lib is None:
         path = os.environ.get("MTSCHED_LIB") or _build.lib_path()   # override: load another build of the library
         if not os.path.exists(path):
             _build.build()
         lib = C.CDLL(path)
+        if not os.environ.get("MTSCHED_LIB") and os.path.isdir(_build.CSRC) and os.path.isdir(_build.INCLUDE):
+            try:
+                built_from = C.string_at(C.addressof(C.c_char.in_dll(lib, "mt_source_digest"))).decode()
+            except ValueError:                                       # a library that does not say
+                built_from = ""
+            if built_from != _build.source_digest():
+                raise RuntimeError("%s was built from other sources than those in %s: build it again" % (path, _build.CSRC))
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype = res

@@ -1,4 +1,5 @@
 """Builds libmtsched.so (gfx950 only) in-tree with hipcc.  No fallback: a missing compiler is an error."""
+import hashlib
 import os
 import subprocess
 import sys
@@ -6,6 +7,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
+INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtsched.so")
 
@@ -37,6 +39,18 @@ def _compile(src, extra, obj_dir=None):
     return out
 
 
+def source_digest():
+    """What a library is built from: names and contents of the sources and headers, and the flags.  The library carries the digest (mt_source_digest),
+    so that one of other sources is not mistaken for theirs."""
+    h = hashlib.sha256(repr((COMMON, DEVICE_FLAGS, HOST_FLAGS)).encode())
+    for folder in (CSRC, INCLUDE):
+        for name in sorted(os.listdir(folder)):
+            if name.endswith((".h", ".hip", ".cpp")):
+                data = open(os.path.join(folder, name), "rb").read()
+                h.update(b"%s %d " % (name.encode(), len(data)) + data)
+    return h.hexdigest()
+
+
 # host-side sanitizers (address + undefined behaviour) for the two host sources; device code is never instrumented
 SANITIZE_HOST = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
 
@@ -51,14 +65,20 @@ def build(verbose=False, lib=None, sanitize=False):
         LIB = lib
     obj_dir = OBJ + ("_asan" if sanitize else "")
     os.makedirs(obj_dir, exist_ok=True)
+    if os.path.exists(out):
+        os.remove(out)                                       # a build that fails leaves no library of older sources behind
+    digest = os.path.join(obj_dir, "source_digest.cpp")
+    with open(digest, "w") as f:
+        f.write('extern "C" const char mt_source_digest[];\nconst char mt_source_digest[] = "%s";\n' % source_digest())
     host_extra = HOST_FLAGS + (SANITIZE_HOST if sanitize else [])
-    jobs = [(s, DEVICE_FLAGS, obj_dir) for s in DEVICE_SOURCES] + [(s, host_extra, obj_dir) for s in HOST_SOURCES]
+    jobs = [(s, DEVICE_FLAGS, obj_dir) for s in DEVICE_SOURCES] + [(s, host_extra, obj_dir) for s in HOST_SOURCES] + [(digest, [], obj_dir)]
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda j: _compile(*j), jobs))
-    cmd = [_hipcc(), "-shared", "-fPIC", "-o", out] + objs + ["--offload-arch=gfx950", "-lhsa-runtime64"]
+    cmd = [_hipcc(), "-shared", "-fPIC", "-o", out + ".new"] + objs + ["--offload-arch=gfx950", "-lhsa-runtime64"]
     if sanitize:
         cmd += ["-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize", "-shared-libsan"]
     subprocess.check_call(cmd)
+    os.replace(out + ".new", out)
     if sanitize:
         return out
     if verbose:

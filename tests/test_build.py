@@ -1,9 +1,12 @@
 """The library is built from the sources that are there."""
 import os
+import shutil
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
 
-from paper_2111_14255_amd import build
+import pytest
+
+from paper_2111_14255_amd import binding, build
 
 
 def test_host_sources_compile():
@@ -13,3 +16,29 @@ def test_host_sources_compile():
     with ThreadPoolExecutor(max_workers=len(build.HOST_SOURCES)) as ex:
         for src, r in zip(build.HOST_SOURCES, ex.map(check, build.HOST_SOURCES)):
             assert r.returncode == 0, "%s\n%s" % (src, r.stderr)
+
+
+def test_a_build_that_fails_leaves_no_library(tmp_path, monkeypatch):
+    lib = tmp_path / "lib.so"
+    lib.write_bytes(b"an older one")
+    (tmp_path / "broken.cpp").write_text("int f( {")
+    for name, value in (("CSRC", str(tmp_path)), ("OBJ", str(tmp_path / "obj")), ("LIB", str(lib)), ("DEVICE_SOURCES", []), ("HOST_SOURCES", ["broken.cpp"])):
+        monkeypatch.setattr(build, name, value)
+    with pytest.raises(RuntimeError, match="compile failed"):
+        build.build()
+    assert not lib.exists()
+
+
+def test_a_library_of_other_sources_is_refused(tmp_path, monkeypatch):
+    monkeypatch.delenv("MTSCHED_LIB", raising=False)
+    binding.load()
+    other = tmp_path / "csrc"
+    shutil.copytree(build.CSRC, other)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(build, "CSRC", str(other))
+    binding.load()                                           # the same contents
+    with open(other / "lanes.h", "a") as f:
+        f.write(" ")
+    monkeypatch.setattr(binding, "_lib", None)
+    with pytest.raises(RuntimeError, match="other sources"):
+        binding.load()
