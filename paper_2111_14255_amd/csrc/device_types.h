@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "record.h"
 
 namespace mt {
@@ -38,7 +40,15 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 // with the divisors of TileWalk, a workgroup requests its first operands after 180 instructions instead of 600 (1.25 us, of which 0.35 the
 // arguments).
 template <typename V>
-__device__ __forceinline__ void hold_one(V &v) { asm volatile("" : "+s"(v)); }
+__device__ __forceinline__ void hold_one(V &v) {
+    if constexpr (std::is_pointer_v<V>) {
+        // As what it is, a pointer to global memory: loads through one of which the compiler does not know that are generic, which may
+        // be to LDS as well, and it waits for all of them where it waits for one.
+        auto g = (__attribute__((address_space(1))) std::remove_pointer_t<V> *)v;
+        asm volatile("" : "+s"(g));
+        v = (V)g;
+    } else asm volatile("" : "+s"(v));
+}
 template <typename... V>
 __device__ __forceinline__ void hold(V &...v) {
     __builtin_amdgcn_sched_barrier(0);                     // all of them are asked for before the first is waited for

@@ -525,6 +525,15 @@ def test_loads_to_lds_keep_their_distance_from_vector_instructions_that_write_sc
     assert n > 1000
 
 
+def test_operands_are_loaded_as_global_memory():
+    """A generic load may be to LDS: it counts among those as well, and waits that go by counts wait for all that is under way."""
+    n = 0
+    for name, code in code_objects.listings():
+        n += 1
+        assert not [hex(a) for a, m, _ in code if m.startswith("flat_")], name
+    assert n > 250
+
+
 def test_kernels_end_with_their_results_in_memory():
     """Packets between dependent launches release nothing, so every store of an operator's kernel goes through to memory (sc1) and no wave
     ends before its stores have arrived there.  Shown on small listings, then in every kernel of the library but the probes."""
