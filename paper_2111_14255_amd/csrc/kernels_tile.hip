@@ -593,12 +593,17 @@ __device__ __forceinline__ void hold_walk(OpArgs &a) {
     else hold(a.gemm_k);
 }
 
-// Tiles of the 16-bit types whose filters are packed in operand order and go straight to registers, a kilobyte a load and as many stages ahead as
-// pixels; waves share a tile such that no filter is loaded twice.  With both operands in LDS these tiles spend three to four times as many cycles on LDS
-// as on matrix instructions and leave room for one or two workgroups a unit.  us, both in LDS / this, f16: 128x64 1x1 256 -> 1024 on 64 x 14 x 14
-// 14.7 / 12.4, 2048 -> 512 on 64 x 7 x 7 17.2 / 15.8; 64x64 1x1 1024 -> 256 on 16 x 14 x 14 alone 5.9 / 6.5, but eight ResNet-50 at batch 16, us a pass: 2326
-// with both in LDS, 2279 with the 128x64 tile like this, 2198 with both.  The others lose: 64x32 (Inception-v3 and AlexNet at batch 5 639 / 670), 64x64 of
-// short reductions (64 -> 256 on 56 x 56 3.1 / 3.6), 128x128 (ResNet-50 at batch 64 1287 / 1346, eight at batch 16 2198 / 2272).
+// Tiles of the 16-bit types whose filters are packed in operand order and go straight to registers, a kilobyte a load and requested as many stages ahead
+// as pixels; waves share a tile such that no filter is loaded twice.  With both operands in LDS these tiles spend three to four times as many cycles on LDS
+// as on matrix instructions and leave room for one or two workgroups a unit.  A wait for filters leaves the (NBUF - 1) * W youngest requests under way, and as the
+// compiler does not count requests for pixels these are the pixels and filters of fewer stages: one to two of the two to four.  us a layer, both in LDS / this, f16:
+//   128x64   1x1 512 -> 512 on 16 x 14 x 14  6.31 / 5.88     1x1 768 -> 768 on 5 x 17 x 17  7.52 / 6.74     3x3, stride 2, 192 -> 384 on 8 x 27 x 27  20.1 / 16.8
+//   64x64    1x1 1024 -> 256 on 16 x 14 x 14  8.04 / 7.84 (a pass of one layer)     2048 -> 512 on 32 x 7 x 7  11.2 / 10.3
+//            1x1 256 -> 256 on 16 x 14 x 14   3.85 / 4.25, 512 -> 256 6.24 / 6.66 alone: four groups of waves have twice the sums to exchange.  But beside others these
+//            gain as well: four ResNet-50 at batch 4, us a pass, 625 with both in LDS up to 640 elements, 588 without.
+// Eight ResNet-50 at batch 16, us a pass: 2467 with both in LDS, 2210 so (patches with packed filters included).  128x128 tiles lose: 1x1 1024 -> 1024 on 16 x 14 x 14
+// 12.4 / 11.0, but ResNet-50 at batch 64 1278 / 1290, eight at batch 16 2234 / 2314.  64x64 of short reductions (one row a stage) and 64x32 are no matter of course: 64 -> 256 on
+// 56 x 56 2.89 / 3.18; 2048 -> 512 on 16 x 7 x 7 9.16 / 8.32 and 512 -> 512 4.18 / 4.39.
 constexpr bool filters_packed(int bn, int bm, int kd) { return (bn == 128 && bm == 64) || (bn == 64 && bm == 64 && kd == 2); }
 
 // This workgroup's tile, as (channel tile, pixel tile), and its part of a split reduction.  False: a workgroup without work.
@@ -817,8 +822,8 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
         for (int j = 0; j < TM; ++j)
             f.x[j] = *reinterpret_cast<const u32x4 *>(&smem[buf + (uint32_t)(kd * BM * 128 + j * MF * 128) + xrow + col]);
     };
-    // One stage; SET: where its packed filters are.  Those of the stage NBUF - 1 ahead, at voff, take their place step by step.
-    auto compute = [&]<int SET>(int buf, uint32_t voff) {
+    // One stage; SET: where its packed filters are.  Those of the stage NBUF - 1 ahead, at voff, take their place step by step if there may be MORE.
+    auto compute = [&]<int SET, bool MORE>(int buf, uint32_t voff) {
         const uint32_t b = (uint32_t)(buf * STAGE);
         Frag f[2];
         const int s0 = wk * MY_STEPS;
@@ -831,7 +836,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
             for (int i = 0; i < TN; ++i)
 #pragma unroll
                 for (int j = 0; j < TM; ++j) acc[i][j] = Mma<T, MF>::run(PACKED ? w[SET][s][i] : f[s & 1].w[PACKED ? 0 : i], f[s & 1].x[j], acc[i][j]);
-            if constexpr (PACKED) {
+            if constexpr (PACKED && MORE) {
                 __builtin_amdgcn_sched_barrier(0);
                 load_filters(SET, s, voff);
             }
@@ -841,7 +846,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
     int rbuf = 0, ibuf = NBUF - 1;
     if constexpr (PACKED) {
         // Stages beyond the reduction are requested out of range: with a branch around a request the compiler would not know how many are under way and
-        // wait for all of them (ResNet-50 at batch 64 1294 / 1288 us, Inception-v3 and AlexNet at batch 5 639 / 635).
+        // wait for all of them.
         auto filters_at = [&](int t) { return t < ns ? (uint32_t)lane * 16u : OUT_OF_RANGE; };
         [&]<int... S>(std::integer_sequence<int, S...>) {
             auto request = [&]<int SET>() {
@@ -853,16 +858,26 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
                 }
             };
             (request.template operator()<S>(), ...);
+            // Whole rounds, then what is left: a loop left from the middle is rewritten such that its ways out run into its way round, where the compiler
+            // then does not know how many filters are under way and waits for all of them once a round: 3x3 96 -> 96 on 8 x 35 x 35 (128x64) 10.9 / 9.6 us,
+            // 2048 -> 512 on 32 x 7 x 7 (64x64) 10.8 / 10.4, eight ResNet-50 at batch 16 2216 / 2204.
             int t = 0;
-            auto stage = [&]<int SET>() {                  // false: that was the last one
+            auto stage = [&]<int SET>() {
                 wait_and_meet<(NBUF - 2) * L + W>();       // requested after this stage's pixels: its filters, and NBUF - 2 stages
                 issue(ibuf, t + NBUF - 1 < ns);
-                compute.template operator()<SET>(rbuf, filters_at(t + NBUF - 1));
+                compute.template operator()<SET, true>(rbuf, filters_at(t + NBUF - 1));
                 rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
                 ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
-                return ++t < ns;
+                ++t;
             };
-            while ((stage.template operator()<S>() && ...)) {}
+            for (int rounds = ns / SETS; rounds > 0; --rounds) (stage.template operator()<S>(), ...);
+            auto rest = [&]<int SET>() {                   // nothing is requested any more
+                if (t + SET >= ns) return;
+                wait_and_meet<(NBUF - 2 - SET) * L + W>();
+                compute.template operator()<SET, false>(rbuf, 0u);
+                rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
+            };
+            [&]<int... R>(std::integer_sequence<int, R...>) { (rest.template operator()<R>(), ...); }(std::make_integer_sequence<int, SETS - 1>{});
         }(std::make_integer_sequence<int, SETS>{});
     } else {
         for (int s = 0; s < NBUF - 1; ++s)
@@ -871,7 +886,7 @@ __device__ __forceinline__ void tile_body(const OpArgs &args, uint32_t slot) {
             // stages issued after stage t: NBUF - 2 of them, fewer at the end
             wait_for_stage<L, NBUF - 2>(min(ns - 1 - t, NBUF - 2));
             if (t + NBUF - 1 < ns) issue(ibuf);
-            compute.template operator()<0>(rbuf, 0u);
+            compute.template operator()<0, false>(rbuf, 0u);
             rbuf = rbuf + 1 == NBUF ? 0 : rbuf + 1;
             ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
         }

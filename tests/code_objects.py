@@ -78,6 +78,19 @@ def predecessors(code):
     return came_from
 
 
+def staging_loop(code):
+    """The shortest run of instructions between a branch backwards and where it goes that copies to LDS and multiplies."""
+    at = {a: i for i, (a, _, _) in enumerate(code)}
+    found = []
+    for i, (a, m, ops) in enumerate(code):
+        if m.startswith(("s_branch", "s_cbranch")):
+            offset = int(re.match(r"\d+", ops[0])[0])
+            j = at[a + 4 + 4 * (offset - 65536 if offset > 32767 else offset)]
+            if j < i and any(w.startswith("v_mfma") for _, w, _ in code[j:i]) and any(o[-1].split()[-1:] == ["lds"] for _, _, o in code[j:i]):
+                found.append(code[j:i + 1])
+    return min(found, key=len)
+
+
 def held_back_stores(code):
     """Stores to memory that stop at the XCD's L2 (no sc1), and stores that a wave may end without waiting for."""
     came_from = predecessors(code)

@@ -534,6 +534,24 @@ def test_operands_are_loaded_as_global_memory():
     assert n > 250
 
 
+def test_tiles_with_filters_in_registers_wait_for_one_stage():
+    """In the loop over the reduction a wave waits for the filters that it multiplies next; those of the stages behind them stay under way."""
+    n = 0
+    for name, code in code_objects.listings():
+        m = re.search(r"tile_(?:walk_|pair_)?kernelI(?:DF16_|NS_4bf16E)Li(128ELi64ELi4|64ELi64ELi2)ELi1ELi(\d)ELi(\d)ELi(\d)ELi\dEE", name)
+        if not m:
+            continue
+        bn, wn = map(int, m[1].split("ELi")[::2])
+        wk, kd, nbuf = int(m[2]), int(m[3]), int(m[4])
+        loop = code_objects.staging_loop(code)
+        waits = [int(re.search(r"vmcnt\((\d+)\)", o[0])[1]) for (_, w, o), (_, after, _) in zip(loop, loop[1:])
+                 if w == "s_waitcnt" and "vmcnt" in o[0] and after != "s_barrier"]
+        requested = (nbuf - 1) * (kd * 4 // wk) * (bn // wn // 32)
+        assert waits and min(waits) == requested - 1, (name, waits)
+        n += 1
+    assert n >= 30
+
+
 def test_kernels_end_with_their_results_in_memory():
     """Packets between dependent launches release nothing, so every store of an operator's kernel goes through to memory (sc1) and no wave
     ends before its stores have arrived there.  Shown on small listings, then in every kernel of the library but the probes."""
