@@ -1224,28 +1224,39 @@ __device__ __forceinline__ void ring_patch_body(const OpArgs &args) {
     finish_pixel<T, 4, BN / 4>(a, v, add, my_m, my_k, vec_ok, (my_row & 3) == 0);
 }
 
+// LDS that the bodies of one kernel share.
+template <int BYTES>
+__device__ __forceinline__ uint8_t *lds_place() {
+    __shared__ __attribute__((aligned(1024))) uint8_t place[BYTES];
+    return place;
+}
+
 // 3x3 windows, stride 1, padding 1, C % 64 == 0: the nine taps of a 64-channel chunk read the same input pixels, so those
 // are staged once per chunk as a patch and every tap reads its operand rows at a shifted position.
 // The map is cut into panels of `panel` columns; inside a panel pixels are numbered row by row through all images, and a
 // tile is BM consecutive ones.  Its patch holds the rows from the one above its first to the one below its last, each
 // panel + 2 pixels wide, with an empty row between two images; what lies outside an image is loaded out of range, i.e. zero.
 // The filter bank is packed in operand order ([32 channels][chunk][tap][16 elements][lane][16 bytes]) and goes straight to registers, a kilobyte a
-// load and DW steps ahead, so LDS holds only the patches and the waves meet once per chunk.
+// load, so LDS holds only the patches and the waves meet once per chunk.  Up to DW steps ahead: requests that belong to the next chunk stand behind a branch, the
+// compiler does not know whether they are under way, and its waits fall to none by the end of a chunk.  Without the branch (out of range after the last chunk) a layer
+// alone is faster, 64x64 256 -> 256 on 16 x 14 x 14 8.7 / 7.8 us, 128x64 512 -> 512 on 64 x 7 x 7 19.4 / 17.9, but ResNet-18, VGG-16 and MobileNetV2 beside each other take 222 us
+// instead of 219, in four stages 287 instead of 283: VGG-16's layers leave the other two less.
 //
 // What bounds it: matrix instructions (with loads of both operands left out a 128x128 tile of 512 channels takes 25.5 us, with them 31.6) and,
 // at short reductions, the first patch and the finish.  Filters that pass through LDS, as they did before, are two thirds of the bytes written to it and half of
 // those read, with a barrier per tap, and their three stages kept a second workgroup from the unit: 64x64 and 128x64 tiles now leave room for one.
 // The wave groups divide the four steps of a tap such that no filter is loaded twice on 64 channels (two waves, four groups) and on the 128x64
-// tile (four waves, two groups); on the wider ones two waves load the same filters, the second from the L1, which costs nothing (two waves and four
-// groups on the 128x128 tile: 31.6 / 32.4 us).  us a layer, filters through LDS / this, f16, 3x3:
-//   128x64   128 -> 128 on 16 x 28 x 28  8.25 / 7.56     512 -> 512 on 64 x 7 x 7   22.3 / 19.5     64 -> 128 on 112 x 112  6.19 / 5.80
-//   64x64    256 -> 256 on 16 x 14 x 14  8.94 / 7.85     512 -> 512 on 8 x 14 x 14  13.9 / 12.0     256 -> 256 on 56 x 56   9.02 / 7.93
-//   64x32    256 -> 512 on 28 x 28       7.90 / 6.20
-//   128x128  256 -> 256 on 64 x 14 x 14  18.8 / 17.5     512 -> 512 on 8 x 28 x 28  32.6 / 31.6
-//   128x256  256 -> 256 on 8 x 56 x 56   30.2 / 30.3     128 -> 128 on 8 x 112 x 112  35.5 / 34.7
-// Passes: ResNet-18, VGG-16 and MobileNetV2 225 / 217, four networks at batch 8 844 / 806, eight ResNet-50 at batch 16 2447 / 2326, on shares of the
-// units in eight stages 4341 / 4164.
-template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC, bool HELD, int ROOM = 0>
+// tile (four waves, two groups); on the 128x128 tile two waves load the same filters, the second from the L1, which costs nothing (two waves and four
+// groups: 31.6 / 32.4 us).  The 128x256 tile has one group of waves up to four chunks, of which four load the same filters: two groups' exchange of sums takes
+// longer there than the filters do.  From five chunks on it has two groups.  us a layer, filters through LDS / this, f16, 3x3:
+//   128x64   128 -> 128 on 16 x 28 x 28  8.73 / 7.78     512 -> 512 on 64 x 7 x 7    22.7 / 19.5     64 -> 128 on 112 x 112  6.59 / 6.10
+//   64x64    256 -> 256 on 16 x 14 x 14  9.06 / 8.66     512 -> 512 on 8 x 14 x 14   14.5 / 13.7     256 -> 256 on 56 x 56   9.04 / 8.66
+//   64x32    256 -> 512 -> 256 on 28 x 28 (64x64 and split the way back)  10.1 / 8.9
+//   128x128  256 -> 256 on 64 x 14 x 14  18.4 / 17.2     512 -> 512 on 8 x 28 x 28   30.9 / 29.5
+//   128x256  (in brackets the other number of groups)
+//            128 -> 128 on 8 x 112 x 112 34.9 / 34.9 (38.5)     on 54 x 28 x 28  17.0 / 16.4 (17.5)     256 -> 256 on 8 x 56 x 56  29.1 / 28.0 (28.5)
+//            448 -> 448 on 32 x 28 x 28  90.9 / 91.6 (93.5)     512 -> 512  104 / 105 (108)             on 64 x 14 x 14  52.4 / 51.0 (53.0)
+template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC, bool HELD, int ROOM = 0, int PLACE = 0>
 __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     OpArgs a = args;
     if constexpr (HELD)
@@ -1263,14 +1274,15 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     constexpr int PL = PC / 8 / NW;                        // loads of a wave per patch
     static_assert(PL * NW * 8 == PC && PL < SPC, "the waves share a patch evenly, and it is requested during a chunk's steps");
     constexpr int P_BYTES = PC * 128;
-    constexpr bool WIDE = WK == 2, SUMS = !WIDE;           // two groups: every wave finishes half of its part of the tile
-    constexpr int OWN = WIDE ? TN * TM / WK : 1;           // products of 32 x 32 in it: a row of them
-    static_assert(!WIDE || (TN * TM % WK == 0 && TM % OWN == 0), "the half is 32 channels x OWN * 32 pixels");
-    constexpr int XCH = NW * OWN * 4096, RED_BYTES = WIDE ? XCH + NW * WaveTile<T, 1, OWN>::BYTES : WK * BN * BM * 4, EP_BYTES = WIDE ? 0 : BM * (BN + 4) * 4;
+    constexpr bool WIDE = WK <= 2, SUMS = !WIDE;           // every wave finishes its part of the tile, of two groups half of it
+    constexpr int CT = WK == 2 ? 1 : TN, OWN = WK == 2 ? TN * TM / 2 : TM;     // products of 32 x 32 in it: CT * 32 channels x OWN * 32 pixels
+    static_assert(WK != 2 || (TN * TM % 2 == 0 && TM % OWN == 0), "the half is a row of products");
+    constexpr int XCH = WK == 2 ? NW * OWN * 4096 : 0, RED_BYTES = WIDE ? XCH + NW * WaveTile<T, CT, OWN>::BYTES : WK * BN * BM * 4, EP_BYTES = WIDE ? 0 : BM * (BN + 4) * 4;
     constexpr int COUNTED = ROOM > 0 ? 160 * 1024 / (ROOM + 1) + 1 : 0;      // a compute unit holds no more workgroups than are counted on
     constexpr int BIAS = std::max({2 * P_BYTES, RED_BYTES, EP_BYTES, COUNTED + 15 & ~15}), LDS_BYTES = BIAS + (WIDE ? BN * 4 : 0);
+    static_assert(PLACE == 0 || LDS_BYTES <= PLACE, "LDS shared with another body");
     typedef typename Mma<T, MF>::Acc Acc;
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    uint8_t *const smem = lds_place<std::max(LDS_BYTES, PLACE)>();
     __shared__ int s_last;
 
     int tid = threadIdx.x;
@@ -1420,36 +1432,47 @@ __device__ __forceinline__ void patch_body(const OpArgs &args, uint32_t slot) {
     };
     wait_and_meet<0>();
     if constexpr (WIDE) {
-        // each group hands the other the sums of half of its products and finishes the other half
-        float *xch = reinterpret_cast<float *>(&smem[0]) + lane * 4;
-        const int other = wave ^ (WN * WM);
-        Acc mine[1][OWN];
+        auto complete = [&](Acc (&sums)[CT][OWN], int c0, int p0) {
+            if (!meet_splits<BN, BM, 64 * NW>(a, sums, &s_last, tile, z, true, tid)) return;
+            WaveTile<T, CT, OWN> part;
+            static_assert(XCH + NW * part.BYTES <= BIAS, "exchanged sums and staging blocks fit");
+            part.k = (uint32_t)(n0 + c0 + (lane % part.LPR) * 8);
 #pragma unroll
-        for (int q = 0; q < 4 * OWN; ++q) {
-            const Acc &low = acc[0][q / 4], &high = acc[(OWN + q / 4) / TM][(OWN + q / 4) % TM];
-            const int e = 4 * (q % 4);
-            float4 v = make_float4(high[e], high[e + 1], high[e + 2], high[e + 3]);
-            if (wk == 1) v = make_float4(low[e], low[e + 1], low[e + 2], low[e + 3]);
-            *reinterpret_cast<float4 *>(&xch[(wave * OWN * 4 + q) * 256]) = v;
+            for (int j = 0; j < OWN; ++j) part.m_lane[j] = pixel(p0 + j * 32 + frow);
+            if (whole_packs<8>(a)) part.finish(a, sums, reinterpret_cast<uint16_t *>(&smem[XCH + wave * part.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + c0, lane);
+            else store_lanes<T, MF>(a, sums, n0 + c0, part.m_lane, fgrp);
+        };
+        if constexpr (WK == 1) {
+            complete(acc, wn * SUBN, wm * SUBM);
+        } else {
+            // each group hands the other the sums of half of its products and finishes the other half.  Each on a path of its own: picked lane by lane the
+            // sums take four cycles a register twice (128x256 tile: 0.4 us of a layer's 18).
+            float *xch = reinterpret_cast<float *>(&smem[0]) + lane * 4;
+            const int other = wave ^ (WN * WM);
+            Acc mine[1][OWN];
+            auto hand_over = [&]<int GROUP>() {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) mine[0][q / 4][e + t] = wk == 1 ? high[e + t] : low[e + t];
+                for (int q = 0; q < OWN; ++q) {
+                    const int h = OWN + q;
+                    const Acc &given = GROUP == 0 ? acc[h / TM][h % TM] : acc[0][q], &kept = GROUP == 0 ? acc[0][q] : acc[h / TM][h % TM];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<float4 *>(&xch[(wave * OWN * 4 + 4 * q + g) * 256]) = make_float4(given[4 * g], given[4 * g + 1], given[4 * g + 2], given[4 * g + 3]);
+                    mine[0][q] = kept;
+                }
+                asm volatile("; group %0" ::"n"(GROUP) : "memory");        // keeps the two paths apart
+            };
+            if (wk == 0) hand_over.template operator()<0>();
+            else hand_over.template operator()<1>();
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4 * OWN; ++q) {
+                const float4 v = *reinterpret_cast<const float4 *>(&xch[(other * OWN * 4 + q) * 256]);
+                Acc &to = mine[0][q / 4];
+                to[4 * (q % 4)] += v.x; to[4 * (q % 4) + 1] += v.y; to[4 * (q % 4) + 2] += v.z; to[4 * (q % 4) + 3] += v.w;
+            }
+            complete(mine, wn * SUBN + wk * OWN / TM * 32, wm * SUBM + wk * OWN % TM * 32);
         }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4 * OWN; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(&xch[(other * OWN * 4 + q) * 256]);
-            Acc &to = mine[0][q / 4];
-            to[4 * (q % 4)] += v.x; to[4 * (q % 4) + 1] += v.y; to[4 * (q % 4) + 2] += v.z; to[4 * (q % 4) + 3] += v.w;
-        }
-        if (!meet_splits<BN, BM, 64 * NW>(a, mine, &s_last, tile, z, true, tid)) return;
-        WaveTile<T, 1, OWN> part;
-        static_assert(XCH + NW * part.BYTES <= BIAS, "exchanged sums and staging blocks fit");
-        const int c0 = wn * SUBN + wk * OWN / TM * 32, p0 = wm * SUBM + wk * OWN % TM * 32;
-        part.k = (uint32_t)(n0 + c0 + (lane % part.LPR) * 8);
-#pragma unroll
-        for (int j = 0; j < OWN; ++j) part.m_lane[j] = pixel(p0 + j * 32 + frow);
-        if (whole_packs<8>(a)) part.finish(a, mine, reinterpret_cast<uint16_t *>(&smem[XCH + wave * part.BYTES]), reinterpret_cast<const float *>(&smem[BIAS]) + c0, lane);
-        else store_lanes<T, MF>(a, mine, n0 + c0, part.m_lane, fgrp);
         return;
     }
     if constexpr (SUMS) {
@@ -1557,12 +1580,23 @@ __global__ void __launch_bounds__(64 * WN * WM * WK) patch_kernel(OpArgs a) {
     results_stored();
 }
 
+// The walking kernel of the widest tile has both its bodies.
+constexpr uint32_t LONG_PATCHES = 4;                       // chunks of the reduction beyond which that tile has two groups of waves (patch_body)
+constexpr int WIDEST_LDS = 152064;
 template <typename T, int BN, int BM, int WN, int WM, int WK, int DW, int PC>
 __global__ void __launch_bounds__(64 * WN * WM * WK, patch_room(BN, BM) * WN * WM * WK / 4) patch_walk_kernel(OpArgs) {
     constexpr int AHEAD = BN == 64 && BM == 64 ? 3 : BM == 256 ? 2 : DW;     // filters further ahead are more registers than there are
     for (uint32_t slot = blockIdx.x / XCDS;;) {
         const OpArgs &a = kernel_arguments();
-        patch_body<T, BN, BM, WN, WM, WK, AHEAD, PC, true, patch_room(BN, BM)>(a, slot);
+        if constexpr (BM == 256) {                         // both in the same LDS; what they share the compiler would move ahead of the branch, and that is more scalars than there are
+            if (a.walk.units <= LONG_PATCHES) {
+                asm volatile("; one group");
+                patch_body<T, BN, BM, WN, WM * WK, 1, 4, PC, true, 1, WIDEST_LDS>(kernel_arguments(), slot);
+            } else {
+                asm volatile("; two groups");
+                patch_body<T, BN, BM, WN, WM, WK, AHEAD, PC, true, 1, WIDEST_LDS>(kernel_arguments(), slot);
+            }
+        } else patch_body<T, BN, BM, WN, WM, WK, AHEAD, PC, true, patch_room(BN, BM)>(a, slot);
         slot += a.walk.step;
         if (slot >= a.walk.per_xcd) break;
         __syncthreads();
@@ -1853,7 +1887,8 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
     // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
     const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int DW, int PC>() {
-        if (const uint32_t g = walkers(patch_room(BN, BM))) return launch((patch_walk_kernel<T, BN, BM, WN, WM, WK, DW, PC>), dim3(g), block, 0, st, walked);
+        if (const uint32_t g = walkers(patch_room(BN, BM)))
+            return launch((patch_walk_kernel<T, BN, BM, WN, BM == 256 ? 2 : WM, BM == 256 ? 2 : WK, BM == 256 ? 3 : DW, PC>), dim3(g), block, 0, st, walked);
         MT_LAUNCH((patch_kernel<T, BN, BM, WN, WM, WK, DW, PC>), (patch_pair_kernel<T, BN, BM, WN, WM, WK, DW, PC>), grid, block, st, a, mate);
     };
     auto wide = [&]<int BN, int BM, int WN, int WM, int NBUF>() {
@@ -1896,7 +1931,7 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
                 switch (a.form) {
                     case 0: if (deep) wide.template operator()<128, 128, 2, 2, 4>(); else tile.template operator()<128, 128, 2, 2, 1, 1, 2>(); break;
                     case 1: if (deep) wide.template operator()<128, 64, 4, 1, 5>(); else tile.template operator()<128, 64, 4, 1, 1, 1, 3>(); break;
-                    case 6: patch.template operator()<128, 256, 2, 2, 2, 3, 384>(); break;
+                    case 6: if (a.walk.units <= LONG_PATCHES) patch.template operator()<128, 256, 2, 4, 1, 4, 384>(); else patch.template operator()<128, 256, 2, 2, 2, 3, 384>(); break;
                     case 7: patch.template operator()<128, 128, 2, 2, 2, 6, 256>(); break;
                     case 8: patch.template operator()<128, 64, 4, 1, 2, 9, 192>(); break;
                     case 9: patch.template operator()<64, 64, 2, 1, 4, 9, 192>(); break;
