@@ -136,6 +136,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_unbuilt = None
 
 
 def load():
@@ -144,7 +145,14 @@ def load():
     if _lib is None:
         path = os.environ.get("MTSCHED_LIB") or _build.lib_path()   # override: load another build of the library
         if not os.path.exists(path):
-            _build.build()
+            global _unbuilt
+            if _unbuilt:                                             # a process tries once
+                raise _unbuilt
+            try:
+                _build.build()
+            except Exception as e:
+                _unbuilt = e
+                raise
         lib = C.CDLL(path)
         if not os.environ.get("MTSCHED_LIB") and os.path.isdir(_build.CSRC) and os.path.isdir(_build.INCLUDE):
             try:

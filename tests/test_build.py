@@ -42,3 +42,18 @@ def test_a_library_of_other_sources_is_refused(tmp_path, monkeypatch):
     monkeypatch.setattr(binding, "_lib", None)
     with pytest.raises(RuntimeError, match="other sources"):
         binding.load()
+
+
+def test_a_process_tries_to_build_once(tmp_path, monkeypatch):
+    monkeypatch.delenv("MTSCHED_LIB", raising=False)
+    tries = []
+
+    def fails():
+        tries.append(1)
+        raise RuntimeError("compile failed")
+    for owner, name, value in ((build, "LIB", str(tmp_path / "none.so")), (build, "build", fails), (binding, "_lib", None), (binding, "_unbuilt", None)):
+        monkeypatch.setattr(owner, name, value, raising=False)
+    for _ in range(2):
+        with pytest.raises(RuntimeError, match="compile failed"):
+            binding.load()
+    assert len(tries) == 1
