@@ -232,6 +232,8 @@ int32_t mt_model_destroy(mt_model *m);
 int32_t mt_model_num_ops(const mt_model *m, int32_t *out);
 int32_t mt_model_op_info(const mt_model *m, int32_t op_index, mt_op_info *out);
 int32_t mt_model_op_form(const mt_model *m, int32_t op_index, mt_op_form *out);
+/* Columns of the rectangle of the map that a ring's tile covers (3x3 layers: 8, two rows; 4, four rows); 0: consecutive pixels, or no ring. */
+int32_t mt_model_op_rectangle(const mt_model *m, int32_t op_index, int32_t *columns);
 int32_t mt_model_out_features(const mt_model *m, int64_t *out);
 /* w: host, storage type, layout as above, exactly w_bytes bytes; bias: host fp32 [n_bias] or NULL (zeros). */
 int32_t mt_model_set_weights(mt_model *m, int32_t op_index, const void *w, size_t w_bytes,

@@ -128,6 +128,11 @@ class Model:
         B.check(B.load().mt_model_op_form(self.h, i, C.byref(form)))
         return form
 
+    def op_rectangle(self, i):
+        columns = C.c_int32()
+        B.check(B.load().mt_model_op_rectangle(self.h, i, C.byref(columns)))
+        return columns.value
+
     def out_features(self):
         n = C.c_int64()
         B.check(B.load().mt_model_out_features(self.h, C.byref(n)))

@@ -106,6 +106,7 @@ SIGNATURES = {
     "mt_model_num_ops": (_i32, [_vp, _pi32]),
     "mt_model_op_info": (_i32, [_vp, _i32, C.POINTER(mt_op_info)]),
     "mt_model_op_form": (_i32, [_vp, _i32, C.POINTER(mt_op_form)]),
+    "mt_model_op_rectangle": (_i32, [_vp, _i32, C.POINTER(_i32)]),
     "mt_model_out_features": (_i32, [_vp, C.POINTER(_i64)]),
     "mt_model_set_weights": (_i32, [_vp, _i32, _vp, _sz, _pf, _sz]),
     "mt_model_arena_bytes": (_i32, [_vp, C.POINTER(_sz)]),

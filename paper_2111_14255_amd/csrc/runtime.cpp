@@ -1636,6 +1636,14 @@ int32_t mt_model_op_form(const mt_model *m, int32_t i, mt_op_form *out) {
     return MT_OK;
 }
 
+int32_t mt_model_op_rectangle(const mt_model *m, int32_t i, int32_t *columns) {
+    if (!m || !columns) return fail(MT_ERR_INVALID_ARG, "NULL argument");
+    if (!m->finalized) return fail(MT_ERR_NOT_FINALIZED, "model is not finalised");
+    if (i < 0 || i >= (int)m->ops.size()) return fail(MT_ERR_INVALID_ARG, "operator index out of range");
+    *columns = m->ops[i].plan.form >= 0 ? std::max(-m->ops[i].plan.panel, 0) : 0;
+    return MT_OK;
+}
+
 int32_t mt_model_out_features(const mt_model *m, int64_t *out) {
     if (!m || !out) return fail(MT_ERR_INVALID_ARG, "NULL argument");
     if (!m->finalized) return fail(MT_ERR_NOT_FINALIZED, "model is not finalised");

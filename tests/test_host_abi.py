@@ -301,6 +301,31 @@ def test_op_form_names_the_kernel_and_tells_a_split_from_a_ring(dtype, n, hw, c,
     m.close()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("n,h,w,win,columns", [
+    (1, 14, 14, 3, 8),       # 14 rectangles of 2 x 8, 13 tiles of consecutive pixels
+    (1, 12, 12, 3, 4),       # 9 of 4 x 4, 12 of 2 x 8
+    (1, 8, 8, 3, 4),         # as many of either
+    (1, 18, 8, 3, 8),        # 9 of 2 x 8, 10 of 4 x 4, 9
+    (1, 22, 40, 3, 8),       # 55 of 2 x 8, 60 of 4 x 4, 55
+    (1, 21, 40, 3, 8),       # 55, 53: 4 % more
+    (5, 4, 5, 3, 0),         # 10 of either, 7
+    (4, 14, 14, 3, 0),       # 56, 49: 14 % more
+    (4, 7, 7, 3, 0),         # 16, 13
+    (1, 14, 14, 5, 0),
+])
+def test_rings_take_rectangles_where_they_cover_the_map(n, h, w, win, columns, dtype):
+    """3x3 windows on rings: the rectangle of which fewer cover the map, unless they are more than a tenth more tiles than consecutive pixels make."""
+    g = GraphBuilder("t", dtype, n, h, w, 128)
+    g.conv(0, 40, win, pad=win // 2)
+    m = api.Model(g.done())
+    assert m.op_form(0).ring_waves
+    assert m.op_rectangle(0) == columns
+    assert B.load().mt_model_op_rectangle(m.h, 0, None) == B.MT_ERR_INVALID_ARG
+    assert B.load().mt_model_op_rectangle(m.h, 1, C.byref(C.c_int32())) == B.MT_ERR_INVALID_ARG
+    m.close()
+
+
 @pytest.mark.parametrize("arch,batch,mib", [("resnet101", 1, 0), ("resnet50", 64, 1.26), ("resnet101", 128, 2.51), ("vgg16", 1, 6.51), ("vgg16", 12, 4.51),
                                             ("vgg16", 128, 12.02), ("inceptionv3", 48, 0.95), ("alexnet", 6, 10.02), ("mobilenetv2", 1, 0)])
 def test_what_a_tenant_takes_of_the_fixed_scratch_array(arch, batch, mib):
