@@ -438,12 +438,14 @@ def report_layers(args):
 def _family_of(kernel_name):
     """The name mt_op_form gives a kernel, from its name in a trace (demangled or not)."""
     import re
-    m = re.search(r"(igemm|tile|patch|ring|dconv)_(?:pair_)?kernel<(?:[A-Za-z_][^,]*, )?([\d, ]+)", kernel_name) or \
-        re.match(r"_ZN2mt\d+(igemm|tile|patch|ring)_(?:pair_)?kernelI(?:f|DF16_|NS_4bf16E)((?:Li\d+E)+)", kernel_name)
+    m = re.search(r"(igemm|tile|patch|ring_patch|ring|dconv)_(?:pair_|walk_)?kernel<(?:[A-Za-z_][^,]*, )?([\d, ]+)", kernel_name) or \
+        re.match(r"_ZN2mt\d+(igemm|tile|patch|ring_patch|ring)_(?:pair_|walk_)?kernelI(?:f|DF16_|NS_4bf16E)((?:Li\d+E)+)", kernel_name)
     if m:
         kind, p = m.group(1), [int(v) for v in re.findall(r"\d+", m.group(2))]
         if kind == "ring":
             return "ring_%dx16" % p[0]
+        if kind == "ring_patch":                  # channel tiles of 16
+            return "ring_%dx16" % (16 * p[0])
         if kind == "dconv":                       # 16 x 16 pieces of a wave, waves over the tile
             return "registers_%dx%d" % (16 * p[0] * p[2], 16 * p[1] * p[3])
         return "%s_%dx%d" % ("elements" if kind == "igemm" else kind, p[0], p[1])

@@ -7,7 +7,7 @@ import re
 import numpy as np
 import pytest
 
-from paper_2111_14255_amd import binding as B, api
+from paper_2111_14255_amd import binding as B, api, report
 from oracle import schedule as S, fold as ofold, ops as oops
 from synth import GraphBuilder, zoo, weights
 import code_objects
@@ -609,3 +609,15 @@ def test_a_unit_holds_as_many_first_layer_workgroups_as_their_grids_count_on(win
     assert len(forms) == 4                               # two types, aligned and general
     for kern in forms:
         assert per_unit <= code_objects.held_by_registers(kern) and per_unit * kern[".group_segment_fixed_size"] <= 160 * 1024
+
+
+@pytest.mark.parametrize("kernel,form", [
+    ("void mt::ring_patch_kernel<mt::bf16, 2, 4>(mt::OpArgs)", "ring_32x16"),
+    ("void mt::ring_patch_kernel<float, 1, 8>(mt::OpArgs)", "ring_16x16"),
+    ("_ZN2mt21ring_patch_pair_kernelINS_4bf16ELi1ELi8EEEvNS_10OpArgsPairE", "ring_16x16"),
+    ("void mt::ring_kernel<_Float16, 16, 8, 2, 1>(mt::OpArgs)", "ring_16x16"),
+    ("void mt::patch_kernel<mt::bf16, 64, 64, 2, 1, 4, 9, 192>(mt::OpArgs)", "patch_64x64"),
+    ("void mt::tile_walk_kernel<mt::bf16, 128, 64, 4, 1, 1, 1, 3, 0>(mt::OpArgs)", "tile_128x64"),
+])
+def test_kernels_of_a_trace_are_grouped_by_their_form(kernel, form):
+    assert report._family_of(kernel) == form
