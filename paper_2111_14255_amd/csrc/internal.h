@@ -197,8 +197,10 @@ int launch_stem(const OpArgs &a, void *stream, const OpArgs *mate = nullptr, int
 int rowb_waves(int R, int S, int C, int channels);
 int rowb_tiles(int R, int S, int C, int channels);   // 32-channel tiles per slice of output channels (a workgroup holds one slice's filters)
 // Tile kernels (kernels_tile.hip): choice of form, its split workspace (tiles, floats per tile), the pooled plan, launch.
-// The filter bank is [n_pad][k_pad]; a patch-staged layer (panel > 0) orders the reduction index (64-channel chunk, tap, channel), a ring on
-// rectangles (panel < 0) packs it in operand order.
+// The filter bank is [groups][n_pad][k_pad], or packed in operand order, what a lane feeds to a matrix instruction in one 16-byte piece:
+//   patches (panel > 0)               [32 channels][64-channel chunk][tap][16 elements][lane][16 bytes]
+//   rings on rectangles (panel < 0)   [16 channels][64-byte chunk][tap][lane][16 bytes]
+//   tile_packs_filters                [groups][32 channels][16 elements][lane][16 bytes]
 bool patch_stageable(const OpArgs &a);
 enum TileChoice {
     TILE_ANY,        // whatever the estimate says
@@ -208,7 +210,7 @@ enum TileChoice {
 };
 bool plan_tile(OpArgs &a, TileChoice choice);
 bool tile_is_narrow(const OpArgs &a);
-bool tile_packs_filters(const OpArgs &a);   // the filter bank is [groups][32 channels][16 elements][lane][8]
+bool tile_packs_filters(const OpArgs &a);
 void describe_tile(const OpArgs &a, mt_op_form *out);    // all but the workspace
 void tile_workspace(const OpArgs &a, size_t *tiles, size_t *floats);
 bool plan_tile_pooled(OpArgs &a);

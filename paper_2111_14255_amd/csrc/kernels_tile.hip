@@ -562,10 +562,11 @@ __device__ __forceinline__ uint32_t window_mask(const OpArgs &a, int ih0, int iw
     return range(ih0, a.H, a.R) | range(iw0, a.W, a.S) << 16;
 }
 
-// A workgroup's arguments, all in one trip.  fetch_walk only asks for them together, which is enough for the kernels of one operator with
-// narrow tiles, and leaves the compiler free to keep what it likes; held, they are two trips there (the scalar registers run out).
-// us, asked for together / held: 64 -> 128 on 112 x 112 (128 x 64 patch) 6.6 / 6.3, eight ResNet-50 at batch 16, two to a launch, 2520 / 2469; but 256 -> 256 on
-// 14 x 14 (ring) 3.5 / 3.6, 64 -> 96 on 5 x 35 x 35 (64 x 64 patch) 5.2 / 5.4.
+// A workgroup's arguments, all in one trip.  fetch_walk only asks for them together and leaves the compiler free to keep what it likes; held, they are two trips
+// in the kernels of one operator with narrow tiles (the scalar registers run out).  us a layer, f16, asked for together / held: 1x7 192 -> 192 on 17 x 17 (ring)
+// 3.46 / 3.57, 3x3 256 -> 256 on 16 x 14 x 14 (64x64 patch) 8.61 / 8.69, 512 -> 512 on 8 x 14 x 14 13.15 / 13.29; rings on rectangles as much either way; 128x64 patch
+// 128 -> 128 on 112 x 112 7.55 / 7.51, on 16 x 28 x 28 7.61 / 7.57.  Launches of several operators hold them as well, for 0.3 % less: eight ResNet-50 at batch 16, two to a
+// launch, 2178 / 2183 us a pass.
 __device__ __forceinline__ void fetch_walk(const OpArgs &a) {
     const TileWalk &w = a.walk;
     asm volatile("" ::"s"(a.x), "s"(a.w), "s"(w.total), "s"(w.per_xcd), "s"(w.pixels), "s"(w.x_bytes), "s"(w.w_bytes), "s"(w.flat), "s"(w.units), "s"(w.per),
@@ -1881,9 +1882,9 @@ static int launch_tile_typed(const OpArgs &a, hipStream_t st, const OpArgs *mate
         };
         by_gather(go);
     };
-    // The widest tiles have two stages of LDS, so that two workgroups, or another tenant's, fit beside them; a launch that has the chip to
-    // itself and at most one workgroup per unit waits for memory at every stage that way (0.75 us, matrix instructions 0.2) and takes four.
-    // The order of the sums is the same.  us, two / four: ResNet-50 alone at batch 16, 32, 64 619 / 607, 903 / 862,
+    // The widest tiles have two stages of LDS (128x64 with filters in registers: three), so that two workgroups, or another tenant's, fit beside them; a launch that
+    // has the chip to itself and at most one workgroup per unit waits for memory at every stage that way (0.75 us, matrix instructions 0.2) and takes four (five).
+    // The order of the sums is the same.  us, two / four, both operands in LDS: ResNet-50 alone at batch 16, 32, 64 619 / 607, 903 / 862,
     // 1434 / 1401; used always: batch 64 1438 (layers of 392 workgroups and more), eight tenants at batch 16 2582 / 2712.
     const bool deep = a.alone && !mate && a.walk.total <= (uint32_t)UNITS;
     auto patch = [&]<int BN, int BM, int WN, int WM, int WK, int DW, int PC>() {

@@ -1174,8 +1174,8 @@ void reserve_static(mt_ctx *ctx, mt_schedule *s) {
 namespace {
 // Filters [groups][K][taps][row of channels] in operand order: [groups][ROWS output channels][RUN bytes of a tap][tap][16 bytes of the run][output channel], zeros
 // where the bank is padded.  Block after block of ROWS * RUN bytes, which stay in the first-level cache while the pieces of a run spread over them: output channel
-// by output channel the pieces of a line of the bank were written far apart, and the whole bank was cleared first (us a bank of 512 -> 512 3x3 filters, f16:
-// 1061, 446 this way).
+// by output channel the pieces of a line of the bank were written far apart, and the whole bank was cleared first.  ms to register a network at batch 8, f16,
+// that way / this: ResNet-18 8.9 / 7.2, ResNet-50 18.3 / 16.1, VGG-16 119.8 / 118.1 (its classifier, nine tenths of it, is not packed), MobileNetV2 3.2 either way.
 template <int ROWS, int RUN>
 void pack_operands(std::vector<uint8_t> &packed, const uint8_t *src, const OpArgs &a, int taps, int es) {
     const size_t group = (size_t)a.n_pad * a.k_pad * es, filter = (size_t)a.gemm_k * es, tap_bytes = filter / taps;
